@@ -81,10 +81,11 @@ enum { kScanFused = 0, kScanTwoPass = 1, kScanDeferAll = 2, kScanRepairAll = 3 }
 hipError_t launch_score_fast(const void *keys, const RowMap &km, int dtype, int LH, int d, const PromptTab &tab, float *a_raw,
                              float *bsum, float *ssum, void *sync_area, int mode, const Prof &prof, hipStream_t st);
 
-// ---- scoring, matrix-core formulation of the fused streaming pass (bf16 or fp16, d = 128, window 64, block size <= 256) ----
+// ---- scoring, matrix-core formulation of the fused streaming pass (16-bit or 8-bit keys, d <= 128, window 64, block size <= 256) ----
+inline int padded_dims(int d) { return d <= 64 ? 64 : (d + 31) / 32 * 32; }   // dims its sums are kept with: 32 KS
 bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, int LH);
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab);    // the list of items the pass works through
-hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int LH, const PromptTab &tab, float *a_raw,
+hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int LH, int d, const PromptTab &tab, float *a_raw,
                              void *accum, float *ssum, void *sync_area, void *plan_area, int mode, const Prof &prof,
                              hipStream_t st);
 

@@ -1,6 +1,8 @@
-// Streaming scoring kernel for bf16 or fp16 keys of head dim 128, window 64, episodic block size <= 256 (paper
-// Sections 2.1-2.3), with every dot product of the pass formed by the matrix cores.  (Written out below for bf16;
-// fp16 differs in the product instruction, in unpacking, and in how an fp32 anchor is cut into three terms.)
+// Streaming scoring kernel for bf16, fp16 or 8-bit (E4M3) keys of head dim <= 128 (64 excepted, see
+// tile_score_supported), window 64, episodic block size <= 256 (paper Sections 2.1-2.3), with every dot product of the
+// pass formed by the matrix cores.  (Written out below for bf16 and head dim 128; fp16 differs in the product
+// instruction, in unpacking, and in how an fp32 anchor is cut into three terms; 8-bit keys become bf16, exactly, on
+// their way from the load; other head dims are padded with zeros to 32 KS, which no dot product and no norm sees.)
 //
 // The pass is a stream over the keys and nothing else is read from memory, but written for the vector unit it
 // needs ~2300 instructions per 64 tokens and is bound by their issue.  Here the vector unit keeps only the work
@@ -47,6 +49,8 @@ using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
 using f16x8 = _Float16 __attribute__((ext_vector_type(8)));
 using f32x4 = float __attribute__((ext_vector_type(4)));
 
+constexpr int kNoByte = 0x40000000;              // an offset past any buffer of the pass, also with a token's offset added:
+                                                 // loads read zeros there, stores are dropped
 constexpr int kGroup = 16;                       // tokens per group
 constexpr int kPitch = 272;                      // bytes between the rows of a staged group: 16 lanes that read the
                                                  // same piece of 16 rows touch every LDS bank once
@@ -152,11 +156,30 @@ template <int KF> __device__ __forceinline__ void stage_anchor(uint8_t *stage, i
 }
 
 // The staged 16 rows as a matrix operand: lane (q, n) takes dims 32 kk + 8 q .. + 7 of row n.
-__device__ __forceinline__ void read_operand(const uint8_t *stage, int lane, u32x4 (&x)[4])
+template <int KS> __device__ __forceinline__ void read_operand(const uint8_t *stage, int lane, u32x4 (&x)[KS])
 {
     const uint8_t *mine = stage + (lane & 15) * kPitch + 16 * (lane >> 4);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) x[kk] = *reinterpret_cast<const u32x4 *>(mine + 64 * kk);
+    for (int kk = 0; kk < KS; ++kk) x[kk] = *reinterpret_cast<const u32x4 *>(mine + 64 * kk);
+}
+
+// The format the staged rows are in: 8-bit keys travel as bf16.
+template <int KF> constexpr int kStaged = KF == kKeyF16 ? kKeyF16 : kKeyBF16;
+
+// A loaded row piece in the staged format.  E4M3 -> bf16 is exact (3 mantissa bits into 7, exponents -9 .. 8): the
+// upper halves of the fp32 values are the bf16 values.
+template <int KF> __device__ __forceinline__ u32x4 staged_piece(const Piece<KF> &r)
+{
+    if constexpr (KF == kKeyF8) {
+        float k[8];
+        unpack8_f8(r, k);
+        u32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_perm(__float_as_uint(k[2 * i + 1]), __float_as_uint(k[2 * i]), 0x07060302u);
+        return o;
+    } else {
+        return r;
+    }
 }
 
 // Sum of the squares of a lane's eight values of a row, ready to be read by any vector instruction (see above).
@@ -201,8 +224,8 @@ template <int KF> __device__ __forceinline__ void group_norms(const u32x4 (&raw)
     }
 }
 
-// The same, and the weighted sum of the group's rows to sum_out (D floats).
-template <int KF> __device__ __forceinline__ void group_sum(const u32x4 (&raw)[4], int tok0, int tok_end, int g, int c, float *w_out,
+// The same, and the weighted sum of the group's rows to sum_out (32 KS floats).
+template <int KF, int KS> __device__ __forceinline__ void group_sum(const u32x4 (&raw)[4], int tok0, int tok_end, int g, int c, float *w_out,
                                           float *ss_out, float *sum_out)
 {
     float ww[4];
@@ -217,7 +240,16 @@ template <int KF> __device__ __forceinline__ void group_sum(const u32x4 (&raw)[4
 #pragma unroll
         for (int e = 0; e < 8; ++e) T[e] = fmaf(ww[j], k[e], T[e]);
     }
-    *reinterpret_cast<float2 *>(sum_out + 8 * c + 2 * g) = sum_over_rows16_transposing(T);
+    const float2 t2 = sum_over_rows16_transposing(T);
+    if (KS == 4 || 8 * c < 32 * KS) *reinterpret_cast<float2 *>(sum_out + 8 * c + 2 * g) = t2;
+}
+
+// Dims 2 lane and 2 lane + 1 of a vector of 32 KS floats (0 past its end).
+template <int KS> __device__ __forceinline__ float2 dim_pair(const float *v, int lane)
+{
+    if (KS == 4) return *reinterpret_cast<const float2 *>(v + 2 * lane);
+    const float2 t = *reinterpret_cast<const float2 *>(v + 2 * min(lane, 16 * KS - 1));
+    return lane < 16 * KS ? t : make_float2(0.f, 0.f);
 }
 
 __device__ __forceinline__ float sum3(const f32x4 &d) { return (d[0] + d[1]) + d[2]; }
@@ -289,12 +321,14 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
 // grid: one workgroup of 256 threads per item, in the items' order.  (Resident workgroups that loop over the items
 // instead were tried: without the hardware handing out blocks as slots fall free, all workgroups of the chip move
 // through their loading and computing phases in step, and the pass takes 0.90 ms instead of 0.77.)
-template <int KF> __global__ __launch_bounds__(64 * kTileWaves, 4)
-void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restrict__ items, float *__restrict__ a_raw,
+// KS: head dims the pass works with, in steps of 32 (the rest of the last step reads as zeros); FULL: d = 32 KS.
+template <int KF, int KS, bool FULL> __global__ __launch_bounds__(64 * kTileWaves, 4)
+void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *__restrict__ items, float *__restrict__ a_raw,
                       unsigned long long *__restrict__ acc, float *__restrict__ ssum, uint32_t *__restrict__ sync, int64_t rows,
                       int poll_limit)
 {
-    constexpr int D = 128, NW = kTileWaves, kRowBytes = D * 2;
+    constexpr int D = 32 * KS, NW = kTileWaves, ES = key_bytes<KF>(), SF = kStaged<KF>;
+    const int row_bytes = FULL ? D * ES : d * ES;
     __shared__ __attribute__((aligned(16))) uint8_t lds_stage[NW][kStageBytes];   // a wave's group on its way to operand layout, later its anchors
     __shared__ __attribute__((aligned(16))) float lds_T[4 + 16][D];               // group sums: 4 halo groups, then the block's
     __shared__ __attribute__((aligned(16))) float lds_w[NW][5][kGroup];           // 1/||k|| per token of a wave's groups (0: no such token)
@@ -315,8 +349,9 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
 
     // ---- first touch: this wave's groups, then its group of the halo.  Rows outside the prompt read as zeros. ----
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t *>(keys) + it.key_off * 2, 0, N * kRowBytes, 0x00020000);
-    u32x4 raw[5][4];
+        const_cast<uint8_t *>(keys) + it.key_off * ES, 0, N * row_bytes, 0x00020000);
+    const int piece_off = FULL && KS == 4 ? 8 * ES * c : (8 * c < (FULL ? D : d) ? 8 * ES * c : kNoByte);
+    Piece<KF> raw[5][4];
     bool ex[5];                                                       // group m - 1 of the chain exists (m = 0: halo)
 #pragma unroll
     for (int mm = 0; mm < 5; ++mm) {
@@ -324,32 +359,37 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
         const int q = w + 4 * (m - 1);                                // block-local group index, < 0: halo
         ex[m] = q < ng;
         if (ex[m]) {
-            const int off = (blk_lo + kGroup * q + 4 * g) * kRowBytes + 16 * c;
+            const int off = (blk_lo + kGroup * q + 4 * g) * row_bytes + piece_off;
 #pragma unroll
             // a full block's last 64 tokens (m = 4) are read again, as the next block's halo, and the halo has just
             // been read by the block in front: those stay in the L2; the other rows are marked non-temporal (aux 2)
             for (int j = 0; j < 4; ++j)
-                raw[m][j] = (m >= 1 && m <= 3) ? row_load<KF, 2>(rsrc, off + j * kRowBytes) : row_load<KF>(rsrc, off + j * kRowBytes);
+                raw[m][j] = (m >= 1 && m <= 3) ? row_load<KF, 2>(rsrc, off + j * row_bytes) : row_load<KF>(rsrc, off + j * row_bytes);
         }
     }
 
     // ---- the block's own groups: norms and partial sums, nothing else in front of the block total ----
+    u32x4 row[5][4];                                                  // the rows in the staged format
 #pragma unroll
     for (int m = 1; m < 5; ++m)
-        if (ex[m]) group_sum<KF>(raw[m], blk_lo + kGroup * (w + 4 * (m - 1)), blk_hi, g, c, lds_w[w][m], lds_ss[w][m], lds_T[4 + w + 4 * (m - 1)]);
+        if (ex[m]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) row[m][j] = staged_piece<KF>(raw[m][j]);
+            group_sum<SF, KS>(row[m], blk_lo + kGroup * (w + 4 * (m - 1)), blk_hi, g, c, lds_w[w][m], lds_ss[w][m], lds_T[4 + w + 4 * (m - 1)]);
+        }
     __syncthreads();
 
     // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1 ----
     unsigned long long *acc_unit = acc + (int64_t)it.unit * D;
     float bsq, b0 = 0.f, b1 = 0.f;
     for (int q = 0; q < ng; ++q) {
-        const float2 t2 = *reinterpret_cast<const float2 *>(&lds_T[4 + q][2 * lane]);
+        const float2 t2 = dim_pair<KS>(lds_T[4 + q], lane);
         b0 += t2.x;
         b1 += t2.y;
     }
     const bool poster = w == (it.id & (NW - 1));                      // one wave adds the block total to the unit's sum
     unsigned long long after0 = 0ull, after1 = 0ull;                  // the accumulators right after this block's add
-    if (poster) {
+    if (poster && (KS == 4 || lane < D / 2)) {
         const unsigned long long t0 = accum_term(b0), t1 = accum_term(b1);
         after0 = __hip_atomic_fetch_add(acc_unit + 2 * lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
         after1 = __hip_atomic_fetch_add(acc_unit + 2 * lane + 1, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
@@ -357,47 +397,47 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
     bsq = sum_over_rows16(row_sum<16>(fmaf(b0, b0, b1 * b1)));
 
     // ---- the halo group's sum (the window sums in front of the block's first groups need it) ----
-    group_sum<KF>(raw[0], blk_lo + kGroup * (w - 4), blk_hi, g, c, lds_w[w][0], lds_ss[w][0], lds_T[w]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) row[0][j] = staged_piece<KF>(raw[0][j]);
+    group_sum<SF, KS>(row[0], blk_lo + kGroup * (w - 4), blk_hi, g, c, lds_w[w][0], lds_ss[w][0], lds_T[w]);
 
     float *S_unit = ssum + (int64_t)it.unit * D;
     if (poster) {                                                     // (the adds have had the halo group to come back)
         const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(S_unit, 0, D * 4, 0x00020000);
-        constexpr int kNoStore = 0x40000000;
         // the last block to add to a word stores the word's final value; a word's adds take turns, so exactly one does
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(accum_value(after0)), prs,
-                                              accum_complete(after0, unblk) ? 8 * lane : kNoStore, 0, 16);
+                                              accum_complete(after0, unblk) ? 8 * lane : kNoByte, 0, 16);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(accum_value(after1)), prs,
-                                              accum_complete(after1, unblk) ? 8 * lane + 4 : kNoStore, 0, 16);
+                                              accum_complete(after1, unblk) ? 8 * lane + 4 : kNoByte, 0, 16);
     }
 
     // ---- every group through the staging rows into operand layout ----
-    u32x4 X[5][4];
+    u32x4 X[5][KS];
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
         if (ex[m]) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4 *>(stage + (4 * g + j) * kPitch + 16 * c) = raw[m][j];
+            for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4 *>(stage + (4 * g + j) * kPitch + 16 * c) = row[m][j];
             __builtin_amdgcn_wave_barrier();
-            read_operand(stage, lane, X[m]);
+            read_operand<KS>(stage, lane, X[m]);
             __builtin_amdgcn_wave_barrier();                          // the next group reuses the staging rows
         }
     }
-    stage_anchor<KF>(stage, 4, lane, b0, b1);                             // rows 4 .. 6: the block total's three terms
+    stage_anchor<SF>(stage, 4, lane, b0, b1);                             // rows 4 .. 6: the block total's three terms
     __syncthreads();                                                  // the halo groups' sums
     // ---- the chain of this wave's groups ----
     // lane (qq, n) of a result holds rows 4 qq + rho, column n.  Masked weights of the rows: rows j <= n count.
     const __amdgpu_buffer_rsrc_t out_c = __builtin_amdgcn_make_buffer_rsrc(a_raw + 2 * rows + row0, 0, blk_hi * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t out_e = __builtin_amdgcn_make_buffer_rsrc(a_raw + rows + row0, 0, blk_hi * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t out_s = __builtin_amdgcn_make_buffer_rsrc(a_raw + row0, 0, blk_hi * 4, 0x00020000);
-    constexpr int kNoStore = 0x40000000;                              // an offset past any buffer, also with a block's offset added: the store is dropped
-    const int off_q0 = qq == 0 ? 4 * n : kNoStore, off_q1 = qq == 1 ? 4 * n : kNoStore;
+    const int off_q0 = qq == 0 ? 4 * n : kNoByte, off_q1 = qq == 1 ? 4 * n : kNoByte;
     float wm_prev[4], alpha_prev;
     {
         const float4 w4 = *reinterpret_cast<const float4 *>(&lds_w[w][0][4 * qq]);
         const float ww[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
         for (int rho = 0; rho < 4; ++rho) wm_prev[rho] = 4 * qq + rho <= n ? ww[rho] : 0.f;
-        alpha_prev = weighted(tile<KF, 4>(X[0], X[0]), wm_prev);          // halo group: its own triangle only
+        alpha_prev = weighted(tile<SF, KS>(X[0], X[0]), wm_prev);          // halo group: its own triangle only
     }
 #pragma unroll
     for (int m = 1; m < 5; ++m) {
@@ -406,24 +446,24 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
             // window sum in front of the group = the four groups before it
             float s0, s1;
             {
-                const float2 t0 = *reinterpret_cast<const float2 *>(&lds_T[q][2 * lane]);
-                const float2 t1 = *reinterpret_cast<const float2 *>(&lds_T[q + 1][2 * lane]);
-                const float2 t2 = *reinterpret_cast<const float2 *>(&lds_T[q + 2][2 * lane]);
-                const float2 t3 = *reinterpret_cast<const float2 *>(&lds_T[q + 3][2 * lane]);
+                const float2 t0 = dim_pair<KS>(lds_T[q], lane);
+                const float2 t1 = dim_pair<KS>(lds_T[q + 1], lane);
+                const float2 t2 = dim_pair<KS>(lds_T[q + 2], lane);
+                const float2 t3 = dim_pair<KS>(lds_T[q + 3], lane);
                 s0 = ((t0.x + t1.x) + t2.x) + t3.x;
                 s1 = ((t0.y + t1.y) + t2.y) + t3.y;
             }
             const float P0 = sum_over_rows16(row_sum<16>(fmaf(s0, s0, s1 * s1)));
-            stage_anchor<KF>(stage, 0, lane, s0, s1);                     // rows 0 .. 2: the seed's three terms
+            stage_anchor<SF>(stage, 0, lane, s0, s1);                     // rows 0 .. 2: the seed's three terms
             __builtin_amdgcn_wave_barrier();
-            u32x4 An[4];
-            read_operand(stage, lane, An);
+            u32x4 An[KS];
+            read_operand<KS>(stage, lane, An);
             __builtin_amdgcn_wave_barrier();                          // the next group rewrites rows 0 .. 2
-            const f32x4 AT = tile<KF, 4>(X[m], X[m]);                     // [j in G][i in G]
-            const f32x4 XT = tile<KF, 4>(X[m - 1], X[m]);                 // [j' in P][i in G]
-            const f32x4 XX = tile<KF, 4>(X[m], X[m - 1]);                 // [j in G][i' in P]
-            const f32x4 AG = tile<KF, 4>(An, X[m]);                       // [anchor row][i in G]
-            const f32x4 AP = tile<KF, 4>(An, X[m - 1]);                   // [anchor row][i' in P]
+            const f32x4 AT = tile<SF, KS>(X[m], X[m]);                     // [j in G][i in G]
+            const f32x4 XT = tile<SF, KS>(X[m - 1], X[m]);                 // [j' in P][i in G]
+            const f32x4 XX = tile<SF, KS>(X[m], X[m - 1]);                 // [j in G][i' in P]
+            const f32x4 AG = tile<SF, KS>(An, X[m]);                       // [anchor row][i in G]
+            const f32x4 AP = tile<SF, KS>(An, X[m - 1]);                   // [anchor row][i' in P]
             float wm[4];
             {
                 const float4 w4 = *reinterpret_cast<const float4 *>(&lds_w[w][m][4 * qq]);
@@ -458,15 +498,15 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
         }
     }
     // ---- stable dots against the unit's sum ----
-    if (w == 0) {                                                     // 32 lanes look, the other waves sit at the barrier
+    if (w == 0) {                                                     // D / 4 lanes look, the other waves sit at the barrier
         const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(S_unit, 0, D * 4, 0x00020000);
         bool got = false;
         for (int polls = 0; poll_limit >= 0; ++polls) {               // poll_limit < 0: defer without looking
             u32x4 sv = {0u, 0u, 0u, 0u};
-            if (lane < 32) sv = agent_load16(srs, lane * 16);
-            got = __all(all_written(sv));
+            if (lane < D / 4) sv = agent_load16(srs, lane * 16);
+            got = __all(all_written(sv));                             // (lanes past the vector hold zeros)
             if (got) {
-                if (lane < 32) *reinterpret_cast<u32x4 *>(&lds_S[4 * lane]) = sv;
+                if (lane < D / 4) *reinterpret_cast<u32x4 *>(&lds_S[4 * lane]) = sv;
                 break;
             }
             if (polls >= poll_limit) break;
@@ -479,18 +519,18 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
     }
     __syncthreads();
     if (s_have != 0) {
-        float2 s2 = *reinterpret_cast<const float2 *>(&lds_S[2 * lane]);
+        float2 s2 = dim_pair<KS>(lds_S, lane);
         if constexpr (KF == kKeyF16) { s2.x *= 0.25f; s2.y *= 0.25f; }   // a sum over 65 536 unit vectors stays inside fp16's range; the cosine does not see the factor
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
-        stage_anchor<KF>(stage, 0, lane, s2.x, s2.y);
+        stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
         __builtin_amdgcn_wave_barrier();
-        u32x4 An[4];
-        read_operand(stage, lane, An);
+        u32x4 An[KS];
+        read_operand<KS>(stage, lane, An);
 #pragma unroll
         for (int m = 1; m < 5; ++m) {
             if (ex[m]) {
                 const int q = w + 4 * (m - 1);
-                const f32x4 AS = tile<KF, 4>(An, X[m]);
+                const f32x4 AS = tile<SF, KS>(An, X[m]);
                 const float wn = lds_w[w][m][n], ssn = lds_ss[w][m][n];
                 const float knn = ssn < 1e-24f ? sqrtf(ssn) * 1e12f : 1.f;
                 const float as = neg_cos(wn * sum3(AS), knn, ssq);
@@ -503,14 +543,15 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, const TileItem *__restri
 // a_s of the blocks whose workgroups did not wait for their unit's sum: the same operands (loaded in operand
 // layout directly), norms, split and product as in scan_tile_kernel, so the values are the ones it would have
 // stored.
-template <int KF>
-__global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(const uint8_t *__restrict__ keys, RowMap km,
+template <int KF, int KS, bool FULL>
+__global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(const uint8_t *__restrict__ keys, int d, RowMap km,
                                                                                PromptTab tab,
                                                                                const float *__restrict__ ssum,
                                                                                const uint32_t *__restrict__ sync,
                                                                                float *__restrict__ a_raw)
 {
-    constexpr int D = 128, NW = kTileWaves, kRowBytes = D * 2;
+    constexpr int D = 32 * KS, NW = kTileWaves, ES = key_bytes<KF>(), SF = kStaged<KF>;
+    const int dims = FULL ? D : d, row_bytes = dims * ES;
     __shared__ __attribute__((aligned(16))) uint8_t lds_stage[NW][kStageBytes];
     __shared__ __attribute__((aligned(16))) float lds_w[NW][kGroup], lds_ss[NW][kGroup];
     const int nblk = tab.blk_off[tab.n];
@@ -518,8 +559,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int qq = lane >> 4, n = lane & 15, g = qq, c = n;
     uint8_t *stage = lds_stage[w];
-    constexpr int kNoStore = 0x40000000;
-    const int off_q0 = qq == 0 ? 4 * n : kNoStore;
+    const int off_q0 = qq == 0 ? 4 * n : kNoByte;
     for (uint32_t i = blockIdx.x; i < count; i += gridDim.x) {
         const int id = (int)sync[kSyncWords + i], lh = id / nblk, blk = id - lh * nblk;
         const int p = prompt_of_block(tab, blk);
@@ -528,32 +568,34 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
         const int ng = (blk_hi - blk_lo + kGroup - 1) / kGroup;
         const int64_t row0 = (int64_t)lh * tab.T + tab.tok_off[p];
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint8_t *>(keys) + km.unit(lh, p, tab) * 2, 0, N * kRowBytes, 0x00020000);
+            const_cast<uint8_t *>(keys) + km.unit(lh, p, tab) * ES, 0, N * row_bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t out_s = __builtin_amdgcn_make_buffer_rsrc(a_raw + row0, 0, blk_hi * 4, 0x00020000);
         // every word of the unit's sum has been stored by now (the pass has ended)
-        float2 s2 = *reinterpret_cast<const float2 *>(ssum + ((int64_t)lh * tab.n + p) * D + 2 * lane);
+        float2 s2 = dim_pair<KS>(ssum + ((int64_t)lh * tab.n + p) * D, lane);
         if constexpr (KF == kKeyF16) { s2.x *= 0.25f; s2.y *= 0.25f; }   // as in scan_tile_kernel
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
         __builtin_amdgcn_wave_barrier();                              // the previous block's reads of the staged rows
-        stage_anchor<KF>(stage, 0, lane, s2.x, s2.y);
+        stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
         __builtin_amdgcn_wave_barrier();
-        u32x4 An[4];
-        read_operand(stage, lane, An);
+        u32x4 An[KS];
+        read_operand<KS>(stage, lane, An);
         for (int q = w; q < ng; q += 4) {
             const int tok0 = blk_lo + kGroup * q;
-            u32x4 raw[4], X[4];                                       // the group row-wise (norms) and as an operand
-            const int roff = (tok0 + 4 * g) * kRowBytes + 16 * c, off = (tok0 + n) * kRowBytes + 16 * qq;
+            u32x4 raw[4], X[KS];                                      // the group row-wise (norms) and as an operand
+            const int roff = (tok0 + 4 * g) * row_bytes + (8 * c < dims ? 8 * ES * c : kNoByte);
+            const int off = (tok0 + n) * row_bytes + 8 * ES * qq;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) raw[j] = row_load<KF>(rsrc, roff + j * kRowBytes);
+            for (int j = 0; j < 4; ++j) raw[j] = staged_piece<KF>(row_load<KF>(rsrc, roff + j * row_bytes));
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) X[kk] = row_load<KF>(rsrc, off + 64 * kk);
+            for (int kk = 0; kk < KS; ++kk)
+                X[kk] = staged_piece<KF>(row_load<KF>(rsrc, 32 * kk + 8 * qq < dims ? off + 32 * ES * kk : kNoByte));
             float ww[4];
-            group_norms<KF>(raw, tok0, blk_hi, g, c, lds_w[w], lds_ss[w], ww);
+            group_norms<SF>(raw, tok0, blk_hi, g, c, lds_w[w], lds_ss[w], ww);
             __builtin_amdgcn_wave_barrier();
             const float wn = lds_w[w][n], ss = lds_ss[w][n];
             __builtin_amdgcn_wave_barrier();                          // the next group rewrites them
             const float knn = ss < 1e-24f ? sqrtf(ss) * 1e12f : 1.f;
-            const f32x4 AS = tile<KF, 4>(An, X);
+            const f32x4 AS = tile<SF, KS>(An, X);
             const float as = neg_cos(wn * sum3(AS), knn, ssq);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + tok0 * 4, 0, 0);
         }
@@ -566,7 +608,7 @@ int resident_tile_workgroups()
     if (cached < 0) {
         int per_cu = 0, dev = 0;
         hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_tile_kernel<kKeyBF16>, 64 * kTileWaves, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_tile_kernel<kKeyBF16, 4, true>, 64 * kTileWaves, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
             return 0;
         cached = per_cu * prop.multiProcessorCount;
@@ -574,15 +616,48 @@ int resident_tile_workgroups()
     return cached;
 }
 
+// the launches of one call, in the instance that fits its keys
+struct TileLaunch {
+    const uint8_t *keys;
+    int d;
+    const RowMap &km;
+    const PromptTab &tab;
+    const TileItem *items;
+    unsigned n_items, n_deferred;
+    float *a_raw, *ssum;
+    unsigned long long *accum;
+    uint32_t *sync;
+    int64_t rows;
+    int poll_limit;
+    const Prof &prof;
+    hipStream_t st;
+
+    template <int KF, int KS, bool FULL> void run() const
+    {
+        prof.begin(NKV_KERNEL_SCAN, st);
+        scan_tile_kernel<KF, KS, FULL><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, ssum, sync, rows, poll_limit);
+        prof.end(NKV_KERNEL_SCAN, st);
+        deferred_stable_tile_kernel<KF, KS, FULL><<<n_deferred, 64 * kTileWaves, 0, st>>>(keys, d, km, tab, ssum, sync, a_raw);
+    }
+    template <int KF> void run_format() const
+    {
+        if (d == 128) run<KF, 4, true>();
+        else if (d > 96) run<KF, 4, false>();
+        else if (d > 64) run<KF, 3, false>();
+        else run<KF, 2, false>();                                     // (matches padded_dims)
+    }
+};
+
 }  // namespace
 
 bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, int LH)
 {
-    if ((dtype != NKV_DTYPE_BF16 && dtype != NKV_DTYPE_F16) || d != 128 || window != 64) return false;
+    // (head dim 64 stays with the vector formulation: half of the lanes of a row would hold nothing here)
+    if (dtype == NKV_DTYPE_F32 || d > 128 || d == 64 || window != 64) return false;
     int max_unit_blocks = 0;
     for (int p = 0; p < tab.n; ++p) {
         if (tab.b[p] > 256) return false;
-        if ((int64_t)(tab.tok_off[p + 1] - tab.tok_off[p] + 256) * d * 2 >= (1ll << 31)) return false;
+        if ((int64_t)(tab.tok_off[p + 1] - tab.tok_off[p] + 512) * d * 2 >= kNoByte) return false;
         max_unit_blocks = max(max_unit_blocks, tab.blk_off[p + 1] - tab.blk_off[p]);
     }
     const int64_t items = (int64_t)LH * (tab.blk_off[tab.n] + tab.n);
@@ -598,35 +673,23 @@ size_t tile_score_plan_bytes(int LH, const PromptTab &tab)
     return (size_t)fill_scan_plan(LH, tab, 1, &plan, false) * sizeof(TileItem);
 }
 
-hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int LH, const PromptTab &tab, float *a_raw,
+hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int LH, int d, const PromptTab &tab, float *a_raw,
                              void *accum, float *ssum, void *sync_area, void *plan_area, int mode, const Prof &prof,
                              hipStream_t st)
 {
-    constexpr int D = 128;
     const bool defer_all = mode == kScanDeferAll || mode == kScanRepairAll;   // no unit is added up by a workgroup of its own here
-    const size_t na = (size_t)LH * tab.n * D * 8 / 16;                        // accumulators, in 16-byte pieces
+    const size_t na = (size_t)LH * tab.n * padded_dims(d) * 8 / 16;           // accumulators, in 16-byte pieces
     ScanPlan plan;
     const unsigned n_items = fill_scan_plan(LH, tab, km.H, &plan, false);
     plan_kernel<<<(unsigned)min(((size_t)n_items + 255) / 256, (size_t)2048), 256, 0, st>>>(
         (TileItem *)plan_area, n_items, km, tab, plan, LH, (uint4 *)sync_area, kSyncWords / 4, (uint4 *)accum, na, (uint4 *)ssum,
         na / 2);
-    const unsigned n_deferred = defer_all ? 4096 : 256;
-    prof.begin(NKV_KERNEL_SCAN, st);
-    if (dtype == NKV_DTYPE_F16)
-        scan_tile_kernel<kKeyF16><<<n_items, 64 * kTileWaves, 0, st>>>((const uint8_t *)keys, (const TileItem *)plan_area, a_raw,
-                                                                      (unsigned long long *)accum, ssum, (uint32_t *)sync_area,
-                                                                      (int64_t)LH * tab.T, defer_all ? -1 : kPollLimit);
-    else
-        scan_tile_kernel<kKeyBF16><<<n_items, 64 * kTileWaves, 0, st>>>((const uint8_t *)keys, (const TileItem *)plan_area, a_raw,
-                                                                       (unsigned long long *)accum, ssum, (uint32_t *)sync_area,
-                                                                       (int64_t)LH * tab.T, defer_all ? -1 : kPollLimit);
-    prof.end(NKV_KERNEL_SCAN, st);
-    if (dtype == NKV_DTYPE_F16)
-        deferred_stable_tile_kernel<kKeyF16><<<n_deferred, 64 * kTileWaves, 0, st>>>((const uint8_t *)keys, km, tab, ssum,
-                                                                                    (const uint32_t *)sync_area, a_raw);
-    else
-        deferred_stable_tile_kernel<kKeyBF16><<<n_deferred, 64 * kTileWaves, 0, st>>>((const uint8_t *)keys, km, tab, ssum,
-                                                                                     (const uint32_t *)sync_area, a_raw);
+    const TileLaunch go{(const uint8_t *)keys, d, km, tab, (const TileItem *)plan_area, n_items, defer_all ? 4096u : 256u, a_raw,
+                        ssum, (unsigned long long *)accum, (uint32_t *)sync_area, (int64_t)LH * tab.T,
+                        defer_all ? -1 : kPollLimit, prof, st};
+    if (dtype == NKV_DTYPE_F16) go.run_format<kKeyF16>();
+    else if (dtype == NKV_DTYPE_F8_E4M3) go.run_format<kKeyF8>();
+    else go.run_format<kKeyBF16>();
     return hipGetLastError();
 }
 

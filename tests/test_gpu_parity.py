@@ -180,6 +180,20 @@ def test_vector_scan_where_the_matrix_core_scan_is_the_default(name, route):
     _report(f"vector {name} route={route}", st)
 
 
+@pytest.mark.parametrize("d,dtype", [(8, "bf16"), (32, "fp16"), (40, "bf16"), (72, "fp16"), (96, "fp16"), (96, "bf16"), (104, "bf16"),
+                                     (120, "fp16"), (16, "fp8"), (80, "fp8"), (112, "fp8"), (128, "fp8")])
+def test_matrix_core_scan_of_every_head_dim(d, dtype):
+    """Head dims around the steps of 32 that the matrix-core scan pads to, in each key format: blocks of one token, of
+    less than a group, of 128 and 200 tokens with ragged tails, against the oracle, and the two routes of the stable
+    anomaly against each other bit for bit."""
+    w = nkv_inputs.small_workload(f"tile_d{d}_{dtype}", 2, 2, d, [1, 777, 6401, 15], dtype=dtype, dv=32, n_out=0)
+    K, V = _kv(w)
+    compare_end_to_end(w, K, V, 0.5, label=w.name)
+    a, _ = run_gpu(w, K, V, 0.5)
+    b, _ = run_gpu(w, K, V, 0.5, params=nkv.params_default(flags=nkv.FLAG_DEFER_STABLE))
+    assert torch.equal(a.scores, b.scores)
+
+
 LIMITS = [
     # the most prompts, head dims, heads and (layer, head) pairs a call accepts
     ("prompts_64", 1, 2, 64, [61 + 37 * (i % 9) + 500 * (i % 3 == 0) for i in range(64)], "bf16", 0),
