@@ -252,6 +252,15 @@ template <int KS> __device__ __forceinline__ float2 dim_pair(const float *v, int
     return lane < 16 * KS ? t : make_float2(0.f, 0.f);
 }
 
+// The same of a unit's sum, which lies in the order of its accumulators: first the even dims, then the odd ones, so that
+// the 64 lanes of an atomic instruction add to consecutive words.
+template <int KS> __device__ __forceinline__ float2 sum_pair(const float *v, int lane)
+{
+    const int at = KS == 4 ? lane : min(lane, 16 * KS - 1);
+    const float2 t = make_float2(v[at], v[16 * KS + at]);
+    return KS == 4 || lane < 16 * KS ? t : make_float2(0.f, 0.f);
+}
+
 __device__ __forceinline__ float sum3(const f32x4 &d) { return (d[0] + d[1]) + d[2]; }
 
 // sum over this lane's four rows of wm[rho] * d[rho]
@@ -391,8 +400,8 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     unsigned long long after0 = 0ull, after1 = 0ull;                  // the accumulators right after this block's add
     if (poster && (KS == 4 || lane < D / 2)) {
         const unsigned long long t0 = accum_term(b0), t1 = accum_term(b1);
-        after0 = __hip_atomic_fetch_add(acc_unit + 2 * lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
-        after1 = __hip_atomic_fetch_add(acc_unit + 2 * lane + 1, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
+        after0 = __hip_atomic_fetch_add(acc_unit + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
+        after1 = __hip_atomic_fetch_add(acc_unit + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
     }
     bsq = sum_over_rows16(row_sum<16>(fmaf(b0, b0, b1 * b1)));
 
@@ -406,9 +415,9 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(S_unit, 0, D * 4, 0x00020000);
         // the last block to add to a word stores the word's final value; a word's adds take turns, so exactly one does
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(accum_value(after0)), prs,
-                                              accum_complete(after0, unblk) ? 8 * lane : kNoByte, 0, 16);
+                                              accum_complete(after0, unblk) ? 4 * lane : kNoByte, 0, 16);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(accum_value(after1)), prs,
-                                              accum_complete(after1, unblk) ? 8 * lane + 4 : kNoByte, 0, 16);
+                                              accum_complete(after1, unblk) ? 4 * lane + D * 2 : kNoByte, 0, 16);
     }
 
     // ---- every group through the staging rows into operand layout ----
@@ -519,7 +528,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     }
     __syncthreads();
     if (s_have != 0) {
-        float2 s2 = dim_pair<KS>(lds_S, lane);
+        float2 s2 = sum_pair<KS>(lds_S, lane);
         if constexpr (KF == kKeyF16) { s2.x *= 0.25f; s2.y *= 0.25f; }   // a sum over 65 536 unit vectors stays inside fp16's range; the cosine does not see the factor
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
         stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
@@ -571,7 +580,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
             const_cast<uint8_t *>(keys) + km.unit(lh, p, tab) * ES, 0, N * row_bytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t out_s = __builtin_amdgcn_make_buffer_rsrc(a_raw + row0, 0, blk_hi * 4, 0x00020000);
         // every word of the unit's sum has been stored by now (the pass has ended)
-        float2 s2 = dim_pair<KS>(ssum + ((int64_t)lh * tab.n + p) * D, lane);
+        float2 s2 = sum_pair<KS>(ssum + ((int64_t)lh * tab.n + p) * D, lane);
         if constexpr (KF == kKeyF16) { s2.x *= 0.25f; s2.y *= 0.25f; }   // as in scan_tile_kernel
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
         __builtin_amdgcn_wave_barrier();                              // the previous block's reads of the staged rows
