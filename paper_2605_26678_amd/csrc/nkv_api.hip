@@ -160,7 +160,7 @@ ScoreWs score_ws(const nkv_shape *s, const PromptTab &tab, bool with_a_raw)
     w.a_raw = off;  off += with_a_raw ? align_up(3 * rows * 4) : 0;
     w.rnorm = off;  off += align_up(rows * 4);
     w.bsum = off;   off += align_up(LH * tab.blk_off[tab.n] * padded_dims(s->d) * 4);
-    w.ssum = off;   off += align_up(LH * tab.n * padded_dims(s->d) * 8);                      // unit sums: fp32, or 64-bit accumulators
+    w.ssum = off;   off += align_up(tile_score_accum_bytes((int)LH, s->d, tab));   // unit sums: fp32, or 64-bit accumulators
     w.stats = off;  off += align_up(LH * tab.n * 3 * 4 * 4);                 // per unit and scale: min, 1/range, gap
     w.wide = off;   off += with_a_raw ? align_up(stats_wide_ws_bytes(s->L, s->H, tab)) : 0;
     w.total_bytes = off;

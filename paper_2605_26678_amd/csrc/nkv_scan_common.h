@@ -441,7 +441,9 @@ __device__ __forceinline__ void ensure_unit_sum(const float *bsum_unit, int unbl
 // the sum does not depend on the order the blocks arrive in, and nothing has to be ordered or fenced -- every
 // word says by itself whether it is complete.  Range: a component of a normalised key is at most 1, so
 // |total| <= 256 per block and |sum| < 2^20 for the at most 4095 blocks of a unit: 20 + 31 bits and the sign
-// above the 12 count bits fill the word exactly.
+// above the 12 count bits fill the word exactly.  (A unit of more blocks is added up in groups, see
+// nkv_score_tile.hip; what is left is |sum| <= tokens <= 2^20.)
+constexpr int kMaxUnitTokens = 1 << 20;
 constexpr int kCountBits = 12;
 constexpr int kMaxUnitBlocks = (1 << kCountBits) - 1;
 constexpr int kAccumFrac = 31;                   // fraction bits of the fixed-point sum
@@ -456,6 +458,8 @@ __device__ __forceinline__ unsigned long long accum_term(float v)
     return ((unsigned long long)q << kCountBits) + 1ull;
 }
 __device__ __forceinline__ bool accum_complete(unsigned long long a, int blocks) { return (int)(a & kMaxUnitBlocks) == blocks; }
+// a completed word as one contribution to the next level's word: the same sum, counted as one add
+__device__ __forceinline__ unsigned long long accum_single(unsigned long long a) { return (a & ~(unsigned long long)kMaxUnitBlocks) + 1ull; }
 // the sum, rounded once to fp32
 __device__ __forceinline__ float accum_value(unsigned long long a)
 {

@@ -143,6 +143,9 @@ template <int KF> __device__ __forceinline__ void split3(float x, uint32_t &hi, 
     lo = __float_as_uint(r2) >> 16;
 }
 
+// The factor that keeps a sum of N unit vectors inside fp16's range; the cosine does not see it.
+__device__ __forceinline__ float fp16_sum_scale(int N) { return N <= 131072 ? 0.25f : 0.03125f; }
+
 // A vector of which this lane holds dims 2 lane and 2 lane + 1, as the three terms of rows row0 .. row0 + 2
 // of a staged left operand.
 template <int KF> __device__ __forceinline__ void stage_anchor(uint8_t *stage, int row0, int lane, float v0, float v1)
@@ -269,6 +272,17 @@ __device__ __forceinline__ float weighted(const f32x4 &d, const float (&wm)[4])
     return fmaf(wm[3], d[3], fmaf(wm[2], d[2], fmaf(wm[1], d[1], wm[0] * d[0])));
 }
 
+// The blocks of a long unit add their totals up in two steps: 32 consecutive blocks into accumulators of their own, and
+// whoever completes a word of a group adds it to the unit's word.  Adds to one word take turns at the memory side, and
+// hundreds of blocks queueing for the same words hold up everything behind them.  Up to 192 blocks (49 152 tokens) the
+// unit is one group, whose words are the unit's: the second step costs more than the queue (8 heads, score call, one
+// step against two: 16 layers of 160 blocks 401 / 411 us, 16 layers of 256 blocks 688 / 640 us, 8 layers of 512 blocks
+// 812 / 700 us).
+constexpr int kOneGroup = 192, kGroupBlocks = 32;
+__host__ __device__ __forceinline__ int blocks_per_group(int unit_blocks) { return unit_blocks > kOneGroup ? kGroupBlocks : kOneGroup; }
+// first group slot of a prompt with `blocks` blocks and `prompts` prompts in front of it: every prompt rounds up by itself
+__host__ __device__ __forceinline__ int group_slots(int blocks, int prompts) { return blocks / kGroupBlocks + prompts; }
+
 // One item of the pass: a block of one (layer, head, prompt) unit with everything a workgroup needs to know about
 // it, worked out once by plan_kernel so that the pass itself starts an item with one scalar load instead of a
 // chain of dependent ones (kernel arguments, per-prompt tables, divisions).
@@ -277,10 +291,10 @@ struct TileItem {
     int64_t row0;                        // the unit's first row in the planes of a_raw
     int32_t N;                           // tokens of the unit; < 0: this slot of the die's queue is empty
     int32_t blk_lo, blk_hi;              // the block's tokens, unit-local
-    int32_t unit;                        // index of the unit's accumulators
-    int32_t unblk;                       // blocks of the unit
+    int32_t unit;                        // index of the unit's accumulators and sum
     int32_t id;                          // (layer, head) * blocks per head + block: what the deferred list holds
-    int32_t pad[2];
+    int32_t group;                       // index of the accumulators of the block's group
+    int32_t group_blocks, unit_groups;   // blocks of that group, groups of the unit
 };
 static_assert(sizeof(TileItem) == 48, "items are read as three 16-byte pieces");
 
@@ -303,12 +317,11 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
         const uint32_t t = (uint32_t)(k >> 3);
         const int len = plan.len[x];
         TileItem it;
-        it.pad[0] = it.pad[1] = 0;
         const int lh = len > 0 ? (int)(t / (uint32_t)len) : LH;
         if (lh >= LH) {
             it.key_off = it.row0 = 0;
             it.N = -1;
-            it.blk_lo = it.blk_hi = it.unit = it.unblk = it.id = 0;
+            it.blk_lo = it.blk_hi = it.unit = it.id = it.group = it.group_blocks = it.unit_groups = 0;
         } else {
             const int r = (int)(t - (uint32_t)lh * (uint32_t)len);
             const int blk = die_block(plan.run, x, r);
@@ -320,8 +333,12 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
             it.key_off = km.unit(lh, p, tab);
             it.row0 = (int64_t)lh * tab.T + tab.tok_off[p];
             it.unit = lh * tab.n + p;
-            it.unblk = tab.blk_off[p + 1] - tab.blk_off[p];
             it.id = lh * plan.nblk + blk;
+            const int unblk = tab.blk_off[p + 1] - tab.blk_off[p], local = blk - tab.blk_off[p];
+            const int per = blocks_per_group(unblk), gi = local / per;
+            it.group = lh * group_slots(plan.nblk, tab.n) + group_slots(tab.blk_off[p], p) + gi;
+            it.group_blocks = min(per, unblk - gi * per);
+            it.unit_groups = (unblk + per - 1) / per;
         }
         items[k] = it;
     }
@@ -333,7 +350,7 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
 // KS: head dims the pass works with, in steps of 32 (the rest of the last step reads as zeros); FULL: d = 32 KS.
 template <int KF, int KS, bool FULL> __global__ __launch_bounds__(64 * kTileWaves, 4)
 void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *__restrict__ items, float *__restrict__ a_raw,
-                      unsigned long long *__restrict__ acc, float *__restrict__ ssum, uint32_t *__restrict__ sync, int64_t rows,
+                      unsigned long long *__restrict__ acc, unsigned long long *__restrict__ acc_group, float *__restrict__ ssum, uint32_t *__restrict__ sync, int64_t rows,
                       int poll_limit)
 {
     constexpr int D = 32 * KS, NW = kTileWaves, ES = key_bytes<KF>(), SF = kStaged<KF>;
@@ -352,7 +369,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     const int qq = g, n = c;                                          // operand / result layout: token n, quarter qq
     uint8_t *stage = lds_stage[w];
 
-    const int N = it.N, blk_lo = it.blk_lo, blk_hi = it.blk_hi, unblk = it.unblk;
+    const int N = it.N, blk_lo = it.blk_lo, blk_hi = it.blk_hi;
     const int ng = (blk_hi - blk_lo + kGroup - 1) / kGroup;           // groups of the block, <= 16
     const int64_t row0 = it.row0;                                     // row of the prompt's token 0
 
@@ -389,7 +406,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     __syncthreads();
 
     // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1 ----
-    unsigned long long *acc_unit = acc + (int64_t)it.unit * D;
+    unsigned long long *acc_mine = acc_group + (int64_t)it.group * D;
     float bsq, b0 = 0.f, b1 = 0.f;
     for (int q = 0; q < ng; ++q) {
         const float2 t2 = dim_pair<KS>(lds_T[4 + q], lane);
@@ -400,8 +417,8 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     unsigned long long after0 = 0ull, after1 = 0ull;                  // the accumulators right after this block's add
     if (poster && (KS == 4 || lane < D / 2)) {
         const unsigned long long t0 = accum_term(b0), t1 = accum_term(b1);
-        after0 = __hip_atomic_fetch_add(acc_unit + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
-        after1 = __hip_atomic_fetch_add(acc_unit + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
+        after0 = __hip_atomic_fetch_add(acc_mine + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
+        after1 = __hip_atomic_fetch_add(acc_mine + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
     }
     bsq = sum_over_rows16(row_sum<16>(fmaf(b0, b0, b1 * b1)));
 
@@ -411,13 +428,27 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     group_sum<SF, KS>(row[0], blk_lo + kGroup * (w - 4), blk_hi, g, c, lds_w[w][0], lds_ss[w][0], lds_T[w]);
 
     float *S_unit = ssum + (int64_t)it.unit * D;
-    if (poster) {                                                     // (the adds have had the halo group to come back)
-        const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(S_unit, 0, D * 4, 0x00020000);
-        // the last block to add to a word stores the word's final value; a word's adds take turns, so exactly one does
+    // (The adds have had the halo group to come back.)  The last block to add to a word of the unit stores the word's final
+    // value, the last block of a group adds its word's to the unit's word: a word's adds take turns, so exactly one does.
+    const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(S_unit, 0, D * 4, 0x00020000);
+    auto store_complete = [&](int adds) {
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(accum_value(after0)), prs,
-                                              accum_complete(after0, unblk) ? 4 * lane : kNoByte, 0, 16);
+                                              accum_complete(after0, adds) ? 4 * lane : kNoByte, 0, 16);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(accum_value(after1)), prs,
-                                              accum_complete(after1, unblk) ? 4 * lane + D * 2 : kNoByte, 0, 16);
+                                              accum_complete(after1, adds) ? 4 * lane + D * 2 : kNoByte, 0, 16);
+    };
+    const bool grouped = it.unit_groups > 1;
+    if (poster) {
+        if (!grouped) {
+            store_complete(it.group_blocks);
+        } else {
+            unsigned long long *acc_unit = acc + (int64_t)it.unit * D;
+            const bool last0 = accum_complete(after0, it.group_blocks), last1 = accum_complete(after1, it.group_blocks);
+            const unsigned long long t0 = accum_single(after0), t1 = accum_single(after1);
+            after0 = after1 = 0ull;
+            if (last0) after0 = __hip_atomic_fetch_add(acc_unit + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
+            if (last1) after1 = __hip_atomic_fetch_add(acc_unit + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
+        }
     }
 
     // ---- every group through the staging rows into operand layout ----
@@ -432,6 +463,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
             __builtin_amdgcn_wave_barrier();                          // the next group reuses the staging rows
         }
     }
+    if (poster && grouped) store_complete(it.unit_groups);            // (the second adds have had the staging to come back)
     stage_anchor<SF>(stage, 4, lane, b0, b1);                             // rows 4 .. 6: the block total's three terms
     __syncthreads();                                                  // the halo groups' sums
     // ---- the chain of this wave's groups ----
@@ -529,7 +561,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     __syncthreads();
     if (s_have != 0) {
         float2 s2 = sum_pair<KS>(lds_S, lane);
-        if constexpr (KF == kKeyF16) { s2.x *= 0.25f; s2.y *= 0.25f; }   // a sum over 65 536 unit vectors stays inside fp16's range; the cosine does not see the factor
+        if constexpr (KF == kKeyF16) { s2.x *= fp16_sum_scale(N); s2.y *= fp16_sum_scale(N); }
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
         stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
         __builtin_amdgcn_wave_barrier();
@@ -581,7 +613,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
         const __amdgpu_buffer_rsrc_t out_s = __builtin_amdgcn_make_buffer_rsrc(a_raw + row0, 0, blk_hi * 4, 0x00020000);
         // every word of the unit's sum has been stored by now (the pass has ended)
         float2 s2 = sum_pair<KS>(ssum + ((int64_t)lh * tab.n + p) * D, lane);
-        if constexpr (KF == kKeyF16) { s2.x *= 0.25f; s2.y *= 0.25f; }   // as in scan_tile_kernel
+        if constexpr (KF == kKeyF16) { s2.x *= fp16_sum_scale(N); s2.y *= fp16_sum_scale(N); }   // as in scan_tile_kernel
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
         __builtin_amdgcn_wave_barrier();                              // the previous block's reads of the staged rows
         stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
@@ -634,7 +666,7 @@ struct TileLaunch {
     const TileItem *items;
     unsigned n_items, n_deferred;
     float *a_raw, *ssum;
-    unsigned long long *accum;
+    unsigned long long *accum, *accum_group;
     uint32_t *sync;
     int64_t rows;
     int poll_limit;
@@ -644,7 +676,7 @@ struct TileLaunch {
     template <int KF, int KS, bool FULL> void run() const
     {
         prof.begin(NKV_KERNEL_SCAN, st);
-        scan_tile_kernel<KF, KS, FULL><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, ssum, sync, rows, poll_limit);
+        scan_tile_kernel<KF, KS, FULL><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, accum_group, ssum, sync, rows, poll_limit);
         prof.end(NKV_KERNEL_SCAN, st);
         deferred_stable_tile_kernel<KF, KS, FULL><<<n_deferred, 64 * kTileWaves, 0, st>>>(keys, d, km, tab, ssum, sync, a_raw);
     }
@@ -663,17 +695,21 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
 {
     // (head dim 64 stays with the vector formulation: half of the lanes of a row would hold nothing here)
     if (dtype == NKV_DTYPE_F32 || d > 128 || d == 64 || window != 64) return false;
-    int max_unit_blocks = 0;
     for (int p = 0; p < tab.n; ++p) {
-        if (tab.b[p] > 256) return false;
-        if ((int64_t)(tab.tok_off[p + 1] - tab.tok_off[p] + 512) * d * 2 >= kNoByte) return false;
-        max_unit_blocks = max(max_unit_blocks, tab.blk_off[p + 1] - tab.blk_off[p]);
+        const int N = tab.tok_off[p + 1] - tab.tok_off[p];
+        if (tab.b[p] > 256 || N > kMaxUnitTokens) return false;
+        if ((int64_t)(N + 512) * d * 2 >= kNoByte) return false;
     }
-    const int64_t items = (int64_t)LH * (tab.blk_off[tab.n] + tab.n);
-    // A unit's blocks have to be resident together, and from a quarter of the chip's resident workgroups per unit on
-    // (prompts of more than 65 536 tokens) the vector formulation, three workgroups per CU and no returning atomics in
-    // front of a barrier, copes better with workgroups that wait for their unit (131 072 tokens: 4.2 against 4.8 ms).
-    return items < (1ll << 28) && max_unit_blocks <= min(resident_tile_workgroups() / 4, kMaxUnitBlocks);
+    return (int64_t)LH * (tab.blk_off[tab.n] + tab.n) < (1ll << 28);
+}
+
+// Do the blocks of every unit fit the chip together?  If not, nobody looks for a unit's sum and all blocks take the
+// deferred route.
+static bool units_fit(const PromptTab &tab)
+{
+    int most = 0;
+    for (int p = 0; p < tab.n; ++p) most = max(most, tab.blk_off[p + 1] - tab.blk_off[p]);
+    return most <= resident_tile_workgroups();
 }
 
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab)
@@ -682,19 +718,26 @@ size_t tile_score_plan_bytes(int LH, const PromptTab &tab)
     return (size_t)fill_scan_plan(LH, tab, 1, &plan, false) * sizeof(TileItem);
 }
 
+size_t tile_score_accum_bytes(int LH, int d, const PromptTab &tab)
+{
+    return (size_t)LH * (tab.n + group_slots(tab.blk_off[tab.n], tab.n)) * padded_dims(d) * 8;
+}
+
 hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int LH, int d, const PromptTab &tab, float *a_raw,
                              void *accum, float *ssum, void *sync_area, void *plan_area, int mode, const Prof &prof,
                              hipStream_t st)
 {
-    const bool defer_all = mode == kScanDeferAll || mode == kScanRepairAll;   // no unit is added up by a workgroup of its own here
-    const size_t na = (size_t)LH * tab.n * padded_dims(d) * 8 / 16;           // accumulators, in 16-byte pieces
+    // (no unit is added up by a workgroup of its own here)
+    const bool defer_all = mode == kScanDeferAll || mode == kScanRepairAll || !units_fit(tab);
+    const size_t nu = (size_t)LH * tab.n * padded_dims(d) * 8 / 16;           // the units' accumulators, in 16-byte pieces
+    const size_t na = tile_score_accum_bytes(LH, d, tab) / 16;                // theirs, and the groups' behind them
     ScanPlan plan;
     const unsigned n_items = fill_scan_plan(LH, tab, km.H, &plan, false);
     plan_kernel<<<(unsigned)min(((size_t)n_items + 255) / 256, (size_t)2048), 256, 0, st>>>(
         (TileItem *)plan_area, n_items, km, tab, plan, LH, (uint4 *)sync_area, kSyncWords / 4, (uint4 *)accum, na, (uint4 *)ssum,
-        na / 2);
+        nu / 2);
     const TileLaunch go{(const uint8_t *)keys, d, km, tab, (const TileItem *)plan_area, n_items, defer_all ? 4096u : 256u, a_raw,
-                        ssum, (unsigned long long *)accum, (uint32_t *)sync_area, (int64_t)LH * tab.T,
+                        ssum, (unsigned long long *)accum, (unsigned long long *)accum + nu * 2, (uint32_t *)sync_area, (int64_t)LH * tab.T,
                         defer_all ? -1 : kPollLimit, prof, st};
     if (dtype == NKV_DTYPE_F16) go.run_format<kKeyF16>();
     else if (dtype == NKV_DTYPE_F8_E4M3) go.run_format<kKeyF8>();

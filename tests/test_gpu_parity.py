@@ -194,6 +194,16 @@ def test_matrix_core_scan_of_every_head_dim(d, dtype):
     assert torch.equal(a.scores, b.scores)
 
 
+@pytest.mark.parametrize("d,dtype,N", [(32, "fp16", 49153), (16, "bf16", 262145), (8, "fp16", 270001)])
+def test_matrix_core_scan_of_long_units(d, dtype, N):
+    """Units whose block totals are added up in two steps (from 193 blocks on) and units of more blocks than the chip
+    holds at once (more than 1024: every block takes the deferred route); 270 001 aligned fp16 keys also need the
+    smaller factor of the unit's sum."""
+    w = nkv_inputs.small_workload(f"long_{d}_{N}", 1, 1, d, [N, 300], dtype=dtype, n_out=0)
+    K, V = _kv(w)
+    compare_end_to_end(w, K, V, 0.9, label=w.name)
+
+
 LIMITS = [
     # the most prompts, head dims, heads and (layer, head) pairs a call accepts
     ("prompts_64", 1, 2, 64, [61 + 37 * (i % 9) + 500 * (i % 3 == 0) for i in range(64)], "bf16", 0),
