@@ -44,12 +44,7 @@ template <bool TOP> __device__ __forceinline__ void block_pick(SelectScratch &s,
     uint32_t c[PER], group = 0u;
 #pragma unroll
     for (int q = 0; q < PER; ++q) { c[q] = s.hist[tid * PER + q]; group += c[q]; }
-    uint32_t incl = group;                                           // inclusive sum towards the scan direction
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = TOP ? __shfl_down(incl, o, 64) : __shfl_up(incl, o, 64);
-        if (TOP ? lane + o < 64 : lane >= o) incl += t;
-    }
+    uint32_t incl = TOP ? wave_suffix_sum(group) : wave_prefix_sum(group);                                          // inclusive sum towards the scan direction
     if (lane == (TOP ? 0 : 63)) s.wsum[w] = incl;
     __syncthreads();
     if (TOP) { for (int ww = w + 1; ww < kSelThreads / 64; ++ww) incl += s.wsum[ww]; }
@@ -85,12 +80,9 @@ __device__ __forceinline__ void block_key_range(const uint32_t (&key)[EPT], int 
         for (int j = 0; j < EPT; ++j)
             if ((int)threadIdx.x + j * kSelThreads < n) { lo = min(lo, key[j]); hi = max(hi, key[j]); }
     }
-    uint32_t nlo = ~lo;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        nlo = max(nlo, (uint32_t)__shfl_xor((int)nlo, o, 64));
-        hi = max(hi, (uint32_t)__shfl_xor((int)hi, o, 64));
-    }
+    auto larger = [](uint32_t x, uint32_t y) { return max(x, y); };
+    const uint32_t nlo = wave_reduce(~lo, larger);
+    hi = wave_reduce(hi, larger);
     if ((threadIdx.x & 63) == 0) { s.red[threadIdx.x >> 6] = nlo; s.wsum[threadIdx.x >> 6] = hi; }
     __syncthreads();
     uint32_t a = s.red[0], b = s.wsum[0];

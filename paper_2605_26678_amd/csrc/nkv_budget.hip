@@ -115,12 +115,7 @@ __device__ __forceinline__ void block_pick_top(const uint32_t *hist, uint32_t wa
     uint32_t c[PER], group = 0u;
 #pragma unroll
     for (int q = 0; q < PER; ++q) { c[q] = hist[tid * PER + q]; group += c[q]; }
-    uint32_t incl = group;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += t;
-    }
+    uint32_t incl = wave_suffix_sum(group);
     if (lane == 0) wsum[w] = incl;
     __syncthreads();
     for (int ww = w + 1; ww < kThreads / 64; ++ww) incl += wsum[ww];

@@ -37,11 +37,7 @@ __device__ __forceinline__ uint32_t pick_from_top(uint32_t mine, uint32_t &want,
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     uint32_t incl = tid < 256 ? mine : 0u;                           // this bin and the wave's higher ones
     if (tid < 256) {
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_down(incl, o, 64);
-            if (lane + o < 64) incl += t;
-        }
+        incl = wave_suffix_sum(incl);
         if (lane == 0) scratch[w] = incl;
     }
     if (tid == 0) scratch[4] = 0u;                                   // bin 0 unless a higher bin claims the rank

@@ -46,12 +46,7 @@ struct LayerPick {
 __device__ __forceinline__ uint32_t scan_from_top(uint32_t group, uint32_t *wsum)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t incl = group;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += t;
-    }
+    uint32_t incl = wave_suffix_sum(group);
     if (lane == 0) wsum[w] = incl;
     return incl;                                                     // inclusive within the wave; add the waves above
 }

@@ -103,12 +103,7 @@ __global__ __launch_bounds__(1024) void decode_plan_kernel(const int64_t *__rest
     }
     // exclusive scan of the 1024 per-thread counts: inside every wave by shuffles, then over the 16 wave totals
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int32_t incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
+    const int32_t incl = (int32_t)wave_prefix_sum((uint32_t)mine);
     if (lane == 63) sums[wv] = incl;
     __syncthreads();
     int32_t before = 0, total = 0;

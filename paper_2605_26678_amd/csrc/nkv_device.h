@@ -66,23 +66,87 @@ __device__ __forceinline__ int prompt_of_block(const PromptTab &tab, int blk)
     return p;
 }
 
+// ---- reductions and scans over a whole wavefront: cross-lane data paths of the vector unit only (DPP inside rows of 16
+// lanes, permlane swaps between them), which answer in a few cycles where a shuffle through the LDS crossbar takes a
+// hundred.  All 64 lanes must be active. ----
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_word(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+}
+// the value of the lane that CTRL pairs this lane with, for 4- and 8-byte types
+template <int CTRL, typename T> __device__ __forceinline__ T dpp_partner(T v)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "4- or 8-byte types");
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, dpp_word<CTRL>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        return __builtin_bit_cast(T, (unsigned long long)dpp_word<CTRL>((uint32_t)(u >> 32)) << 32 | dpp_word<CTRL>((uint32_t)u));
+    }
+}
+// op over the lanes that differ in bit 4 (ROWS = 16) or bit 5 (ROWS = 32) of the lane index
+template <int ROWS, typename T, typename Op> __device__ __forceinline__ T swap_reduce(T v, Op op)
+{
+    auto swap = [](uint32_t u, uint32_t &x, uint32_t &y) {
+        if constexpr (ROWS == 16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+            x = r[0];
+            y = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+            x = r[0];
+            y = r[1];
+        }
+    };
+    uint32_t x, y;
+    if constexpr (sizeof(T) == 4) {
+        swap(__builtin_bit_cast(uint32_t, v), x, y);
+        return op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+    } else {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        uint32_t xh, yh;
+        swap((uint32_t)u, x, y);
+        swap((uint32_t)(u >> 32), xh, yh);
+        return op(__builtin_bit_cast(T, (unsigned long long)xh << 32 | x), __builtin_bit_cast(T, (unsigned long long)yh << 32 | y));
+    }
+}
+template <typename T, typename Op> __device__ __forceinline__ T wave_reduce(T v, Op op)
+{
+    v = op(v, dpp_partner<0xB1>(v));             // quad_perm [1,0,3,2]
+    v = op(v, dpp_partner<0x4E>(v));             // quad_perm [2,3,0,1]
+    v = op(v, dpp_partner<0x141>(v));            // row_half_mirror: the other quad of the 8-lane half
+    v = op(v, dpp_partner<0x140>(v));            // row_mirror: the other half of the 16-lane row
+    v = swap_reduce<16>(v, op);
+    return swap_reduce<32>(v, op);
+}
 template <typename T> __device__ __forceinline__ T wave_sum(T v)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    return wave_reduce(v, [](T a, T b) { return a + b; });
 }
 __device__ __forceinline__ float wave_min(float v)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, kWave));
-    return v;
+    return wave_reduce(v, [](float a, float b) { return fminf(a, b); });
 }
 __device__ __forceinline__ float wave_max(float v)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
+    return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
+}
+
+// inclusive sum over the lanes up to / from this one
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);    // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);    // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);    // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);    // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_suffix_sum(uint32_t x)
+{
+    const uint32_t incl = wave_prefix_sum(x);
+    return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl + x;
 }
 
 // Block-wide reductions for blockDim.x a multiple of 64 and <= 1024.  `scratch` holds >= 16 elements.

@@ -122,12 +122,7 @@ __global__ __launch_bounds__(kWideThreads) void stats_pick_kernel(int L, int H, 
     uint32_t group = 0u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) group += c[i];
-    uint32_t incl = group;                                           // inclusive prefix from bin 0 upwards
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
+    uint32_t incl = wave_prefix_sum(group);                                           // inclusive prefix from bin 0 upwards
     if (lane == 63) wtot[w] = incl;
     __syncthreads();
     for (int ww = 0; ww < w; ++ww) incl += wtot[ww];

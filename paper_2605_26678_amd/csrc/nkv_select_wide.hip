@@ -68,12 +68,7 @@ __device__ __forceinline__ SelPick pick_boundary_bin(const uint16_t *__restrict_
     uint32_t group = 0u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) group += c[i];
-    uint32_t incl = group;                                           // inclusive sum from the top bin downwards
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += t;
-    }
+    uint32_t incl = wave_suffix_sum(group);                                           // inclusive sum from the top bin downwards
     if (lane == 0) wtot[w] = incl;
     __syncthreads();
     for (int ww = w + 1; ww < kWideThreads / 64; ++ww) incl += wtot[ww];
@@ -311,13 +306,7 @@ __global__ __launch_bounds__(kWideThreads) void sel_compact_kernel(const float *
             tg += g[q];
             te += e[q];
         }
-        uint32_t ig = tg, ie = te;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t a = __shfl_up(ig, o, 64), b = __shfl_up(ie, o, 64);
-            if (lane >= o) { ig += a; ie += b; }
-        }
-        uint32_t rg = ig - tg, re = ie - te;
+        uint32_t rg = wave_prefix_sum(tg) - tg, re = wave_prefix_sum(te) - te;
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             cnt_gt[lane * PER + q] = rg;

@@ -25,12 +25,7 @@ __device__ __forceinline__ uint32_t wave_select_fn(int n, uint32_t want, uint32_
         // lane owns digits 4 lane .. 4 lane + 3; running count from the top
         const uint32_t c0 = hist[lane * 4], c1 = hist[lane * 4 + 1], c2 = hist[lane * 4 + 2], c3 = hist[lane * 4 + 3];
         const uint32_t group = c0 + c1 + c2 + c3;
-        uint32_t incl = group;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_down(incl, o, 64);
-            if (lane + o < 64) incl += t;
-        }
+        const uint32_t incl = wave_suffix_sum(group);
         const uint32_t cum = incl - group;
         uint32_t dig = 0u, below = 0u;
         const bool mine = cum < want && want <= incl;
@@ -42,8 +37,8 @@ __device__ __forceinline__ uint32_t wave_select_fn(int n, uint32_t want, uint32_
         }
         const unsigned long long who = __ballot(mine);
         const int src = __ffsll((long long)who) - 1;
-        dig = (uint32_t)__shfl((int)dig, src, 64);
-        below = (uint32_t)__shfl((int)below, src, 64);
+        dig = (uint32_t)__builtin_amdgcn_readlane((int)dig, src);
+        below = (uint32_t)__builtin_amdgcn_readlane((int)below, src);
         want -= below;
         prefix |= dig << shift;
         __builtin_amdgcn_wave_barrier();
@@ -59,10 +54,27 @@ __device__ __forceinline__ uint32_t wave_select_fn(int n, uint32_t want, uint32_
     return prefix;
 }
 
+// The same for n <= 64 keys, one per lane (lanes from n on are ignored): every lane ranks its key against all others.
+__device__ __forceinline__ uint32_t wave_select_64(uint32_t mine, int n, uint32_t want, uint32_t &gt, uint32_t &eq)
+{
+    uint32_t beyond = 0u, equal = 0u;
+    for (int i = 0; i < n; ++i) {
+        const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+        beyond += other > mine ? 1u : 0u;
+        equal += other == mine ? 1u : 0u;
+    }
+    const bool it = (int)(threadIdx.x & 63) < n && beyond < want && want <= beyond + equal;   // lanes of equal keys
+    const int src = __ffsll((long long)__ballot(it)) - 1;
+    gt = (uint32_t)__builtin_amdgcn_readlane((int)beyond, src);
+    eq = (uint32_t)__builtin_amdgcn_readlane((int)equal, src);
+    return (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
+}
+
 // The same over an array (LDS or memory).
 __device__ __forceinline__ uint32_t wave_select(const uint32_t *key, int n, uint32_t want, uint32_t *hist,
                                                 uint32_t &gt, uint32_t &eq)
 {
+    if (n <= 64) return wave_select_64((int)(threadIdx.x & 63) < n ? key[threadIdx.x & 63] : 0u, n, want, gt, eq);
     return wave_select_fn(n, want, hist, gt, eq, [key](int i) { return key[i]; });
 }
 
