@@ -1,18 +1,22 @@
 // Outer learner: from the three raw anomalies of a head to its final scores
 // (paper Section 2.3 min-max, Section 2.4 reliability gaps / blend / surprise / gate, sink pinning).
 //
-// One workgroup of 1024 threads per unit (prompt, layer, head).  The head's 3*N floats (384 KB at
-// N = 32768) stay resident in L2 while the workgroup walks them seven times:
-//   pass 1      min / max of each scale
-//   pass 2..5   byte-wise radix select (most significant digit first) of the m_p-th largest and the
-//               m_p-th smallest value of each scale, six selects at once in LDS histograms
-//   pass 6      sums above / below those thresholds (fp64), and min / max / sum of the surprise
-//   pass 7      blend, gate, route, pin, write
+//   finalize_unit_kernel  prompts of up to 16384 tokens: one workgroup of 1024 threads per unit (prompt, layer, head),
+//                         values in registers, one launch
+//   nkv_finalize_wide.hip longer prompts: slice by slice over the whole chip
+//   finalize_kernel       longer prompts where the caller asks for per-head kernels: one workgroup of 1024 threads per
+//                         unit walks the head's values in memory seven times:
+//     pass 1      min / max of each scale
+//     pass 2..5   byte-wise radix select (most significant digit first) of the m_p-th largest and the
+//                 m_p-th smallest value of each scale, six selects at once in LDS histograms
+//     pass 6      sums above / below those thresholds (fp64), and min / max / sum of the surprise
+//     pass 7      blend, gate, route, pin, write
 // The sum of the m largest values is  sum(a > T) + (m - count(a > T)) * T  with T the m-th largest,
 // which does not depend on how ties at T are broken.  Min-max is affine and increasing, so the
 // selects run on the raw anomalies and the gap is rescaled afterwards.
 #include "nkv_blocksel.h"
 #include "nkv_learner.h"
+#include "nkv_slices.h"
 
 namespace nkv {
 namespace {
@@ -160,143 +164,223 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const float *__restr
 
 
 // ------------------------------------------------------------------------------------------------------
-// Units of up to 1024 * EPT tokens: two kernels with the values held in registers.
-//   scale_stats_kernel : one workgroup per (unit, scale): min, max and the reliability gap of that scale
-//   route_kernel       : one workgroup per unit: weights, surprise statistics, routed score, pinning
+// Units of up to 1024 * EPT tokens: everything in one launch, the three anomalies of a token in registers from the only
+// read of them to the routed score.  One workgroup of 1024 threads per unit.
+//
+// A short unit's arithmetic is small and what takes time is the chain of dependent steps, so there are few of them (as
+// two kernels of radix selects, one workgroup per scale, 16 x 8 units of 4096 tokens took 33 us, this takes 11):
+//   1. histograms of the three scales over the fixed range of a cosine (2048 bins), min and max of each;
+//   2. one scan per scale gives the bins that hold the m-th largest and the m-th smallest value;
+//   3. sums beyond those bins, their entries into six lists; surprise statistics (the ranges are known);
+//   4. six wavefronts find the exact thresholds in the lists, another one adds the surprise up;
+//   5. weights; blend, gate, route, pin.
+// Same numbers as the slice-wise kernels (the sums over a boundary bin's entries in fixed point: independent of the
+// order the entries arrive in).  A list that overflows (more than 1024 equal or nearly equal values) sends its wavefront
+// over the unit's values in memory.
 // ------------------------------------------------------------------------------------------------------
-// stats[(u * 3 + k) * 4 + {0, 1, 2}] = min, 1 / range (0 if flat), reliability gap of scale k of unit u
-template <int EPT>
-__global__ __launch_bounds__(kSelThreads, EPT <= 16 ? 8 : 4) void scale_stats_kernel(const float *__restrict__ a_raw, int L, int H,
-                                                                   PromptTab tab, int u0,
-                                                                   float *__restrict__ stats)
-{
-    __shared__ SelectScratch sel;
-    __shared__ double dscratch[32];
-    const int k = blockIdx.x, u = u0 + blockIdx.y;
-    const int h = u % H, l = (u / H) % L, p = u / (H * L);
-    const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-    const int64_t rows = (int64_t)L * H * tab.T;
-    const float *a = a_raw + (int64_t)k * rows + ((int64_t)l * H + h) * tab.T + tab.tok_off[p];
-    const int tid = threadIdx.x;
+constexpr int kUnitList = 1024;              // keys a list holds
 
-    uint32_t key[EPT];
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-        const int i = tid + j * kSelThreads;
-        const float v = a[min(i, N - 1)];                      // unconditional: the loads of a thread pipeline
-        key[j] = i < N ? ord_key(v) : 0u;
-    }
-    // Warm the L2 of this die for the workgroup that will follow on this compute unit: only one workgroup of
-    // this size fits a compute unit, so nothing else overlaps its load phase with this one's arithmetic.
-    // Workgroups go to the dies round-robin, so the one 256 places further on lands on this die again.
-    {
-        const int id = blockIdx.y * 3 + blockIdx.x + 256, kn = id % 3, un = u0 + id / 3;
-        if (un < u0 + (int)gridDim.y) {
-            const int hn = un % H, ln = (un / H) % L, pn = un / (H * L);
-            const int Nn = tab.tok_off[pn + 1] - tab.tok_off[pn];
-            const float *an = a_raw + (int64_t)kn * rows + ((int64_t)ln * H + hn) * tab.T + tab.tok_off[pn];
-            if (tid * 32 < Nn) (void)*(const volatile float *)(an + tid * 32);   // one word per 128-byte line
-        }
-    }
-    uint32_t kmin, kmax;
-    block_key_range<EPT>(key, N, sel, kmin, kmax);
-    const uint32_t m = (uint32_t)min(tab.m_p[p], N);
-    uint32_t rem_top, rem_bot, t_top, t_bot;
-    block_select_both<EPT>(key, N, m, sel, kmin, kmax, t_top, rem_top, t_bot, rem_bot);
-    // sums beyond the thresholds: per thread in fp32 (a handful of terms of magnitude <= 1), across the
-    // workgroup in fp64
-    float p_top = 0.f, p_bot = 0.f;
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-        const bool in = N == EPT * kSelThreads || tid + j * kSelThreads < N;
-        const float v = key_value(key[j]);
-        p_top += in && key[j] > t_top ? v : 0.f;
-        p_bot += in && key[j] < t_bot ? v : 0.f;
-    }
-    double s_top = wave_sum((double)p_top), s_bot = wave_sum((double)p_bot);
-    if ((tid & 63) == 0) { dscratch[tid >> 6] = s_top; dscratch[16 + (tid >> 6)] = s_bot; }
-    __syncthreads();
-    if (tid == 0) {
-        s_top = 0.0;
-        s_bot = 0.0;
-        for (int i = 0; i < kSelThreads / 64; ++i) { s_top += dscratch[i]; s_bot += dscratch[16 + i]; }
-        const float lo = key_value(kmin), range = key_value(kmax) - lo;
-        const float inv = range < kFlat ? 0.f : 1.0f / range;
-        // ties at the threshold: rem of them belong to the set
-        const double top = s_top + (double)rem_top * (double)key_value(t_top);
-        const double bot = s_bot + (double)rem_bot * (double)key_value(t_bot);
-        float *o = stats + ((int64_t)u * 3 + k) * 4;
-        o[0] = lo;
-        o[1] = inv;
-        o[2] = (float)((top - bot) / (double)m * (double)inv);
-    }
-}
-
-__global__ __launch_bounds__(kSelThreads) void route_kernel(const float *__restrict__ a_raw, int L, int H,
-                                                            PromptTab tab, LearnerConsts lc,
-                                                            const float *__restrict__ stats,
-                                                            float *__restrict__ scores)
+template <int EPT, bool ALL>
+__global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_kernel(const float *__restrict__ a_raw, int L, int H,
+                                                                                      PromptTab tab, int u0, LearnerConsts lc,
+                                                                                      float *__restrict__ scores)
 {
-    __shared__ float fscratch[16];
-    __shared__ double dscratch[16];
+    constexpr int NW = kSelThreads / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t buf[3 * kBins];  // the histograms, then the lists
+    __shared__ uint32_t whist[6][256];
+    __shared__ uint32_t ext[6];                  // per scale: max of ~key and of key = ~min, max as ordered integers
+    __shared__ uint32_t wtot[3][NW];
+    __shared__ int bin[6];                       // list 2k: upper boundary bin of scale k, 2k + 1: lower
+    __shared__ uint32_t need[6], cnt[6];
+    __shared__ double sums[7][NW];               // beyond the boundary bins, per wavefront; the surprise
+    __shared__ float sext[2][NW];
+    __shared__ double side[6];
     __shared__ HeadStats hs;
-    const int u = blockIdx.x;
+    static_assert(6 * kUnitList <= 3 * kBins, "the lists lie where the histograms were");
+
+    const int u = u0 + blockIdx.x;
     const int h = u % H, l = (u / H) % L, p = u / (H * L);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
     const int64_t rows = (int64_t)L * H * tab.T;
     const int64_t base = ((int64_t)l * H + h) * tab.T + tab.tok_off[p];
-    const float *a0 = a_raw + base, *a1 = a_raw + rows + base, *a2 = a_raw + 2 * rows + base;
-    const int tid = threadIdx.x;
+    const float *a = a_raw + base;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint32_t m = (uint32_t)min(tab.m_p[p], N);
 
-    if (tid == 0) head_weights(stats + (int64_t)u * 12, lc, hs);
+    float v[3][EPT];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) v[k][j] = a[k * rows + min(tid + j * kSelThreads, N - 1)];
+#pragma unroll
+    for (int j = 0; j < 3 * kBins / 4 / kSelThreads + 1; ++j)
+        if (tid + j * kSelThreads < 3 * kBins / 4) reinterpret_cast<uint4 *>(buf)[tid + j * kSelThreads] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < 6) { ext[tid] = 0u; cnt[tid] = 0u; }
     __syncthreads();
-    HeadStats st = hs;
-    float smin = INFINITY, smax = -INFINITY;
-    double ssum = 0.0;
-    constexpr int U = 4;                                  // independent loads in flight per thread and scale
-    for (int i0 = tid; i0 < N; i0 += U * kSelThreads) {
-        float av[U][3];
+
+    // ---- 1: histograms, ranges ----
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int i = min(i0 + q * kSelThreads, N - 1);
-            av[q][0] = a0[i]; av[q][1] = a1[i]; av[q][2] = a2[i];
+    for (int k = 0; k < 3; ++k) {
+        float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) {
+            if (tid + j * kSelThreads < N) {
+                lo = fminf(lo, v[k][j]);
+                hi = fmaxf(hi, v[k][j]);
+                atomicAdd(&buf[k * kBins + anomaly_bin(v[k][j])], 1u);
+            }
         }
+        lo = wave_min(lo);
+        hi = wave_max(hi);
+        if (lane == 0) {
+            atomicMax(&ext[2 * k], ~ord_key(lo));
+            atomicMax(&ext[2 * k + 1], ord_key(hi));
+        }
+    }
+    __syncthreads();
+
+    // ---- 2: boundary bins; thread: bins 2 tid, 2 tid + 1 of every scale ----
+    uint2 c[3];
+    uint32_t incl[3];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            if (i0 + q * kSelThreads < N) {
-                float at[3];
-                normalised(av[q], st, at);
-                const float s = surprise_std(at, lc.scale_mask);
+    for (int k = 0; k < 3; ++k) {
+        c[k] = reinterpret_cast<const uint2 *>(buf + k * kBins)[tid];
+        incl[k] = wave_prefix_sum(c[k].x + c[k].y);
+        if (lane == 63) wtot[k][w] = incl[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t group = c[k].x + c[k].y;
+        const uint32_t up = incl[k] + wave_sum(lane < w ? wtot[k][lane & (NW - 1)] : 0u);   // entries up to and with my bins
+        const uint32_t below = up - group, above = (uint32_t)N - up;
+        if (below < m && m <= up) {                                   // the m-th smallest lies in one of my bins
+            const bool second = below + c[k].x < m;
+            bin[2 * k + 1] = 2 * tid + (second ? 1 : 0);
+            need[2 * k + 1] = m - below - (second ? c[k].x : 0u);
+        }
+        if (above < m && m <= above + group) {                        // the m-th largest
+            const bool first = above + c[k].y < m;
+            bin[2 * k] = 2 * tid + (first ? 0 : 1);
+            need[2 * k] = m - above - (first ? c[k].y : 0u);
+        }
+    }
+    __syncthreads();
+
+    // ---- 3: sums beyond the boundary bins, their entries, the surprise ----
+    HeadStats st;
+    float pt[3], pb[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        st.lo[k] = key_value(~ext[2 * k]);
+        const float range = key_value(ext[2 * k + 1]) - st.lo[k];
+        st.inv_range[k] = range < kFlat ? 0.f : 1.0f / range;
+        pt[k] = pb[k] = 0.f;                                          // at most EPT terms of magnitude <= 1
+    }
+    float smin = INFINITY, smax = -INFINITY, ssum = 0.f;
+    {
+        int bT[3], bB[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) { bT[k] = bin[2 * k]; bB[k] = bin[2 * k + 1]; }
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) {
+            if (tid + j * kSelThreads < N) {
+                float raw[3], at[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const float x = raw[k] = v[k][j];
+                    const int b = anomaly_bin(x);
+                    pt[k] += b > bT[k] ? x : 0.f;
+                    pb[k] += b < bB[k] ? x : 0.f;
+                    if (b == bT[k]) {
+                        const uint32_t i = atomicAdd(&cnt[2 * k], 1u);
+                        if (i < (uint32_t)kUnitList) buf[2 * k * kUnitList + i] = ord_key(x);
+                    }
+                    if (b == bB[k]) {                                 // inverted: the smallest value has the largest key
+                        const uint32_t i = atomicAdd(&cnt[2 * k + 1], 1u);
+                        if (i < (uint32_t)kUnitList) buf[(2 * k + 1) * kUnitList + i] = ~ord_key(x);
+                    }
+                }
+                normalised(raw, st, at);
+                const float s = surprise_std<ALL>(at, lc.scale_mask);
                 smin = fminf(smin, s);
                 smax = fmaxf(smax, s);
-                ssum += (double)s;
+                ssum += s;                                            // at most EPT terms of magnitude <= 0.5
             }
         }
     }
-    smin = block_min(smin, fscratch);
-    smax = block_max(smax, fscratch);
-    ssum = block_sum(ssum, dscratch);
-    const float srange = smax - smin;
-    st.s_lo = smin;
-    st.s_inv_range = srange < kFlat ? 0.f : 1.0f / srange;
-    st.s_mean = (float)((ssum / (double)N - (double)smin) * (double)st.s_inv_range);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double t = wave_sum((double)pt[k]), b = wave_sum((double)pb[k]);
+        if (lane == 0) { sums[2 * k][w] = t; sums[2 * k + 1][w] = b; }
+    }
+    {
+        const double t = wave_sum((double)ssum);
+        smin = wave_min(smin);
+        smax = wave_max(smax);
+        if (lane == 0) { sums[6][w] = t; sext[0][w] = smin; sext[1][w] = smax; }
+    }
+    __syncthreads();
 
-    float *out = scores + base;
-    for (int i0 = tid; i0 < N; i0 += U * kSelThreads) {
-        float av[U][3];
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int i = min(i0 + q * kSelThreads, N - 1);
-            av[q][0] = a0[i]; av[q][1] = a1[i]; av[q][2] = a2[i];
+    // ---- 4: exact thresholds in the lists (wavefront = list), the surprise's range and mean ----
+    if (w < 6) {
+        constexpr double kFix = 1099511627776.0;                      // 2^40: exact for fp32 values of magnitude <= 1 down to that step
+        const int k = w >> 1;
+        const bool low = (w & 1) != 0;
+        const uint32_t n = cnt[w];
+        uint32_t T, gt, eq;
+        long long part = 0;
+        double total;
+        if (n <= (uint32_t)kUnitList) {
+            const uint32_t *list = buf + w * kUnitList;
+            T = wave_select(list, (int)n, need[w], whist[w], gt, eq);
+            for (uint32_t i = lane; i < n; i += 64)
+                part += list[i] > T ? __double2ll_rn((double)key_value(low ? ~list[i] : list[i]) * kFix) : 0ll;
+            total = wave_sum(lane < NW ? sums[w][lane & (NW - 1)] : 0.0) + (double)(need[w] - gt) * (double)key_value(low ? ~T : T);
+        } else {
+            const float *x = a + k * rows;
+            auto key_at = [x, low](int i) { return low ? ~ord_key(x[i]) : ord_key(x[i]); };
+            T = wave_select_fn(N, m, whist[w], gt, eq, key_at);
+            for (int i = lane; i < N; i += 64) part += key_at(i) > T ? __double2ll_rn((double)x[i] * kFix) : 0ll;
+            total = (double)(m - gt) * (double)key_value(low ? ~T : T);
         }
+        total += (double)wave_sum(part) / kFix;
+        if (lane == 0) side[w] = total;
+    } else if (w == 6) {
+        const int i = lane & (NW - 1);
+        const float lo = wave_min(sext[0][i]), hi = wave_max(sext[1][i]);
+        const double t = wave_sum(lane < NW ? sums[6][i] : 0.0);
+        if (lane == 0) {
+            const float range = hi - lo;
+            hs.s_lo = lo;
+            hs.s_inv_range = range < kFlat ? 0.f : 1.0f / range;
+            hs.s_mean = (float)((t / (double)N - (double)lo) * (double)hs.s_inv_range);
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        float stats[12];
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int i = i0 + q * kSelThreads;
-            if (i < N) {
-                float at[3];
-                normalised(av[q], st, at);
-                out[i] = i < lc.n_sink ? NKV_PIN : routed_score(at, st, lc);
-            }
+        for (int k = 0; k < 3; ++k) {
+            stats[4 * k] = st.lo[k];
+            stats[4 * k + 1] = st.inv_range[k];
+            stats[4 * k + 2] = (float)((side[2 * k] - side[2 * k + 1]) / (double)m * (double)st.inv_range[k]);
+        }
+        head_weights(stats, lc, hs);
+    }
+    __syncthreads();
+
+    // ---- 5: blend, gate, route, pin ----
+    st = hs;
+    float *out = scores + base;
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+        const int i = tid + j * kSelThreads;
+        if (i < N) {
+            const float raw[3] = {v[0][j], v[1][j], v[2][j]};
+            float at[3];
+            normalised(raw, st, at);
+            out[i] = i < lc.n_sink ? NKV_PIN : routed_score<ALL>(at, st, lc);
         }
     }
 }
@@ -310,26 +394,27 @@ hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &ta
     int nmax = 0;
     for (int p = 0; p < tab.n; ++p) nmax = max(nmax, tab.tok_off[p + 1] - tab.tok_off[p]);
     const unsigned units = (unsigned)(tab.n * L * H);
+    const int per_unit = kUnitTokens;                                 // prompts of up to this length: one launch, a workgroup per unit
     prof.begin(NKV_KERNEL_FINALIZE, st);
-    if (wide_ws != nullptr && (nmax > 8192 || units >= 256) && !per_head_route) {
-        // Slice-wise kernels where a head has more than one slice (any length) or there are many units (their
-        // 256-thread workgroups pack the chip four times as densely); for a few short units the per-head
-        // kernels are quicker.
-        hipError_t e = launch_stats_wide(a_raw, L, H, tab, lc.scale_mask, stats, wide_ws, st);
-        if (e != hipSuccess) return e;
-        e = launch_route_wide(a_raw, L, H, tab, lc, stats, wide_ws, scores, st);
-        if (e != hipSuccess) return e;
-    } else if (nmax <= 32 * kSelThreads) {
-        for_each_length_class(tab, L * H, [&](int ept, int u0, int n) {
-            const dim3 grid(3, (unsigned)n);
-            if (ept == 4) scale_stats_kernel<4><<<grid, kSelThreads, 0, st>>>(a_raw, L, H, tab, u0, stats);
-            else if (ept == 8) scale_stats_kernel<8><<<grid, kSelThreads, 0, st>>>(a_raw, L, H, tab, u0, stats);
-            else if (ept == 16) scale_stats_kernel<16><<<grid, kSelThreads, 0, st>>>(a_raw, L, H, tab, u0, stats);
-            else scale_stats_kernel<32><<<grid, kSelThreads, 0, st>>>(a_raw, L, H, tab, u0, stats);
-        });
-        route_kernel<<<units, kSelThreads, 0, st>>>(a_raw, L, H, tab, lc, stats, scores);
-    } else {
+    if (nmax > per_unit && (wide_ws == nullptr || per_head_route)) {
         finalize_kernel<<<units, kThreads, 0, st>>>(a_raw, L, H, tab, lc, scores);
+    } else {
+        for_each_length_class(tab, L * H, [&](int ept, int u0, int n) {
+#define NKV_UNIT(EPT)                                                                                                        \
+    (lc.scale_mask == 7 ? finalize_unit_kernel<EPT, true> : finalize_unit_kernel<EPT, false>)<<<(unsigned)n, kSelThreads, 0, st>>>( \
+        a_raw, L, H, tab, u0, lc, scores)
+            if (1024 * ept > per_unit) return;
+            if (ept == 4) NKV_UNIT(4);
+            else if (ept == 8) NKV_UNIT(8);
+            else NKV_UNIT(16);
+#undef NKV_UNIT
+        });
+        if (nmax > per_unit) {
+            hipError_t e = launch_stats_wide(a_raw, L, H, tab, lc.scale_mask, stats, wide_ws, st);
+            if (e != hipSuccess) return e;
+            e = launch_route_wide(a_raw, L, H, tab, lc, stats, wide_ws, scores, st);
+            if (e != hipSuccess) return e;
+        }
     }
     prof.end(NKV_KERNEL_FINALIZE, st);
     return hipGetLastError();

@@ -100,6 +100,7 @@ __global__ __launch_bounds__(kWideThreads) void stats_pick_kernel(int L, int H, 
     const int u = blockIdx.x, k = blockIdx.y;
     const int lh = u % (L * H), p = u / (L * H);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
+    if (N <= kUnitTokens) return;
     const int S = (N + kSlice - 1) / kSlice;
     const uint32_t m = (uint32_t)min(tab.m_p[p], N);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -341,9 +342,10 @@ __global__ __launch_bounds__(64) void stats_finish_kernel(const float *__restric
     __shared__ uint32_t hist[256];
     const int u = blockIdx.x, k = blockIdx.y;
     const int64_t job = (int64_t)u * 3 + k;
-    bool bad = failed[job] != 0u;
     const int lh = u % (L * H), p = u / (L * H);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
+    if (N <= kUnitTokens) return;
+    bool bad = failed[job] != 0u;
     const int S = (N + kSlice - 1) / kSlice;
     const uint32_t m = (uint32_t)min(tab.m_p[p], N);
     const int lane = threadIdx.x;
@@ -437,7 +439,7 @@ struct WideWs {
 WideWs wide_ws(int L, int H, const PromptTab &tab)
 {
     SliceTab st;
-    const size_t slices = 3 * (size_t)fill_slices(L, H, tab, &st), jobs = 3 * (size_t)tab.n * L * H;
+    const size_t slices = 3 * (size_t)fill_slices(L, H, tab, &st, kUnitTokens), jobs = 3 * (size_t)tab.n * L * H;
     WideWs w;
     size_t off = 0;
     w.part = off;    off += align256(slices * kBins * sizeof(uint16_t));
@@ -460,7 +462,7 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
                              hipStream_t st)
 {
     SliceTab stab;
-    const int slices = fill_slices(L, H, tab, &stab);
+    const int slices = fill_slices(L, H, tab, &stab, kUnitTokens);
     const WideWs lay = wide_ws(L, H, tab);
     char *base = (char *)ws;
     uint16_t *part = (uint16_t *)(base + lay.part);
@@ -490,7 +492,7 @@ hipError_t launch_route_wide(const float *a_raw, int L, int H, const PromptTab &
                              const float *stats, void *ws, float *scores, hipStream_t st)
 {
     SliceTab stab;
-    const int slices = fill_slices(L, H, tab, &stab);
+    const int slices = fill_slices(L, H, tab, &stab, kUnitTokens);
     const WideWs lay = wide_ws(L, H, tab);
     const SliceSurprise *sur = (const SliceSurprise *)((char *)ws + lay.sur);
     if (lc.scale_mask == 7)

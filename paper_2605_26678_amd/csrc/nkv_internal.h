@@ -107,6 +107,8 @@ template <typename F> inline void for_each_length_class(const PromptTab &tab, in
 }
 
 // ---- per-head statistics, blend weights, gate and final scores ----
+// prompts of up to kUnitTokens are done unit by unit, longer ones slice by slice
+constexpr int kUnitTokens = 16384;
 // wide_ws: scratch of stats_wide_ws_bytes() for the slice-wise statistics (NULL: per-head kernels only);
 // per_head_route: do not use the slice-wise kernels
 hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &tab, const LearnerConsts &lc,

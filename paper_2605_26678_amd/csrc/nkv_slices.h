@@ -27,13 +27,14 @@ struct SliceTab {                        // first slice of every prompt; a promp
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-inline int fill_slices(int L, int H, const PromptTab &tab, SliceTab *st)
+// longer_than: prompts of up to that length get no slices (the kernels that run per unit pass them over as well)
+inline int fill_slices(int L, int H, const PromptTab &tab, SliceTab *st, int longer_than = 0)
 {
     int n = 0;
     for (int p = 0; p < tab.n; ++p) {
         st->off[p] = n;
         const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-        n += L * H * ((N + kSlice - 1) / kSlice);
+        if (N > longer_than) n += L * H * ((N + kSlice - 1) / kSlice);
     }
     st->off[tab.n] = n;
     return n;
