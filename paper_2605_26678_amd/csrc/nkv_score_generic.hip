@@ -1,43 +1,48 @@
 // Shape-generic scoring kernels: per-scale cosine anomalies a_s, a_e, a_c (paper Sections 2.1-2.3)
 // for any head dim (multiple of 8, <= 1024), any window and block size, fp32, bf16, fp16 or 8-bit (E4M3) keys.
 //
-// Four small kernels, none of them tuned -- they cover what the streaming kernels do not:
-//   1. rnorm   : 1 / max(||k_i||, eps) per token                       (Section 2.1)
-//   2. bsum    : sum of k_hat over every episodic block                (Section 2.2, episodic memory)
-//   3. ssum    : sum of k_hat over the prompt = sum of its block sums  (Section 2.2, stable memory)
-//   4. anomaly : a_s, a_e from the two sums; a_c from the window summed directly for every token
-//                (Section 2.2 current memory; Section 2.3)
+// Three kernels that cover what the streaming kernels do not (fp32 keys, head dims above 128, other windows or blocks):
+//   1. block   : 1 / max(||k_i||, eps) per token (Section 2.1) and the sum of k_hat over every episodic block
+//                (Section 2.2, episodic memory); one workgroup per block
+//   2. ssum    : sum of k_hat over the prompt = sum of its block sums  (Section 2.2, stable memory)
+//   3. anomaly : a_s, a_e from the two sums; a_c from a window sum that slides over 16 consecutive tokens and is formed
+//                afresh in front of them (Section 2.2 current memory; Section 2.3); one wavefront per 16 tokens
+// Everywhere a lane owns dims lane, lane + 64, ... of a row.  The time of a small call is a chain of load latencies, so
+// loads go out eight rows at a time.  (With the window added up for every token, a wave per token and a serial loop over
+// a block's tokens, 2 heads x 4096 fp32 tokens took 86 us.)
 // Cosines do not depend on the length of the anchor, so sums stand in for the means.
 #include "nkv_device.h"
 
 namespace nkv {
 namespace {
 
-template <typename T>
-__global__ __launch_bounds__(256) void rnorm_kernel(const T *__restrict__ keys, RowMap km, PromptTab tab,
-                                                    int64_t rows, int d, float *__restrict__ rnorm)
+constexpr int kBlockThreads = 1024, kSsumThreads = 1024;
+constexpr int kChunk = 16;               // tokens a wavefront slides the window over
+
+template <int NQ> constexpr int rows_in_flight() { return NQ <= 2 ? 8 : NQ <= 4 ? 4 : 2; }
+
+// U rows from row0 on that are `step` rows apart, as floats; rows below 0 or from `end` >= 1 on and dims from d on are
+// zeros.  The loads are unconditional (of a clamped address), so that all of them go out together.
+template <typename T, int NQ, int U>
+__device__ __forceinline__ void load_rows(const T *__restrict__ unit, int d, int lane, int row0, int step, int end, float (&x)[U][NQ])
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (row >= rows) return;
-    const int lh = (int)(row / tab.T), tg = (int)(row - (int64_t)lh * tab.T);
-    const int p = prompt_of_token(tab, tg);
-    const T *k = keys + km.unit(lh, p, tab) + (int64_t)(tg - tab.tok_off[p]) * d;
-    float ss = 0.f;
-    for (int c = lane; c < d; c += kWave) {
-        float x = load_elem<T>(k + c);
-        ss = fmaf(x, x, ss);
-    }
-    ss = wave_sum(ss);
-    if (lane == 0) rnorm[row] = 1.0f / fmaxf(sqrtf(ss), kEps);
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int row = row0 + j * step, c = lane + q * kWave;
+            const float v = load_elem<T>(unit + (int64_t)min(max(row, 0), end - 1) * d + min(c, d - 1));
+            x[j][q] = row >= 0 && row < end && c < d ? v : 0.f;
+        }
 }
 
-// grid (blocks per head, L*H); thread c owns dims c, c+256, ...
-template <typename T>
-__global__ __launch_bounds__(256) void bsum_kernel(const T *__restrict__ keys, RowMap km,
-                                                   const float *__restrict__ rnorm, int d, PromptTab tab,
-                                                   float *__restrict__ bsum)
+// grid (blocks per head, L*H); wave w takes the block's tokens w, w + 16, ...
+template <typename T, int NQ>
+__global__ __launch_bounds__(kBlockThreads) void block_kernel(const T *__restrict__ keys, RowMap km, int d, PromptTab tab,
+                                                              float *__restrict__ rnorm, float *__restrict__ bsum)
 {
+    constexpr int NW = kBlockThreads / kWave, U = rows_in_flight<NQ>();
+    __shared__ float part[NW][kWave];
     const int blk = blockIdx.x, lh = blockIdx.y;
     const int p = prompt_of_block(tab, blk);
     const int b = tab.b[p];
@@ -46,87 +51,171 @@ __global__ __launch_bounds__(256) void bsum_kernel(const T *__restrict__ keys, R
     const int hi = min(lo + b, n);
     const int64_t row0 = (int64_t)lh * tab.T + tab.tok_off[p];
     const T *unit = keys + km.unit(lh, p, tab);
-    for (int c = threadIdx.x; c < d; c += blockDim.x) {
-        float s = 0.f;
-        for (int t = lo; t < hi; ++t) s = fmaf(rnorm[row0 + t], load_elem<T>(unit + (int64_t)t * d + c), s);
-        bsum[((int64_t)lh * tab.blk_off[tab.n] + blk) * d + c] = s;
-    }
-}
-
-// grid (prompts, L*H)
-__global__ __launch_bounds__(256) void ssum_kernel(const float *__restrict__ bsum, int d, PromptTab tab,
-                                                   float *__restrict__ ssum)
-{
-    const int p = blockIdx.x, lh = blockIdx.y;
-    const int nblk = tab.blk_off[tab.n];
-    for (int c = threadIdx.x; c < d; c += blockDim.x) {
-        float s = 0.f;
-        for (int blk = tab.blk_off[p]; blk < tab.blk_off[p + 1]; ++blk)
-            s += bsum[((int64_t)lh * nblk + blk) * d + c];
-        ssum[((int64_t)lh * tab.n + p) * d + c] = s;
-    }
-}
-
-// One wavefront per token; lane owns dims lane, lane+64, ... (NQ of them).
-template <typename T, int NQ>
-__global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys, RowMap km,
-                                                      const float *__restrict__ rnorm,
-                                                      const float *__restrict__ bsum,
-                                                      const float *__restrict__ ssum, int LH, int d, int window,
-                                                      PromptTab tab, float *__restrict__ a_raw)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t rows = (int64_t)LH * tab.T;
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (row >= rows) return;
-    const int lh = (int)(row / tab.T);
-    const int tg = (int)(row - (int64_t)lh * tab.T);
-    const int p = prompt_of_token(tab, tg);
-    const int i = tg - tab.tok_off[p];
-    const int blk = tab.blk_off[p] + i / tab.b[p];
-    const int64_t row0 = (int64_t)lh * tab.T + tab.tok_off[p];
-    const T *unit = keys + km.unit(lh, p, tab);
-    const float *S = ssum + ((int64_t)lh * tab.n + p) * d;
-    const float *Bs = bsum + ((int64_t)lh * tab.blk_off[tab.n] + blk) * d;
-
-    float kh[NQ], acc[NQ];
-    const float rn = rnorm[row];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    float acc[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int c = lane + q * kWave;
-        kh[q] = c < d ? rn * load_elem<T>(unit + (int64_t)i * d + c) : 0.f;
-        acc[q] = 0.f;
-    }
-    const int lo = max(0, i - window + 1);
-    for (int j = lo; j <= i; ++j) {
-        const float rj = rnorm[row0 + j];
-        const T *kj = unit + (int64_t)j * d;
+    for (int q = 0; q < NQ; ++q) acc[q] = 0.f;
+    for (int t = lo + w; t < hi; t += U * NW) {
+        float x[U][NQ], rn[U];
+        load_rows<T, NQ, U>(unit, d, lane, t, NW, hi, x);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int c = lane + q * kWave;
-            if (c < d) acc[q] = fmaf(rj, load_elem<T>(kj + c), acc[q]);
+        for (int j = 0; j < U; ++j) {
+            float ss = 0.f;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) ss = fmaf(x[j][q], x[j][q], ss);
+            rn[j] = 1.0f / fmaxf(sqrtf(wave_sum(ss)), kEps);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            if (lane == 0 && t + j * NW < hi) rnorm[row0 + t + j * NW] = rn[j];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) acc[q] = fmaf(rn[j], x[j][q], acc[q]);   // (rows past the block are zeros)
         }
     }
-    float kk = 0.f, ds = 0.f, ns = 0.f, de = 0.f, ne = 0.f, dc = 0.f, nc = 0.f;
+    float *out = bsum + ((int64_t)lh * tab.blk_off[tab.n] + blk) * d;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        if (q > 0) __syncthreads();
+        part[w][lane] = acc[q];
+        __syncthreads();
+        if (w == 0 && lane + q * kWave < d) {
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) s += part[i][lane];
+            out[lane + q * kWave] = s;
+        }
+    }
+}
+
+// grid (prompts, L*H); thread = (slice, dim): slice s adds blocks s, s + slices, ... up
+__global__ __launch_bounds__(kSsumThreads) void ssum_kernel(const float *__restrict__ bsum, int d, PromptTab tab, float *__restrict__ ssum)
+{
+    __shared__ float part[kSsumThreads];
+    const int p = blockIdx.x, lh = blockIdx.y;
+    const int nblk = tab.blk_off[tab.n], n = tab.blk_off[p + 1] - tab.blk_off[p];
+    const int slices = kSsumThreads / d, c = threadIdx.x % d, slice = threadIdx.x / d;       // d <= 1024; some threads may be idle
+    const float *mine = bsum + ((int64_t)lh * nblk + tab.blk_off[p]) * d + c;
+    float s = 0.f;
+    if (slice < slices) {
+        for (int b = slice; b < n; b += 4 * slices) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = b + i * slices < n ? mine[(int64_t)(b + i * slices) * d] : 0.f;
+            s += (v[0] + v[1]) + (v[2] + v[3]);
+        }
+    }
+    part[threadIdx.x] = s;
+    __syncthreads();
+    if ((int)threadIdx.x < d) {
+        float t = 0.f;
+        for (int i = 0; i < slices; ++i) t += part[i * d + threadIdx.x];
+        ssum[((int64_t)lh * tab.n + p) * d + threadIdx.x] = t;
+    }
+}
+
+// grid (chunks of 16 tokens / 4, L*H): every wavefront takes one chunk of one prompt.
+template <typename T, int NQ>
+__global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys, RowMap km, const float *__restrict__ rnorm,
+                                                      const float *__restrict__ bsum, const float *__restrict__ ssum, int LH, int d,
+                                                      int window, PromptTab tab, float *__restrict__ a_raw)
+{
+    constexpr int U = rows_in_flight<NQ>(), US = NQ <= 2 ? 4 : NQ <= 8 ? 2 : 1;
+    const int lane = threadIdx.x & (kWave - 1), lh = blockIdx.y;
+    const int64_t rows = (int64_t)LH * tab.T;
+    int chunk = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave, p = 0;
+    for (;; ++p) {
+        if (p == tab.n) return;                                       // (uniform in the wavefront)
+        const int nc = (tab.tok_off[p + 1] - tab.tok_off[p] + kChunk - 1) / kChunk;
+        if (chunk < nc) break;
+        chunk -= nc;
+    }
+    const int N = tab.tok_off[p + 1] - tab.tok_off[p], b = tab.b[p];
+    const int i0 = chunk * kChunk, i1 = min(i0 + kChunk, N);
+    const int64_t row0 = (int64_t)lh * tab.T + tab.tok_off[p];
+    const T *unit = keys + km.unit(lh, p, tab);
+    const float *rn_unit = rnorm + row0;
+    const float *S = ssum + ((int64_t)lh * tab.n + p) * d;
+    const float *B0 = bsum + ((int64_t)lh * tab.blk_off[tab.n] + tab.blk_off[p]) * d;
+
+    // the weighted sum of rows [lo, hi)
+    auto add_rows = [&](int lo, int hi, float (&sum)[NQ]) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) sum[q] = 0.f;
+        for (int j = lo; j < hi; j += U) {
+            float x[U][NQ];
+            load_rows<T, NQ, U>(unit, d, lane, j, 1, hi, x);
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const float r = rn_unit[min(j + i, hi - 1)];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) sum[q] = fmaf(r, x[i][q], sum[q]);
+            }
+        }
+    };
+    float s[NQ], e[NQ], W[NQ], ns = 0.f, ne = 0.f;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int c = lane + q * kWave;
-        const float s = c < d ? S[c] : 0.f, e = c < d ? Bs[c] : 0.f;
-        kk = fmaf(kh[q], kh[q], kk);
-        ds = fmaf(kh[q], s, ds);
-        ns = fmaf(s, s, ns);
-        de = fmaf(kh[q], e, de);
-        ne = fmaf(e, e, ne);
-        dc = fmaf(kh[q], acc[q], dc);
-        nc = fmaf(acc[q], acc[q], nc);
+        s[q] = c < d ? S[c] : 0.f;
+        e[q] = 0.f;
+        ns = fmaf(s[q], s[q], ns);
     }
-    kk = wave_sum(kk); ds = wave_sum(ds); ns = wave_sum(ns); de = wave_sum(de);
-    ne = wave_sum(ne); dc = wave_sum(dc); nc = wave_sum(nc);
-    if (lane == 0) {
-        const float nk = fmaxf(sqrtf(kk), kEps);
-        a_raw[row] = -ds / (nk * fmaxf(sqrtf(ns), kEps));
-        a_raw[rows + row] = -de / (nk * fmaxf(sqrtf(ne), kEps));
-        a_raw[2 * rows + row] = -dc / (nk * fmaxf(sqrtf(nc), kEps));
+    ns = wave_sum(ns);
+    // a window that is not much longer than the chunk is cheaper to add up for every token
+    const bool slide = window > kChunk;
+    if (slide) add_rows(max(0, i0 - window), i0, W);
+    int blk = -1;
+    float as = 0.f, ae = 0.f, ac = 0.f;                               // lane t: the anomalies of token i0 + t
+    for (int i = i0; i < i1; i += US) {
+        float x[US][NQ], y[US][NQ];                                   // rows that enter and that leave the window
+        load_rows<T, NQ, US>(unit, d, lane, i, 1, i1, x);
+        if (slide) load_rows<T, NQ, US>(unit, d, lane, i - window, 1, i1, y);
+#pragma unroll
+        for (int j = 0; j < US; ++j) {
+            const int tok = i + j;
+            if (tok >= i1) break;
+            if (tok / b != blk) {                                     // the token's episodic block
+                blk = tok / b;
+                ne = 0.f;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int c = lane + q * kWave;
+                    e[q] = c < d ? B0[(int64_t)blk * d + c] : 0.f;
+                    ne = fmaf(e[q], e[q], ne);
+                }
+                ne = wave_sum(ne);
+            }
+            const float rn = rn_unit[tok];
+            float kk = 0.f, ds = 0.f, de = 0.f, dc = 0.f, nc = 0.f;
+            if (slide) {
+                const float ry = tok >= window ? rn_unit[tok - window] : 0.f;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) W[q] = fmaf(rn, x[j][q], fmaf(-ry, y[j][q], W[q]));
+            } else {
+                add_rows(max(0, tok - window + 1), tok + 1, W);
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const float kh = rn * x[j][q];
+                kk = fmaf(kh, kh, kk);
+                ds = fmaf(kh, s[q], ds);
+                de = fmaf(kh, e[q], de);
+                dc = fmaf(kh, W[q], dc);
+                nc = fmaf(W[q], W[q], nc);
+            }
+            kk = wave_sum(kk); ds = wave_sum(ds); de = wave_sum(de); dc = wave_sum(dc); nc = wave_sum(nc);
+            const float nk = fmaxf(sqrtf(kk), kEps);
+            const bool me = lane == tok - i0;
+            as = me ? -ds / (nk * fmaxf(sqrtf(ns), kEps)) : as;
+            ae = me ? -de / (nk * fmaxf(sqrtf(ne), kEps)) : ae;
+            ac = me ? -dc / (nk * fmaxf(sqrtf(nc), kEps)) : ac;
+        }
+    }
+    if (lane < i1 - i0) {
+        float *out = a_raw + row0 + i0 + lane;
+        out[0] = as;
+        out[rows] = ae;
+        out[2 * rows] = ac;
     }
 }
 
@@ -134,20 +223,21 @@ template <typename T>
 hipError_t run(const T *keys, const RowMap &km, int LH, int d, int window, const PromptTab &tab, float *a_raw, float *rnorm,
                float *bsum, float *ssum, const Prof &prof, hipStream_t st)
 {
-    const int64_t rows = (int64_t)LH * tab.T;
-    const unsigned row_grid = (unsigned)((rows + 3) / 4);
-    rnorm_kernel<T><<<row_grid, 256, 0, st>>>(keys, km, tab, rows, d, rnorm);
-    bsum_kernel<T><<<dim3(tab.blk_off[tab.n], LH), 256, 0, st>>>(keys, km, rnorm, d, tab, bsum);
-    ssum_kernel<<<dim3(tab.n, LH), 256, 0, st>>>(bsum, d, tab, ssum);
+    int chunks = 0;
+    for (int p = 0; p < tab.n; ++p) chunks += (tab.tok_off[p + 1] - tab.tok_off[p] + kChunk - 1) / kChunk;
+    const dim3 blocks((unsigned)tab.blk_off[tab.n], (unsigned)LH), waves((unsigned)(chunks + 3) / 4, (unsigned)LH);
     const int nq = (d + kWave - 1) / kWave;
+#define NKV_BY_DIMS(CALL) \
+    do { if (nq <= 1) CALL(1); else if (nq <= 2) CALL(2); else if (nq <= 4) CALL(4); else if (nq <= 8) CALL(8); else CALL(16); } while (0)
+#define NKV_BLOCK(NQ) block_kernel<T, NQ><<<blocks, kBlockThreads, 0, st>>>(keys, km, d, tab, rnorm, bsum)
+#define NKV_ANOM(NQ) anomaly_kernel<T, NQ><<<waves, 256, 0, st>>>(keys, km, rnorm, bsum, ssum, LH, d, window, tab, a_raw)
+    NKV_BY_DIMS(NKV_BLOCK);
+    ssum_kernel<<<dim3(tab.n, LH), kSsumThreads, 0, st>>>(bsum, d, tab, ssum);
     prof.begin(NKV_KERNEL_SCAN, st);
-#define NKV_ANOM(NQ) anomaly_kernel<T, NQ><<<row_grid, 256, 0, st>>>(keys, km, rnorm, bsum, ssum, LH, d, window, tab, a_raw)
-    if (nq <= 1) NKV_ANOM(1);
-    else if (nq <= 2) NKV_ANOM(2);
-    else if (nq <= 4) NKV_ANOM(4);
-    else if (nq <= 8) NKV_ANOM(8);
-    else NKV_ANOM(16);
+    NKV_BY_DIMS(NKV_ANOM);
+#undef NKV_BLOCK
 #undef NKV_ANOM
+#undef NKV_BY_DIMS
     prof.end(NKV_KERNEL_SCAN, st);
     return hipGetLastError();
 }

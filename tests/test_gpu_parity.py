@@ -204,6 +204,17 @@ def test_matrix_core_scan_of_long_units(d, dtype, N):
     compare_end_to_end(w, K, V, 0.9, label=w.name)
 
 
+@pytest.mark.parametrize("d,dtype,window,block", [(8, "fp32", 1, 128), (128, "fp32", 64, 128), (136, "bf16", 16, 128),
+                                                  (256, "fp16", 17, 300), (80, "fp8", 100, 7), (1024, "fp32", 30, 5)])
+def test_generic_scan_windows_and_blocks(d, dtype, window, block):
+    """The shape-generic kernels where the window slides and where it is added up for every token (up to 16), with blocks
+    shorter than the 16 tokens of a wavefront and longer than the streaming kernels take."""
+    w = nkv_inputs.small_workload(f"generic_{d}_{window}", 1, 2, d, [1, 333, 16, 47], dtype=dtype, n_out=0)
+    K, V = _kv(w)
+    p = nkv.params_default(window=window, block_min=block, block_max=block)
+    compare_end_to_end(w, K, V, 0.5, params=p, label=w.name)
+
+
 LIMITS = [
     # the most prompts, head dims, heads and (layer, head) pairs a call accepts
     ("prompts_64", 1, 2, 64, [61 + 37 * (i % 9) + 500 * (i % 3 == 0) for i in range(64)], "bf16", 0),
