@@ -47,8 +47,8 @@ template <bool TOP> __device__ __forceinline__ void block_pick(SelectScratch &s,
     uint32_t incl = TOP ? wave_suffix_sum(group) : wave_prefix_sum(group);                                          // inclusive sum towards the scan direction
     if (lane == (TOP ? 0 : 63)) s.wsum[w] = incl;
     __syncthreads();
-    if (TOP) { for (int ww = w + 1; ww < kSelThreads / 64; ++ww) incl += s.wsum[ww]; }
-    else     { for (int ww = 0; ww < w; ++ww) incl += s.wsum[ww]; }
+    // the wavefronts in front of this one in the scan's direction
+    incl += wave_sum(lane < kSelThreads / 64 && (TOP ? lane > w : lane < w) ? s.wsum[lane & (kSelThreads / 64 - 1)] : 0u);
     uint32_t cum = incl - group;                                     // entries ranked before this thread's bins
     if (cum < want && want <= incl) {
 #pragma unroll
@@ -85,11 +85,8 @@ __device__ __forceinline__ void block_key_range(const uint32_t (&key)[EPT], int 
     hi = wave_reduce(hi, larger);
     if ((threadIdx.x & 63) == 0) { s.red[threadIdx.x >> 6] = nlo; s.wsum[threadIdx.x >> 6] = hi; }
     __syncthreads();
-    uint32_t a = s.red[0], b = s.wsum[0];
-#pragma unroll
-    for (int i = 1; i < kSelThreads / 64; ++i) { a = max(a, s.red[i]); b = max(b, s.wsum[i]); }
-    kmin = ~a;
-    kmax = b;
+    kmin = ~wave_reduce(s.red[threadIdx.x & (kSelThreads / 64 - 1)], larger);
+    kmax = wave_reduce(s.wsum[threadIdx.x & (kSelThreads / 64 - 1)], larger);
     __syncthreads();                                                 // red / wsum are free again
 }
 

@@ -118,7 +118,7 @@ __device__ __forceinline__ void block_pick_top(const uint32_t *hist, uint32_t wa
     uint32_t incl = wave_suffix_sum(group);
     if (lane == 0) wsum[w] = incl;
     __syncthreads();
-    for (int ww = w + 1; ww < kThreads / 64; ++ww) incl += wsum[ww];
+    incl += wave_sum(lane < kThreads / 64 && lane > w ? wsum[lane & (kThreads / 64 - 1)] : 0u);
     uint32_t cum = incl - group;
     if (cum < want && want <= incl) {
 #pragma unroll

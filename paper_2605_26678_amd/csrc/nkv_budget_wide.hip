@@ -51,6 +51,13 @@ __device__ __forceinline__ uint32_t scan_from_top(uint32_t group, uint32_t *wsum
     return incl;                                                     // inclusive within the wave; add the waves above
 }
 
+// the sum over the wavefronts above this one of 16 per-wavefront values
+__device__ __forceinline__ uint32_t above_waves(const uint32_t *wsum)
+{
+    const int lane = threadIdx.x & 63;
+    return wave_sum(lane < 16 && lane > (int)(threadIdx.x >> 6) ? wsum[lane & 15] : 0u);
+}
+
 __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTab tab, SliceTab st,
                                                           const uint16_t *__restrict__ part,
                                                           LayerPick *__restrict__ picks, uint32_t *__restrict__ failed,
@@ -65,7 +72,7 @@ __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTa
     const int S = (N + kSlice - 1) / kSlice;
     const int k0 = tab.k0[p], m_safe = tab.m_safe[p];
     const uint32_t R = (uint32_t)H * (uint32_t)(k0 - m_safe);
-    const int tid = threadIdx.x, w = tid >> 6;
+    const int tid = threadIdx.x;
     if (tid < kMaxH) {
         s_gt[tid] = 0u;
         s_bT[tid] = kBins;                                           // nothing protected unless a pick says so
@@ -112,8 +119,7 @@ __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTa
 #pragma unroll
         for (int h = 0; h < kMaxH; ++h) {
             if (h < H) {
-                uint32_t up = incl[h];
-                for (int ww = w + 1; ww < 16; ++ww) up += wsum[h][ww];
+                const uint32_t up = incl[h] + above_waves(wsum[h]);
                 const uint32_t cum = up - (a[h] + b[h]), want = (uint32_t)m_safe;
                 if (cum < want && want <= up) {
                     if (want <= cum + b[h]) { s_bT[h] = tid * 2 + 1; s_needT[h] = want - cum; }
@@ -138,7 +144,7 @@ __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTa
     {
         uint32_t up = scan_from_top(pa + pb, wsum[kMaxH]);
         __syncthreads();
-        for (int ww = w + 1; ww < 16; ++ww) up += wsum[kMaxH][ww];
+        up += above_waves(wsum[kMaxH]);
         const uint32_t cum = up - (pa + pb);
         if (cum < R && R <= up) {
             if (R <= cum + pb) { s_bL = (uint32_t)(tid * 2 + 1); s_needL = R - cum; }
@@ -171,7 +177,8 @@ __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTa
 
 // Every slice has its own segment of kSeg keys in each of the two lists and a count: no atomics on memory,
 // nobody waits for a returned value.
-__global__ __launch_bounds__(kWideThreads) void slice_collect_kernel(const float *__restrict__ scores, int L, int H,
+template <int TH>
+__global__ __launch_bounds__(TH) void slice_collect_kernel(const float *__restrict__ scores, int L, int H,
                                                                      PromptTab tab, SliceTab st,
                                                                      const LayerPick *__restrict__ picks,
                                                                      uint32_t *__restrict__ segT,
@@ -180,6 +187,7 @@ __global__ __launch_bounds__(kWideThreads) void slice_collect_kernel(const float
                                                                      uint32_t *__restrict__ nSegL,
                                                                      uint32_t *__restrict__ failed)
 {
+    constexpr int PT = per_thread<TH>();
     __shared__ uint32_t nT, nL;
     int p, lh, s, S;
     locate(st, tab, blockIdx.x, p, lh, s, S);
@@ -187,10 +195,10 @@ __global__ __launch_bounds__(kWideThreads) void slice_collect_kernel(const float
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
     const float *sc = scores + (int64_t)lh * tab.T + tab.tok_off[p];
     const int tid = threadIdx.x;
-    float v[kPerThread];
+    float v[PT];
     const __amdgpu_buffer_rsrc_t vals = slice_values(sc, s, N);
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) v[j] = slice_value(vals, tid, j);
+    for (int j = 0; j < PT; ++j) v[j] = slice_value<TH>(vals, tid, j);
     const LayerPick *pk = picks + pl;
     const int bT = pk->bT[h], bL = pk->bL;
     const uint32_t done = pk->done;
@@ -199,8 +207,8 @@ __global__ __launch_bounds__(kWideThreads) void slice_collect_kernel(const float
     if (done) return;
     uint32_t *outT = segT + (int64_t)blockIdx.x * kSeg, *outL = segL + (int64_t)blockIdx.x * kSeg;
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-        if (s * kSlice + j * kWideThreads + tid < N) {
+    for (int j = 0; j < PT; ++j) {
+        if (s * kSlice + j * TH + tid < N) {
             const int b = score_bin(v[j]);
             if (b == bT) {
                 const uint32_t at = atomicAdd(&nT, 1u);
@@ -378,10 +386,12 @@ hipError_t launch_budget_wide(const float *scores, int L, int H, const PromptTab
     uint32_t *segL = (uint32_t *)(base + lay.segL), *nSegL = (uint32_t *)(base + lay.nSegL);
     uint32_t *failed = (uint32_t *)(base + lay.failed);
     const unsigned layers = (unsigned)(tab.n * L);
-    slice_hist_kernel<<<(unsigned)slices, kWideThreads, 0, st>>>(scores, tab, stab, part);
+    const bool few = few_slices(slices);
+    const unsigned threads = few ? 1024 : 256;
+    (few ? slice_hist_kernel<1024> : slice_hist_kernel<256>)<<<(unsigned)slices, threads, 0, st>>>(scores, tab, stab, part);
     layer_pick_kernel<<<layers, 1024, 0, st>>>(L, H, tab, stab, part, picks, failed, k_per_head);
-    slice_collect_kernel<<<(unsigned)slices, kWideThreads, 0, st>>>(scores, L, H, tab, stab, picks, segT, nSegT, segL,
-                                                                   nSegL, failed);
+    (few ? slice_collect_kernel<1024> : slice_collect_kernel<256>)<<<(unsigned)slices, threads, 0, st>>>(
+        scores, L, H, tab, stab, picks, segT, nSegT, segL, nSegL, failed);
     layer_finish_kernel<<<layers, 1024, 0, st>>>(L, H, tab, stab, picks, segT, nSegT, segL, nSegL, failed, k_per_head);
     *failed_flags = failed;
     return hipGetLastError();

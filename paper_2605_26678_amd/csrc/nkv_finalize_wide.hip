@@ -45,31 +45,33 @@ struct SlicePart {                       // what one slice contributes besides i
 };
 
 // grid (slices, 3)
-__global__ __launch_bounds__(kWideThreads) void stats_hist_kernel(const float *__restrict__ a_raw, int64_t rows,
+template <int TH>
+__global__ __launch_bounds__(TH) void stats_hist_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                   PromptTab tab, SliceTab st, int n_slices,
                                                                   uint16_t *__restrict__ part,
                                                                   SlicePart *__restrict__ sp)
 {
-    __shared__ uint32_t hist[kBins];
-    __shared__ float red[2][kWideThreads / 64];
+    constexpr int PT = per_thread<TH>();
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
+    __shared__ float red[2][TH / 64];
     int p, lh, s, S;
     locate(st, tab, blockIdx.x, p, lh, s, S);
     const int k = blockIdx.y;
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
     const float *a = a_raw + (int64_t)k * rows + (int64_t)lh * tab.T + tab.tok_off[p];
     const int tid = threadIdx.x;
-    for (int j = tid; j < kBins; j += kWideThreads) hist[j] = 0u;
-    float v[kPerThread / 4][4];
+    for (int j = tid; j < kBins; j += TH) hist[j] = 0u;
+    float v[PT / 4][4];
     const __amdgpu_buffer_rsrc_t vals = slice_values(a, s, N);
 #pragma unroll
-    for (int j = 0; j < kPerThread / 4; ++j) slice_values4(vals, tid, j, v[j]);
+    for (int j = 0; j < PT / 4; ++j) slice_values4<TH>(vals, tid, j, v[j]);
     __syncthreads();
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kPerThread / 4; ++j) {
+    for (int j = 0; j < PT / 4; ++j) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (s * kSlice + 4 * (j * kWideThreads + tid) + e < N) {
+            if (s * kSlice + 4 * (j * TH + tid) + e < N) {
                 lo = fminf(lo, v[j][e]);
                 hi = fmaxf(hi, v[j][e]);
                 atomicAdd(&hist[anomaly_bin(v[j][e])], 1u);
@@ -82,7 +84,7 @@ __global__ __launch_bounds__(kWideThreads) void stats_hist_kernel(const float *_
     __syncthreads();
     const int64_t job_slice = (int64_t)k * n_slices + blockIdx.x;
     if (tid == 0) {
-        for (int i = 1; i < kWideThreads / 64; ++i) { lo = fminf(lo, red[0][i]); hi = fmaxf(hi, red[1][i]); }
+        for (int i = 1; i < TH / 64; ++i) { lo = fminf(lo, red[0][i]); hi = fmaxf(hi, red[1][i]); }
         sp[job_slice].lo = lo;
         sp[job_slice].hi = hi;
     }
@@ -90,13 +92,13 @@ __global__ __launch_bounds__(kWideThreads) void stats_hist_kernel(const float *_
 }
 
 // grid (units, 3); 256 threads, 8 bins each
-__global__ __launch_bounds__(kWideThreads) void stats_pick_kernel(int L, int H, PromptTab tab, SliceTab st,
+__global__ __launch_bounds__(256) void stats_pick_kernel(int L, int H, PromptTab tab, SliceTab st,
                                                                   int n_slices, const uint16_t *__restrict__ part,
                                                                   const SlicePart *__restrict__ sp,
                                                                   StatPick *__restrict__ picks,
                                                                   uint32_t *__restrict__ failed)
 {
-    __shared__ uint32_t wtot[kWideThreads / 64];
+    __shared__ uint32_t wtot[256 / 64];
     const int u = blockIdx.x, k = blockIdx.y;
     const int lh = u % (L * H), p = u / (L * H);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
@@ -166,8 +168,8 @@ __global__ __launch_bounds__(kWideThreads) void stats_pick_kernel(int L, int H, 
 
 // grid: slices.  All three scales of the slice in one pass: what stats_finish_kernel needs of each scale, and --
 // the ranges being known -- min, max and sum of the surprise statistic of the slice's tokens.
-template <bool ALL>
-__global__ __launch_bounds__(kWideThreads, 5) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows,
+template <int TH, bool ALL>
+__global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                      int L, int H, PromptTab tab, SliceTab st,
                                                                      int n_slices, int scale_mask,
                                                                      const StatPick *__restrict__ picks,
@@ -177,10 +179,10 @@ __global__ __launch_bounds__(kWideThreads, 5) void stats_collect_kernel(const fl
                                                                      SliceSurprise *__restrict__ sur,
                                                                      uint32_t *__restrict__ failed)
 {
-    constexpr int HALF = kPerThread / 2;
+    constexpr int HALF = per_thread<TH>() / 2;
     __shared__ uint32_t nTop[3], nBot[3];
-    __shared__ double red[8][kWideThreads / 64];
-    __shared__ float fred[2][kWideThreads / 64];
+    __shared__ double red[8][TH / 64];
+    __shared__ float fred[2][TH / 64];
     int p, lh, s, S;
     locate(st, tab, blockIdx.x, p, lh, s, S);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
@@ -207,10 +209,10 @@ __global__ __launch_bounds__(kWideThreads, 5) void stats_collect_kernel(const fl
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int j = 0; j < HALF; ++j) v[k][j] = slice_value(vals[k], tid, half * HALF + j);
+            for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, half * HALF + j);
 #pragma unroll
         for (int j = 0; j < HALF; ++j) {
-            if (s * kSlice + (half * HALF + j) * kWideThreads + tid < N) {
+            if (s * kSlice + (half * HALF + j) * TH + tid < N) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     const float x = v[k][j];
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(kWideThreads, 5) void stats_collect_kernel(const fl
     if (tid < 3) {
         const int k = tid;
         double t = 0.0, b = 0.0;
-        for (int i = 0; i < kWideThreads / 64; ++i) { t += red[2 * k][i]; b += red[2 * k + 1][i]; }
+        for (int i = 0; i < TH / 64; ++i) { t += red[2 * k][i]; b += red[2 * k + 1][i]; }
         SlicePart *q = sp + (int64_t)k * n_slices + blockIdx.x;
         q->sTop = t;
         q->sBot = b;
@@ -262,15 +264,15 @@ __global__ __launch_bounds__(kWideThreads, 5) void stats_collect_kernel(const fl
     if (tid == 64) {
         double t = 0.0;
         float lo = INFINITY, hi = -INFINITY;
-        for (int i = 0; i < kWideThreads / 64; ++i) { t += red[6][i]; lo = fminf(lo, fred[0][i]); hi = fmaxf(hi, fred[1][i]); }
+        for (int i = 0; i < TH / 64; ++i) { t += red[6][i]; lo = fminf(lo, fred[0][i]); hi = fmaxf(hi, fred[1][i]); }
         sur[blockIdx.x] = SliceSurprise{lo, hi, t};
     }
 }
 
 // grid: slices.  Blend, gate, route and pinning of the slice's tokens (Section 2.4); every workgroup forms its
 // head's weights and surprise statistics itself from the few numbers they depend on.
-template <bool ALL>
-__global__ __launch_bounds__(kWideThreads, 5) void route_slice_kernel(const float *__restrict__ a_raw, int64_t rows,
+template <int TH, bool ALL>
+__global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                    int L, int H, PromptTab tab, SliceTab st,
                                                                    LearnerConsts lc, const float *__restrict__ stats,
                                                                    const SliceSurprise *__restrict__ sur,
@@ -283,13 +285,13 @@ __global__ __launch_bounds__(kWideThreads, 5) void route_slice_kernel(const floa
     const int64_t base = (int64_t)lh * tab.T + tab.tok_off[p];
     const float *a = a_raw + base;
     const int tid = threadIdx.x;
-    constexpr int HALF = kPerThread / 2;
+    constexpr int HALF = per_thread<TH>() / 2;
     float v[3][HALF];
     const __amdgpu_buffer_rsrc_t vals[3] = {slice_values(a, s, N), slice_values(a + rows, s, N), slice_values(a + 2 * rows, s, N)};
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int j = 0; j < HALF; ++j) v[k][j] = slice_value(vals[k], tid, j);
+        for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, j);
     if (tid == 0) {
         head_weights(stats + ((int64_t)p * L * H + lh) * 12, lc, hs);
         float smin = INFINITY, smax = -INFINITY;
@@ -314,11 +316,11 @@ __global__ __launch_bounds__(kWideThreads, 5) void route_slice_kernel(const floa
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int j = 0; j < HALF; ++j) v[k][j] = slice_value(vals[k], tid, HALF + j);
+                for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, HALF + j);
         }
 #pragma unroll
         for (int j = 0; j < HALF; ++j) {
-            const int i = s * kSlice + (half * HALF + j) * kWideThreads + tid;
+            const int i = s * kSlice + (half * HALF + j) * TH + tid;
             if (i < N) {
                 const float raw[3] = {v[0][j], v[1][j], v[2][j]};
                 float at[3];
@@ -351,25 +353,28 @@ __global__ __launch_bounds__(64) void stats_finish_kernel(const float *__restric
     const int lane = threadIdx.x;
     const int64_t slice0 = (int64_t)k * n_slices + st.off[p] + (int64_t)lh * S;
     const StatPick pk = picks[job];
-    // slices in order: lists, sums, min, max
+    // lists; sums over the slices (slice s0 + lane of a batch), min, max
     uint32_t nT = 0u, nB = 0u;
     double sTop = 0.0, sBot = 0.0;
     float lo = INFINITY, hi = -INFINITY;
-    for (int s = 0; s < S && !bad; ++s) {
-        const SlicePart q = sp[slice0 + s];
-        if (q.nTop > (uint32_t)kSeg || q.nBot > (uint32_t)kSeg || nT + q.nTop > (uint32_t)kList ||
-            nB + q.nBot > (uint32_t)kList) {
-            bad = true;
-            break;
+    if (!bad) {
+        int none;
+        const int t = gather_segments(segTop + slice0 * kSeg, S, [&](int s) { return sp[slice0 + s].nTop; }, keys[0], kList, -1, none);
+        const int b = gather_segments(segBot + slice0 * kSeg, S, [&](int s) { return sp[slice0 + s].nBot; }, keys[1], kList, -1, none);
+        bad = t < 0 || b < 0;
+        nT = (uint32_t)t;
+        nB = (uint32_t)b;
+        for (int s = lane; s < S; s += 64) {
+            const SlicePart q = sp[slice0 + s];
+            sTop += q.sTop;
+            sBot += q.sBot;
+            lo = fminf(lo, q.lo);
+            hi = fmaxf(hi, q.hi);
         }
-        for (uint32_t i = lane; i < q.nTop; i += 64) keys[0][nT + i] = segTop[(slice0 + s) * kSeg + i];
-        for (uint32_t i = lane; i < q.nBot; i += 64) keys[1][nB + i] = segBot[(slice0 + s) * kSeg + i];
-        nT += q.nTop;
-        nB += q.nBot;
-        sTop += q.sTop;
-        sBot += q.sBot;
-        lo = fminf(lo, q.lo);
-        hi = fmaxf(hi, q.hi);
+        sTop = wave_sum(sTop);
+        sBot = wave_sum(sBot);
+        lo = wave_min(lo);
+        hi = wave_max(hi);
     }
     // The lists' order depends on the timing of the collecting workgroups, so their entries are added up in
     // fixed point (2^-40 units, exact for fp32 values of magnitude <= 1 down to that resolution): the sum does
@@ -472,15 +477,16 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
     uint32_t *failed = (uint32_t *)(base + lay.failed);
     const int64_t rows = (int64_t)L * H * tab.T;
     const unsigned units = (unsigned)(tab.n * L * H);
-    stats_hist_kernel<<<dim3((unsigned)slices, 3), kWideThreads, 0, st>>>(a_raw, rows, tab, stab, slices, part, sp);
+    const bool few = few_slices(slices);
+    (few ? stats_hist_kernel<1024> : stats_hist_kernel<256>)<<<dim3((unsigned)slices, 3), few ? 1024 : 256, 0, st>>>(
+        a_raw, rows, tab, stab, slices, part, sp);
     SliceSurprise *sur = (SliceSurprise *)(base + lay.sur);
-    stats_pick_kernel<<<dim3(units, 3), kWideThreads, 0, st>>>(L, H, tab, stab, slices, part, sp, picks, failed);
-    if (scale_mask == 7)
-        stats_collect_kernel<true><<<(unsigned)slices, kWideThreads, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask,
-                                                                             picks, segTop, segBot, sp, sur, failed);
-    else
-        stats_collect_kernel<false><<<(unsigned)slices, kWideThreads, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask,
-                                                                              picks, segTop, segBot, sp, sur, failed);
+    stats_pick_kernel<<<dim3(units, 3), 256, 0, st>>>(L, H, tab, stab, slices, part, sp, picks, failed);
+    const bool all = scale_mask == 7;
+    const auto collect = few ? (all ? stats_collect_kernel<1024, true> : stats_collect_kernel<1024, false>)
+                             : (all ? stats_collect_kernel<256, true> : stats_collect_kernel<256, false>);
+    collect<<<(unsigned)slices, few ? 1024 : 256, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask, picks, segTop, segBot, sp,
+                                                           sur, failed);
     stats_finish_kernel<<<dim3(units, 3), 64, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, picks, segTop, segBot,
                                                        sp, failed, stats);
     return hipGetLastError();
@@ -495,12 +501,10 @@ hipError_t launch_route_wide(const float *a_raw, int L, int H, const PromptTab &
     const int slices = fill_slices(L, H, tab, &stab, kUnitTokens);
     const WideWs lay = wide_ws(L, H, tab);
     const SliceSurprise *sur = (const SliceSurprise *)((char *)ws + lay.sur);
-    if (lc.scale_mask == 7)
-        route_slice_kernel<true><<<(unsigned)slices, kWideThreads, 0, st>>>(a_raw, (int64_t)L * H * tab.T, L, H, tab, stab,
-                                                                           lc, stats, sur, scores);
-    else
-        route_slice_kernel<false><<<(unsigned)slices, kWideThreads, 0, st>>>(a_raw, (int64_t)L * H * tab.T, L, H, tab, stab,
-                                                                            lc, stats, sur, scores);
+    const bool few = few_slices(slices), all = lc.scale_mask == 7;
+    const auto route = few ? (all ? route_slice_kernel<1024, true> : route_slice_kernel<1024, false>)
+                           : (all ? route_slice_kernel<256, true> : route_slice_kernel<256, false>);
+    route<<<(unsigned)slices, few ? 1024 : 256, 0, st>>>(a_raw, (int64_t)L * H * tab.T, L, H, tab, stab, lc, stats, sur, scores);
     return hipGetLastError();
 }
 

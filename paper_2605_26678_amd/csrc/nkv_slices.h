@@ -1,9 +1,10 @@
 // Slices: the unit of work of the kernels that spread a head's per-token values over the whole chip.
 //
-// A head's N values are cut into slices of 8192 tokens; a kernel that touches the values runs one 256-thread
-// workgroup per slice (32 values per thread, element i of the slice in slot i / 256 of thread i % 256, so
-// every load instruction of a wavefront is one contiguous 256-byte piece).  Slices are numbered prompt by
-// prompt; inside a prompt (layer * H + head)-major, so the slices of a head -- and of a layer -- are contiguous.
+// A head's N values are cut into slices of 8192 tokens; a kernel that touches the values runs one workgroup of TH
+// threads per slice (8192 / TH values per thread, element i of the slice in slot i / TH of thread i % TH, so
+// every load instruction of a wavefront is one contiguous 256-byte piece).  TH is 256, four workgroups to a compute unit,
+// or 1024 where there are too few slices to fill the chip: a slice is then done in a quarter of the time (see
+// slice_threads).  Slices are numbered prompt by prompt; inside a prompt (layer * H + head)-major, so the slices of a head -- and of a layer -- are contiguous.
 //
 // Values are binned by a monotone map of the value into 2048 bins; a per-slice histogram is stored as 2048
 // 16-bit counts.  Exact work happens only on the entries of one boundary bin, which every slice copies into
@@ -17,8 +18,12 @@ namespace {
 
 constexpr int kSlice = 8192;             // tokens per slice (the counts of a slice fit 16 bits)
 constexpr int kBins = 2048;
-constexpr int kWideThreads = 256;
-constexpr int kPerThread = kSlice / kWideThreads;
+// Up to two slices per compute unit: with 1024 threads each they are all resident, and quicker (one layer of 8 heads x
+// 32768 tokens, 32 slices: statistics' collecting kernel 17 -> 7 us); many slices keep the chip full either way, and the
+// smaller workgroup has fewer wavefronts at its barriers.
+constexpr int kFewSlices = 512;
+inline bool few_slices(int slices) { return slices <= kFewSlices; }
+template <int TH> constexpr int per_thread() { return kSlice / TH; }
 constexpr int kSeg = 256;                // keys one slice may contribute to a list
 
 struct SliceTab {                        // first slice of every prompt; a prompt has L*H*S_p slices
@@ -54,7 +59,7 @@ __device__ __forceinline__ void locate(const SliceTab &st, const PromptTab &tab,
 }
 
 // The values of slice s of a head of N tokens, as the hardware's bounds-checked buffer: slot j of thread tid is
-// element j * 256 + tid of the slice (one instruction of a wavefront reads one contiguous 256-byte piece, the
+// element j * TH + tid of the slice (one instruction of a wavefront reads one contiguous 256-byte piece, the
 // address is a 32-bit register and a constant), and elements past the head's last token read as 0.  The whole
 // offset goes into the per-lane offset, which the range check is sure to cover.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_values(const float *head, int s, int N)
@@ -63,17 +68,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slice_values(const float *head
                                              min(N - s * kSlice, kSlice) * 4, 0x00020000);
 }
 
-__device__ __forceinline__ float slice_value(__amdgpu_buffer_rsrc_t r, int tid, int j)
+template <int TH> __device__ __forceinline__ float slice_value(__amdgpu_buffer_rsrc_t r, int tid, int j)
 {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, tid * 4 + j * (kWideThreads * 4), 0, 0));
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, tid * 4 + j * (TH * 4), 0, 0));
 }
 
 // Four consecutive values per thread and load, for kernels that do not care which thread holds which value
-// (histograms, minima): slot j of thread tid holds elements 4 (j * 256 + tid) .. + 3 of the slice.  The range check
+// (histograms, minima): slot j of thread tid holds elements 4 (j * TH + tid) .. + 3 of the slice.  The range check
 // is per 32-bit word, so a head's last values are delivered and the words behind them read as 0.
-__device__ __forceinline__ void slice_values4(__amdgpu_buffer_rsrc_t r, int tid, int j, float (&v)[4])
+template <int TH> __device__ __forceinline__ void slice_values4(__amdgpu_buffer_rsrc_t r, int tid, int j, float (&v)[4])
 {
-    const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, (j * kWideThreads + tid) * 16, 0, 0);
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(r, (j * TH + tid) * 16, 0, 0);
     v[0] = __uint_as_float(q[0]); v[1] = __uint_as_float(q[1]); v[2] = __uint_as_float(q[2]); v[3] = __uint_as_float(q[3]);
 }
 
@@ -91,37 +96,75 @@ __device__ __forceinline__ int anomaly_bin(float a)
     return x >= 2047.0f ? 2047 : (x > 0.f ? (int)x : 0);
 }
 
-// The 2048 counts of a workgroup's LDS histogram as 16-bit values: 8 bins per thread, one 16-byte store.
+// The 2048 counts of a workgroup's LDS histogram as 16-bit values: 8 bins per thread and 16-byte store, by 256 threads.
 __device__ __forceinline__ void store_hist16(const uint32_t *hist, uint16_t *row)
 {
-    const uint32_t *h8 = hist + threadIdx.x * 8;
-    reinterpret_cast<uint4 *>(row)[threadIdx.x] = make_uint4(h8[0] | (h8[1] << 16), h8[2] | (h8[3] << 16),
-                                                             h8[4] | (h8[5] << 16), h8[6] | (h8[7] << 16));
+    if (threadIdx.x >= kBins / 8) return;
+    const uint4 a = reinterpret_cast<const uint4 *>(hist)[2 * threadIdx.x], b = reinterpret_cast<const uint4 *>(hist)[2 * threadIdx.x + 1];
+    reinterpret_cast<uint4 *>(row)[threadIdx.x] = make_uint4(a.x | (a.y << 16), a.z | (a.w << 16), b.x | (b.y << 16), b.z | (b.w << 16));
 }
 
 // Histogram of the scores of one slice.  grid: slices; part: [slices][kBins] 16-bit counts.
-__global__ __launch_bounds__(kWideThreads) void slice_hist_kernel(const float *__restrict__ scores, PromptTab tab,
-                                                                  SliceTab st, uint16_t *__restrict__ part)
+template <int TH>
+__global__ __launch_bounds__(TH) void slice_hist_kernel(const float *__restrict__ scores, PromptTab tab, SliceTab st,
+                                                        uint16_t *__restrict__ part)
 {
-    __shared__ uint32_t hist[kBins];
+    constexpr int PT = per_thread<TH>();
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
     int p, lh, s, S;
     locate(st, tab, blockIdx.x, p, lh, s, S);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
     const float *sc = scores + (int64_t)lh * tab.T + tab.tok_off[p];
     const int tid = threadIdx.x;
-    for (int j = tid; j < kBins; j += kWideThreads) hist[j] = 0u;
-    float v[kPerThread / 4][4];
+    for (int j = tid; j < kBins; j += TH) hist[j] = 0u;
+    float v[PT / 4][4];
     const __amdgpu_buffer_rsrc_t vals = slice_values(sc, s, N);
 #pragma unroll
-    for (int j = 0; j < kPerThread / 4; ++j) slice_values4(vals, tid, j, v[j]);
+    for (int j = 0; j < PT / 4; ++j) slice_values4<TH>(vals, tid, j, v[j]);
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kPerThread / 4; ++j)
+    for (int j = 0; j < PT / 4; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (s * kSlice + 4 * (j * kWideThreads + tid) + e < N) atomicAdd(&hist[score_bin(v[j][e])], 1u);
+            if (s * kSlice + 4 * (j * TH + tid) + e < N) atomicAdd(&hist[score_bin(v[j][e])], 1u);
     __syncthreads();
     store_hist16(hist, part + (int64_t)blockIdx.x * kBins);
+}
+
+// Copies the lists of a unit's S slices (segment s: `count(s)` keys from seg + s * kSeg on) one behind the other to
+// keys[0 .. cap), by one wavefront with the loads of four segments in flight; returns the number of keys, or -1 if a
+// segment or the list overflows.  before: keys of the slices in front of slice `own`.
+template <typename F>
+__device__ __forceinline__ int gather_segments(const uint32_t *__restrict__ seg, int S, F count, uint32_t *keys, int cap, int own,
+                                               int &before)
+{
+    const int lane = threadIdx.x & 63;
+    int n = 0;
+    before = 0;
+    for (int s0 = 0; s0 < S; s0 += 64) {
+        const uint32_t c = s0 + lane < S ? count(s0 + lane) : 0u;
+        if (__any(c > (uint32_t)kSeg)) return -1;
+        const uint32_t incl = wave_prefix_sum(c);
+        const int total = __builtin_amdgcn_readlane((int)incl, 63);
+        if (n + total > cap) return -1;
+        const int off = n + (int)(incl - c);
+        if (own >= s0 && own < s0 + 64) before = __builtin_amdgcn_readlane(off, own - s0);
+        const int m = min(64, S - s0);
+        for (int i0 = 0; i0 < m; i0 += 4) {
+            uint32_t first[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) first[i] = seg[(int64_t)(s0 + min(i0 + i, m - 1)) * kSeg + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (i0 + i >= m) break;
+                const int ci = __builtin_amdgcn_readlane((int)c, i0 + i), oi = __builtin_amdgcn_readlane(off, i0 + i);
+                if (lane < ci) keys[oi + lane] = first[i];
+                for (int j = lane + 64; j < ci; j += 64) keys[oi + j] = seg[(int64_t)(s0 + i0 + i) * kSeg + j];
+            }
+        }
+        n += total;
+    }
+    return n;
 }
 
 }  // namespace
