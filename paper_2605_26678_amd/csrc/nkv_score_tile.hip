@@ -185,54 +185,52 @@ template <int KF> __device__ __forceinline__ u32x4 staged_piece(const Piece<KF> 
     }
 }
 
-// Sum of the squares of a lane's eight values of a row, ready to be read by any vector instruction (see above).
-template <int KF> __device__ __forceinline__ float piece_sumsq(const u32x4 &r)
+// Sums of the squares of a lane's eight values of each of its four rows, ready to be read by any vector instruction (the
+// compiler does not see the writes inside the assembly): four independent chains of exact products.
+template <int KF> __device__ __forceinline__ void rows_sumsq(const u32x4 (&r)[4], float (&ss)[4])
 {
-    float acc = 0.f;
-    if constexpr (KF == kKeyF16)
-        asm("v_dot2c_f32_f16 %0, %1, %1\n\t"
-            "v_dot2c_f32_f16 %0, %2, %2\n\t"
-            "v_dot2c_f32_f16 %0, %3, %3\n\t"
-            "v_dot2c_f32_f16 %0, %4, %4\n\t"
-            "s_nop 3"
-            : "+v"(acc)
-            : "v"(r.x), "v"(r.y), "v"(r.z), "v"(r.w));
-    else
-        asm("v_dot2c_f32_bf16 %0, %1, %1\n\t"
-            "v_dot2c_f32_bf16 %0, %2, %2\n\t"
-            "v_dot2c_f32_bf16 %0, %3, %3\n\t"
-            "v_dot2c_f32_bf16 %0, %4, %4\n\t"
-            "s_nop 3"
-            : "+v"(acc)
-            : "v"(r.x), "v"(r.y), "v"(r.z), "v"(r.w));
-    return acc;
+#define NKV_DOTS(OP)                                                                                                      \
+    asm(OP " %0, %4, %4\n\t" OP " %1, %8, %8\n\t" OP " %2, %12, %12\n\t" OP " %3, %16, %16\n\t"                            \
+        OP " %0, %5, %5\n\t" OP " %1, %9, %9\n\t" OP " %2, %13, %13\n\t" OP " %3, %17, %17\n\t"                            \
+        OP " %0, %6, %6\n\t" OP " %1, %10, %10\n\t" OP " %2, %14, %14\n\t" OP " %3, %18, %18\n\t"                          \
+        OP " %0, %7, %7\n\t" OP " %1, %11, %11\n\t" OP " %2, %15, %15\n\t" OP " %3, %19, %19\n\t"                          \
+        "s_nop 3"                                                                                                         \
+        : "+v"(ss[0]), "+v"(ss[1]), "+v"(ss[2]), "+v"(ss[3])                                                              \
+        : "v"(r[0].x), "v"(r[0].y), "v"(r[0].z), "v"(r[0].w), "v"(r[1].x), "v"(r[1].y), "v"(r[1].z), "v"(r[1].w),          \
+          "v"(r[2].x), "v"(r[2].y), "v"(r[2].z), "v"(r[2].w), "v"(r[3].x), "v"(r[3].y), "v"(r[3].z), "v"(r[3].w))
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ss[j] = 0.f;
+    if constexpr (KF == kKeyF16) NKV_DOTS("v_dot2c_f32_f16");
+    else NKV_DOTS("v_dot2c_f32_bf16");
+#undef NKV_DOTS
 }
 
 // One group of 16 tokens in row-wise layout (lane (g, c): rows 4g .. 4g+3, dims 8c .. 8c+7; tok0 = the group's
 // first token, which may lie in front of the prompt): ||k||^2 and the weight 1/||k|| of every row (0 for tokens
-// outside [0, tok_end)) go to ss_out / w_out, and to ww for this lane's own rows.
+// outside [0, tok_end)) go to ss_out / w_out.  The four rows of a lane are reduced together by a transposing butterfly,
+// after which lane (g, c) holds row 4g + c % 4: one square root per group instead of one per row.
 template <int KF> __device__ __forceinline__ void group_norms(const u32x4 (&raw)[4], int tok0, int tok_end, int g, int c, float *w_out,
-                                            float *ss_out, float (&ww)[4])
+                                            float *ss_out)
 {
     float ss[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        ss[j] = row_sum<16>(piece_sumsq<KF>(raw[j]));
-        const int tok = tok0 + 4 * g + j;
-        ww[j] = (tok >= 0 && tok < tok_end) ? inv_norm(ss[j]) : 0.f;
-    }
-    if (c == 0) {
-        *reinterpret_cast<float4 *>(w_out + 4 * g) = make_float4(ww[0], ww[1], ww[2], ww[3]);
-        *reinterpret_cast<float4 *>(ss_out + 4 * g) = make_float4(ss[0], ss[1], ss[2], ss[3]);
+    rows_sumsq<KF>(raw, ss);
+    float s = merge_low4(ss);
+    s += dpp_mov<0x124>(s);                                           // row_ror:4
+    s += dpp_mov<0x128>(s);                                           // row_ror:8
+    const int tok = tok0 + 4 * g + (c & 3);
+    const float ww = tok >= 0 && tok < tok_end ? inv_norm(s) : 0.f;
+    if (c < 4) {                                                      // (the quads' sums may differ in the last bit: one of them counts)
+        w_out[4 * g + c] = ww;
+        ss_out[4 * g + c] = s;
     }
 }
 
-// The same, and the weighted sum of the group's rows to sum_out (32 KS floats).
-template <int KF, int KS> __device__ __forceinline__ void group_sum(const u32x4 (&raw)[4], int tok0, int tok_end, int g, int c, float *w_out,
-                                          float *ss_out, float *sum_out)
+// The weighted sum of the group's rows to sum_out (32 KS floats), with the weights that group_norms left (same wave: in
+// order).
+template <int KF, int KS> __device__ __forceinline__ void group_sum(const u32x4 (&raw)[4], int g, int c, const float *w_in, float *sum_out)
 {
-    float ww[4];
-    group_norms<KF>(raw, tok0, tok_end, g, c, w_out, ss_out, ww);
+    const float4 w4 = *reinterpret_cast<const float4 *>(w_in + 4 * g);
+    const float ww[4] = {w4.x, w4.y, w4.z, w4.w};
     float T[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) T[e] = 0.f;
@@ -245,6 +243,14 @@ template <int KF, int KS> __device__ __forceinline__ void group_sum(const u32x4 
     }
     const float2 t2 = sum_over_rows16_transposing(T);
     if (KS == 4 || 8 * c < 32 * KS) *reinterpret_cast<float2 *>(sum_out + 8 * c + 2 * g) = t2;
+}
+
+// ||k_hat|| of a token, 1 unless its norm is below the clamp (rare: one uniform test instead of a square root per token)
+__device__ __forceinline__ float unit_norm(float ss)
+{
+    float k = 1.f;
+    if (__any(ss < 1e-24f)) k = ss < 1e-24f ? sqrtf(ss) * 1e12f : 1.f;
+    return k;
 }
 
 // Dims 2 lane and 2 lane + 1 of a vector of 32 KS floats (0 past its end).
@@ -397,12 +403,14 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     // ---- the block's own groups: norms and partial sums, nothing else in front of the block total ----
     u32x4 row[5][4];                                                  // the rows in the staged format
 #pragma unroll
-    for (int m = 1; m < 5; ++m)
-        if (ex[m]) {
+    for (int m = 1; m < 6; ++m) {                                     // a group's sum behind the next one's norms
+        if (m < 5 && ex[m]) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) row[m][j] = staged_piece<KF>(raw[m][j]);
-            group_sum<SF, KS>(row[m], blk_lo + kGroup * (w + 4 * (m - 1)), blk_hi, g, c, lds_w[w][m], lds_ss[w][m], lds_T[4 + w + 4 * (m - 1)]);
+            group_norms<SF>(row[m], blk_lo + kGroup * (w + 4 * (m - 1)), blk_hi, g, c, lds_w[w][m], lds_ss[w][m]);
         }
+        if (m > 1 && ex[m - 1]) group_sum<SF, KS>(row[m - 1], g, c, lds_w[w][m - 1], lds_T[4 + w + 4 * (m - 2)]);
+    }
     __syncthreads();
 
     // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1 ----
@@ -425,7 +433,8 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     // ---- the halo group's sum (the window sums in front of the block's first groups need it) ----
 #pragma unroll
     for (int j = 0; j < 4; ++j) row[0][j] = staged_piece<KF>(raw[0][j]);
-    group_sum<SF, KS>(row[0], blk_lo + kGroup * (w - 4), blk_hi, g, c, lds_w[w][0], lds_ss[w][0], lds_T[w]);
+    group_norms<SF>(row[0], blk_lo + kGroup * (w - 4), blk_hi, g, c, lds_w[w][0], lds_ss[w][0]);
+    group_sum<SF, KS>(row[0], g, c, lds_w[w][0], lds_T[w]);
 
     float *S_unit = ssum + (int64_t)it.unit * D;
     // (The adds have had the halo group to come back.)  The last block to add to a word of the unit stores the word's final
@@ -526,7 +535,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
             const float d_part = 2.f * (wn * c_part - wp * e_part) + (2.f * wn * wp * xd - gsum);
             const float cdot = sum_over_rows16(c_part);               // <k_i, W_i>
             const float Pn = P0 + row_prefix_sum(sum_over_rows16(d_part));
-            const float knn = ssn < 1e-24f ? sqrtf(ssn) * 1e12f : 1.f;
+            const float knn = unit_norm(ssn);
             const float ac = neg_cos(wn * cdot, knn, Pn);
             const float ae = neg_cos(wn * sum3(AG), knn, bsq);        // meaningful in lane group 1 (rows 4 .. 6)
             const int soff = (blk_lo + kGroup * q) * 4;                // (an offset that was past the buffer stays past it)
@@ -573,7 +582,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
                 const int q = w + 4 * (m - 1);
                 const f32x4 AS = tile<SF, KS>(An, X[m]);
                 const float wn = lds_w[w][m][n], ssn = lds_ss[w][m][n];
-                const float knn = ssn < 1e-24f ? sqrtf(ssn) * 1e12f : 1.f;
+                const float knn = unit_norm(ssn);
                 const float as = neg_cos(wn * sum3(AS), knn, ssq);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + (blk_lo + kGroup * q) * 4, 0, 0);
             }
@@ -630,12 +639,11 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk)
                 X[kk] = staged_piece<KF>(row_load<KF>(rsrc, 32 * kk + 8 * qq < dims ? off + 32 * ES * kk : kNoByte));
-            float ww[4];
-            group_norms<SF>(raw, tok0, blk_hi, g, c, lds_w[w], lds_ss[w], ww);
+            group_norms<SF>(raw, tok0, blk_hi, g, c, lds_w[w], lds_ss[w]);
             __builtin_amdgcn_wave_barrier();
             const float wn = lds_w[w][n], ss = lds_ss[w][n];
             __builtin_amdgcn_wave_barrier();                          // the next group rewrites them
-            const float knn = ss < 1e-24f ? sqrtf(ss) * 1e12f : 1.f;
+            const float knn = unit_norm(ss);
             const f32x4 AS = tile<SF, KS>(An, X);
             const float as = neg_cos(wn * sum3(AS), knn, ssq);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + tok0 * 4, 0, 0);
