@@ -8,7 +8,10 @@
 // The work is one read of every retained K and V row, so it is bound by HBM.  Units have different lengths
 // (head-wise budgets), so they are cut into chunks of 256 rows and one workgroup handles one chunk for all G
 // query heads at once (K and V are read once, not G times):
-//   decode_plan_kernel    : chunk_off[u] = chunks before unit u (exclusive scan of ceil(len_u / 256))
+//   decode_plan_kernel    : chunk_off[u] = chunks before unit u (exclusive scan of ceil(len_u / 256)); with few chunks
+//                           and units every workgroup of the other two kernels works its place out itself (SELF: one
+//                           launch fewer, 17 -> 13 us for 64 units of 204 to 1638 rows; with thousands of chunks it costs
+//                           more than it saves)
 //   decode_chunk_kernel   : per chunk, running-maximum softmax in base 2: (m, l, o[0..D)) per query head
 //   decode_combine_kernel : per (unit, query head) merges the chunks' partial results
 // Lane layout in decode_chunk_kernel as in the scoring kernel: a row is spread over D/8 lanes (16 bytes each),
@@ -121,13 +124,43 @@ __global__ __launch_bounds__(1024) void decode_plan_kernel(const int64_t *__rest
     }
 }
 
+// Few units: chunk_off of units 0 .. n_units (n_units <= kSelfUnits) to LDS, by a whole workgroup of TH threads.
+constexpr int kSelfUnits = 256, kSelfChunks = 1024;
+template <int TH>
+__device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, int n_units, int64_t rows, int32_t *chunk_off)
+{
+    constexpr int PER = kSelfUnits / TH, NW = TH / 64;
+    __shared__ uint32_t wtot[NW];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    uint32_t c[PER], mine = 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int u = tid * PER + i;
+        const int64_t a = clamp_row(head_off[min(u, n_units)], rows), b = clamp_row(head_off[min(u + 1, n_units)], rows);
+        c[i] = (uint32_t)((max(b - a, (int64_t)0) + kChunk - 1) / kChunk);
+        mine += c[i];
+    }
+    const uint32_t incl = wave_prefix_sum(mine);
+    if (lane == 63) wtot[w] = incl;
+    __syncthreads();
+    uint32_t run = incl - mine;
+    for (int i = 0; i < w; ++i) run += wtot[i];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (tid * PER + i <= n_units) chunk_off[tid * PER + i] = (int32_t)run;
+        run += c[i];
+    }
+    if (tid == TH - 1) chunk_off[kSelfUnits] = (int32_t)run;          // (only read if n_units == kSelfUnits)
+    __syncthreads();
+}
+
 // part: per chunk and query head D + 2 floats: running maximum (base-2 logits), sum of weights, weighted values.
-template <int D, int G, bool F16>
+template <int D, int G, bool F16, bool SELF>
 __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_t *__restrict__ q,
                                                                    const uint16_t *__restrict__ pk,
                                                                    const uint16_t *__restrict__ pv,
                                                                    const int64_t *__restrict__ head_off,
-                                                                   const int32_t *__restrict__ chunk_off, int n_units,
+                                                                   const int32_t *chunk_off, int n_units,
                                                                    int64_t rows, float scale_log2,
                                                                    float *__restrict__ part)
 {
@@ -136,13 +169,13 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
     __shared__ float lds_m[NW * RPW][G], lds_l[NW * RPW][G];
     __shared__ float lds_o[NW * RPW][G][D];
     const int chunk = blockIdx.x;
-    if (chunk >= chunk_off[n_units]) return;
-    int lo = 0, hi = n_units;                                        // largest u with chunk_off[u] <= chunk
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (chunk_off[mid] <= chunk) lo = mid; else hi = mid;
+    __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
+    if constexpr (SELF) {
+        plan_here<kDecThreads>(head_off, n_units, rows, lds_off);
+        chunk_off = lds_off;
     }
-    const int u = lo, ci = chunk - chunk_off[u];
+    if (chunk >= chunk_off[n_units]) return;
+    const int u = wave_search(chunk_off, n_units, chunk), ci = chunk - chunk_off[u];
     const int64_t first = clamp_row(head_off[u], rows), len = clamp_row(head_off[u + 1], rows) - first;
     const int n = (int)min((int64_t)kChunk, len - (int64_t)ci * kChunk);     // rows of this chunk, >= 1
     const int64_t r0 = first + (int64_t)ci * kChunk;
@@ -250,12 +283,17 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
 }
 
 // grid: n_units * G workgroups of D threads (D = 64 or 128: one or two waves)
-template <int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(const float *__restrict__ part,
-                                                           const int32_t *__restrict__ chunk_off, int G,
+template <int D, bool SELF>
+__global__ __launch_bounds__(D) void decode_combine_kernel(const float *__restrict__ part, const int64_t *__restrict__ head_off,
+                                                           int n_units, int64_t rows, const int32_t *chunk_off, int G,
                                                            float *__restrict__ out, float *__restrict__ lse)
 {
     __shared__ float red[D / 64];
+    __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
+    if constexpr (SELF) {
+        plan_here<D>(head_off, n_units, rows, lds_off);
+        chunk_off = lds_off;
+    }
     const int u = blockIdx.x / G, g = blockIdx.x - u * G, e = threadIdx.x;
     const int c0 = chunk_off[u], c1 = chunk_off[u + 1];
     // the largest running maximum: chunks spread over the threads, then one reduction
@@ -357,13 +395,14 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
 {
     int32_t *chunk_off = (int32_t *)ws;
     float *part = (float *)((char *)ws + ((size_t)(n_units + 1) * 4 + 255) / 256 * 256);
-    decode_plan_kernel<<<1, 1024, 0, st>>>(head_off, n_units, rows, chunk_off);
     const unsigned groups = (unsigned)max_chunks(n_units, rows);
+    const bool self = n_units <= kSelfUnits && groups <= (unsigned)kSelfChunks;
+    if (!self) decode_plan_kernel<<<1, 1024, 0, st>>>(head_off, n_units, rows, chunk_off);
     prof.begin(NKV_KERNEL_DECODE, st);
-#define NKV_DEC(GG)                                                                                             \
-    case GG:                                                                                                   \
-        decode_chunk_kernel<D, GG, F16><<<groups, kDecThreads, 0, st>>>(q, pk, pv, head_off, chunk_off, n_units, rows, \
-                                                                   scale_log2, part);                         \
+#define NKV_DEC(GG)                                                                                                     \
+    case GG:                                                                                                           \
+        (self ? decode_chunk_kernel<D, GG, F16, true> : decode_chunk_kernel<D, GG, F16, false>)<<<groups, kDecThreads, 0, st>>>( \
+            q, pk, pv, head_off, chunk_off, n_units, rows, scale_log2, part);                                          \
         break
     switch (G) {
         NKV_DEC(1); NKV_DEC(2); NKV_DEC(3); NKV_DEC(4); NKV_DEC(5); NKV_DEC(6); NKV_DEC(7); NKV_DEC(8);
@@ -371,7 +410,8 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     }
 #undef NKV_DEC
     prof.end(NKV_KERNEL_DECODE, st);
-    decode_combine_kernel<D><<<(unsigned)(n_units * G), D, 0, st>>>(part, chunk_off, G, out, lse);
+    (self ? decode_combine_kernel<D, true> : decode_combine_kernel<D, false>)<<<(unsigned)(n_units * G), D, 0, st>>>(
+        part, head_off, n_units, rows, chunk_off, G, out, lse);
     return hipGetLastError();
 }
 

@@ -180,6 +180,7 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const float *__restr
 // ------------------------------------------------------------------------------------------------------
 constexpr int kUnitList = 1024;              // keys a list holds
 
+// EPT: values a thread holds per scale, enough for the longest prompt done this way; longer prompts' units are passed over
 template <int EPT, bool ALL>
 __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_kernel(const float *__restrict__ a_raw, int L, int H,
                                                                                       PromptTab tab, int u0, LearnerConsts lc,

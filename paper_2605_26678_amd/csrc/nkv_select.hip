@@ -154,10 +154,11 @@ template <int EPT>
 __global__ __launch_bounds__(kSelThreads, 8) void select_fast_kernel(const float *__restrict__ scores,
                                                                   const int32_t *__restrict__ k_per_head, int L,
                                                                   int H, PromptTab tab, int u0, float near_tol,
-                                                                  const int64_t *__restrict__ head_off,
+                                                                  int64_t *__restrict__ head_off,
                                                                   int64_t row_capacity,
                                                                   int32_t *__restrict__ kept_idx,
-                                                                  int64_t *__restrict__ near_count)
+                                                                  int64_t *__restrict__ near_count,
+                                                                  uint32_t *__restrict__ near_units)
 {
     __shared__ SelectScratch sel;
     __shared__ unsigned long long group_cnt[EPT * kWaves];           // (gt << 32 | eq) per (chunk, wave)
@@ -167,10 +168,25 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_fast_kernel(const float
     const int h = u % H, l = (u / H) % L, p = u / (H * L);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
     const int B = min(max(k_per_head[u], 0), N);
-    if (B == 0) return;
     const float *sc = scores + ((int64_t)l * H + h) * tab.T + tab.tok_off[p];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t out0 = head_off[u];
+    int64_t out0;
+    if (near_units) {
+        // A few thousand units at most: this workgroup places its unit in the output itself -- the rows the units in
+        // front of it keep -- which saves the scan kernel that otherwise runs first and zeroes near_count; the unit's
+        // near-threshold scores are left for the gather to add up.
+        unsigned long long run = 0ull;
+        for (int v = tid; v < u; v += kSelThreads) run += (unsigned long long)min(max(k_per_head[v], 0), unit_len(tab, L, H, v));
+        out0 = (int64_t)block_sum(run, near_acc);
+        if (tid == 0) {
+            head_off[u] = out0;
+            if (u == tab.n * L * H - 1) head_off[u + 1] = out0 + B;
+            if (B == 0 || B == N) near_units[u] = 0u;
+        }
+    } else {
+        out0 = head_off[u];
+    }
+    if (B == 0) return;
 
     uint32_t key[EPT];
 #pragma unroll
@@ -184,14 +200,17 @@ __global__ __launch_bounds__(kSelThreads, 8) void select_fast_kernel(const float
         uint32_t kmin, kmax;
         block_key_range<EPT>(key, N, sel, kmin, kmax);
         T = block_select<EPT, true>(key, N, (uint32_t)B, sel, kmin, kmax, rem, ties);
-        if (near_count) {                                             // tokens within near_tol of the threshold score
+        if (near_count || near_units) {                               // tokens within near_tol of the threshold score
             const float tv = key_value(T);
             unsigned long long c = 0;
 #pragma unroll
             for (int j = 0; j < EPT; ++j)
                 if (tid + j * kSelThreads < N && fabsf(key_value(key[j]) - tv) <= near_tol) ++c;
             c = block_sum(c, near_acc);
-            if (tid == 0) atomicAdd((unsigned long long *)near_count, c);
+            if (tid == 0) {
+                if (near_units) near_units[u] = (uint32_t)c;
+                else atomicAdd((unsigned long long *)near_count, c);
+            }
         }
     }
     // population of every (chunk, wave) group
@@ -246,17 +265,27 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint4 *__restrict__ k
                                                      int L, int H, int krow16, int vrow16, PromptTab tab,
                                                      const int64_t *__restrict__ head_off,
                                                      const int32_t *__restrict__ kept_idx, int64_t row_capacity,
-                                                     uint4 *__restrict__ packed_k, uint4 *__restrict__ packed_v)
+                                                     uint4 *__restrict__ packed_k, uint4 *__restrict__ packed_v,
+                                                     const uint32_t *__restrict__ near_units, int64_t *__restrict__ near_count)
 {
+    __shared__ unsigned long long near_acc[16];
     __shared__ int64_t srck[kRowsPerGroup], srcv[kRowsPerGroup];       // first vector of the source rows
     const int n_units = tab.n * L * H;
+    if (near_units && near_count && blockIdx.x == 0) {                              // the units' counts of near-threshold scores
+        unsigned long long t = 0ull;
+        for (int u = threadIdx.x; u < n_units; u += 256) t += near_units[u];
+        t = block_sum(t, near_acc);
+        if (threadIdx.x == 0) *near_count = (int64_t)t;
+    }
     const int64_t rows = min(head_off[n_units], row_capacity);
     const int64_t r0 = (int64_t)blockIdx.x * kRowsPerGroup;
     if (r0 >= rows) return;
     const int nr = (int)min((int64_t)kRowsPerGroup, rows - r0);
+    const int u_first = wave_search(head_off, n_units, r0);           // the last unit that starts at or in front of r0
+    const int64_t next = head_off[u_first + 1];
     if ((int)threadIdx.x < nr) {
         const int64_t r = r0 + threadIdx.x;
-        int lo = 0, hi = n_units;                   // largest u with head_off[u] <= r
+        int lo = u_first, hi = r < next ? lo + 1 : n_units;           // largest u with head_off[u] <= r
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
             if (head_off[mid] <= r) lo = mid; else hi = mid;
@@ -394,11 +423,17 @@ hipError_t launch_select_compact(const void *keys, const void *values, const Row
     for (int p = 0; p < tab.n; ++p) nmax = max(nmax, tab.tok_off[p + 1] - tab.tok_off[p]);
     const bool wide = wide_ws != nullptr && (nmax > 16384 || n_units >= 2048);
     const bool wide_places = wide && select_wide_places_units(n_units);
-    if (!wide_places) head_off_kernel<<<1, kThreads, 0, st>>>(k_per_head, L, H, tab, head_off, near_count);
+    // no unit keeps more than its prompt length, so the row count is bounded by L*H*T as well
+    const int64_t max_rows = row_capacity < (int64_t)L * H * tab.T ? row_capacity : (int64_t)L * H * tab.T;
+    // the per-unit kernels place their units themselves if a gather follows and there is scratch for a word per unit
+    const bool unit_places = !wide && wide_ws != nullptr && nmax <= 32 * kSelThreads && max_rows > 0 && !in_place &&
+                             select_wide_places_units(n_units);
+    uint32_t *const near_units = unit_places ? (uint32_t *)wide_ws : nullptr;
+    if (!wide_places && !unit_places) head_off_kernel<<<1, kThreads, 0, st>>>(k_per_head, L, H, tab, head_off, near_count);
     prof.begin(NKV_KERNEL_SELECT, st);
 #define NKV_SELECT_FAST(EPT)                                                                              \
     select_fast_kernel<EPT><<<(unsigned)n, kSelThreads, 0, st>>>(scores, k_per_head, L, H, tab, u0, near_tol, \
-                                                                 head_off, row_capacity, kept_idx, near_count)
+                                                                 head_off, row_capacity, kept_idx, near_count, near_units)
     // Slice-wise kernels where a head has more than two slices or there are thousands of units, and the caller
     // gave scratch (for a few hundred units of up to two slices the six launches cost what they save).
     if (wide) {
@@ -417,8 +452,6 @@ hipError_t launch_select_compact(const void *keys, const void *values, const Row
                                                               row_capacity, kept_idx, near_count);
 #undef NKV_SELECT_FAST
     prof.end(NKV_KERNEL_SELECT, st);
-    // no unit keeps more than its prompt length, so the row count is bounded by L*H*T as well
-    const int64_t max_rows = row_capacity < (int64_t)L * H * tab.T ? row_capacity : (int64_t)L * H * tab.T;
     if (max_rows > 0 && in_place) {
         const int krow16 = d * esize / 16, vrow16 = dv * esize / 16;
         prof.begin(NKV_KERNEL_GATHER, st);
@@ -451,7 +484,7 @@ hipError_t launch_select_compact(const void *keys, const void *values, const Row
         gather_kernel<<<groups, 256, 0, st>>>((const uint4 *)keys, (const uint4 *)values, km, vm, 16 / esize, L, H,
                                               d * esize / 16,
                                               dv * esize / 16, tab, head_off, kept_idx, row_capacity,
-                                              (uint4 *)packed_k, (uint4 *)packed_v);
+                                              (uint4 *)packed_k, (uint4 *)packed_v, near_units, near_count);
         prof.end(NKV_KERNEL_GATHER, st);
     }
     return hipGetLastError();
