@@ -476,7 +476,7 @@ int nkv_decode_workspace_bytes(const nkv_shape *shape, int32_t n_q_heads, int64_
     if (n_q_heads < shape->H || n_q_heads % shape->H) return NKV_EINVAL;
     if (shape->dtype == NKV_DTYPE_F8_E4M3) return NKV_EUNSUPPORTED;
     *bytes = decode_ws_bytes(shape->dtype, shape->d, shape->dv, n_q_heads / shape->H,
-                             (int64_t)shape->n_prompts * shape->L * shape->H, rows);
+                             (int64_t)shape->n_prompts * shape->L * shape->H, rows, false);
     return NKV_OK;
 }
 
@@ -496,10 +496,10 @@ int nkv_decode_attention(const void *q, const void *packed_k, const void *packed
     const int G = n_q_heads / shape->H;
     const int64_t n_units = (int64_t)shape->n_prompts * shape->L * shape->H;
     if (n_units * G >= (1ll << 31) || rows / 256 + n_units >= (1ll << 31)) return NKV_ESHAPE;
-    rc = check_ws(ws, ws_bytes, decode_ws_bytes(shape->dtype, shape->d, shape->dv, G, n_units, rows));
+    rc = check_ws(ws, ws_bytes, decode_ws_bytes(shape->dtype, shape->d, shape->dv, G, n_units, rows, true));
     if (rc) return rc;
     return launch_decode(q, packed_k, packed_v, head_off, shape->dtype, (int)n_units, G, shape->d, shape->dv, rows,
-                         scale, out, lse, ws, Prof{params->prof_start, params->prof_stop},
+                         scale, out, lse, ws, ws_bytes, Prof{params->prof_start, params->prof_stop},
                          (hipStream_t)hip_stream) == hipSuccess
                ? NKV_OK : NKV_EHIP;
 }

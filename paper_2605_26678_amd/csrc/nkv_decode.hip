@@ -26,7 +26,9 @@
 namespace nkv {
 namespace {
 
-constexpr int kChunk = 256;              // rows per workgroup
+// Rows per workgroup: 256, or 64 where a call has too few rows to fill the chip with workgroups of 256 (a wavefront then
+// has one batch of rows instead of four in turn).
+constexpr int kChunk = 256, kSmallChunk = 64;
 constexpr int kDecThreads = 256;
 constexpr float kNone = -1.0e30f;        // running maximum before any row was seen
 constexpr float kLn2 = 0.6931471805599453f;
@@ -125,11 +127,11 @@ __global__ __launch_bounds__(1024) void decode_plan_kernel(const int64_t *__rest
 }
 
 // Few units: chunk_off of units 0 .. n_units (n_units <= kSelfUnits) to LDS, by a whole workgroup of TH threads.
-constexpr int kSelfUnits = 256, kSelfChunks = 1024;
-template <int TH>
+constexpr int kSelfUnits = 256;
+template <int TH, int CH>
 __device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, int n_units, int64_t rows, int32_t *chunk_off)
 {
-    constexpr int PER = kSelfUnits / TH, NW = TH / 64;
+    constexpr int PER = (kSelfUnits + TH - 1) / TH, NW = TH / 64;
     __shared__ uint32_t wtot[NW];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     uint32_t c[PER], mine = 0u;
@@ -137,7 +139,7 @@ __device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, 
     for (int i = 0; i < PER; ++i) {
         const int u = tid * PER + i;
         const int64_t a = clamp_row(head_off[min(u, n_units)], rows), b = clamp_row(head_off[min(u + 1, n_units)], rows);
-        c[i] = (uint32_t)((max(b - a, (int64_t)0) + kChunk - 1) / kChunk);
+        c[i] = (uint32_t)((max(b - a, (int64_t)0) + CH - 1) / CH);
         mine += c[i];
     }
     const uint32_t incl = wave_prefix_sum(mine);
@@ -147,7 +149,7 @@ __device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, 
     for (int i = 0; i < w; ++i) run += wtot[i];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        if (tid * PER + i <= n_units) chunk_off[tid * PER + i] = (int32_t)run;
+        if (tid * PER + i <= min(n_units, kSelfUnits - 1)) chunk_off[tid * PER + i] = (int32_t)run;
         run += c[i];
     }
     if (tid == TH - 1) chunk_off[kSelfUnits] = (int32_t)run;          // (only read if n_units == kSelfUnits)
@@ -155,7 +157,7 @@ __device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, 
 }
 
 // part: per chunk and query head D + 2 floats: running maximum (base-2 logits), sum of weights, weighted values.
-template <int D, int G, bool F16, bool SELF>
+template <int D, int G, bool F16, bool SELF, int CH>
 __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_t *__restrict__ q,
                                                                    const uint16_t *__restrict__ pk,
                                                                    const uint16_t *__restrict__ pv,
@@ -164,21 +166,22 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
                                                                    int64_t rows, float scale_log2,
                                                                    float *__restrict__ part)
 {
-    constexpr int LPR = D / 8, RPW = 64 / LPR, NLD = 64 / RPW, U = 4, NW = kDecThreads / 64;
+    constexpr int LPR = D / 8, RPW = 64 / LPR, NW = kDecThreads / 64;
+    constexpr int WR = CH / NW, NLD = WR / RPW, U = NLD < 4 ? NLD : 4;   // rows of a wavefront, loads they take, in flight
     constexpr int kRowBytes = D * 2;
     __shared__ float lds_m[NW * RPW][G], lds_l[NW * RPW][G];
     __shared__ float lds_o[NW * RPW][G][D];
     const int chunk = blockIdx.x;
     __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
     if constexpr (SELF) {
-        plan_here<kDecThreads>(head_off, n_units, rows, lds_off);
+        plan_here<kDecThreads, CH>(head_off, n_units, rows, lds_off);
         chunk_off = lds_off;
     }
     if (chunk >= chunk_off[n_units]) return;
     const int u = wave_search(chunk_off, n_units, chunk), ci = chunk - chunk_off[u];
     const int64_t first = clamp_row(head_off[u], rows), len = clamp_row(head_off[u + 1], rows) - first;
-    const int n = (int)min((int64_t)kChunk, len - (int64_t)ci * kChunk);     // rows of this chunk, >= 1
-    const int64_t r0 = first + (int64_t)ci * kChunk;
+    const int n = (int)min((int64_t)CH, len - (int64_t)ci * CH);     // rows of this chunk, >= 1
+    const int64_t r0 = first + (int64_t)ci * CH;
 
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, gi = lane / LPR, c = lane % LPR;
     u32x4 qv[G];
@@ -199,11 +202,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
                                                                          n * kRowBytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(pv) + r0 * D, 0,
                                                                          n * kRowBytes, 0x00020000);
-    if (w * 64 < n) {
+    if (w * WR < n) {
 #pragma unroll 1
         for (int b0 = 0; b0 < NLD; b0 += U) {
-            const int row0 = w * 64 + b0 * RPW + gi;                 // this lane group's row in load b0
-            if (w * 64 + b0 * RPW >= n) break;                       // uniform in the wave
+            const int row0 = w * WR + b0 * RPW + gi;                 // this lane group's row in load b0
+            if (w * WR + b0 * RPW >= n) break;                       // uniform in the wave
             u32x4 kr[U], vr[U];
 #pragma unroll
             for (int i = 0; i < U; ++i)
@@ -282,52 +285,59 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
     }
 }
 
-// grid: n_units * G workgroups of D threads (D = 64 or 128: one or two waves)
-template <int D, bool SELF>
-__global__ __launch_bounds__(D) void decode_combine_kernel(const float *__restrict__ part, const int64_t *__restrict__ head_off,
-                                                           int n_units, int64_t rows, const int32_t *chunk_off, int G,
-                                                           float *__restrict__ out, float *__restrict__ lse)
+// grid: n_units * G workgroups of 512 threads: 512 / D slices of the unit's chunks, added up in the slices' order.
+constexpr int kCombineThreads = 512;
+template <int D, bool SELF, int CH>
+__global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(const float *__restrict__ part,
+                                                                         const int64_t *__restrict__ head_off, int n_units, int64_t rows,
+                                                                         const int32_t *chunk_off, int G, float *__restrict__ out,
+                                                                         float *__restrict__ lse)
 {
-    __shared__ float red[D / 64];
+    constexpr int NS = kCombineThreads / D, NW = kCombineThreads / 64, U = 4;
+    __shared__ float red[NW];
+    __shared__ float lds_l[NS], lds_o[NS][D];
     __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
     if constexpr (SELF) {
-        plan_here<D>(head_off, n_units, rows, lds_off);
+        plan_here<kCombineThreads, CH>(head_off, n_units, rows, lds_off);
         chunk_off = lds_off;
     }
-    const int u = blockIdx.x / G, g = blockIdx.x - u * G, e = threadIdx.x;
+    const int u = blockIdx.x / G, g = blockIdx.x - u * G, tid = threadIdx.x, e = tid % D, sl = tid / D;
     const int c0 = chunk_off[u], c1 = chunk_off[u + 1];
     // the largest running maximum: chunks spread over the threads, then one reduction
     float mm = kNone;
-    for (int ch = c0 + e; ch < c1; ch += D) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
+    for (int ch = c0 + tid; ch < c1; ch += kCombineThreads) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
     mm = wave_max(mm);
-    if ((e & 63) == 0) red[e >> 6] = mm;
+    if ((tid & 63) == 0) red[tid >> 6] = mm;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) mm = fmaxf(mm, red[i]);
+    for (int i = 0; i < NW; ++i) mm = fmaxf(mm, red[i]);
     // weighted sums, four chunks' loads in flight at a time; the order of the additions is fixed
     float ll = 0.f, oo = 0.f;
-    int ch = c0;
-    for (; ch + 4 <= c1; ch += 4) {
-        float pm[4], pl[4], po[4];
+    for (int ch = c0 + sl; ch < c1; ch += U * NS) {
+        float pm[U], pl[U], po[U];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float *src = part + ((int64_t)(ch + i) * G + g) * (D + 2);
+        for (int i = 0; i < U; ++i) {
+            const float *src = part + ((int64_t)min(ch + i * NS, c1 - 1) * G + g) * (D + 2);
             pm[i] = src[0];
             pl[i] = src[1];
             po[i] = src[2 + e];
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float f = __builtin_amdgcn_exp2f(pm[i] - mm);
-            ll = fmaf(f, pl[i], ll);
-            oo = fmaf(f, po[i], oo);
+        for (int i = 0; i < U; ++i) {
+            if (ch + i * NS < c1) {
+                const float f = __builtin_amdgcn_exp2f(pm[i] - mm);
+                ll = fmaf(f, pl[i], ll);
+                oo = fmaf(f, po[i], oo);
+            }
         }
     }
-    for (; ch < c1; ++ch) {
-        const float *src = part + ((int64_t)ch * G + g) * (D + 2);
-        const float f = __builtin_amdgcn_exp2f(src[0] - mm);
-        ll = fmaf(f, src[1], ll);
-        oo = fmaf(f, src[2 + e], oo);
+    lds_o[sl][e] = oo;
+    if (e == 0) lds_l[sl] = ll;
+    __syncthreads();
+    if (sl > 0) return;
+    for (int i = 1; i < NS; ++i) {
+        oo += lds_o[i][e];
+        ll += lds_l[i];
     }
     out[((int64_t)u * G + g) * D + e] = ll > 0.f ? oo / ll : 0.f;
     if (lse && e == 0) lse[(int64_t)u * G + g] = ll > 0.f ? (mm + log2f(ll)) * kLn2 : -INFINITY;
@@ -386,23 +396,31 @@ __global__ __launch_bounds__(kDecThreads) void decode_generic_kernel(const T *__
     if (lse && threadIdx.x == 0) lse[(int64_t)u * G + g] = ll > 0.f ? (mm + log2f(ll)) * kLn2 : -INFINITY;
 }
 
-int64_t max_chunks(int64_t n_units, int64_t rows) { return rows / kChunk + n_units; }
+int64_t max_chunks(int64_t n_units, int64_t rows, int chunk) { return rows / chunk + n_units; }
+
+// Few units and at most two workgroups of 256 rows per compute unit: chunks of 64 rows, if the caller's scratch holds
+// their partial results (it need not, see decode_ws_bytes).
+bool decode_small(int64_t n_units, int64_t rows) { return n_units <= kSelfUnits && max_chunks(n_units, rows, kChunk) <= 512; }
+
+size_t part_offset(int64_t n_units) { return ((size_t)(n_units + 1) * 4 + 255) / 256 * 256; }
+size_t ws_for(int64_t chunks, int64_t n_units, int G, int d) { return part_offset(n_units) + (size_t)chunks * G * (d + 2) * 4; }
 
 template <int D, bool F16>
 hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, const int64_t *head_off, int n_units,
-                    int G, int64_t rows, float scale_log2, float *out, float *lse, void *ws, const Prof &prof,
+                    int G, int64_t rows, float scale_log2, float *out, float *lse, void *ws, size_t ws_bytes, const Prof &prof,
                     hipStream_t st)
 {
     int32_t *chunk_off = (int32_t *)ws;
-    float *part = (float *)((char *)ws + ((size_t)(n_units + 1) * 4 + 255) / 256 * 256);
-    const unsigned groups = (unsigned)max_chunks(n_units, rows);
-    const bool self = n_units <= kSelfUnits && groups <= (unsigned)kSelfChunks;
-    if (!self) decode_plan_kernel<<<1, 1024, 0, st>>>(head_off, n_units, rows, chunk_off);
+    float *part = (float *)((char *)ws + part_offset(n_units));
+    const bool small = decode_small(n_units, rows) && ws_bytes >= ws_for(max_chunks(n_units, rows, kSmallChunk), n_units, G, D);
+    const unsigned groups = (unsigned)max_chunks(n_units, rows, small ? kSmallChunk : kChunk);
+    if (!small) decode_plan_kernel<<<1, 1024, 0, st>>>(head_off, n_units, rows, chunk_off);
     prof.begin(NKV_KERNEL_DECODE, st);
-#define NKV_DEC(GG)                                                                                                     \
-    case GG:                                                                                                           \
-        (self ? decode_chunk_kernel<D, GG, F16, true> : decode_chunk_kernel<D, GG, F16, false>)<<<groups, kDecThreads, 0, st>>>( \
-            q, pk, pv, head_off, chunk_off, n_units, rows, scale_log2, part);                                          \
+#define NKV_DEC(GG)                                                                                                       \
+    case GG:                                                                                                             \
+        (small ? decode_chunk_kernel<D, GG, F16, true, kSmallChunk>                                                      \
+               : decode_chunk_kernel<D, GG, F16, false, kChunk>)<<<groups, kDecThreads, 0, st>>>(                         \
+            q, pk, pv, head_off, chunk_off, n_units, rows, scale_log2, part);                                            \
         break
     switch (G) {
         NKV_DEC(1); NKV_DEC(2); NKV_DEC(3); NKV_DEC(4); NKV_DEC(5); NKV_DEC(6); NKV_DEC(7); NKV_DEC(8);
@@ -410,7 +428,7 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     }
 #undef NKV_DEC
     prof.end(NKV_KERNEL_DECODE, st);
-    (self ? decode_combine_kernel<D, true> : decode_combine_kernel<D, false>)<<<(unsigned)(n_units * G), D, 0, st>>>(
+    (small ? decode_combine_kernel<D, true, kSmallChunk> : decode_combine_kernel<D, false, kChunk>)<<<(unsigned)(n_units * G), kCombineThreads, 0, st>>>(
         part, head_off, n_units, rows, chunk_off, G, out, lse);
     return hipGetLastError();
 }
@@ -442,25 +460,30 @@ bool decode_fast_supported(int dtype, int d, int dv, int G)
     return (dtype == NKV_DTYPE_BF16 || dtype == NKV_DTYPE_F16) && d == dv && (d == 64 || d == 128) && G >= 1 && G <= 8;
 }
 
-size_t decode_ws_bytes(int dtype, int d, int dv, int G, int64_t n_units, int64_t rows)
+size_t decode_ws_bytes(int dtype, int d, int dv, int G, int64_t n_units, int64_t rows, bool least)
 {
     if (!decode_fast_supported(dtype, d, dv, G)) return 0;
-    return ((size_t)(n_units + 1) * 4 + 255) / 256 * 256 + (size_t)max_chunks(n_units, rows) * G * (d + 2) * 4;
+    const size_t need = ws_for(max_chunks(n_units, rows, kChunk), n_units, G, d);
+    if (least || n_units > kSelfUnits) return need;
+    // room for chunks of 64 rows up to the row count where they end, so that more rows never ask for less
+    const int64_t most = (512 - n_units) * kChunk + kChunk - 1;
+    const size_t small = ws_for(max_chunks(n_units, rows < most ? rows : most, kSmallChunk), n_units, G, d);
+    return need > small ? need : small;
 }
 
 hipError_t launch_decode(const void *q, const void *pk, const void *pv, const int64_t *head_off, int dtype,
                          int n_units, int G, int d, int dv, int64_t rows, double scale, float *out, float *lse,
-                         void *ws, const Prof &prof, hipStream_t st)
+                         void *ws, size_t ws_bytes, const Prof &prof, hipStream_t st)
 {
     const float scale_log2 = (float)(scale * 1.4426950408889634);
     if (decode_fast_supported(dtype, d, dv, G)) {
         const uint16_t *q16 = (const uint16_t *)q, *k16 = (const uint16_t *)pk, *v16 = (const uint16_t *)pv;
         if (dtype == NKV_DTYPE_F16) {
-            if (d == 128) return run_fast<128, true>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, prof, st);
-            return run_fast<64, true>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, prof, st);
+            if (d == 128) return run_fast<128, true>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, ws_bytes, prof, st);
+            return run_fast<64, true>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, ws_bytes, prof, st);
         }
-        if (d == 128) return run_fast<128, false>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, prof, st);
-        return run_fast<64, false>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, prof, st);
+        if (d == 128) return run_fast<128, false>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, ws_bytes, prof, st);
+        return run_fast<64, false>(q16, k16, v16, head_off, n_units, G, rows, scale_log2, out, lse, ws, ws_bytes, prof, st);
     }
     if (dtype == NKV_DTYPE_F32)
         return run_generic<float>((const float *)q, (const float *)pk, (const float *)pv, head_off, n_units, G, d, dv,

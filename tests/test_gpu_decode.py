@@ -146,3 +146,33 @@ def test_headline_size_cache_sampled_units():
         worst = max(worst, _check(out[:, l:l + 1, j:j + 1], lse[:, l:l + 1, j:j + 1], o_out, o_lse,
                                   float(pv[a:b].abs().max()), f"layer {l} query head {j}"))
     print(f"\n[decode qwen4b_32k] rows {pk.shape[0]}, sampled worst |out - oracle| {worst:.2e}")
+
+
+@pytest.mark.parametrize("d,G,dtype", [(64, 8, "bf16"), (128, 3, "fp16"), (64, 1, "fp16"), (128, 5, "bf16")])
+@pytest.mark.parametrize("lens", [[63, 64, 65, 0], [255, 256, 257, 1], [8000, 3, 0, 0], [20000, 20000, 20000, 65536]])
+def test_chunk_sizes_of_few_and_many_rows(d, G, dtype, lens):
+    """Units around the chunk lengths of a call with few rows (64) and with many (256, the last case), empty units at
+    either end; and the same call with scratch for chunks of 256 rows only, as an earlier size query may have given."""
+    H = 2
+    w = nkv_inputs.small_workload(f"chunks_{d}_{G}", 1, H, d, [1] * (len(lens) // H), dtype=dtype, n_out=0)
+    g = torch.Generator().manual_seed(sum(lens) + d)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    rows = sum(lens)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+    pk, pv = (torch.randn(rows, d, generator=g).to(dt).to(DEV) for _ in range(2))
+    q = torch.randn(len(w.prompt_lens), 1, H * G, d, generator=g).to(dt).to(DEV)
+    scale = 1.0 / float(np.sqrt(d))
+    want, want_lse = oracle_decode(_f64(q), _f64(pk), _f64(pv), off.numpy(), H, scale)
+    shape, p = shape_of(w), nkv.params_default()
+    part_off = (4 * (len(lens) + 1) + 255) // 256 * 256
+    least = part_off + (rows // 256 + len(lens)) * G * (d + 2) * 4
+    for nbytes in (max(nkv.decode_workspace_bytes(shape, H * G, rows), 256), least):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+        out = torch.full(want.shape, float("nan"), dtype=torch.float32, device=DEV)
+        lse = torch.full(want_lse.shape, float("nan"), dtype=torch.float32, device=DEV)
+        nkv.decode_attention(q, pk, pv, off.to(DEV), rows, shape, p, H * G, scale, out, lse, ws)
+        torch.cuda.synchronize()
+        assert np.abs(_f64(out) - want).max() <= DECODE_TOL * max(1.0, float(pv.abs().max()))
+        got, has = _f64(lse), np.isfinite(want_lse)
+        assert np.array_equal(np.isfinite(got), has)
+        assert (np.abs(got[has] - want_lse[has]) <= DECODE_TOL * np.maximum(1.0, np.abs(want_lse[has]))).all()
