@@ -23,6 +23,7 @@
 //     workgroup per head;
 //   * anything else (no scratch given): budget_kernel, one workgroup per (prompt, layer), nine byte-wise passes.
 #include "nkv_blocksel.h"
+#include "nkv_budget_layer.h"
 
 namespace nkv {
 namespace {
@@ -240,124 +241,11 @@ __global__ __launch_bounds__(kThreads) void layer_budget_kernel(const float *__r
 
 // ---------------------------------------------------------------------------------------------------
 // Shape-generic version: any prompt length, up to NKV_MAX_HEADS heads.
-// only_if (may be NULL): one word per (prompt, layer); layers whose word is zero are left alone.
 __global__ __launch_bounds__(kThreads) void budget_kernel(const float *__restrict__ scores, int L, int H,
-                                                          PromptTab tab, const uint32_t *__restrict__ only_if,
-                                                          int32_t *__restrict__ k_per_head)
+                                                          PromptTab tab, int32_t *__restrict__ k_per_head)
 {
-    __shared__ uint32_t hist[NKV_MAX_HEADS][256];      // 32 KB
-    __shared__ uint32_t Th[NKV_MAX_HEADS];             // key of the m_safe-th best score of the head
-    __shared__ uint32_t want_h[NKV_MAX_HEADS];         // running rank, ends as #protected among ties at Th
-    __shared__ uint32_t ties_h[NKV_MAX_HEADS];         // #scores of the head equal to Th
-    __shared__ uint32_t cnt_gt[NKV_MAX_HEADS], cnt_eq[NKV_MAX_HEADS];
-    __shared__ uint32_t lhist[256];
-    __shared__ uint32_t TL, want_l;
-
-    const int pl = blockIdx.x;                          // p * L + l
-    if (only_if && only_if[pl] == 0u) return;
-    const int l = pl % L, p = pl / L;
-    const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-    const int k0 = tab.k0[p], m_safe = tab.m_safe[p];
-    const int64_t R = (int64_t)H * (k0 - m_safe);
-    const float *sc = scores + (int64_t)l * H * tab.T + tab.tok_off[p];   // head h at sc + h*T
-    const int tid = threadIdx.x;
-
-    // ---- A: per-head safeguard thresholds ----
-    if (tid < H) { Th[tid] = 0xFFFFFFFFu; want_h[tid] = (uint32_t)m_safe; ties_h[tid] = 0u; }
-    __syncthreads();
-    if (m_safe > 0) {
-        if (tid < H) Th[tid] = 0u;
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
-            for (int j = tid; j < H * 256; j += kThreads) (&hist[0][0])[j] = 0u;
-            __syncthreads();
-            for (int h = 0; h < H; ++h) {
-                const uint32_t th = Th[h];
-                for (int i = tid; i < N; i += kThreads) {
-                    const uint32_t key = ord_key(sc[(int64_t)h * tab.T + i]);
-                    if (pass == 0 || (key >> (shift + 8)) == (th >> (shift + 8)))
-                        atomicAdd(&hist[h][(key >> shift) & 255u], 1u);
-                }
-            }
-            __syncthreads();
-            if (tid < H) {
-                uint32_t want = want_h[tid];
-                const uint32_t dig = radix_pick(hist[tid], want, 1);
-                want_h[tid] = want;
-                Th[tid] |= dig << shift;
-                if (pass == 3) ties_h[tid] = hist[tid][dig];
-            }
-            __syncthreads();
-        }
-    }
-
-    // ---- B: layer threshold over the unprotected pool ----
-    if (tid == 0) { TL = 0u; want_l = (uint32_t)R; }
-    __syncthreads();
-    if (R > 0) {
-        for (int pass = 0; pass < 4; ++pass) {
-            const int shift = 24 - 8 * pass;
-            if (tid < 256) lhist[tid] = 0u;
-            __syncthreads();
-            const uint32_t pre = TL;
-            for (int h = 0; h < H; ++h) {
-                const uint32_t th = Th[h];
-                for (int i = tid; i < N; i += kThreads) {
-                    const uint32_t key = ord_key(sc[(int64_t)h * tab.T + i]);
-                    if (key < th && (pass == 0 || (key >> (shift + 8)) == (pre >> (shift + 8))))
-                        atomicAdd(&lhist[(key >> shift) & 255u], 1u);
-                }
-            }
-            if (tid < H) {                               // unprotected ties at the head's own threshold
-                const uint32_t ex = ties_h[tid] - (m_safe > 0 ? want_h[tid] : 0u);
-                const uint32_t key = Th[tid];
-                if (m_safe > 0 && ex > 0u && (pass == 0 || (key >> (shift + 8)) == (pre >> (shift + 8))))
-                    atomicAdd(&lhist[(key >> shift) & 255u], ex);
-            }
-            __syncthreads();
-            if (tid == 0) {
-                uint32_t want = want_l;
-                const uint32_t dig = radix_pick(lhist, want, 1);
-                want_l = want;
-                TL |= dig << shift;
-            }
-            __syncthreads();
-        }
-    }
-
-    // ---- C: per-head counts ----
-    if (tid < H) { cnt_gt[tid] = 0u; cnt_eq[tid] = 0u; }
-    __syncthreads();
-    if (R > 0) {
-        const uint32_t tl = TL;
-        for (int h = 0; h < H; ++h) {
-            const uint32_t th = Th[h];
-            for (int i = tid; i < N; i += kThreads) {
-                const uint32_t key = ord_key(sc[(int64_t)h * tab.T + i]);
-                if (key < th) {
-                    if (key > tl) atomicAdd(&cnt_gt[h], 1u);
-                    else if (key == tl) atomicAdd(&cnt_eq[h], 1u);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t remaining = R > 0 ? want_l : 0u;
-        for (int h = 0; h < H; ++h) {
-            uint32_t b = (uint32_t)m_safe;
-            if (R > 0) {
-                const uint32_t ex = m_safe > 0 ? ties_h[h] - want_h[h] : 0u;
-                uint32_t gt = cnt_gt[h], eq = cnt_eq[h];
-                if (Th[h] > TL) gt += ex;
-                else if (Th[h] == TL) eq += ex;
-                const uint32_t take = min(remaining, eq);
-                remaining -= take;
-                b += gt + take;
-            }
-            k_per_head[(int64_t)pl * H + h] = (int32_t)b;
-        }
-    }
+    __shared__ BudgetScratch sc;
+    budget_of_layer(scores, L, H, tab, blockIdx.x, sc, k_per_head);
 }
 
 }  // namespace
@@ -381,10 +269,8 @@ hipError_t launch_budget(const float *scores, int L, int H, const PromptTab &tab
     // for a few short units the two per-head launches are quicker.
     const bool per_head_ok = ws != nullptr && H <= kFastHeads && nmax <= 32 * kSelThreads;
     if (ws != nullptr && budget_wide_supported(H) && !(per_head_ok && (per_head_route || (nmax <= 8192 && units < 256)))) {
-        const uint32_t *failed = nullptr;
-        hipError_t e = launch_budget_wide(scores, L, H, tab, k_per_head, ws, &failed, st);
+        const hipError_t e = launch_budget_wide(scores, L, H, tab, k_per_head, ws, st);
         if (e != hipSuccess) return e;
-        budget_kernel<<<(unsigned)(tab.n * L), kThreads, 0, st>>>(scores, L, H, tab, failed, k_per_head);
     } else if (per_head_ok) {
         HeadSafe *safe = (HeadSafe *)ws;
         uint32_t *pool_hist = (uint32_t *)(safe + units);
@@ -399,7 +285,7 @@ hipError_t launch_budget(const float *scores, int L, int H, const PromptTab &tab
         const hipError_t e = launch_budget_heads(scores, L, H, tab, k_per_head, ws, st);
         if (e != hipSuccess) return e;
     } else {
-        budget_kernel<<<(unsigned)(tab.n * L), kThreads, 0, st>>>(scores, L, H, tab, nullptr, k_per_head);
+        budget_kernel<<<(unsigned)(tab.n * L), kThreads, 0, st>>>(scores, L, H, tab, k_per_head);
     }
     prof.end(NKV_KERNEL_BUDGET, st);
     return hipGetLastError();

@@ -18,8 +18,9 @@
 //                                            into the layer's boundary bin -> two short lists per slice
 //   layer_finish_kernel (per prompt, layer)  exact thresholds inside the two boundary bins (radix selects
 //                                            over the lists), ties by head order, B_h
-// A list that does not fit (thousands of equal scores in one bin) marks the layer, and the shape-generic
-// kernel of nkv_budget.hip computes that layer instead.
+// A list that does not fit (thousands of equal scores in one bin) marks the layer, whose finishing workgroup then
+// computes it from the scores by the shape-generic method (nkv_budget_layer.h).
+#include "nkv_budget_layer.h"
 #include "nkv_slices.h"
 
 namespace nkv {
@@ -228,19 +229,26 @@ __global__ __launch_bounds__(TH) void slice_collect_kernel(const float *__restri
     }
 }
 
-__global__ __launch_bounds__(1024) void layer_finish_kernel(int L, int H, PromptTab tab, SliceTab st,
+__global__ __launch_bounds__(1024) void layer_finish_kernel(const float *__restrict__ scores, int L, int H, PromptTab tab, SliceTab st,
                                                             const LayerPick *__restrict__ picks,
                                                             const uint32_t *__restrict__ segT,
                                                             const uint32_t *__restrict__ nSegT,
                                                             const uint32_t *__restrict__ segL,
                                                             const uint32_t *__restrict__ nSegL,
-                                                            uint32_t *__restrict__ failed,
+                                                            const uint32_t *__restrict__ failed,
                                                             int32_t *__restrict__ k_per_head)
 {
-    __shared__ uint32_t keysT[kMaxH][kListT];                        // 16 KB
-    __shared__ uint32_t keysL[kListL];                               // 16 KB: pool candidates of the layer's boundary bin
-    __shared__ uint8_t headL[kListL];
-    __shared__ uint32_t whist[kMaxH][256];
+    struct Lists {
+        uint32_t keysT[kMaxH][kListT];                               // 16 KB
+        uint32_t keysL[kListL];                                      // 16 KB: pool candidates of the layer's boundary bin
+        uint32_t whist[kMaxH][256];
+        uint8_t headL[kListL];
+    };
+    __shared__ union { Lists lists; BudgetScratch generic; } mem;
+    auto &keysT = mem.lists.keysT;
+    auto &keysL = mem.lists.keysL;
+    auto &whist = mem.lists.whist;
+    auto &headL = mem.lists.headL;
     __shared__ uint32_t Th[kMaxH], remT[kMaxH], totT[kMaxH], dropped[kMaxH], gtL[kMaxH], eqL[kMaxH];
     __shared__ uint32_t cT[kMaxSeg], cL[kMaxSeg], oT[kMaxSeg];       // segment counts and offsets
     __shared__ uint32_t nPool, s_TL, s_gtAll, s_bad;
@@ -262,7 +270,7 @@ __global__ __launch_bounds__(1024) void layer_finish_kernel(int L, int H, Prompt
     }
     __syncthreads();
     if (s_bad) {
-        if (tid == 0) failed[pl] = 1u;
+        budget_of_layer(scores, L, H, tab, pl, mem.generic, k_per_head);
         return;
     }
     if (tid < nseg) {
@@ -275,7 +283,7 @@ __global__ __launch_bounds__(1024) void layer_finish_kernel(int L, int H, Prompt
     }
     __syncthreads();
     if (s_bad) {
-        if (tid == 0) failed[pl] = 1u;
+        budget_of_layer(scores, L, H, tab, pl, mem.generic, k_per_head);
         return;
     }
     // the keys of every head's boundary bin: wave w copies the segments w, w + 16, ...
@@ -317,8 +325,9 @@ __global__ __launch_bounds__(1024) void layer_finish_kernel(int L, int H, Prompt
         }
     }
     __syncthreads();
-    if (s_bad || nPool > (uint32_t)kListL) {
-        if (tid == 0) failed[pl] = 1u;
+    if (nPool > (uint32_t)kListL) {
+        __syncthreads();                                             // (the lists' memory is used anew)
+        budget_of_layer(scores, L, H, tab, pl, mem.generic, k_per_head);
         return;
     }
     const int n = (int)nPool;
@@ -371,10 +380,9 @@ bool budget_wide_supported(int H) { return H <= kMaxH; }
 
 size_t budget_wide_ws_bytes(int L, int H, const PromptTab &tab) { return wide_ws(L, H, tab).total; }
 
-// Enqueues the four kernels; *failed_flags receives the device address of the per-(prompt, layer) words that
-// are non-zero for layers whose budgets have not been written.
+// Enqueues the four kernels.
 hipError_t launch_budget_wide(const float *scores, int L, int H, const PromptTab &tab, int32_t *k_per_head, void *ws,
-                              const uint32_t **failed_flags, hipStream_t st)
+                              hipStream_t st)
 {
     SliceTab stab;
     const int slices = fill_slices(L, H, tab, &stab);
@@ -392,8 +400,7 @@ hipError_t launch_budget_wide(const float *scores, int L, int H, const PromptTab
     layer_pick_kernel<<<layers, 1024, 0, st>>>(L, H, tab, stab, part, picks, failed, k_per_head);
     (few ? slice_collect_kernel<1024> : slice_collect_kernel<256>)<<<(unsigned)slices, threads, 0, st>>>(
         scores, L, H, tab, stab, picks, segT, nSegT, segL, nSegL, failed);
-    layer_finish_kernel<<<layers, 1024, 0, st>>>(L, H, tab, stab, picks, segT, nSegT, segL, nSegL, failed, k_per_head);
-    *failed_flags = failed;
+    layer_finish_kernel<<<layers, 1024, 0, st>>>(scores, L, H, tab, stab, picks, segT, nSegT, segL, nSegL, failed, k_per_head);
     return hipGetLastError();
 }
 

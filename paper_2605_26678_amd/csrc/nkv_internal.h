@@ -135,7 +135,7 @@ hipError_t launch_budget_heads(const float *scores, int L, int H, const PromptTa
 bool budget_wide_supported(int H);
 size_t budget_wide_ws_bytes(int L, int H, const PromptTab &tab);
 hipError_t launch_budget_wide(const float *scores, int L, int H, const PromptTab &tab, int32_t *k_per_head, void *ws,
-                              const uint32_t **failed_flags, hipStream_t st);
+                              hipStream_t st);
 
 // ---- selection, ordered compaction, gather ----
 // wide_ws: scratch of select_wide_ws_bytes() for the slice-wise selection (NULL: per-unit kernels only)
