@@ -93,9 +93,10 @@ hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int 
 // Units are numbered prompt by prompt, so the units of consecutive prompts of similar length form one
 // range.  Calls f(ept, unit0, units) for every maximal run of prompts whose lengths need the same number
 // ept in {4, 8, 16, 32} of values per thread in the 1024-thread per-unit kernels (N <= 1024 * ept).
+__host__ __device__ inline int length_class(int N) { return N <= 4096 ? 4 : N <= 8192 ? 8 : N <= 16384 ? 16 : 32; }
 template <typename F> inline void for_each_length_class(const PromptTab &tab, int LH, F f)
 {
-    auto cls = [](int N) { return N <= 4096 ? 4 : N <= 8192 ? 8 : N <= 16384 ? 16 : 32; };
+    auto cls = [](int N) { return length_class(N); };
     int p = 0;
     while (p < tab.n) {
         const int c = cls(tab.tok_off[p + 1] - tab.tok_off[p]);
