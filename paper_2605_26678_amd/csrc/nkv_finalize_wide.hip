@@ -14,8 +14,8 @@
 //                                        boundary bin; the boundary bins' entries (as order-preserving keys)
 //                                        into two short lists per slice and scale; and, the ranges being known,
 //                                        min / max / sum of the slice's surprise statistic
-//   stats_finish_kernel  (unit, scale)   one wavefront: exact thresholds inside the boundary bins, the two
-//                                        means, min, 1/range, gap
+//   stats_finish_kernel  (unit, scale)   two wavefronts, one per boundary bin: exact thresholds inside the bins, the
+//                                        two means, min, 1/range, gap
 //   route_slice_kernel   (slice)         weights, surprise statistics of the head, routed scores, pinning
 // A list that overflows (hundreds of values of one slice in one bin) marks the (unit, scale) and the per-head
 // kernel, launched behind and idle otherwise, computes it.
@@ -331,57 +331,58 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
     }
 }
 
-// grid (units, 3); one wavefront.  stats[(u * 3 + k) * 4 + {0, 1, 2}] = min, 1 / range (0 if flat), gap
-__global__ __launch_bounds__(64) void stats_finish_kernel(const float *__restrict__ a_raw, int64_t rows, int L, int H,
-                                                          PromptTab tab, SliceTab st, int n_slices,
-                                                          const StatPick *__restrict__ picks,
-                                                          const uint32_t *__restrict__ segTop,
-                                                          const uint32_t *__restrict__ segBot,
-                                                          const SlicePart *__restrict__ sp,
-                                                          uint32_t *__restrict__ failed, float *__restrict__ stats)
+// grid (units, 3); two wavefronts: 0 takes the upper boundary bin, 1 the lower one (on inverted keys).
+// stats[(u * 3 + k) * 4 + {0, 1, 2}] = min, 1 / range (0 if flat), gap
+__global__ __launch_bounds__(128) void stats_finish_kernel(const float *__restrict__ a_raw, int64_t rows, int L, int H,
+                                                           PromptTab tab, SliceTab st, int n_slices,
+                                                           const StatPick *__restrict__ picks,
+                                                           const uint32_t *__restrict__ segTop,
+                                                           const uint32_t *__restrict__ segBot,
+                                                           const SlicePart *__restrict__ sp,
+                                                           const uint32_t *__restrict__ failed, float *__restrict__ stats)
 {
     __shared__ uint32_t keys[2][kList];
-    __shared__ uint32_t hist[256];
+    __shared__ uint32_t hist[2][256];
+    __shared__ double total[2];
+    __shared__ uint32_t s_bad;
     const int u = blockIdx.x, k = blockIdx.y;
     const int64_t job = (int64_t)u * 3 + k;
     const int lh = u % (L * H), p = u / (L * H);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
     if (N <= kUnitTokens) return;
-    bool bad = failed[job] != 0u;
     const int S = (N + kSlice - 1) / kSlice;
     const uint32_t m = (uint32_t)min(tab.m_p[p], N);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, side = threadIdx.x >> 6;
     const int64_t slice0 = (int64_t)k * n_slices + st.off[p] + (int64_t)lh * S;
     const StatPick pk = picks[job];
-    // lists; sums over the slices (slice s0 + lane of a batch), min, max
-    uint32_t nT = 0u, nB = 0u;
-    double sTop = 0.0, sBot = 0.0;
+    const bool marked = failed[job] != 0u;
+    if (threadIdx.x == 0) s_bad = 0u;
+    // this side's list; sums over the slices (slice s0 + lane of a batch), min, max
+    int none;
+    const uint32_t *seg = (side == 0 ? segTop : segBot) + slice0 * kSeg;
+    const int n = marked ? -1 : gather_segments(seg, S, [&](int s) { return side == 0 ? sp[slice0 + s].nTop : sp[slice0 + s].nBot; },
+                                                keys[side], kList, -1, none);
+    double sum = 0.0;
     float lo = INFINITY, hi = -INFINITY;
-    if (!bad) {
-        int none;
-        const int t = gather_segments(segTop + slice0 * kSeg, S, [&](int s) { return sp[slice0 + s].nTop; }, keys[0], kList, -1, none);
-        const int b = gather_segments(segBot + slice0 * kSeg, S, [&](int s) { return sp[slice0 + s].nBot; }, keys[1], kList, -1, none);
-        bad = t < 0 || b < 0;
-        nT = (uint32_t)t;
-        nB = (uint32_t)b;
-        for (int s = lane; s < S; s += 64) {
-            const SlicePart q = sp[slice0 + s];
-            sTop += q.sTop;
-            sBot += q.sBot;
-            lo = fminf(lo, q.lo);
-            hi = fmaxf(hi, q.hi);
-        }
-        sTop = wave_sum(sTop);
-        sBot = wave_sum(sBot);
-        lo = wave_min(lo);
-        hi = wave_max(hi);
+    for (int s = lane; s < S; s += 64) {
+        const SlicePart q = sp[slice0 + s];
+        sum += side == 0 ? q.sTop : q.sBot;
+        lo = fminf(lo, q.lo);
+        hi = fmaxf(hi, q.hi);
     }
+    sum = wave_sum(sum);
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    __syncthreads();
+    if (n < 0 && lane == 0) s_bad = 1u;
+    __syncthreads();
     // The lists' order depends on the timing of the collecting workgroups, so their entries are added up in
     // fixed point (2^-40 units, exact for fp32 values of magnitude <= 1 down to that resolution): the sum does
     // not depend on the order, and the statistics are reproducible bit for bit.
     constexpr double kFix = 1099511627776.0;                         // 2^40
-    if (bad) {
-        // More values in one bin than the lists hold (thousands of equal anomalies): this wavefront walks the
+    if (s_bad) {
+        if (side != 0) return;
+        // More values in one bin than the lists hold (thousands of equal anomalies): the first wavefront walks the
         // head's values itself -- slow, exact, and rare.
         const float *a = a_raw + (int64_t)k * rows + (int64_t)lh * tab.T + tab.tok_off[p];
         lo = INFINITY;
@@ -393,12 +394,12 @@ __global__ __launch_bounds__(64) void stats_finish_kernel(const float *__restric
         lo = wave_min(lo);
         hi = wave_max(hi);
         uint32_t gt, eq;
-        const uint32_t Tt = wave_select_fn(N, m, hist, gt, eq, [a](int i) { return ord_key(a[i]); });
+        const uint32_t Tt = wave_select_fn(N, m, hist[0], gt, eq, [a](int i) { return ord_key(a[i]); });
         long long part = 0;
         for (int i = lane; i < N; i += 64)
             part += ord_key(a[i]) > Tt ? __double2ll_rn((double)a[i] * kFix) : 0ll;
         const double top = (double)wave_sum(part) / kFix + (double)(m - gt) * (double)key_value(Tt);
-        const uint32_t Tb = wave_select_fn(N, m, hist, gt, eq, [a](int i) { return ~ord_key(a[i]); });
+        const uint32_t Tb = wave_select_fn(N, m, hist[0], gt, eq, [a](int i) { return ~ord_key(a[i]); });
         part = 0;
         for (int i = lane; i < N; i += 64)
             part += ~ord_key(a[i]) > Tb ? __double2ll_rn((double)a[i] * kFix) : 0ll;
@@ -413,27 +414,27 @@ __global__ __launch_bounds__(64) void stats_finish_kernel(const float *__restric
         }
         return;
     }
-    __builtin_amdgcn_wave_barrier();
-    // upper boundary bin: the needTop largest of its entries belong to the m largest
-    uint32_t gt, eq;
-    const uint32_t Tt = wave_select(keys[0], (int)nT, pk.needTop, hist, gt, eq);
-    long long part = 0;
-    for (uint32_t i = lane; i < nT; i += 64)
-        part += keys[0][i] > Tt ? __double2ll_rn((double)key_value(keys[0][i]) * kFix) : 0ll;
-    double top = sTop + (double)wave_sum(part) / kFix + (double)(pk.needTop - gt) * (double)key_value(Tt);
-    // lower boundary bin, on inverted keys
-    const uint32_t Tb = wave_select(keys[1], (int)nB, pk.needBot, hist, gt, eq);
-    part = 0;
-    for (uint32_t i = lane; i < nB; i += 64)
-        part += keys[1][i] > Tb ? __double2ll_rn((double)key_value(~keys[1][i]) * kFix) : 0ll;
-    double bot = sBot + (double)wave_sum(part) / kFix + (double)(pk.needBot - gt) * (double)key_value(~Tb);
-    if (lane == 0) {
+    {
+        // the `need` best of the bin's entries belong to the m largest / smallest
+        const uint32_t need = side == 0 ? pk.needTop : pk.needBot;
+        uint32_t gt, eq;
+        const uint32_t T = wave_select(keys[side], n, need, hist[side], gt, eq);
+        long long part = 0;
+        for (int i = lane; i < n; i += 64) {
+            const uint32_t key = keys[side][i];
+            part += key > T ? __double2ll_rn((double)key_value(side == 0 ? key : ~key) * kFix) : 0ll;
+        }
+        const double t = sum + (double)wave_sum(part) / kFix + (double)(need - gt) * (double)key_value(side == 0 ? T : ~T);
+        if (lane == 0) total[side] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
         const float range = hi - lo;
         const float inv = range < kFlat ? 0.f : 1.0f / range;
         float *o = stats + job * 4;
         o[0] = lo;
         o[1] = inv;
-        o[2] = (float)((top - bot) / (double)m * (double)inv);
+        o[2] = (float)((total[0] - total[1]) / (double)m * (double)inv);
     }
 }
 
@@ -487,7 +488,7 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
                              : (all ? stats_collect_kernel<256, true> : stats_collect_kernel<256, false>);
     collect<<<(unsigned)slices, few ? 1024 : 256, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask, picks, segTop, segBot, sp,
                                                            sur, failed);
-    stats_finish_kernel<<<dim3(units, 3), 64, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, picks, segTop, segBot,
+    stats_finish_kernel<<<dim3(units, 3), 128, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, picks, segTop, segBot,
                                                        sp, failed, stats);
     return hipGetLastError();
 }

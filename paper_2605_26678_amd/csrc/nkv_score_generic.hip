@@ -8,7 +8,7 @@
 //   3. anomaly : a_s, a_e from the two sums; a_c from a window sum that slides over 16 consecutive tokens and is formed
 //                afresh in front of them (Section 2.2 current memory; Section 2.3); one wavefront per 16 tokens
 // Everywhere a lane owns dims lane, lane + 64, ... of a row.  The time of a small call is a chain of load latencies, so
-// loads go out eight rows at a time.  (With the window added up for every token, a wave per token and a serial loop over
+// loads go out eight or sixteen rows at a time.  (With the window added up for every token, a wave per token and a serial loop over
 // a block's tokens, 2 heads x 4096 fp32 tokens took 86 us.)
 // Cosines do not depend on the length of the anchor, so sums stand in for the means.
 #include "nkv_device.h"
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys
                                                       const float *__restrict__ bsum, const float *__restrict__ ssum, int LH, int d,
                                                       int window, PromptTab tab, float *__restrict__ a_raw)
 {
-    constexpr int U = rows_in_flight<NQ>(), US = NQ <= 2 ? 4 : NQ <= 8 ? 2 : 1;
+    constexpr int U = NQ <= 2 ? 16 : rows_in_flight<NQ>(), US = NQ <= 2 ? 8 : NQ <= 4 ? 4 : NQ <= 8 ? 2 : 1;
     const int lane = threadIdx.x & (kWave - 1), lh = blockIdx.y;
     const int64_t rows = (int64_t)LH * tab.T;
     int chunk = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave, p = 0;
