@@ -80,8 +80,8 @@ enum {
     NKV_FLAG_STATS_PER_HEAD = 32u,    /* nkv_score: the same choice for the per-head statistics              */
     NKV_FLAG_SELECT_PER_HEAD = 64u,   /* nkv_select_compact: the same choice for the top-B_h selection       */
     NKV_FLAG_VECTOR_SCAN = 128u,      /* streaming kernels: the vector-unit formulation of the fused pass    */
-                                      /* also for 16-bit keys of head dim 128, where the matrix-core one is  */
-                                      /* the default                                                         */
+                                      /* also for keys of head dim 128, where the matrix-core one is the     */
+                                      /* default                                                             */
     NKV_FLAG_COMPACT_IN_PLACE = 256u  /* nkv_select_compact: the kept rows of a unit move to the front of    */
                                       /* the unit's own rows in keys / values (no packed buffers)            */
 };

@@ -257,38 +257,4 @@ __device__ __forceinline__ uint32_t block_select(const uint32_t (&key)[EPT], int
     return lo;
 }
 
-// The k-th largest and the k-th smallest at once: the first histogram over [kmin, kmax] serves both.
-template <int EPT>
-__device__ __forceinline__ void block_select_both(const uint32_t (&key)[EPT], int n, uint32_t k, SelectScratch &s,
-                                                  uint32_t kmin, uint32_t kmax, uint32_t &t_top, uint32_t &rem_top,
-                                                  uint32_t &t_bot, uint32_t &rem_bot)
-{
-    const int shift = select_shift(kmin, kmax);
-    if (threadIdx.x < 2) s.nlist[threadIdx.x] = 0u;
-    hist_all<EPT>(key, n, s, kmin, shift);
-    uint32_t lo[2], hi[2], want[2], count[2], ties[2];
-    block_pick<true>(s, k);
-    lo[0] = kmin + (s.bin << shift);
-    hi[0] = shift == 0 ? lo[0] : min(kmax, lo[0] + ((1u << shift) - 1u));
-    want[0] = s.rank;
-    count[0] = s.count;
-    __syncthreads();
-    block_pick<false>(s, k);
-    lo[1] = kmin + (s.bin << shift);
-    hi[1] = shift == 0 ? lo[1] : min(kmax, lo[1] + ((1u << shift) - 1u));
-    want[1] = s.rank;
-    count[1] = s.count;
-    if (shift != 0) {
-        if (count[0] <= (uint32_t)kSelList) collect<EPT>(key, n, s, 0, lo[0], hi[0] - lo[0]);
-        if (count[1] <= (uint32_t)kSelList) collect<EPT>(key, n, s, 1, lo[1], hi[1] - lo[1]);
-        __syncthreads();
-        finish_select<EPT, true>(key, n, s, 0, count[0], lo[0], hi[0], want[0], ties[0]);
-        __syncthreads();
-        finish_select<EPT, false>(key, n, s, 1, count[1], lo[1], hi[1], want[1], ties[1]);
-    }
-    __syncthreads();
-    t_top = lo[0]; rem_top = want[0];
-    t_bot = lo[1]; rem_bot = want[1];
-}
-
 }  // namespace nkv

@@ -1,10 +1,10 @@
 // Outer learner: from the three raw anomalies of a head to its final scores
 // (paper Section 2.3 min-max, Section 2.4 reliability gaps / blend / surprise / gate, sink pinning).
 //
-//   finalize_unit_kernel  prompts of up to 16384 tokens: one workgroup of 1024 threads per unit (prompt, layer, head),
-//                         values in registers, one launch
-//   nkv_finalize_wide.hip longer prompts: slice by slice over the whole chip
-//   finalize_kernel       longer prompts where the caller asks for per-head kernels: one workgroup of 1024 threads per
+//   finalize_unit_kernel  calls whose prompts are all of up to 16384 tokens: one workgroup of 1024 threads per unit
+//                         (prompt, layer, head), values in registers
+//   nkv_finalize_wide.hip calls with a longer prompt: slice by slice over the whole chip
+//   finalize_kernel       the same where the caller asks for per-head kernels: one workgroup of 1024 threads per
 //                         unit walks the head's values in memory seven times:
 //     pass 1      min / max of each scale
 //     pass 2..5   byte-wise radix select (most significant digit first) of the m_p-th largest and the
@@ -400,14 +400,18 @@ hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &ta
     const unsigned units = (unsigned)(tab.n * L * H);
     const int per_unit = kUnitTokens;                                 // prompts of up to this length: one launch, a workgroup per unit
     prof.begin(NKV_KERNEL_FINALIZE, st);
-    if (nmax > per_unit && (wide_ws == nullptr || per_head_route)) {
-        finalize_kernel<<<units, kThreads, 0, st>>>(a_raw, L, H, tab, lc, scores);
+    if (nmax > per_unit) {
+        if (wide_ws == nullptr || per_head_route) {
+            finalize_kernel<<<units, kThreads, 0, st>>>(a_raw, L, H, tab, lc, scores);
+        } else {
+            hipError_t e = launch_stats_wide(a_raw, L, H, tab, lc.scale_mask, stats, wide_ws, st);
+            if (e != hipSuccess) return e;
+            e = launch_route_wide(a_raw, L, H, tab, lc, stats, wide_ws, scores, st);
+            if (e != hipSuccess) return e;
+        }
     } else {
         bool present[17] = {};
-        for (int p = 0; p < tab.n; ++p) {
-            const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-            if (N <= per_unit) present[length_class(N)] = true;
-        }
+        for (int p = 0; p < tab.n; ++p) present[length_class(tab.tok_off[p + 1] - tab.tok_off[p])] = true;
 #define NKV_UNIT(EPT)                                                                                                         \
     if (present[EPT])                                                                                                         \
     (lc.scale_mask == 7 ? finalize_unit_kernel<EPT, true> : finalize_unit_kernel<EPT, false>)<<<units, kSelThreads, 0, st>>>( \
@@ -416,12 +420,6 @@ hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &ta
         NKV_UNIT(8);
         NKV_UNIT(16);
 #undef NKV_UNIT
-        if (nmax > per_unit) {
-            hipError_t e = launch_stats_wide(a_raw, L, H, tab, lc.scale_mask, stats, wide_ws, st);
-            if (e != hipSuccess) return e;
-            e = launch_route_wide(a_raw, L, H, tab, lc, stats, wide_ws, scores, st);
-            if (e != hipSuccess) return e;
-        }
     }
     prof.end(NKV_KERNEL_FINALIZE, st);
     return hipGetLastError();

@@ -1,7 +1,7 @@
 // Per-head statistics of the three anomaly scales (paper Sections 2.3-2.4: min-max range, reliability gap =
 // mean of the m_p largest minus mean of the m_p smallest normalised anomalies) spread over the whole chip.
 //
-// Same numbers as scale_stats_kernel in nkv_finalize.hip (up to the order of floating-point additions), but a
+// Same numbers as finalize_unit_kernel in nkv_finalize.hip (up to the order of floating-point additions), but a
 // head's anomalies are not held by one workgroup: they are cut into slices of 8192 tokens and every step
 // that touches them runs on one small workgroup per (slice, scale).
 //
@@ -102,7 +102,6 @@ __global__ __launch_bounds__(256) void stats_pick_kernel(int L, int H, PromptTab
     const int u = blockIdx.x, k = blockIdx.y;
     const int lh = u % (L * H), p = u / (L * H);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-    if (N <= kUnitTokens) return;
     const int S = (N + kSlice - 1) / kSlice;
     const uint32_t m = (uint32_t)min(tab.m_p[p], N);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -349,7 +348,6 @@ __global__ __launch_bounds__(128) void stats_finish_kernel(const float *__restri
     const int64_t job = (int64_t)u * 3 + k;
     const int lh = u % (L * H), p = u / (L * H);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-    if (N <= kUnitTokens) return;
     const int S = (N + kSlice - 1) / kSlice;
     const uint32_t m = (uint32_t)min(tab.m_p[p], N);
     const int lane = threadIdx.x & 63, side = threadIdx.x >> 6;
@@ -445,7 +443,7 @@ struct WideWs {
 WideWs wide_ws(int L, int H, const PromptTab &tab)
 {
     SliceTab st;
-    const size_t slices = 3 * (size_t)fill_slices(L, H, tab, &st, kUnitTokens), jobs = 3 * (size_t)tab.n * L * H;
+    const size_t slices = 3 * (size_t)fill_slices(L, H, tab, &st), jobs = 3 * (size_t)tab.n * L * H;
     WideWs w;
     size_t off = 0;
     w.part = off;    off += align256(slices * kBins * sizeof(uint16_t));
@@ -468,7 +466,7 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
                              hipStream_t st)
 {
     SliceTab stab;
-    const int slices = fill_slices(L, H, tab, &stab, kUnitTokens);
+    const int slices = fill_slices(L, H, tab, &stab);
     const WideWs lay = wide_ws(L, H, tab);
     char *base = (char *)ws;
     uint16_t *part = (uint16_t *)(base + lay.part);
@@ -499,7 +497,7 @@ hipError_t launch_route_wide(const float *a_raw, int L, int H, const PromptTab &
                              const float *stats, void *ws, float *scores, hipStream_t st)
 {
     SliceTab stab;
-    const int slices = fill_slices(L, H, tab, &stab, kUnitTokens);
+    const int slices = fill_slices(L, H, tab, &stab);
     const WideWs lay = wide_ws(L, H, tab);
     const SliceSurprise *sur = (const SliceSurprise *)((char *)ws + lay.sur);
     const bool few = few_slices(slices), all = lc.scale_mask == 7;

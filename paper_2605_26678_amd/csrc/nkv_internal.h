@@ -108,7 +108,9 @@ template <typename F> inline void for_each_length_class(const PromptTab &tab, in
 }
 
 // ---- per-head statistics, blend weights, gate and final scores ----
-// prompts of up to kUnitTokens are done unit by unit, longer ones slice by slice
+// A call whose prompts are all of up to kUnitTokens is done unit by unit, one with a longer prompt slice by slice as a
+// whole: the per-unit launches for its short prompts would run in front of the slices' (16 layers x 4 heads x prompts of
+// 7184, 50226 and 1561 tokens: score 293 us with both, 274 us slice-wise).
 constexpr int kUnitTokens = 16384;
 // wide_ws: scratch of stats_wide_ws_bytes() for the slice-wise statistics (NULL: per-head kernels only);
 // per_head_route: do not use the slice-wise kernels

@@ -1,4 +1,5 @@
-// Streaming scoring kernel for bf16, fp16 or 8-bit (E4M3) keys, head dim 64 or 128, window 64, episodic block size <= 256
+// Streaming scoring kernel for bf16, fp16 or 8-bit (E4M3) keys, head dim 64 (and 128 on request; other head dims and, by
+// default, 128 take the matrix-core formulation of nkv_score_tile.hip), window 64, episodic block size <= 256
 // (paper Sections 2.1-2.3: normalised keys, stable / episodic / current anchors, cosine anomalies).
 //
 // Work decomposition.  One workgroup per (layer, head, episodic block).  The block (<= 256 tokens) is cut

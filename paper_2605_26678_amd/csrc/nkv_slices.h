@@ -32,14 +32,13 @@ struct SliceTab {                        // first slice of every prompt; a promp
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// longer_than: prompts of up to that length get no slices (the kernels that run per unit pass them over as well)
-inline int fill_slices(int L, int H, const PromptTab &tab, SliceTab *st, int longer_than = 0)
+inline int fill_slices(int L, int H, const PromptTab &tab, SliceTab *st)
 {
     int n = 0;
     for (int p = 0; p < tab.n; ++p) {
         st->off[p] = n;
         const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-        if (N > longer_than) n += L * H * ((N + kSlice - 1) / kSlice);
+        n += L * H * ((N + kSlice - 1) / kSlice);
     }
     st->off[tab.n] = n;
     return n;
