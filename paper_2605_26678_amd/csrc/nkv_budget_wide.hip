@@ -251,7 +251,8 @@ __global__ __launch_bounds__(1024) void layer_finish_kernel(const float *__restr
     auto &headL = mem.lists.headL;
     __shared__ uint32_t Th[kMaxH], remT[kMaxH], totT[kMaxH], dropped[kMaxH], gtL[kMaxH], eqL[kMaxH];
     __shared__ uint32_t cT[kMaxSeg], cL[kMaxSeg], oT[kMaxSeg];       // segment counts and offsets
-    __shared__ uint32_t nPool, s_TL, s_gtAll, s_bad;
+    // s_marked and s_overflow are two words: a wavefront may still be reading the first while another one sets the second
+    __shared__ uint32_t nPool, s_TL, s_gtAll, s_marked, s_overflow;
     const int pl = blockIdx.x, l = pl % L, p = pl / L;
     const LayerPick &pk = picks[pl];                                 // read in place: a private copy would sit in scratch
     if (pk.done) return;
@@ -262,14 +263,14 @@ __global__ __launch_bounds__(1024) void layer_finish_kernel(const float *__restr
     const int64_t slice0 = (int64_t)st.off[p] + (int64_t)l * H * S;  // first slice of the layer's first head
     const int nseg = H * S;
     if (tid < kMaxH) { dropped[tid] = 0u; gtL[tid] = 0u; eqL[tid] = 0u; totT[tid] = 0u; }
-    if (tid == 0) { nPool = 0u; s_bad = failed[pl] | (nseg > kMaxSeg ? 1u : 0u); }
+    if (tid == 0) { nPool = 0u; s_marked = failed[pl] | (nseg > kMaxSeg ? 1u : 0u); s_overflow = 0u; }
     // counts of all segments of the layer, then where every segment starts in its head's list
     if (tid < nseg && nseg <= kMaxSeg) {
         cT[tid] = nSegT[slice0 + tid];
         cL[tid] = nSegL[slice0 + tid];
     }
     __syncthreads();
-    if (s_bad) {
+    if (s_marked) {
         budget_of_layer(scores, L, H, tab, pl, mem.generic, k_per_head);
         return;
     }
@@ -278,11 +279,11 @@ __global__ __launch_bounds__(1024) void layer_finish_kernel(const float *__restr
         uint32_t off = 0u;
         for (int q = h * S; q < tid; ++q) off += cT[q];
         oT[tid] = off;
-        if (cT[tid] > (uint32_t)kSeg || cL[tid] > (uint32_t)kSeg || off + cT[tid] > (uint32_t)kListT) s_bad = 1u;
+        if (cT[tid] > (uint32_t)kSeg || cL[tid] > (uint32_t)kSeg || off + cT[tid] > (uint32_t)kListT) s_overflow = 1u;
         if (tid == h * S + S - 1) totT[h] = off + cT[tid];
     }
     __syncthreads();
-    if (s_bad) {
+    if (s_overflow) {
         budget_of_layer(scores, L, H, tab, pl, mem.generic, k_per_head);
         return;
     }

@@ -301,6 +301,32 @@ def test_heavy_ties_stage_parity(H, flags):
         assert np.array_equal(bits(out.packed_k), ref.packed_k) and np.array_equal(bits(out.packed_v), ref.packed_v)
 
 
+@pytest.mark.parametrize("which", ["head list", "layer list"])
+def test_budget_lists_that_overflow_without_an_overflowing_slice(which):
+    """Slice-wise budgets whose boundary bins hold more entries than the finishing workgroup's lists (512 of a head, 4096
+    of a layer) although no slice holds more than its segment's 256: the finishing workgroup finds that out by itself and
+    computes the layer from the scores.  Next to such layers one without overflow."""
+    L, H, N, r, per = 3, 8, 3 * 8192 + 5000, 0.5, 200
+    rng = np.random.default_rng(11)
+    sc = rng.random((L, H, N)).astype(np.float32)
+    k0 = oracle.k0(N, r)
+    at_head, at_layer = np.float32(1.0 - oracle.m_safe(k0) / N), np.float32(1.0 - k0 / N)   # about where the two cuts lie
+    for l in range(2):
+        for h in range(H):
+            for a in range(0, N, 8192):
+                spots = a + rng.permutation(min(8192, N - a))[:2 * per]
+                sc[l, h, spots[:per]] = at_head if which == "head list" else at_layer
+                sc[l, h, spots[per:]] = 0.05
+    want = np.stack([oracle.budget_layer(sc[l], r) for l in range(L)])
+    shape, p = nkv.Shape(L, H, 64, 64, nkv.DTYPE_BF16, [0, N]), nkv.params_default()
+    dev = torch.from_numpy(sc).to(DEV)
+    ws = torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV)
+    for _ in range(3):
+        got = torch.full((1, L, H), -1, dtype=torch.int32, device=DEV)
+        nkv.budget(dev, shape, p, [r], got, ws)
+        assert np.array_equal(got[0].cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("flags", [0, nkv.FLAG_BUDGET_PER_HEAD])
 def test_budget_routes_meet_the_stage_bar(flags):
     """Slice-wise and per-head budget kernels on a shape both cover (one prompt of several slices, one short,
