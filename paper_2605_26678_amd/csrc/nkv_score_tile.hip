@@ -286,6 +286,7 @@ __device__ __forceinline__ float weighted(const f32x4 &d, const float (&wm)[4])
 // 812 / 700 us).
 constexpr int kOneGroup = 192, kGroupBlocks = 32;
 __host__ __device__ __forceinline__ int blocks_per_group(int unit_blocks) { return unit_blocks > kOneGroup ? kGroupBlocks : kOneGroup; }
+__host__ __device__ __forceinline__ int unit_groups(int unit_blocks) { const int per = blocks_per_group(unit_blocks); return (unit_blocks + per - 1) / per; }
 // first group slot of a prompt with `blocks` blocks and `prompts` prompts in front of it: every prompt rounds up by itself
 __host__ __device__ __forceinline__ int group_slots(int blocks, int prompts) { return blocks / kGroupBlocks + prompts; }
 
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
             const int per = blocks_per_group(unblk), gi = local / per;
             it.group = lh * group_slots(plan.nblk, tab.n) + group_slots(tab.blk_off[p], p) + gi;
             it.group_blocks = min(per, unblk - gi * per);
-            it.unit_groups = (unblk + per - 1) / per;
+            it.unit_groups = unit_groups(unblk);
         }
         items[k] = it;
     }
@@ -706,6 +707,8 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
     for (int p = 0; p < tab.n; ++p) {
         const int N = tab.tok_off[p + 1] - tab.tok_off[p];
         if (tab.b[p] > 256 || N > kMaxUnitTokens) return false;
+        // the count of a word of the unit holds its groups (blocks of fewer than 32 tokens only)
+        if (unit_groups(tab.blk_off[p + 1] - tab.blk_off[p]) > kMaxUnitBlocks) return false;
         if ((int64_t)(N + 512) * d * 2 >= kNoByte) return false;
     }
     return (int64_t)LH * (tab.blk_off[tab.n] + tab.n) < (1ll << 28);

@@ -204,6 +204,16 @@ def test_matrix_core_scan_of_long_units(d, dtype, N):
     compare_end_to_end(w, K, V, 0.9, label=w.name)
 
 
+@pytest.mark.parametrize("d,dtype", [(8, "bf16"), (16, "fp8"), (128, "fp16")])
+@pytest.mark.parametrize("N", [131040, 131041])
+def test_units_of_more_blocks_than_two_step_adding_counts(N, d, dtype):
+    """Blocks of one token: 131 040 of them are 4095 groups of 32, as many as a unit's word of the matrix-core scan can
+    count; a unit of one more takes another scan.  Against the oracle, beside a short prompt."""
+    w = nkv_inputs.small_workload(f"blocks_{d}_{N}", 1, 1, d, [N, 300], dtype=dtype, n_out=0)
+    K, V = _kv(w)
+    compare_end_to_end(w, K, V, 0.9, params=nkv.params_default(block_min=1, block_max=1), label=w.name)
+
+
 @pytest.mark.parametrize("d,dtype,window,block", [(8, "fp32", 1, 128), (128, "fp32", 64, 128), (136, "bf16", 16, 128),
                                                   (256, "fp16", 17, 300), (80, "fp8", 100, 7), (1024, "fp32", 30, 5)])
 def test_generic_scan_windows_and_blocks(d, dtype, window, block):
