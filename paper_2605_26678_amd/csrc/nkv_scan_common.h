@@ -439,13 +439,13 @@ __device__ __forceinline__ void ensure_unit_sum(const float *bsum_unit, int unbl
 // * 2^12 + 1 with one integer atomic per dimension, so the low 12 bits of a word count the blocks that have
 // added to it and a word is complete when they equal the unit's number of blocks.  Integer additions commute:
 // the sum does not depend on the order the blocks arrive in, and nothing has to be ordered or fenced -- every
-// word says by itself whether it is complete.  Range: a component of a normalised key is at most 1, so
-// |total| <= 256 per block and |sum| < 2^20 for the at most 4095 blocks of a unit: 20 + 31 bits and the sign
-// above the 12 count bits fill the word exactly.  (A unit of more blocks is added up in groups, see
-// nkv_score_tile.hip; what is left is |sum| <= tokens <= 2^20.)
-constexpr int kMaxUnitTokens = 1 << 20;
+// word says by itself whether it is complete.  Range: 20 + 31 bits and the sign above the 12 count bits fill the word,
+// so |sum| has to stay below 2^20.  A component of a normalised key is at most 1 (up to rounding), so 4095 blocks of
+// 256 tokens are the most a unit may have, 2^20 - 256 tokens: 1 part in 4096 below the limit, far more than the roundings
+// of the keys' norms and of the block totals can add (a few parts in 10^6).
 constexpr int kCountBits = 12;
-constexpr int kMaxUnitBlocks = (1 << kCountBits) - 1;
+constexpr int kMaxUnitBlocks = (1 << kCountBits) - 1;    // adds a word can count: blocks, or groups of blocks (nkv_score_tile.hip)
+constexpr int kMaxUnitTokens = kMaxUnitBlocks * 256;
 constexpr int kAccumFrac = 31;                   // fraction bits of the fixed-point sum
 
 // what a block adds for its total v

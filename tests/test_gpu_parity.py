@@ -214,6 +214,23 @@ def test_units_of_more_blocks_than_two_step_adding_counts(N, d, dtype):
     compare_end_to_end(w, K, V, 0.9, params=nkv.params_default(block_min=1, block_max=1), label=w.name)
 
 
+@pytest.mark.parametrize("N", [4095 * 256, 4095 * 256 + 1, 1 << 20])
+@pytest.mark.parametrize("d,dtype", [(8, "bf16"), (8, "fp16"), (128, "bf16")])
+def test_unit_sum_at_the_most_tokens_of_a_unit(N, d, dtype):
+    """Keys that all point along one axis (powers of two, whose normalised keys are exactly 1), on both sides of the longest
+    prompt whose sum the matrix-core scan's fixed-point words are sure to hold: the stable anomaly of every token is -1."""
+    K = torch.zeros(1, 1, N, d, dtype=torch.bfloat16 if dtype == "bf16" else torch.float16, device=DEV)
+    K[..., 5] = torch.exp2((torch.arange(N, device=DEV) % 5).float()).to(K.dtype)
+    shape = nkv.Shape(1, 1, d, d, nkv.DTYPE_BF16 if dtype == "bf16" else nkv.DTYPE_F16, [0, N])
+    p = nkv.params_default()
+    a = torch.empty(3, 1, 1, N, dtype=torch.float32, device=DEV)
+    ws = torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV)
+    nkv.score_raw(K, shape, p, a, ws)
+    torch.cuda.synchronize()
+    assert torch.isfinite(a).all()
+    assert (a + 1.0).abs().max().item() < 2e-6
+
+
 @pytest.mark.parametrize("d,dtype,window,block", [(8, "fp32", 1, 128), (128, "fp32", 64, 128), (136, "bf16", 16, 128),
                                                   (256, "fp16", 17, 300), (80, "fp8", 100, 7), (1024, "fp32", 30, 5)])
 def test_generic_scan_windows_and_blocks(d, dtype, window, block):
