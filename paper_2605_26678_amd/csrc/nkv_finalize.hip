@@ -168,17 +168,44 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const float *__restr
 // read of them to the routed score.  One workgroup of 1024 threads per unit.
 //
 // A short unit's arithmetic is small and what takes time is the chain of dependent steps, so there are few of them (as
-// two kernels of radix selects, one workgroup per scale, 16 x 8 units of 4096 tokens took 33 us, this takes 11):
-//   1. histograms of the three scales over the fixed range of a cosine (2048 bins), min and max of each;
-//   2. one scan per scale gives the bins that hold the m-th largest and the m-th smallest value;
+// two kernels of radix selects, one workgroup per scale, 16 x 8 units of 4096 tokens took 33 us, this takes 14):
+//   1. min and max of each scale, then its histogram over that range (2048 bins);
+//   2. one scan per scale gives the bins that hold the m-th largest and the m-th smallest value; a bin that holds more
+//      than kUnitList values is narrowed down first (see below);
 //   3. sums beyond those bins, their entries into six lists; surprise statistics (the ranges are known);
 //   4. six wavefronts find the exact thresholds in the lists, another one adds the surprise up;
 //   5. weights; blend, gate, route, pin.
 // Same numbers as the slice-wise kernels (the sums over a boundary bin's entries in fixed point: independent of the
-// order the entries arrive in).  A list that overflows (more than 1024 equal or nearly equal values) sends its wavefront
-// over the unit's values in memory.
+// order the entries arrive in).
+//
+// Narrowing: anomalies may all lie close together but for a few outliers (keys with a strong common direction), or be
+// equal by the thousand (repeated keys).  A crowded bin is cut, between the smallest and the largest key in it, into 1024
+// bins of integer keys, all six boundary bins at once, until it holds few keys or a single one: one round for
+// values that are merely close, two where they also repeat.  With a histogram over the whole range of a cosine, a wavefront
+// that walked the unit's values where a list overflowed, and an add per value, the scores of 8 heads x 8192 tokens took
+// 34 us for spread-out keys, 224 us for keys close together; now 35 and 35, 50 where half of the keys are equal.
 // ------------------------------------------------------------------------------------------------------
-constexpr int kUnitList = 1024;              // keys a list holds
+constexpr int kUnitList = 256;              // keys a list holds
+
+// Where the m largest (list 2k of scale k) or the m smallest (2k + 1, on inverted keys) end.
+struct UnitCut {
+    int bin;                                  // boundary bin
+    uint32_t need, pop;                       // of the pop values between lo and hi in it, the need best belong to the m
+    uint32_t lo, hi;                          // keys; better ones of the bin belong to the m, worse ones do not
+};
+
+// Adds the active lanes to their bins, those of the first lane's bin with one add: equal values would queue for one word,
+// a few cycles each.
+__device__ __forceinline__ void count_bin(uint32_t *hist, int bin)
+{
+    const unsigned long long same = __ballot(bin == __builtin_amdgcn_readfirstlane(bin));
+    const bool mine = (same >> (threadIdx.x & 63)) & 1ull;
+    const bool first = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) == 0u;
+    if (!mine || first) atomicAdd(&hist[bin], mine ? (uint32_t)__popcll(same) : 1u);
+}
+
+// monotone in x
+__device__ __forceinline__ int unit_bin(float x, float lo, float scale) { return min(max((int)((x - lo) * scale), 0), kBins - 1); }
 
 // grid: units.  EPT: values a thread holds per scale; units of prompts of another length class are passed over, so that a
 // ragged batch takes one launch per class it holds, not one per run of prompts (4 layers x 32 heads x prompts of 1531,
@@ -188,18 +215,20 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
                                                                                       PromptTab tab, LearnerConsts lc,
                                                                                       float *__restrict__ scores)
 {
-    constexpr int NW = kSelThreads / 64;
+    constexpr int NW = kSelThreads / 64, kSub = kSelThreads;
     __shared__ __attribute__((aligned(16))) uint32_t buf[3 * kBins];  // the histograms, then the lists
     __shared__ uint32_t whist[6][256];
-    __shared__ uint32_t ext[6];                  // per scale: max of ~key and of key = ~min, max as ordered integers
-    __shared__ uint32_t wtot[3][NW];
-    __shared__ int bin[6];                       // list 2k: upper boundary bin of scale k, 2k + 1: lower
-    __shared__ uint32_t need[6], cnt[6];
+    __shared__ uint32_t ext[12];                 // per scale, of the wavefronts' minima and maxima as keys: max of ~min, max, min, ~max
+    __shared__ uint32_t wtot[6][NW];
+    __shared__ UnitCut s_cut[6];
+    __shared__ float s_lo[3], s_to_bin[3];
+    __shared__ uint32_t range[6][2];             // of a crowded bin: max of ~key and of key
+    __shared__ uint32_t cnt[6];
     __shared__ double sums[7][NW];               // beyond the boundary bins, per wavefront; the surprise
     __shared__ float sext[2][NW];
     __shared__ double side[6];
     __shared__ HeadStats hs;
-    static_assert(6 * kUnitList <= 3 * kBins, "the lists lie where the histograms were");
+    static_assert(6 * kUnitList <= 3 * kBins && 6 * kSub <= 3 * kBins, "lists and narrowed bins lie where the histograms were");
 
     const int u = blockIdx.x;
     const int h = u % H, l = (u / H) % L, p = u / (H * L);
@@ -216,29 +245,76 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     for (int k = 0; k < 3; ++k)
 #pragma unroll
         for (int j = 0; j < EPT; ++j) v[k][j] = a[k * rows + min(tid + j * kSelThreads, N - 1)];
+    auto clear_buf = [&]() {
+        const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (int j = 0; j < 3 * kBins / 4 / kSelThreads + 1; ++j)
-        if (tid + j * kSelThreads < 3 * kBins / 4) reinterpret_cast<uint4 *>(buf)[tid + j * kSelThreads] = make_uint4(0u, 0u, 0u, 0u);
-    if (tid < 6) { ext[tid] = 0u; cnt[tid] = 0u; }
+        for (int j = 0; j < 3 * kBins / 4 / kSelThreads + 1; ++j)
+            if (tid + j * kSelThreads < 3 * kBins / 4) reinterpret_cast<uint4 *>(buf)[tid + j * kSelThreads] = zero;
+    };
+    clear_buf();
+    if (tid < 12) ext[tid] = 0u;
+    if (tid < 6) {
+        cnt[tid] = range[tid][0] = range[tid][1] = 0u;
+        s_cut[tid] = UnitCut{-1, 0u, 0u, 0u, 0xffffffffu};            // (what a flat scale keeps: its gap does not count)
+    }
     __syncthreads();
 
-    // ---- 1: histograms, ranges ----
+    // ---- 1: ranges, histograms ----
+    // The histogram's range leaves the outliers aside that a few wavefronts hold (they go to its end bins): it lies between
+    // the largest minimum and the smallest maximum of a wavefront, where there is anything between them and a wavefront
+    // holds 128 values and more (the tenth of them that is looked for lies inside, then).
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        float lo = INFINITY, hi = -INFINITY;
+        float lo = INFINITY, hi = -INFINITY;                          // (what a thread holds past the unit repeats its last value)
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
-            if (tid + j * kSelThreads < N) {
-                lo = fminf(lo, v[k][j]);
-                hi = fmaxf(hi, v[k][j]);
-                atomicAdd(&buf[k * kBins + anomaly_bin(v[k][j])], 1u);
-            }
+            lo = fminf(lo, v[k][j]);
+            hi = fmaxf(hi, v[k][j]);
         }
-        lo = wave_min(lo);
-        hi = wave_max(hi);
+        const uint32_t least = ord_key(wave_min(lo)), most = ord_key(wave_max(hi));
         if (lane == 0) {
-            atomicMax(&ext[2 * k], ~ord_key(lo));
-            atomicMax(&ext[2 * k + 1], ord_key(hi));
+            atomicMax(&ext[4 * k], ~least);
+            atomicMax(&ext[4 * k + 1], most);
+            atomicMax(&ext[4 * k + 2], least);
+            atomicMax(&ext[4 * k + 3], ~most);
+        }
+    }
+    __syncthreads();
+    auto uniform = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
+    HeadStats st;
+    float bins_lo[3], to_bin[3];                                      // to_bin: bins per unit of the scale; 0: the scale is flat
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        st.lo[k] = uniform(key_value(~ext[4 * k]));
+        const float hi = key_value(ext[4 * k + 1]), inner_lo = key_value(ext[4 * k + 2]), inner_hi = key_value(~ext[4 * k + 3]);
+        const float range = hi - st.lo[k];
+        st.inv_range[k] = uniform(range < kFlat ? 0.f : 1.0f / range);
+        const bool inner = inner_hi > inner_lo && N >= 2 * kSelThreads;
+        bins_lo[k] = uniform(inner ? inner_lo : st.lo[k]);
+        to_bin[k] = uniform(range < kFlat ? 0.f : (float)kBins / (inner ? inner_hi - inner_lo : range));
+    }
+    if (tid == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) { s_lo[k] = bins_lo[k]; s_to_bin[k] = to_bin[k]; }
+    }
+    auto bin_of = [&](int k, float x) { return unit_bin(x, bins_lo[k], to_bin[k]); };
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (to_bin[k] == 0.f) continue;
+        bool queue = false;                                           // many equal values, going by three of the slots
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int b = bin_of(k, v[k][i * (EPT - 1) / 2]);
+            queue |= __popcll(__ballot(b == __builtin_amdgcn_readfirstlane(b))) > 16;
+        }
+        if (queue) {
+#pragma unroll
+            for (int j = 0; j < EPT; ++j)
+                if (tid + j * kSelThreads < N) count_bin(buf + k * kBins, bin_of(k, v[k][j]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < EPT; ++j)
+                if (tid + j * kSelThreads < N) atomicAdd(&buf[k * kBins + bin_of(k, v[k][j])], 1u);
         }
     }
     __syncthreads();
@@ -255,62 +331,150 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
+        if (to_bin[k] == 0.f) continue;
         const uint32_t group = c[k].x + c[k].y;
         const uint32_t up = incl[k] + wave_sum(lane < w ? wtot[k][lane & (NW - 1)] : 0u);   // entries up to and with my bins
         const uint32_t below = up - group, above = (uint32_t)N - up;
         if (below < m && m <= up) {                                   // the m-th smallest lies in one of my bins
             const bool second = below + c[k].x < m;
-            bin[2 * k + 1] = 2 * tid + (second ? 1 : 0);
-            need[2 * k + 1] = m - below - (second ? c[k].x : 0u);
+            s_cut[2 * k + 1].bin = 2 * tid + (second ? 1 : 0);
+            s_cut[2 * k + 1].need = m - below - (second ? c[k].x : 0u);
+            s_cut[2 * k + 1].pop = second ? c[k].y : c[k].x;
         }
         if (above < m && m <= above + group) {                        // the m-th largest
             const bool first = above + c[k].y < m;
-            bin[2 * k] = 2 * tid + (first ? 0 : 1);
-            need[2 * k] = m - above - (first ? c[k].y : 0u);
+            s_cut[2 * k].bin = 2 * tid + (first ? 0 : 1);
+            s_cut[2 * k].need = m - above - (first ? c[k].y : 0u);
+            s_cut[2 * k].pop = first ? c[k].x : c[k].y;
         }
     }
     __syncthreads();
+    auto key_of = [](int i, float x) { return i & 1 ? ~ord_key(x) : ord_key(x); };   // inverted: the smallest value has the largest key
+    auto crowded = [](const UnitCut &q) { return q.pop > (uint32_t)kUnitList && q.lo != q.hi; };
+    auto any_crowded = [&]() {                                        // the same for every thread
+        bool any = false;
+        for (int i = 0; i < 6; ++i) any |= crowded(s_cut[i]);
+        return any;
+    };
+    if (any_crowded()) {
+        // f(list, its cut, a thread's keys, which of them are in the list's boundary bin).  16 values a thread are read again:
+        // the rare path then costs the common one no registers.
+        auto for_crowded = [&](auto f) {
+#pragma unroll(EPT < 16 ? 6 : 1)
+            for (int i = 0; i < 6; ++i) {
+                const UnitCut q = s_cut[i];
+                if (!crowded(q)) continue;
+                const int k = i >> 1;
+                const float lo = s_lo[k], scale = s_to_bin[k];
+                uint32_t key[EPT];
+                bool in[EPT];
+                float x[EPT];
+#pragma unroll
+                for (int j = 0; j < EPT; ++j) {
+                    x[j] = EPT < 16 ? v[k][j] : a[k * rows + min(tid + j * kSelThreads, N - 1)];
+                    asm volatile("" : "+v"(x[j]));
+                }
+#pragma unroll
+                for (int j = 0; j < EPT; ++j) {
+                    key[j] = key_of(i, x[j]);
+                    in[j] = tid + j * kSelThreads < N && unit_bin(x[j], lo, scale) == q.bin;
+                }
+                f(i, q, key, in);
+            }
+        };
+        for_crowded([&](int i, const UnitCut &, const uint32_t (&key)[EPT], const bool (&in)[EPT]) {
+            uint32_t nlo = 0u, hi = 0u;
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) {
+                nlo = max(nlo, in[j] ? ~key[j] : 0u);
+                hi = max(hi, in[j] ? key[j] : 0u);
+            }
+            auto larger = [](uint32_t x, uint32_t y) { return max(x, y); };
+            nlo = wave_reduce(nlo, larger);
+            hi = wave_reduce(hi, larger);
+            if (lane == 0) {
+                atomicMax(&range[i][0], nlo);
+                atomicMax(&range[i][1], hi);
+            }
+        });
+        __syncthreads();
+        if (tid < 6 && crowded(s_cut[tid])) {
+            s_cut[tid].lo = ~range[tid][0];
+            s_cut[tid].hi = range[tid][1];
+        }
+        __syncthreads();
+        auto shift_of = [](const UnitCut &q) { return q.hi - q.lo < (uint32_t)kSub ? 0 : 22 - __builtin_clz(q.hi - q.lo); };
+        for (int round = 0; round < 4 && any_crowded(); ++round) {    // every round cuts an interval to a 1024th
+            clear_buf();
+            __syncthreads();
+            for_crowded([&](int i, const UnitCut &q, const uint32_t (&key)[EPT], const bool (&in)[EPT]) {
+                const int shift = shift_of(q);
+#pragma unroll
+                for (int j = 0; j < EPT; ++j)
+                    if (in[j] && key[j] - q.lo <= q.hi - q.lo) count_bin(buf + i * kSub, (int)((key[j] - q.lo) >> shift));
+            });
+            __syncthreads();
+#pragma unroll 1
+            for (int i = 0; i < 6; ++i) {                             // thread: bin tid of the interval, counted from the top
+                const UnitCut q = s_cut[i];
+                if (!crowded(q)) continue;
+                const uint32_t mine = buf[i * kSub + tid], up = wave_suffix_sum(mine);
+                if (lane == 0) wtot[0][w] = up;
+                __syncthreads();
+                const uint32_t counted = up + wave_sum(lane > w && lane < NW ? wtot[0][lane & (NW - 1)] : 0u), above = counted - mine;
+                if (above < q.need && q.need <= counted) {
+                    const uint32_t lo = q.lo + ((uint32_t)tid << shift_of(q));
+                    s_cut[i] = UnitCut{q.bin, q.need - above, mine, lo, min(q.hi, lo + ((1u << shift_of(q)) - 1u))};
+                }
+                __syncthreads();
+            }
+        }
+    }
+    // (bins are cheaper worked out again than kept: the compiler would carry those of all values over from step 1)
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < EPT; ++j) asm volatile("" : "+v"(v[k][j]));
+    UnitCut cut[6];                                                   // uniform
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        cut[i].bin = __builtin_amdgcn_readfirstlane(s_cut[i].bin);
+        cut[i].lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cut[i].lo);
+        cut[i].hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cut[i].hi);
+    }
 
     // ---- 3: sums beyond the boundary bins, their entries, the surprise ----
-    HeadStats st;
-    float pt[3], pb[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        st.lo[k] = key_value(~ext[2 * k]);
-        const float range = key_value(ext[2 * k + 1]) - st.lo[k];
-        st.inv_range[k] = range < kFlat ? 0.f : 1.0f / range;
-        pt[k] = pb[k] = 0.f;                                          // at most EPT terms of magnitude <= 1
-    }
+    float pt[3] = {0.f, 0.f, 0.f}, pb[3] = {0.f, 0.f, 0.f};           // at most EPT terms of magnitude <= 1
     float smin = INFINITY, smax = -INFINITY, ssum = 0.f;
-    {
-        int bT[3], bB[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) { bT[k] = bin[2 * k]; bB[k] = bin[2 * k + 1]; }
+    for (int j = 0; j < EPT; ++j) {
+        if (tid + j * kSelThreads < N) {
+            float raw[3], at[3];
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            if (tid + j * kSelThreads < N) {
-                float raw[3], at[3];
+            for (int k = 0; k < 3; ++k) {
+                const float x = raw[k] = v[k][j];
+                const int b = bin_of(k, x);
+                pt[k] += b > cut[2 * k].bin ? x : 0.f;
+                pb[k] += b < cut[2 * k + 1].bin ? x : 0.f;
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const float x = raw[k] = v[k][j];
-                    const int b = anomaly_bin(x);
-                    pt[k] += b > bT[k] ? x : 0.f;
-                    pb[k] += b < bB[k] ? x : 0.f;
-                    if (b == bT[k]) {
-                        const uint32_t i = atomicAdd(&cnt[2 * k], 1u);
-                        if (i < (uint32_t)kUnitList) buf[2 * k * kUnitList + i] = ord_key(x);
-                    }
-                    if (b == bB[k]) {                                 // inverted: the smallest value has the largest key
-                        const uint32_t i = atomicAdd(&cnt[2 * k + 1], 1u);
-                        if (i < (uint32_t)kUnitList) buf[(2 * k + 1) * kUnitList + i] = ~ord_key(x);
+                for (int e = 0; e < 2; ++e) {
+                    const int i = 2 * k + e;
+                    if (b == cut[i].bin) {
+                        const uint32_t key = key_of(i, x);
+                        if (key > cut[i].hi) {
+                            (e == 0 ? pt : pb)[k] += x;
+                        } else if (key >= cut[i].lo && cut[i].lo != cut[i].hi) {   // (a single key needs no list)
+                            const uint32_t at = atomicAdd(&cnt[i], 1u);
+                            if (at < (uint32_t)kUnitList) buf[i * kUnitList + at] = key;
+                        }
                     }
                 }
-                normalised(raw, st, at);
-                const float s = surprise_std<ALL>(at, lc.scale_mask);
-                smin = fminf(smin, s);
-                smax = fmaxf(smax, s);
-                ssum += s;                                            // at most EPT terms of magnitude <= 0.5
             }
+            normalised(raw, st, at);
+            const float s = surprise_std<ALL>(at, lc.scale_mask);
+            smin = fminf(smin, s);
+            smax = fmaxf(smax, s);
+            ssum += s;                                                // at most EPT terms of magnitude <= 0.5
         }
     }
 #pragma unroll
@@ -329,26 +493,19 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     // ---- 4: exact thresholds in the lists (wavefront = list), the surprise's range and mean ----
     if (w < 6) {
         constexpr double kFix = 1099511627776.0;                      // 2^40: exact for fp32 values of magnitude <= 1 down to that step
-        const int k = w >> 1;
         const bool low = (w & 1) != 0;
-        const uint32_t n = cnt[w];
-        uint32_t T, gt, eq;
+        const UnitCut q = s_cut[w];
+        const int n = min((int)cnt[w], kUnitList);
+        uint32_t T = q.lo, gt = 0u, eq;
         long long part = 0;
-        double total;
-        if (n <= (uint32_t)kUnitList) {
+        if (n > 0) {
             const uint32_t *list = buf + w * kUnitList;
-            T = wave_select(list, (int)n, need[w], whist[w], gt, eq);
-            for (uint32_t i = lane; i < n; i += 64)
+            T = wave_select(list, n, q.need, whist[w], gt, eq);
+            for (int i = lane; i < n; i += 64)
                 part += list[i] > T ? __double2ll_rn((double)key_value(low ? ~list[i] : list[i]) * kFix) : 0ll;
-            total = wave_sum(lane < NW ? sums[w][lane & (NW - 1)] : 0.0) + (double)(need[w] - gt) * (double)key_value(low ? ~T : T);
-        } else {
-            const float *x = a + k * rows;
-            auto key_at = [x, low](int i) { return low ? ~ord_key(x[i]) : ord_key(x[i]); };
-            T = wave_select_fn(N, m, whist[w], gt, eq, key_at);
-            for (int i = lane; i < N; i += 64) part += key_at(i) > T ? __double2ll_rn((double)x[i] * kFix) : 0ll;
-            total = (double)(m - gt) * (double)key_value(low ? ~T : T);
         }
-        total += (double)wave_sum(part) / kFix;
+        double total = wave_sum(lane < NW ? sums[w][lane & (NW - 1)] : 0.0) + (double)wave_sum(part) / kFix;
+        if (q.need > 0u) total += (double)(q.need - gt) * (double)key_value(low ? ~T : T);   // (0: a flat scale)
         if (lane == 0) side[w] = total;
     } else if (w == 6) {
         const int i = lane & (NW - 1);

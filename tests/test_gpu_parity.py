@@ -378,6 +378,70 @@ def test_statistics_routes_meet_the_score_bar(flags):
     compare_end_to_end(w, Kc, V, 0.75, params=nkv.params_default(flags=flags), label=f"stats const flags={flags}")
 
 
+def _learner64(a, p):
+    """Scores of one head from its raw anomalies a [3, N] (fp32) in 64 bits, every ranking a full sort, and what an error of
+    the normalised readings is multiplied by on its way to a score: the surprise's range is scaled to 1 and the gate rises
+    by kappa / 4 at most."""
+    N = a.shape[1]
+    flat = np.float32(1e-6)
+    lo, hi = a.min(1), a.max(1)
+    inv = np.where(hi - lo < flat, 0.0, 1.0 / np.maximum((hi - lo).astype(np.float64), 1e-30))[:, None]
+    at = (a.astype(np.float64) - lo[:, None]) * inv
+    m = oracle.m_p(N, p.top_frac)
+    ranked = np.sort(at, axis=1)
+    gap = ranked[:, N - m:].mean(1) - ranked[:, :m].mean(1)
+    on = np.array([(p.scale_mask >> k) & 1 for k in range(3)], bool)
+    z = np.where(on, np.log(np.where(on, np.array(list(p.prior)), 1.0)) + p.beta * gap, -np.inf)
+    weight = np.exp(z - z.max())
+    weight /= weight.sum()
+    s = at[on].std(0)
+    srange = s.max() - s.min()
+    s = (s - s.min()) / srange if srange >= flat else np.zeros(N)
+    gate = 1.0 / (1.0 + np.exp(-p.kappa * (np.maximum(s - s.mean(), 0.0) - p.tau)))
+    out = (1.0 - gate) * (weight[:, None] * at).sum(0) + gate * at[on].max(0)
+    return out, 1.0 + 0.5 * p.kappa / max(srange, flat) if srange >= 0.5 * flat else 1.0
+
+
+@pytest.mark.parametrize("N", [1000, 2049, 4096, 8192, 16384])
+@pytest.mark.parametrize("kind", ["close", "close but a few", "every other the same", "half zero", "one from 100 on", "two halves"])
+def test_statistics_of_crowded_anomalies(kind, N):
+    """Short prompts whose anomalies crowd into few bins of the per-unit statistics' histograms: keys with a strong common
+    direction, without and with a few outliers; the same key over and over; zero keys; two keys and nothing in between.
+    Lengths of every class of values per thread.  Against 64 bits from the library's own raw anomalies (which these keys
+    leave few digits of)."""
+    lens = [N, 130]
+    g = torch.Generator().manual_seed(N)
+    K = torch.randn(1, 2, sum(lens), 64, generator=g) + 20.0 * torch.randn(1, 2, 1, 64, generator=g)
+    if kind == "close but a few":
+        K[:, :, :4] *= -1.0
+        K[:, :, 700::500] = torch.randn(K[:, :, 700::500].shape, generator=g)
+    elif kind == "every other the same":
+        K[:, :, ::2] = K[:, :, :1]
+    elif kind == "half zero":
+        K[:, :, :N // 2] = 0
+    elif kind == "one from 100 on":
+        K[:, :, 100:N] = K[:, :, 100:101]
+    elif kind == "two halves":
+        K[:, :, :N // 3] = K[:, :, :1]
+        K[:, :, N // 3:N] = -K[:, :, 1:2]
+    K = K.to(torch.bfloat16).to(DEV)
+    shape = nkv.Shape(1, 2, 64, 64, nkv.DTYPE_BF16, [0, N, N + 130])
+    for over in (dict(), dict(scale_mask=5, top_frac=0.37), dict(top_frac=0.0001)):
+        p = nkv.params_default(n_sink=0, **over)
+        ws = torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV)
+        a = torch.empty(3, 2, N + 130, device=DEV)
+        sc = torch.empty(2, N + 130, device=DEV)
+        nkv.score_raw(K, shape, p, a, ws)
+        nkv.score(K, shape, p, sc, ws)
+        a, sc = a.cpu().numpy(), sc.cpu().numpy()
+        for lo, hi in ((0, N), (N, N + 130)):
+            for h in range(2):
+                want, gain = _learner64(a[:, h, lo:hi], p)
+                # a reading is good to about two steps of fp32 at 1, its deviation to four
+                tol = 1e-6 + 5e-7 * gain
+                assert np.abs(sc[h, lo:hi] - want).max() <= tol, (over, lo, h, tol)
+
+
 @pytest.mark.parametrize("flags", [0, nkv.FLAG_SELECT_PER_HEAD])
 def test_selection_routes_meet_the_stage_bar(flags):
     """Slice-wise and per-unit selection kernels, fed the oracle's scores and budgets: bit-exact kept indices and
