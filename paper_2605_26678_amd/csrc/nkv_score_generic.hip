@@ -6,7 +6,10 @@
 //                (Section 2.2, episodic memory); one workgroup per block
 //   2. ssum    : sum of k_hat over the prompt = sum of its block sums  (Section 2.2, stable memory)
 //   3. anomaly : a_s, a_e from the two sums; a_c from a window sum that slides over 16 consecutive tokens and is formed
-//                afresh in front of them (Section 2.2 current memory; Section 2.3); one wavefront per 16 tokens
+//                afresh in front of them (Section 2.2 current memory; Section 2.3); one wavefront per 16 tokens.  The window
+//                sum is held in 64 bits (the products of 32-bit factors are exact then), so that what has entered
+//                leaves again without a trace: in 32 bits, keys that cancel inside the window left twice the error of a
+//                window added up afresh for every token
 // Everywhere a lane owns dims lane, lane + 64, ... of a row.  The time of a small call is a chain of load latencies, so
 // loads go out eight or sixteen rows at a time.  (With the window added up for every token, a wave per token and a serial loop over
 // a block's tokens, 2 heads x 4096 fp32 tokens took 86 us.)
@@ -79,10 +82,10 @@ __global__ __launch_bounds__(kBlockThreads) void block_kernel(const T *__restric
         part[w][lane] = acc[q];
         __syncthreads();
         if (w == 0 && lane + q * kWave < d) {
-            float s = 0.f;
+            double s = 0.0;
 #pragma unroll
-            for (int i = 0; i < NW; ++i) s += part[i][lane];
-            out[lane + q * kWave] = s;
+            for (int i = 0; i < NW; ++i) s += (double)part[i][lane];
+            out[lane + q * kWave] = (float)s;
         }
     }
 }
@@ -90,26 +93,26 @@ __global__ __launch_bounds__(kBlockThreads) void block_kernel(const T *__restric
 // grid (prompts, L*H); thread = (slice, dim): slice s adds blocks s, s + slices, ... up
 __global__ __launch_bounds__(kSsumThreads) void ssum_kernel(const float *__restrict__ bsum, int d, PromptTab tab, float *__restrict__ ssum)
 {
-    __shared__ float part[kSsumThreads];
+    __shared__ double part[kSsumThreads];
     const int p = blockIdx.x, lh = blockIdx.y;
     const int nblk = tab.blk_off[tab.n], n = tab.blk_off[p + 1] - tab.blk_off[p];
     const int slices = kSsumThreads / d, c = threadIdx.x % d, slice = threadIdx.x / d;       // d <= 1024; some threads may be idle
     const float *mine = bsum + ((int64_t)lh * nblk + tab.blk_off[p]) * d + c;
-    float s = 0.f;
+    double s = 0.0;
     if (slice < slices) {
         for (int b = slice; b < n; b += 4 * slices) {
             float v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = b + i * slices < n ? mine[(int64_t)(b + i * slices) * d] : 0.f;
-            s += (v[0] + v[1]) + (v[2] + v[3]);
+            s += ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
         }
     }
     part[threadIdx.x] = s;
     __syncthreads();
     if ((int)threadIdx.x < d) {
-        float t = 0.f;
+        double t = 0.0;
         for (int i = 0; i < slices; ++i) t += part[i * d + threadIdx.x];
-        ssum[((int64_t)lh * tab.n + p) * d + threadIdx.x] = t;
+        ssum[((int64_t)lh * tab.n + p) * d + threadIdx.x] = (float)t;
     }
 }
 
@@ -138,21 +141,22 @@ __global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys
     const float *B0 = bsum + ((int64_t)lh * tab.blk_off[tab.n] + tab.blk_off[p]) * d;
 
     // the weighted sum of rows [lo, hi)
-    auto add_rows = [&](int lo, int hi, float (&sum)[NQ]) {
+    auto add_rows = [&](int lo, int hi, double (&sum)[NQ]) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) sum[q] = 0.f;
+        for (int q = 0; q < NQ; ++q) sum[q] = 0.0;
         for (int j = lo; j < hi; j += U) {
             float x[U][NQ];
             load_rows<T, NQ, U>(unit, d, lane, j, 1, hi, x);
 #pragma unroll
             for (int i = 0; i < U; ++i) {
-                const float r = rn_unit[min(j + i, hi - 1)];
+                const double r = (double)rn_unit[min(j + i, hi - 1)];
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) sum[q] = fmaf(r, x[i][q], sum[q]);
+                for (int q = 0; q < NQ; ++q) sum[q] = fma(r, (double)x[i][q], sum[q]);
             }
         }
     };
-    float s[NQ], e[NQ], W[NQ], ns = 0.f, ne = 0.f;
+    float s[NQ], e[NQ], ns = 0.f, ne = 0.f;
+    double W[NQ];                                                     // the window in front of the next token
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int c = lane + q * kWave;
@@ -161,15 +165,13 @@ __global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys
         ns = fmaf(s[q], s[q], ns);
     }
     ns = wave_sum(ns);
-    // a window that is not much longer than the chunk is cheaper to add up for every token
-    const bool slide = window > kChunk;
-    if (slide) add_rows(max(0, i0 - window), i0, W);
+    add_rows(max(0, i0 - window), i0, W);
     int blk = -1;
     float as = 0.f, ae = 0.f, ac = 0.f;                               // lane t: the anomalies of token i0 + t
     for (int i = i0; i < i1; i += US) {
         float x[US][NQ], y[US][NQ];                                   // rows that enter and that leave the window
         load_rows<T, NQ, US>(unit, d, lane, i, 1, i1, x);
-        if (slide) load_rows<T, NQ, US>(unit, d, lane, i - window, 1, i1, y);
+        load_rows<T, NQ, US>(unit, d, lane, i - window, 1, i1, y);
 #pragma unroll
         for (int j = 0; j < US; ++j) {
             const int tok = i + j;
@@ -187,21 +189,16 @@ __global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys
             }
             const float rn = rn_unit[tok];
             float kk = 0.f, ds = 0.f, de = 0.f, dc = 0.f, nc = 0.f;
-            if (slide) {
-                const float ry = tok >= window ? rn_unit[tok - window] : 0.f;
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) W[q] = fmaf(rn, x[j][q], fmaf(-ry, y[j][q], W[q]));
-            } else {
-                add_rows(max(0, tok - window + 1), tok + 1, W);
-            }
+            const float ry = tok >= window ? rn_unit[tok - window] : 0.f;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                const float kh = rn * x[j][q];
+                W[q] = fma((double)rn, (double)x[j][q], fma(-(double)ry, (double)y[j][q], W[q]));
+                const float kh = rn * x[j][q], wq = (float)W[q];
                 kk = fmaf(kh, kh, kk);
                 ds = fmaf(kh, s[q], ds);
                 de = fmaf(kh, e[q], de);
-                dc = fmaf(kh, W[q], dc);
-                nc = fmaf(W[q], W[q], nc);
+                dc = fmaf(kh, wq, dc);
+                nc = fmaf(wq, wq, nc);
             }
             kk = wave_sum(kk); ds = wave_sum(ds); de = wave_sum(de); dc = wave_sum(dc); nc = wave_sum(nc);
             const float nk = fmaxf(sqrtf(kk), kEps);

@@ -231,6 +231,33 @@ def test_unit_sum_at_the_most_tokens_of_a_unit(N, d, dtype):
     assert (a + 1.0).abs().max().item() < 2e-6
 
 
+@pytest.mark.parametrize("window", [1, 8, 17, 32, 64, 200])
+def test_generic_scan_slides_its_window_without_loss(window):
+    """The shape-generic scan slides its window sum over 16 tokens; keys that cancel inside the window (their common direction
+    turns around every 64 tokens) show what that leaves behind.  No further off 64 bits than a window added up afresh for
+    every token in 32 bits."""
+    N, d = 3000, 128
+    g = torch.Generator().manual_seed(3)
+    turn = ((torch.arange(N) // 64) % 2 * 2 - 1).float()[:, None]
+    K = 0.05 * torch.randn(N, d, generator=g) + torch.randn(d, generator=g) * turn
+    shape, p = nkv.Shape(1, 1, d, d, nkv.DTYPE_F32, [0, N]), nkv.params_default(window=window)
+    a = torch.empty(3, N, device=DEV)
+    ws = torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV)
+    nkv.score_raw(K.to(DEV), shape, p, a, ws)
+
+    def current(k):                                            # a_c in the arithmetic of k's type
+        kh = k / k.norm(dim=-1, keepdim=True)
+        w = torch.zeros_like(kh)
+        for back in range(min(window, N) - 1, -1, -1):
+            w[back:] += kh[:N - back]
+        return (-(kh * w).sum(-1) / (kh.norm(dim=-1) * w.norm(dim=-1))).double()
+
+    exact, afresh = current(K.double()), current(K)
+    rms = lambda x: float((x - exact).pow(2).mean().sqrt())
+    print(f"window {window}: rms {rms(a[2].cpu().double()):.2e}, afresh {rms(afresh):.2e}")
+    assert rms(a[2].cpu().double()) <= 1.1 * rms(afresh)
+
+
 @pytest.mark.parametrize("d,dtype,window,block", [(8, "fp32", 1, 128), (128, "fp32", 64, 128), (136, "bf16", 16, 128),
                                                   (256, "fp16", 17, 300), (80, "fp8", 100, 7), (1024, "fp32", 30, 5)])
 def test_generic_scan_windows_and_blocks(d, dtype, window, block):
