@@ -304,8 +304,8 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         bool queue = false;                                           // many equal values, going by three of the slots
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const int b = bin_of(k, v[k][i * (EPT - 1) / 2]);
-            queue |= __popcll(__ballot(b == __builtin_amdgcn_readfirstlane(b))) > 16;
+            const int j = i * (EPT - 1) / 2, b = bin_of(k, v[k][j]);
+            queue |= __popcll(__ballot(b == __builtin_amdgcn_readfirstlane(b) && tid + j * kSelThreads < N)) > 16;
         }
         if (queue) {
 #pragma unroll
