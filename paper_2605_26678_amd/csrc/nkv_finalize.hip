@@ -445,7 +445,8 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
 
     // ---- 3: sums beyond the boundary bins, their entries, the surprise ----
     float pt[3] = {0.f, 0.f, 0.f}, pb[3] = {0.f, 0.f, 0.f};           // at most EPT terms of magnitude <= 1
-    float smin = INFINITY, smax = -INFINITY, ssum = 0.f;
+    float smin = INFINITY, smax = -INFINITY;
+    double ssum = 0.0;
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
         if (tid + j * kSelThreads < N) {
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
             const float s = surprise_std<ALL>(at, lc.scale_mask);
             smin = fminf(smin, s);
             smax = fmaxf(smax, s);
-            ssum += s;                                                // at most EPT terms of magnitude <= 0.5
+            ssum += (double)s;
         }
     }
 #pragma unroll
@@ -483,7 +484,7 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         if (lane == 0) { sums[2 * k][w] = t; sums[2 * k + 1][w] = b; }
     }
     {
-        const double t = wave_sum((double)ssum);
+        const double t = wave_sum(ssum);
         smin = wave_min(smin);
         smax = wave_max(smax);
         if (lane == 0) { sums[6][w] = t; sext[0][w] = smin; sext[1][w] = smax; }
