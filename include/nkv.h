@@ -77,7 +77,8 @@ enum {
                                       /* them come from the kernel that fills in missing ones (exercises it) */
     NKV_FLAG_BUDGET_PER_HEAD = 16u,   /* nkv_budget: the kernels that hold a whole head in one workgroup     */
                                       /* instead of the slice-wise ones                                      */
-    NKV_FLAG_STATS_PER_HEAD = 32u,    /* nkv_score: the same choice for the per-head statistics              */
+    NKV_FLAG_STATS_PER_HEAD = 32u,    /* nkv_score: the same choice for the per-head statistics (calls whose */
+                                      /* prompts are all of up to 16384 tokens always take those kernels)   */
     NKV_FLAG_SELECT_PER_HEAD = 64u,   /* nkv_select_compact: the same choice for the top-B_h selection       */
     NKV_FLAG_VECTOR_SCAN = 128u,      /* streaming kernels: the vector-unit formulation of the fused pass    */
                                       /* also for keys of head dim 128, where the matrix-core one is the     */

@@ -2,10 +2,11 @@
 // (paper Section 2.3 min-max, Section 2.4 reliability gaps / blend / surprise / gate, sink pinning).
 //
 //   finalize_unit_kernel  calls whose prompts are all of up to 16384 tokens: one workgroup of 1024 threads per unit
-//                         (prompt, layer, head), values in registers
+//                         (prompt, layer, head), values in registers; up to 32768 tokens where the caller asks for
+//                         per-head kernels
 //   nkv_finalize_wide.hip calls with a longer prompt: slice by slice over the whole chip
-//   finalize_kernel       the same where the caller asks for per-head kernels: one workgroup of 1024 threads per
-//                         unit walks the head's values in memory seven times:
+//   finalize_kernel       calls with a still longer prompt where the caller asks for per-head kernels: one workgroup of
+//                         1024 threads per unit walks the head's values in memory seven times:
 //     pass 1      min / max of each scale
 //     pass 2..5   byte-wise radix select (most significant digit first) of the m_p-th largest and the
 //                 m_p-th smallest value of each scale, six selects at once in LDS histograms
@@ -209,7 +210,8 @@ __device__ __forceinline__ int unit_bin(float x, float lo, float scale) { return
 
 // grid: units.  EPT: values a thread holds per scale; units of prompts of another length class are passed over, so that a
 // ragged batch takes one launch per class it holds, not one per run of prompts (4 layers x 32 heads x prompts of 1531,
-// 4099, 777 and 2050 tokens: 39 -> 28 us).
+// 4099, 777 and 2050 tokens: 39 -> 28 us).  32 values a thread (asked for by flag only) do not fit the registers and are read
+// from the caches every time.
 template <int EPT, bool ALL>
 __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_kernel(const float *__restrict__ a_raw, int L, int H,
                                                                                       PromptTab tab, LearnerConsts lc,
@@ -240,11 +242,17 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint32_t m = (uint32_t)min(tab.m_p[p], N);
 
-    float v[3][EPT];
+    constexpr bool kHeld = EPT <= 16;
+    constexpr int kUnroll = kHeld ? EPT : 4;
+    float v[3][kHeld ? EPT : 1];
+    auto load = [&](int k, int j) { return a[k * rows + min(tid + j * kSelThreads, N - 1)]; };
+    auto value = [&](int k, int j) { return kHeld ? v[k][kHeld ? j : 0] : load(k, j); };
+    if constexpr (kHeld) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) v[k][j] = a[k * rows + min(tid + j * kSelThreads, N - 1)];
+            for (int j = 0; j < EPT; ++j) v[k][j] = load(k, j);
+    }
     auto clear_buf = [&]() {
         const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
@@ -266,10 +274,11 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         float lo = INFINITY, hi = -INFINITY;                          // (what a thread holds past the unit repeats its last value)
-#pragma unroll
+#pragma unroll(kUnroll)
         for (int j = 0; j < EPT; ++j) {
-            lo = fminf(lo, v[k][j]);
-            hi = fmaxf(hi, v[k][j]);
+            const float x = value(k, j);
+            lo = fminf(lo, x);
+            hi = fmaxf(hi, x);
         }
         const uint32_t least = ord_key(wave_min(lo)), most = ord_key(wave_max(hi));
         if (lane == 0) {
@@ -304,17 +313,21 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         bool queue = false;                                           // many equal values, going by three of the slots
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const int j = i * (EPT - 1) / 2, b = bin_of(k, v[k][j]);
+            const int j = i * (EPT - 1) / 2, b = bin_of(k, value(k, j));
             queue |= __popcll(__ballot(b == __builtin_amdgcn_readfirstlane(b) && tid + j * kSelThreads < N)) > 16;
         }
         if (queue) {
-#pragma unroll
-            for (int j = 0; j < EPT; ++j)
-                if (tid + j * kSelThreads < N) count_bin(buf + k * kBins, bin_of(k, v[k][j]));
+#pragma unroll(kUnroll)
+            for (int j = 0; j < EPT; ++j) {
+                const float x = value(k, j);
+                if (tid + j * kSelThreads < N) count_bin(buf + k * kBins, bin_of(k, x));
+            }
         } else {
-#pragma unroll
-            for (int j = 0; j < EPT; ++j)
-                if (tid + j * kSelThreads < N) atomicAdd(&buf[k * kBins + bin_of(k, v[k][j])], 1u);
+#pragma unroll(kUnroll)
+            for (int j = 0; j < EPT; ++j) {
+                const float x = value(k, j);
+                if (tid + j * kSelThreads < N) atomicAdd(&buf[k * kBins + bin_of(k, x)], 1u);
+            }
         }
     }
     __syncthreads();
@@ -357,8 +370,9 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         return any;
     };
     if (any_crowded()) {
-        // f(list, its cut, a thread's keys, which of them are in the list's boundary bin).  16 values a thread are read again:
-        // the rare path then costs the common one no registers.
+        // f(list, its cut, up to 16 of a thread's keys, which of them are in the list's boundary bin).  From 16 values a thread
+        // on they are read again: the rare path then costs the common one no registers.
+        constexpr int kKeys = EPT < 16 ? EPT : 16;
         auto for_crowded = [&](auto f) {
 #pragma unroll(EPT < 16 ? 6 : 1)
             for (int i = 0; i < 6; ++i) {
@@ -366,26 +380,29 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
                 if (!crowded(q)) continue;
                 const int k = i >> 1;
                 const float lo = s_lo[k], scale = s_to_bin[k];
-                uint32_t key[EPT];
-                bool in[EPT];
-                float x[EPT];
+#pragma unroll 1
+                for (int j0 = 0; j0 < EPT; j0 += kKeys) {
+                    uint32_t key[kKeys];
+                    bool in[kKeys];
+                    float x[kKeys];
 #pragma unroll
-                for (int j = 0; j < EPT; ++j) {
-                    x[j] = EPT < 16 ? v[k][j] : a[k * rows + min(tid + j * kSelThreads, N - 1)];
-                    asm volatile("" : "+v"(x[j]));
-                }
+                    for (int j = 0; j < kKeys; ++j) {
+                        x[j] = EPT < 16 ? v[k][EPT < 16 ? j : 0] : load(k, j0 + j);
+                        asm volatile("" : "+v"(x[j]));
+                    }
 #pragma unroll
-                for (int j = 0; j < EPT; ++j) {
-                    key[j] = key_of(i, x[j]);
-                    in[j] = tid + j * kSelThreads < N && unit_bin(x[j], lo, scale) == q.bin;
+                    for (int j = 0; j < kKeys; ++j) {
+                        key[j] = key_of(i, x[j]);
+                        in[j] = tid + (j0 + j) * kSelThreads < N && unit_bin(x[j], lo, scale) == q.bin;
+                    }
+                    f(i, q, key, in);
                 }
-                f(i, q, key, in);
             }
         };
-        for_crowded([&](int i, const UnitCut &, const uint32_t (&key)[EPT], const bool (&in)[EPT]) {
+        for_crowded([&](int i, const UnitCut &, const uint32_t (&key)[kKeys], const bool (&in)[kKeys]) {
             uint32_t nlo = 0u, hi = 0u;
 #pragma unroll
-            for (int j = 0; j < EPT; ++j) {
+            for (int j = 0; j < kKeys; ++j) {
                 nlo = max(nlo, in[j] ? ~key[j] : 0u);
                 hi = max(hi, in[j] ? key[j] : 0u);
             }
@@ -407,10 +424,10 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         for (int round = 0; round < 4 && any_crowded(); ++round) {    // every round cuts an interval to a 1024th
             clear_buf();
             __syncthreads();
-            for_crowded([&](int i, const UnitCut &q, const uint32_t (&key)[EPT], const bool (&in)[EPT]) {
+            for_crowded([&](int i, const UnitCut &q, const uint32_t (&key)[kKeys], const bool (&in)[kKeys]) {
                 const int shift = shift_of(q);
 #pragma unroll
-                for (int j = 0; j < EPT; ++j)
+                for (int j = 0; j < kKeys; ++j)
                     if (in[j] && key[j] - q.lo <= q.hi - q.lo) count_bin(buf + i * kSub, (int)((key[j] - q.lo) >> shift));
             });
             __syncthreads();
@@ -431,10 +448,12 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         }
     }
     // (bins are cheaper worked out again than kept: the compiler would carry those of all values over from step 1)
+    if constexpr (kHeld) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) asm volatile("" : "+v"(v[k][j]));
+            for (int j = 0; j < EPT; ++j) asm volatile("" : "+v"(v[k][j]));
+    }
     UnitCut cut[6];                                                   // uniform
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
@@ -447,13 +466,14 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     float pt[3] = {0.f, 0.f, 0.f}, pb[3] = {0.f, 0.f, 0.f};           // at most EPT terms of magnitude <= 1
     float smin = INFINITY, smax = -INFINITY;
     double ssum = 0.0;
-#pragma unroll
+#pragma unroll(kUnroll)
     for (int j = 0; j < EPT; ++j) {
+        float raw[3] = {value(0, j), value(1, j), value(2, j)};
         if (tid + j * kSelThreads < N) {
-            float raw[3], at[3];
+            float at[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const float x = raw[k] = v[k][j];
+                const float x = raw[k];
                 const int b = bin_of(k, x);
                 pt[k] += b > cut[2 * k].bin ? x : 0.f;
                 pb[k] += b < cut[2 * k + 1].bin ? x : 0.f;
@@ -535,11 +555,11 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     // ---- 5: blend, gate, route, pin ----
     st = hs;
     float *out = scores + base;
-#pragma unroll
+#pragma unroll(kUnroll)
     for (int j = 0; j < EPT; ++j) {
         const int i = tid + j * kSelThreads;
+        const float raw[3] = {value(0, j), value(1, j), value(2, j)};
         if (i < N) {
-            const float raw[3] = {v[0][j], v[1][j], v[2][j]};
             float at[3];
             normalised(raw, st, at);
             out[i] = i < lc.n_sink ? NKV_PIN : routed_score<ALL>(at, st, lc);
@@ -556,10 +576,13 @@ hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &ta
     int nmax = 0;
     for (int p = 0; p < tab.n; ++p) nmax = max(nmax, tab.tok_off[p + 1] - tab.tok_off[p]);
     const unsigned units = (unsigned)(tab.n * L * H);
-    const int per_unit = kUnitTokens;                                 // prompts of up to this length: one launch, a workgroup per unit
+    const bool per_head = wide_ws == nullptr || per_head_route;
     prof.begin(NKV_KERNEL_FINALIZE, st);
-    if (nmax > per_unit) {
-        if (wide_ws == nullptr || per_head_route) {
+    // By default one launch with a workgroup per unit for prompts of up to kUnitTokens and slices for longer ones; asked for
+    // whole heads, a workgroup per unit as far as it goes (a score call of 8 heads x 32768 tokens: 89 us, 406 with
+    // finalize_kernel).
+    if (nmax > (per_head ? 2 * kUnitTokens : kUnitTokens)) {
+        if (per_head) {
             finalize_kernel<<<units, kThreads, 0, st>>>(a_raw, L, H, tab, lc, scores);
         } else {
             hipError_t e = launch_stats_wide(a_raw, L, H, tab, lc.scale_mask, stats, wide_ws, st);
@@ -568,7 +591,7 @@ hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &ta
             if (e != hipSuccess) return e;
         }
     } else {
-        bool present[17] = {};
+        bool present[33] = {};
         for (int p = 0; p < tab.n; ++p) present[length_class(tab.tok_off[p + 1] - tab.tok_off[p])] = true;
 #define NKV_UNIT(EPT)                                                                                                         \
     if (present[EPT])                                                                                                         \
@@ -577,6 +600,7 @@ hipError_t launch_finalize(const float *a_raw, int L, int H, const PromptTab &ta
         NKV_UNIT(4);
         NKV_UNIT(8);
         NKV_UNIT(16);
+        NKV_UNIT(32);
 #undef NKV_UNIT
     }
     prof.end(NKV_KERNEL_FINALIZE, st);

@@ -429,6 +429,21 @@ def _learner64(a, p):
     return out, 1.0 + 0.5 * p.kappa / max(srange, flat) if srange >= 0.5 * flat else 1.0
 
 
+@pytest.mark.parametrize("longest,flags", [(20000, 0), (20000, nkv.FLAG_STATS_PER_HEAD), (32768, nkv.FLAG_STATS_PER_HEAD),
+                                           (32769, nkv.FLAG_STATS_PER_HEAD)])
+def test_statistics_routes_take_prompts_of_every_length(longest, flags):
+    """The longest prompt of a call chooses the statistics' kernels for all of its prompts: slice-wise, a workgroup per unit
+    with 4 to 32 values a thread, or the one that walks memory; short and ragged prompts beside the longest one, a head of
+    one repeated key among them, against the oracle."""
+    w = nkv_inputs.small_workload(f"stat_lengths_{longest}", 1, 2, 64, [longest, 300, 1, 5000, 12001, 4096], n_out=0)
+    K, V = _kv(w)
+    p = nkv.params_default(flags=flags)
+    compare_end_to_end(w, K, V, 0.75, params=p, label=f"{longest} flags={flags}")
+    compare_end_to_end(w, K, V, 0.75, params=nkv.params_default(flags=flags, scale_mask=6), label=f"{longest} two scales flags={flags}")
+    K[:, 1] = K[:, 1, :1]
+    compare_end_to_end(w, K, V, 0.75, params=p, label=f"{longest} one key flags={flags}")
+
+
 @pytest.mark.parametrize("N", [1000, 2049, 4096, 8192, 16384])
 @pytest.mark.parametrize("kind", ["close", "close but a few", "every other the same", "half zero", "one from 100 on", "two halves"])
 def test_statistics_of_crowded_anomalies(kind, N):
