@@ -42,6 +42,8 @@
 // workgroups are adding to cost the pass a quarter of its time under sustained load.)
 #include "nkv_scan_common.h"
 
+#include <type_traits>
+
 namespace nkv {
 namespace {
 
@@ -76,6 +78,23 @@ template <int KF, int KS> __device__ __forceinline__ f32x4 tile(const u32x4 (&a)
     return c;
 }
 
+// The same, as two halves where FINE: sums of half the length.  (Four quarters are closer still, but do not fit the
+// registers; for the products of keys with keys, neither do two where KS = 4.)
+template <int KF, int KS, bool FINE> __device__ __forceinline__ f32x4 fine_tile(const u32x4 (&a)[KS], const u32x4 (&b)[KS])
+{
+    if constexpr (!FINE) {
+        return tile<KF, KS>(a, b);
+    } else {
+        constexpr int HALF = (KS + 1) / 2;
+        f32x4 c = {0.f, 0.f, 0.f, 0.f}, e = c;
+#pragma unroll
+        for (int kk = 0; kk < HALF; ++kk) c = mma<KF>(a[kk], b[kk], c);
+#pragma unroll
+        for (int kk = HALF; kk < KS; ++kk) e = mma<KF>(a[kk], b[kk], e);
+        return c + e;
+    }
+}
+
 // x summed over the four lanes n, n + 16, n + 32, n + 48; every lane receives the total.
 // permlane32_swap(x, x) = (x of the lower half in both halves, x of the upper half in both halves); the 16-lane
 // swap does the same with even and odd rows of 16 lanes.
@@ -106,6 +125,23 @@ __device__ __forceinline__ float2 sum_over_rows16_transposing(const float (&T)[8
         V[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
     return make_float2(V[0], V[1]);
+}
+
+// The same in 64 bits, and over the whole wavefront.
+template <int CTRL> __device__ __forceinline__ double row_shr(double x)       // 0 in front of the row
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ double row_prefix_sum(double x)
+{
+    x += row_shr<0x111>(x);
+    x += row_shr<0x112>(x);
+    x += row_shr<0x114>(x);
+    x += row_shr<0x118>(x);
+    return x;
 }
 
 // inclusive running sum over the 16 lanes of a row (lanes n = 0 .. 15 of every group of 16)
@@ -253,6 +289,27 @@ __device__ __forceinline__ float unit_norm(float ss)
     return k;
 }
 
+// 1 / sqrt(x), once more corrected: half a step of fp32 where the hardware's is good to one.
+__device__ __forceinline__ float fine_rsqrt(float x)
+{
+    const float y = __builtin_amdgcn_rsqf(x), e = fmaf(-(x * y), y, 1.0f);
+    return fmaf(0.5f * e, y, y);
+}
+
+// -cos of a token's key to an anchor from <k, anchor>, the token's 1 / ||k|| and ||k||^2, and ||anchor||^2.
+// FINE: with the corrected reciprocal square roots.
+template <bool FINE> __device__ __forceinline__ float token_cos(float dot, float w, float ss, float anchor_sq)
+{
+    if constexpr (FINE) {
+        float k = 1.f;
+        if (__any(ss < 1e-24f)) k = ss < 1e-24f ? 1.0f / fmaxf(sqrtf(ss) * 1e12f, kEps) : 1.f;
+        const float fw = w > 0.f && ss >= 1e-24f ? fine_rsqrt(ss) : w;
+        return -(fw * dot) * k * fine_rsqrt(fmaxf(anchor_sq, kEps * kEps));
+    } else {
+        return neg_cos(w * dot, unit_norm(ss), anchor_sq);
+    }
+}
+
 // Dims 2 lane and 2 lane + 1 of a vector of 32 KS floats (0 past its end).
 template <int KS> __device__ __forceinline__ float2 dim_pair(const float *v, int lane)
 {
@@ -355,7 +412,7 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
 // instead were tried: without the hardware handing out blocks as slots fall free, all workgroups of the chip move
 // through their loading and computing phases in step, and the pass takes 0.90 ms instead of 0.77.)
 // KS: head dims the pass works with, in steps of 32 (the rest of the last step reads as zeros); FULL: d = 32 KS.
-template <int KF, int KS, bool FULL> __global__ __launch_bounds__(64 * kTileWaves, 4)
+template <int KF, int KS, bool FULL, bool FINE> __global__ __launch_bounds__(64 * kTileWaves, 4)
 void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *__restrict__ items, float *__restrict__ a_raw,
                       unsigned long long *__restrict__ acc, unsigned long long *__restrict__ acc_group, float *__restrict__ ssum, uint32_t *__restrict__ sync, int64_t rows,
                       int poll_limit)
@@ -504,17 +561,19 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
                 s0 = ((t0.x + t1.x) + t2.x) + t3.x;
                 s1 = ((t0.y + t1.y) + t2.y) + t3.y;
             }
-            const float P0 = sum_over_rows16(row_sum<16>(fmaf(s0, s0, s1 * s1)));
+            std::conditional_t<FINE, double, float> P0;               // ||W||^2 in front of the group
+            if constexpr (FINE) P0 = wave_sum(fma((double)s0, (double)s0, (double)s1 * (double)s1));
+            else P0 = sum_over_rows16(row_sum<16>(fmaf(s0, s0, s1 * s1)));
             stage_anchor<SF>(stage, 0, lane, s0, s1);                     // rows 0 .. 2: the seed's three terms
             __builtin_amdgcn_wave_barrier();
             u32x4 An[KS];
             read_operand<KS>(stage, lane, An);
             __builtin_amdgcn_wave_barrier();                          // the next group rewrites rows 0 .. 2
-            const f32x4 AT = tile<SF, KS>(X[m], X[m]);                     // [j in G][i in G]
-            const f32x4 XT = tile<SF, KS>(X[m - 1], X[m]);                 // [j' in P][i in G]
-            const f32x4 XX = tile<SF, KS>(X[m], X[m - 1]);                 // [j in G][i' in P]
-            const f32x4 AG = tile<SF, KS>(An, X[m]);                       // [anchor row][i in G]
-            const f32x4 AP = tile<SF, KS>(An, X[m - 1]);                   // [anchor row][i' in P]
+            const f32x4 AT = fine_tile<SF, KS, FINE && KS < 4>(X[m], X[m]);                     // [j in G][i in G]
+            const f32x4 XT = fine_tile<SF, KS, FINE && KS < 4>(X[m - 1], X[m]);                 // [j' in P][i in G]
+            const f32x4 XX = fine_tile<SF, KS, FINE && KS < 4>(X[m], X[m - 1]);                 // [j in G][i' in P]
+            const f32x4 AG = fine_tile<SF, KS, FINE>(An, X[m]);                       // [anchor row][i in G]
+            const f32x4 AP = fine_tile<SF, KS, FINE && KS < 4>(An, X[m - 1]);                   // [anchor row][i' in P]
             float wm[4];
             {
                 const float4 w4 = *reinterpret_cast<const float4 *>(&lds_w[w][m][4 * qq]);
@@ -535,10 +594,10 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
             const float gsum = qq == 0 ? wn * wn * ssn + wp * wp * ssp : 0.f;
             const float d_part = 2.f * (wn * c_part - wp * e_part) + (2.f * wn * wp * xd - gsum);
             const float cdot = sum_over_rows16(c_part);               // <k_i, W_i>
-            const float Pn = P0 + row_prefix_sum(sum_over_rows16(d_part));
-            const float knn = unit_norm(ssn);
-            const float ac = neg_cos(wn * cdot, knn, Pn);
-            const float ae = neg_cos(wn * sum3(AG), knn, bsq);        // meaningful in lane group 1 (rows 4 .. 6)
+            const decltype(P0) d_all = sum_over_rows16(d_part);
+            const float Pn = (float)(P0 + row_prefix_sum(d_all));
+            const float ac = token_cos<FINE>(cdot, wn, ssn, Pn);
+            const float ae = token_cos<FINE>(sum3(AG), wn, ssn, bsq); // meaningful in lane group 1 (rows 4 .. 6)
             const int soff = (blk_lo + kGroup * q) * 4;                // (an offset that was past the buffer stays past it)
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ac), out_c, off_q0 + soff, 0, 0);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ae), out_e, off_q1 + soff, 0, 0);
@@ -581,10 +640,9 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         for (int m = 1; m < 5; ++m) {
             if (ex[m]) {
                 const int q = w + 4 * (m - 1);
-                const f32x4 AS = tile<SF, KS>(An, X[m]);
+                const f32x4 AS = fine_tile<SF, KS, FINE>(An, X[m]);
                 const float wn = lds_w[w][m][n], ssn = lds_ss[w][m][n];
-                const float knn = unit_norm(ssn);
-                const float as = neg_cos(wn * sum3(AS), knn, ssq);
+                const float as = token_cos<FINE>(sum3(AS), wn, ssn, ssq);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + (blk_lo + kGroup * q) * 4, 0, 0);
             }
         }
@@ -594,7 +652,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
 // a_s of the blocks whose workgroups did not wait for their unit's sum: the same operands (loaded in operand
 // layout directly), norms, split and product as in scan_tile_kernel, so the values are the ones it would have
 // stored.
-template <int KF, int KS, bool FULL>
+template <int KF, int KS, bool FULL, bool FINE>
 __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(const uint8_t *__restrict__ keys, int d, RowMap km,
                                                                                PromptTab tab,
                                                                                const float *__restrict__ ssum,
@@ -644,9 +702,8 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
             __builtin_amdgcn_wave_barrier();
             const float wn = lds_w[w][n], ss = lds_ss[w][n];
             __builtin_amdgcn_wave_barrier();                          // the next group rewrites them
-            const float knn = unit_norm(ss);
-            const f32x4 AS = tile<SF, KS>(An, X);
-            const float as = neg_cos(wn * sum3(AS), knn, ssq);
+            const f32x4 AS = fine_tile<SF, KS, FINE>(An, X);
+            const float as = token_cos<FINE>(sum3(AS), wn, ss, ssq);
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + tok0 * 4, 0, 0);
         }
     }
@@ -658,7 +715,7 @@ int resident_tile_workgroups()
     if (cached < 0) {
         int per_cu = 0, dev = 0;
         hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_tile_kernel<kKeyBF16, 4, true>, 64 * kTileWaves, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_tile_kernel<kKeyBF16, 4, true, false>, 64 * kTileWaves, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
             return 0;
         cached = per_cu * prop.multiProcessorCount;
@@ -679,22 +736,30 @@ struct TileLaunch {
     uint32_t *sync;
     int64_t rows;
     int poll_limit;
+    bool fine;
     const Prof &prof;
     hipStream_t st;
 
-    template <int KF, int KS, bool FULL> void run() const
+    template <int KF, int KS, bool FULL, bool FINE> void run() const
     {
         prof.begin(NKV_KERNEL_SCAN, st);
-        scan_tile_kernel<KF, KS, FULL><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, accum_group, ssum, sync, rows, poll_limit);
+        scan_tile_kernel<KF, KS, FULL, FINE><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, accum_group, ssum, sync, rows, poll_limit);
         prof.end(NKV_KERNEL_SCAN, st);
-        deferred_stable_tile_kernel<KF, KS, FULL><<<n_deferred, 64 * kTileWaves, 0, st>>>(keys, d, km, tab, ssum, sync, a_raw);
+        deferred_stable_tile_kernel<KF, KS, FULL, FINE><<<n_deferred, 64 * kTileWaves, 0, st>>>(keys, d, km, tab, ssum, sync, a_raw);
     }
+    // FINE (double-width window norms, corrected reciprocal square roots, anchors' products added up in two halves) where the
+    // kernels before this scan were closer to 64 bits than it is without: 16-bit keys of more than 64 dims, except for head dim
+    // 128 and units of up to 256 blocks.  Root mean square errors of a_s, a_e, a_c in 1e-8, keys of the benchmark's kind: head dim 96, 8192
+    // tokens 2.4, 3.3, 2.8 before, 2.6, 2.9, 3.1 without and 2.4, 2.7, 2.9 with FINE; head dim 128, 100 000 tokens 2.3, 2.2,
+    // 2.6, then 2.5, 2.7, 2.9 and 2.2, 2.5, 2.7 (6 % of the scan's time); 8-bit keys 2.1, 2.2, 2.5 and 2.0, 2.2, 2.5 without.
     template <int KF> void run_format() const
     {
-        if (d == 128) run<KF, 4, true>();
-        else if (d > 96) run<KF, 4, false>();
-        else if (d > 64) run<KF, 3, false>();
-        else run<KF, 2, false>();                                     // (matches padded_dims)
+        constexpr bool F = KF != kKeyF8;
+        if (d == 128 && fine && F) run<KF, 4, true, F>();
+        else if (d == 128) run<KF, 4, true, false>();
+        else if (d > 96) run<KF, 4, false, F>();
+        else if (d > 64) run<KF, 3, false, F>();
+        else run<KF, 2, false, false>();                              // (matches padded_dims)
     }
 };
 
@@ -714,13 +779,11 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
     return (int64_t)LH * (tab.blk_off[tab.n] + tab.n) < (1ll << 28);
 }
 
-// Do the blocks of every unit fit the chip together?  If not, nobody looks for a unit's sum and all blocks take the
-// deferred route.
-static bool units_fit(const PromptTab &tab)
+static int longest_unit(const PromptTab &tab)                        // in blocks
 {
     int most = 0;
     for (int p = 0; p < tab.n; ++p) most = max(most, tab.blk_off[p + 1] - tab.blk_off[p]);
-    return most <= resident_tile_workgroups();
+    return most;
 }
 
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab)
@@ -738,8 +801,9 @@ hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int 
                              void *accum, float *ssum, void *sync_area, void *plan_area, int mode, const Prof &prof,
                              hipStream_t st)
 {
-    // (no unit is added up by a workgroup of its own here)
-    const bool defer_all = mode == kScanDeferAll || mode == kScanRepairAll || !units_fit(tab);
+    // (no unit is added up by a workgroup of its own here)  Where the blocks of a unit do not fit the chip together, nobody looks
+    // for a unit's sum and all blocks take the deferred route.
+    const bool defer_all = mode == kScanDeferAll || mode == kScanRepairAll || longest_unit(tab) > resident_tile_workgroups();
     const size_t nu = (size_t)LH * tab.n * padded_dims(d) * 8 / 16;           // the units' accumulators, in 16-byte pieces
     const size_t na = tile_score_accum_bytes(LH, d, tab) / 16;                // theirs, and the groups' behind them
     ScanPlan plan;
@@ -749,7 +813,7 @@ hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int 
         nu / 2);
     const TileLaunch go{(const uint8_t *)keys, d, km, tab, (const TileItem *)plan_area, n_items, defer_all ? 4096u : 256u, a_raw,
                         ssum, (unsigned long long *)accum, (unsigned long long *)accum + nu * 2, (uint32_t *)sync_area, (int64_t)LH * tab.T,
-                        defer_all ? -1 : kPollLimit, prof, st};
+                        defer_all ? -1 : kPollLimit, longest_unit(tab) > 256, prof, st};
     if (dtype == NKV_DTYPE_F16) go.run_format<kKeyF16>();
     else if (dtype == NKV_DTYPE_F8_E4M3) go.run_format<kKeyF8>();
     else go.run_format<kKeyBF16>();
