@@ -193,11 +193,13 @@ int run_raw(const void *keys, const nkv_shape *s, const nkv_params *p, const Pro
     const int mode = (p->flags & NKV_FLAG_TWO_PASS_STABLE)  ? kScanTwoPass
                      : (p->flags & NKV_FLAG_NO_UNIT_SUMS)  ? kScanRepairAll
                      : (p->flags & NKV_FLAG_DEFER_STABLE)  ? kScanDeferAll : kScanFused;
-    if (!(p->flags & NKV_FLAG_GENERIC_KERNELS) && !(p->flags & NKV_FLAG_VECTOR_SCAN) && mode != kScanTwoPass &&
-        tile_score_supported(s->dtype, s->d, p->window, tab, LH))
+    const bool tile = !(p->flags & (NKV_FLAG_GENERIC_KERNELS | NKV_FLAG_VECTOR_SCAN)) && mode != kScanTwoPass &&
+                      tile_score_supported(s->dtype, s->d, p->window, tab, LH);
+    const TinyBlocks tiny = tile && mode == kScanFused ? tile_tiny_blocks(s->dtype, s->d, tab, LH) : kTinyNone;
+    if (tile && tiny == kTinyNone)
         e = launch_score_tile(keys, km, s->dtype, LH, s->d, tab, a_raw, ws + lay.ssum, (float *)(ws + lay.bsum), ws + lay.sync, ws + lay.plan,
                               mode, prof, st);
-    else if (!(p->flags & NKV_FLAG_GENERIC_KERNELS) && fast_score_supported(s->dtype, s->d, p->window, tab))
+    else if (!(p->flags & NKV_FLAG_GENERIC_KERNELS) && tiny != kTinyGeneric && fast_score_supported(s->dtype, s->d, p->window, tab))
         e = launch_score_fast(keys, km, s->dtype, LH, s->d, tab, a_raw, (float *)(ws + lay.bsum), (float *)(ws + lay.ssum),
                               ws + lay.sync, mode, prof, st);
     else {

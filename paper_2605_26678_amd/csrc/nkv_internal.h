@@ -84,6 +84,9 @@ hipError_t launch_score_fast(const void *keys, const RowMap &km, int dtype, int 
 // ---- scoring, matrix-core formulation of the fused streaming pass (16-bit or 8-bit keys, d <= 128, window 64, block size <= 256) ----
 inline int padded_dims(int d) { return d <= 64 ? 64 : (d + 31) / 32 * 32; }   // dims its sums are kept with: 32 KS
 bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, int LH);
+// which kernels are quicker for what tile_score_supported takes
+enum TinyBlocks { kTinyNone, kTinyVector, kTinyGeneric };
+TinyBlocks tile_tiny_blocks(int dtype, int d, const PromptTab &tab, int LH);
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab);    // the list of items the pass works through
 size_t tile_score_accum_bytes(int LH, int d, const PromptTab &tab);
 hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int LH, int d, const PromptTab &tab, float *a_raw,

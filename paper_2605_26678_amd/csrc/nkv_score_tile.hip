@@ -765,6 +765,13 @@ struct TileLaunch {
 
 }  // namespace
 
+static int longest_unit(const PromptTab &tab)                        // in blocks
+{
+    int most = 0;
+    for (int p = 0; p < tab.n; ++p) most = max(most, tab.blk_off[p + 1] - tab.blk_off[p]);
+    return most;
+}
+
 bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, int LH)
 {
     // (head dim 64 stays with the vector formulation: half of the lanes of a row would hold nothing here)
@@ -779,11 +786,19 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
     return (int64_t)LH * (tab.blk_off[tab.n] + tab.n) < (1ll << 28);
 }
 
-static int longest_unit(const PromptTab &tab)                        // in blocks
+// A workgroup of this scan takes a block and loads 64 tokens in front of it whatever the block's length.  Blocks of fewer
+// than 8 tokens, more of a unit than fit the chip together (so that every one is deferred as well), are done sooner by
+// other kernels.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / vector scan / shape-generic: bf16, head
+// dim 128, one layer 466 / 1204 / 423 us, four layers 1722 / 1800 / 1128; head dim 40 457 / - / 291 and 1683 / - / 883; 8-bit,
+// head dim 128 470 / 1135 / 643 and 1727 / 1558 / 1988 (in blocks of one 6746 / 8167 / 6226).  In blocks of 8: bf16 258 / 639 / 288 and 891 / 946 / 785.
+TinyBlocks tile_tiny_blocks(int dtype, int d, const PromptTab &tab, int LH)
 {
-    int most = 0;
-    for (int p = 0; p < tab.n; ++p) most = max(most, tab.blk_off[p + 1] - tab.blk_off[p]);
-    return most;
+    int shortest = 8;
+    for (int p = 0; p < tab.n; ++p)
+        if (tab.blk_off[p + 1] - tab.blk_off[p] > resident_tile_workgroups()) shortest = min(shortest, (int)tab.b[p]);
+    if (shortest == 8) return kTinyNone;
+    if (dtype != NKV_DTYPE_F8_E4M3) return kTinyGeneric;
+    return shortest > 1 && d == 128 && (int64_t)LH * tab.blk_off[tab.n] > 65536 ? kTinyVector : kTinyNone;
 }
 
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab)
