@@ -8,10 +8,10 @@
 // The work is one read of every retained K and V row, so it is bound by HBM.  Units have different lengths
 // (head-wise budgets), so they are cut into chunks of 256 rows and one workgroup handles one chunk for all G
 // query heads at once (K and V are read once, not G times):
-//   decode_plan_kernel    : chunk_off[u] = chunks before unit u (exclusive scan of ceil(len_u / 256)); with few chunks
-//                           and units every workgroup of the other two kernels works its place out itself (SELF: one
-//                           launch fewer, 17 -> 13 us for 64 units of 204 to 1638 rows; with thousands of chunks it costs
-//                           more than it saves)
+//   decode_plan_kernel    : chunk_off[u] = chunks before unit u (exclusive scan of ceil(len_u / 256)); where the chunks are
+//                           of 64 rows (few chunks and units) every workgroup of the next kernel works its place out
+//                           itself and the first one leaves the offsets for the last kernel (SELF: one launch fewer,
+//                           17 -> 13 us for 64 units of 204 to 1638 rows; with thousands of chunks it costs more than it saves)
 //   decode_chunk_kernel   : per chunk, running-maximum softmax in base 2: (m, l, o[0..D)) per query head
 //   decode_combine_kernel : per (unit, query head) merges the chunks' partial results
 // Lane layout in decode_chunk_kernel as in the scoring kernel: a row is spread over D/8 lanes (16 bytes each),
@@ -23,12 +23,17 @@
 // unit and query head, no scratch).
 #include "nkv_device.h"
 
+#include <algorithm>
+
 namespace nkv {
 namespace {
 
 // Rows per workgroup: 256, or 64 where a call has too few rows to fill the chip with workgroups of 256 (a wavefront then
 // has one batch of rows instead of four in turn).
 constexpr int kChunk = 256, kSmallChunk = 64;
+// Chunks per unit from which 512 threads combine them instead of one per dimension (64 units of G = 3, head dim 64: 7 chunks a
+// unit 8.0 -> 7.1 us; 256 units of G = 8, 300 rows in two chunks 21.4 us with 512, 19.4 with 64).
+constexpr int kManyChunks = 4;
 constexpr int kDecThreads = 256;
 constexpr float kNone = -1.0e30f;        // running maximum before any row was seen
 constexpr float kLn2 = 0.6931471805599453f;
@@ -162,7 +167,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
                                                                    const uint16_t *__restrict__ pk,
                                                                    const uint16_t *__restrict__ pv,
                                                                    const int64_t *__restrict__ head_off,
-                                                                   const int32_t *chunk_off, int n_units,
+                                                                   int32_t *planned, int n_units,
                                                                    int64_t rows, float scale_log2,
                                                                    float *__restrict__ part)
 {
@@ -173,9 +178,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
     __shared__ float lds_o[NW * RPW][G][D];
     const int chunk = blockIdx.x;
     __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
+    const int32_t *chunk_off = planned;
     if constexpr (SELF) {
         plan_here<kDecThreads, CH>(head_off, n_units, rows, lds_off);
         chunk_off = lds_off;
+        if (chunk == 0)                                               // for the combining kernel
+            for (int u = threadIdx.x; u <= n_units; u += kDecThreads) planned[u] = lds_off[u];
     }
     if (chunk >= chunk_off[n_units]) return;
     const int u = wave_search(chunk_off, n_units, chunk), ci = chunk - chunk_off[u];
@@ -285,27 +293,19 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
     }
 }
 
-// grid: n_units * G workgroups of 512 threads: 512 / D slices of the unit's chunks, added up in the slices' order.
-constexpr int kCombineThreads = 512;
-template <int D, bool SELF, int CH>
-__global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(const float *__restrict__ part,
-                                                                         const int64_t *__restrict__ head_off, int n_units, int64_t rows,
-                                                                         const int32_t *chunk_off, int G, float *__restrict__ out,
-                                                                         float *__restrict__ lse)
+// grid: n_units * G workgroups of TH threads: TH / D slices of the unit's chunks, added up in the slices' order.
+template <int D, int TH>
+__global__ __launch_bounds__(TH) void decode_combine_kernel(const float *__restrict__ part, const int32_t *__restrict__ chunk_off, int G,
+                                                            float *__restrict__ out, float *__restrict__ lse)
 {
-    constexpr int NS = kCombineThreads / D, NW = kCombineThreads / 64, U = 4;
+    constexpr int NS = TH / D, NW = TH / 64, U = 4;
     __shared__ float red[NW];
     __shared__ float lds_l[NS], lds_o[NS][D];
-    __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
-    if constexpr (SELF) {
-        plan_here<kCombineThreads, CH>(head_off, n_units, rows, lds_off);
-        chunk_off = lds_off;
-    }
     const int u = blockIdx.x / G, g = blockIdx.x - u * G, tid = threadIdx.x, e = tid % D, sl = tid / D;
     const int c0 = chunk_off[u], c1 = chunk_off[u + 1];
     // the largest running maximum: chunks spread over the threads, then one reduction
     float mm = kNone;
-    for (int ch = c0 + tid; ch < c1; ch += kCombineThreads) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
+    for (int ch = c0 + tid; ch < c1; ch += TH) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
     mm = wave_max(mm);
     if ((tid & 63) == 0) red[tid >> 6] = mm;
     __syncthreads();
@@ -398,9 +398,15 @@ __global__ __launch_bounds__(kDecThreads) void decode_generic_kernel(const T *__
 
 int64_t max_chunks(int64_t n_units, int64_t rows, int chunk) { return rows / chunk + n_units; }
 
-// Few units and at most two workgroups of 256 rows per compute unit: chunks of 64 rows, if the caller's scratch holds
-// their partial results (it need not, see decode_ws_bytes).
-bool decode_small(int64_t n_units, int64_t rows) { return n_units <= kSelfUnits && max_chunks(n_units, rows, kChunk) <= 512; }
+// Chunks of 64 rows where there are few units, at most two chunks of 256 rows per compute unit, and no more of 64 rows than
+// the chip holds at once (what a chunk merges, 16 or 32 partial results of G heads, takes 8 KB of LDS a head), if the caller's
+// scratch holds their partial results (it need not, see decode_ws_bytes).  128 units of G = 8, head dim 128, 700 rows: 34 us with
+// 1528 chunks of 64 rows, 27 with 478 of 256; 64 units: 19.7 with 704 of 64, 20.4 with 256 rows; 64 units of 300 rows 13 against 20.
+int64_t small_chunks_limit(int G) { return 256 * std::min(8, 160 * 1024 / (8448 * G + 1032)); }
+bool decode_small(int64_t n_units, int64_t rows, int G)
+{
+    return n_units <= kSelfUnits && max_chunks(n_units, rows, kChunk) <= 512 && max_chunks(n_units, rows, kSmallChunk) <= small_chunks_limit(G);
+}
 
 size_t part_offset(int64_t n_units) { return ((size_t)(n_units + 1) * 4 + 255) / 256 * 256; }
 size_t ws_for(int64_t chunks, int64_t n_units, int G, int d) { return part_offset(n_units) + (size_t)chunks * G * (d + 2) * 4; }
@@ -412,7 +418,7 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
 {
     int32_t *chunk_off = (int32_t *)ws;
     float *part = (float *)((char *)ws + part_offset(n_units));
-    const bool small = decode_small(n_units, rows) && ws_bytes >= ws_for(max_chunks(n_units, rows, kSmallChunk), n_units, G, D);
+    const bool small = decode_small(n_units, rows, G) && ws_bytes >= ws_for(max_chunks(n_units, rows, kSmallChunk), n_units, G, D);
     const unsigned groups = (unsigned)max_chunks(n_units, rows, small ? kSmallChunk : kChunk);
     if (!small) decode_plan_kernel<<<1, 1024, 0, st>>>(head_off, n_units, rows, chunk_off);
     prof.begin(NKV_KERNEL_DECODE, st);
@@ -428,8 +434,10 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     }
 #undef NKV_DEC
     prof.end(NKV_KERNEL_DECODE, st);
-    (small ? decode_combine_kernel<D, true, kSmallChunk> : decode_combine_kernel<D, false, kChunk>)<<<(unsigned)(n_units * G), kCombineThreads, 0, st>>>(
-        part, head_off, n_units, rows, chunk_off, G, out, lse);
+    if (groups > (unsigned)(kManyChunks * n_units))
+        decode_combine_kernel<D, 512><<<(unsigned)(n_units * G), 512, 0, st>>>(part, chunk_off, G, out, lse);
+    else
+        decode_combine_kernel<D, D><<<(unsigned)(n_units * G), D, 0, st>>>(part, chunk_off, G, out, lse);
     return hipGetLastError();
 }
 
@@ -466,7 +474,7 @@ size_t decode_ws_bytes(int dtype, int d, int dv, int G, int64_t n_units, int64_t
     const size_t need = ws_for(max_chunks(n_units, rows, kChunk), n_units, G, d);
     if (least || n_units > kSelfUnits) return need;
     // room for chunks of 64 rows up to the row count where they end, so that more rows never ask for less
-    const int64_t most = (512 - n_units) * kChunk + kChunk - 1;
+    const int64_t most = std::max<int64_t>(0, std::min((512 - n_units) * kChunk + kChunk - 1, (small_chunks_limit(G) - n_units) * kSmallChunk + kSmallChunk - 1));
     const size_t small = ws_for(max_chunks(n_units, rows < most ? rows : most, kSmallChunk), n_units, G, d);
     return need > small ? need : small;
 }

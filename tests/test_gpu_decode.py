@@ -176,3 +176,32 @@ def test_chunk_sizes_of_few_and_many_rows(d, G, dtype, lens):
         got, has = _f64(lse), np.isfinite(want_lse)
         assert np.array_equal(np.isfinite(got), has)
         assert (np.abs(got[has] - want_lse[has]) <= DECODE_TOL * np.maximum(1.0, np.abs(want_lse[has]))).all()
+
+
+@pytest.mark.parametrize("units,G,rows", [(1, 1, 2000), (1, 8, 40000), (8, 8, 8192), (256, 1, 300), (256, 8, 16), (256, 5, 130),
+                                          (257, 3, 70), (128, 8, 300), (64, 3, 2000)])
+def test_both_chunk_lengths_and_both_ways_to_combine(units, G, rows):
+    """Calls on either side of the rules for the chunks' length (few units, few rows, as many workgroups as the chip holds for
+    G query heads) and for the threads that combine a unit's chunks; uneven units, one of them empty."""
+    H, d = (8, 64) if units % 8 == 0 else (1, 128)
+    w = nkv_inputs.small_workload(f"combine_{units}_{G}_{rows}", units // H, H, d, [64], n_out=0)
+    g = torch.Generator().manual_seed(units * 1000 + rows)
+    lens = (torch.rand(units, generator=g) * 2.0 * rows).long()
+    lens[units // 2] = 0 if units > 1 else rows
+    off = torch.zeros(units + 1, dtype=torch.int64)
+    off[1:] = lens.cumsum(0)
+    n = int(off[-1])
+    pk, pv = (torch.randn(n, d, generator=g).to(torch.bfloat16).to(DEV) for _ in range(2))
+    q = torch.randn(1, units // H, H * G, d, generator=g).to(torch.bfloat16).to(DEV)
+    scale = 1.0 / float(np.sqrt(d))
+    want, want_lse = oracle_decode(_f64(q), _f64(pk), _f64(pv), off.numpy(), H, scale)
+    shape = shape_of(w)
+    out = torch.full(want.shape, float("nan"), dtype=torch.float32, device=DEV)
+    lse = torch.full(want_lse.shape, float("nan"), dtype=torch.float32, device=DEV)
+    ws = torch.empty(max(nkv.decode_workspace_bytes(shape, H * G, n), 256), dtype=torch.uint8, device=DEV)
+    nkv.decode_attention(q, pk, pv, off.to(DEV), n, shape, nkv.params_default(), H * G, scale, out, lse, ws)
+    torch.cuda.synchronize()
+    assert np.abs(_f64(out) - want).max() <= DECODE_TOL * max(1.0, float(pv.abs().max()))
+    got, has = _f64(lse), np.isfinite(want_lse)
+    assert np.array_equal(np.isfinite(got), has)
+    assert (np.abs(got[has] - want_lse[has]) <= DECODE_TOL * np.maximum(1.0, np.abs(want_lse[has]))).all()
