@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const float *__restr
 // read of them to the routed score.  One workgroup of 1024 threads per unit.
 //
 // A short unit's arithmetic is small and what takes time is the chain of dependent steps, so there are few of them (as
-// two kernels of radix selects, one workgroup per scale, 16 x 8 units of 4096 tokens took 33 us, this takes 14):
+// two kernels of radix selects, one workgroup per scale, 16 x 8 units of 4096 tokens took 33 us, this takes 15):
 //   1. min and max of each scale, then its histogram over that range (2048 bins);
 //   2. one scan per scale gives the bins that hold the m-th largest and the m-th smallest value; a bin that holds more
 //      than kUnitList values is narrowed down first (see below);
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         float lo = INFINITY, hi = -INFINITY;                          // (what a thread holds past the unit repeats its last value)
-#pragma unroll(kUnroll)
+#pragma unroll kUnroll
         for (int j = 0; j < EPT; ++j) {
             const float x = value(k, j);
             lo = fminf(lo, x);
@@ -317,13 +317,13 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
             queue |= __popcll(__ballot(b == __builtin_amdgcn_readfirstlane(b) && tid + j * kSelThreads < N)) > 16;
         }
         if (queue) {
-#pragma unroll(kUnroll)
+#pragma unroll kUnroll
             for (int j = 0; j < EPT; ++j) {
                 const float x = value(k, j);
                 if (tid + j * kSelThreads < N) count_bin(buf + k * kBins, bin_of(k, x));
             }
         } else {
-#pragma unroll(kUnroll)
+#pragma unroll kUnroll
             for (int j = 0; j < EPT; ++j) {
                 const float x = value(k, j);
                 if (tid + j * kSelThreads < N) atomicAdd(&buf[k * kBins + bin_of(k, x)], 1u);
@@ -372,9 +372,9 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     if (any_crowded()) {
         // f(list, its cut, up to 16 of a thread's keys, which of them are in the list's boundary bin).  From 16 values a thread
         // on they are read again: the rare path then costs the common one no registers.
-        constexpr int kKeys = EPT < 16 ? EPT : 16;
+        constexpr int kKeys = EPT < 16 ? EPT : 16, kLists = EPT < 16 ? 6 : 1;
         auto for_crowded = [&](auto f) {
-#pragma unroll(EPT < 16 ? 6 : 1)
+#pragma unroll kLists
             for (int i = 0; i < 6; ++i) {
                 const UnitCut q = s_cut[i];
                 if (!crowded(q)) continue;
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     float pt[3] = {0.f, 0.f, 0.f}, pb[3] = {0.f, 0.f, 0.f};           // at most EPT terms of magnitude <= 1
     float smin = INFINITY, smax = -INFINITY;
     double ssum = 0.0;
-#pragma unroll(kUnroll)
+#pragma unroll kUnroll
     for (int j = 0; j < EPT; ++j) {
         float raw[3] = {value(0, j), value(1, j), value(2, j)};
         if (tid + j * kSelThreads < N) {
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     // ---- 5: blend, gate, route, pin ----
     st = hs;
     float *out = scores + base;
-#pragma unroll(kUnroll)
+#pragma unroll kUnroll
     for (int j = 0; j < EPT; ++j) {
         const int i = tid + j * kSelThreads;
         const float raw[3] = {value(0, j), value(1, j), value(2, j)};

@@ -4,13 +4,14 @@
 //   slice_hist_kernel   (per slice)  2048-bin value histogram of the slice
 //   sel_collect_kernel  (per slice)  the bin that holds the unit's B_h-th best score (found by every slice's workgroup
 //                                    from the unit's histograms); how many of the slice's scores lie in bins above
-//                                    it; the keys of that bin -> the slice's segment
+//                                    it; the keys of that bin -> the slice's segment.  The first workgroup also places
+//                                    all units in the output
 //   sel_compact_kernel  (per slice)  the exact threshold T inside the bin, how many of the scores tied at T are kept and
 //                                    how many kept / tied scores precede the slice, found by one wavefront of every
 //                                    slice's workgroup from the unit's segments (a few dozen keys: cheaper than a
-//                                    kernel of its own in between); the rows the units in front keep; then ballots
-//                                    over 64 consecutive tokens + a scan over the slice's groups give every kept token
-//                                    its output row; optional count of near-threshold scores
+//                                    kernel of its own in between); then ballots over 64 consecutive tokens + a scan
+//                                    over the slice's groups give every kept token its output row; optional count of
+//                                    near-threshold scores
 // If a segment overflows (thousands of equal scores in one bin), that wavefront walks the head's scores itself.
 #include "nkv_slices.h"
 
@@ -79,10 +80,43 @@ __device__ __forceinline__ SelPick pick_boundary_bin(const uint16_t *__restrict_
     return SelPick{s_pick[0], (uint32_t)s_pick[1]};
 }
 
+// head_off of all units, from their budgets, by one workgroup of TH threads.
+template <int TH>
+__device__ __forceinline__ void place_units(const int32_t *__restrict__ k_per_head, int LH, const PromptTab &tab, int64_t *__restrict__ head_off)
+{
+    constexpr int NW = TH / 64;
+    __shared__ unsigned long long wave_rows[NW];
+    const int n = tab.n * LH, per = (n + TH - 1) / TH, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int u0 = min(tid * per, n), u1 = min(u0 + per, n);
+    auto rows = [&](int u) {
+        const int p = u / LH;
+        return (unsigned long long)min(max(k_per_head[u], 0), tab.tok_off[p + 1] - tab.tok_off[p]);
+    };
+    unsigned long long mine = 0ull;
+    for (int u = u0; u < u1; ++u) mine += rows(u);
+    unsigned long long incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+    }
+    if (lane == 63) wave_rows[w] = incl;
+    __syncthreads();
+    unsigned long long run = incl - mine;
+    for (int i = 0; i < w; ++i) run += wave_rows[i];
+    for (int u = u0; u < u1; ++u) {
+        head_off[u] = (int64_t)run;
+        run += rows(u);
+    }
+    if (tid == TH - 1) head_off[n] = (int64_t)run;
+}
+
 // grid: slices.  Every slice's workgroup finds the boundary bin of its unit itself from the unit's slice histograms
 // (a few 4 KB rows that the histogram kernel has just written: cheaper than a kernel of its own in between), counts
 // its own slice's scores above that bin, and copies its scores of that bin into its segment.  The first slice's
-// workgroup records the unit's pick.
+// workgroup records the unit's pick.  place: head_off is not filled yet, the first workgroup of all does it.  (Where every
+// workgroup of the compaction added up the budgets in front of its unit, that kernel took 51.3 us instead of 49.7 for 1792
+// units in 3584 slices.)
 template <int TH>
 __global__ __launch_bounds__(TH) void sel_collect_kernel(const float *__restrict__ scores,
                                                                    const int32_t *__restrict__ k_per_head, int L, int H,
@@ -91,7 +125,8 @@ __global__ __launch_bounds__(TH) void sel_collect_kernel(const float *__restrict
                                                                    SelPick *__restrict__ picks,
                                                                    uint32_t *__restrict__ seg,
                                                                    SelSlice *__restrict__ ss,
-                                                                   int64_t *__restrict__ near_count)
+                                                                   int64_t *__restrict__ near_count, bool place,
+                                                                   int64_t *__restrict__ head_off)
 {
     constexpr int PT = per_thread<TH>();
     __shared__ uint32_t n_hit;
@@ -107,6 +142,7 @@ __global__ __launch_bounds__(TH) void sel_collect_kernel(const float *__restrict
     const __amdgpu_buffer_rsrc_t vals = slice_values(sc, s, N);
 #pragma unroll
     for (int j = 0; j < PT; ++j) v[j] = slice_value<TH>(vals, tid, j);
+    if (place && blockIdx.x == 0) place_units<TH>(k_per_head, L * H, tab, head_off);
     uint32_t c_own[8];
     const SelPick pk = pick_boundary_bin(part, blockIdx.x - s, S, min(max(k_per_head[u], 0), N), N, s, c_own, wtot, s_pick);
     const int bT = pk.bT;
@@ -147,13 +183,12 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// grid: slices.  place: head_off is not filled yet; every workgroup adds up the rows that the units in front of its own
-// keep, and the first slice's records it.
+// grid: slices
 template <int TH>
 __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict__ scores, const int32_t *__restrict__ k_per_head,
                                                          int L, int H, PromptTab tab, SliceTab st, const SelPick *__restrict__ picks,
-                                                         const uint32_t *__restrict__ seg, const SelSlice *__restrict__ ss, bool place,
-                                                         int64_t *__restrict__ head_off, int64_t row_capacity, float near_tol,
+                                                         const uint32_t *__restrict__ seg, const SelSlice *__restrict__ ss,
+                                                         const int64_t *__restrict__ head_off, int64_t row_capacity, float near_tol,
                                                          int32_t *__restrict__ kept_idx, int64_t *__restrict__ near_count)
 {
     constexpr int PT = per_thread<TH>(), NW = TH / 64;
@@ -163,7 +198,6 @@ __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict
     __shared__ uint32_t keys[kList];
     __shared__ uint32_t hist[256];
     __shared__ uint32_t found[4];                                    // T, rem, kept-for-sure / tied scores of the unit before this slice
-    __shared__ unsigned long long before_rows[NW];
     int p, lh, s, S;
     locate(st, tab, blockIdx.x, p, lh, s, S);
     const int u = p * L * H + lh;
@@ -176,22 +210,15 @@ __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict
     for (int j = 0; j < PT; ++j) v[j] = slice_value<TH>(vals, tid, j);
     const SelPick pk = picks[u];
     const bool all = pk.bT < 0, none = pk.bT >= kBins;
-    if (place) {
-        unsigned long long run = 0ull;
-        for (int q = tid; q < u; q += TH) {
-            const int pq = q / (L * H);
-            run += (unsigned long long)min(max(k_per_head[q], 0), tab.tok_off[pq + 1] - tab.tok_off[pq]);
-        }
-        run = wave_sum(run);
-        if (lane == 0) before_rows[w] = run;
-    }
+    const int64_t out0 = head_off[u];
+    if (none) return;                                                // nothing kept
     if (w == 0) {
         const SelSlice *unit_ss = ss + (blockIdx.x - s);
         const uint32_t *unit_seg = seg + (int64_t)(blockIdx.x - s) * kSeg;
         uint32_t T = 0u, rem = 0u, gt_before = 0u, eq_before = 0u;
         for (int q = lane; q < s; q += 64) gt_before += unit_ss[q].above;
         gt_before = wave_sum(gt_before);
-        if (!all && !none) {
+        if (!all) {
             int mine;                                                // where this slice's keys start in the list
             const int n = gather_segments(unit_seg, S, [&](int q) { return unit_ss[q].n; }, keys, kList, s, mine);
             __builtin_amdgcn_wave_barrier();
@@ -225,19 +252,6 @@ __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict
         if (lane == 0) { found[0] = T; found[1] = rem; found[2] = gt_before; found[3] = eq_before; }
     }
     __syncthreads();
-    int64_t out0;
-    if (place) {
-        unsigned long long run = 0ull;
-        for (int i = 0; i < NW; ++i) run += before_rows[i];
-        out0 = (int64_t)run;
-        if (s == 0 && tid == 0) {
-            head_off[u] = out0;
-            if (u == tab.n * L * H - 1) head_off[u + 1] = out0 + min(max(k_per_head[u], 0), N);
-        }
-    } else {
-        out0 = head_off[u];
-    }
-    if (none) return;                                                // nothing kept
     const uint32_t T = found[0], rem = found[1], unit_gt = found[2], unit_eq = found[3];
     // population of every 64-token group (chunk j, wave w) = tokens s*kSlice + j*TH + w*64 ...
     uint32_t near = 0u;
@@ -332,8 +346,8 @@ WideWs wide_ws(int L, int H, const PromptTab &tab)
 
 size_t select_wide_ws_bytes(int L, int H, const PromptTab &tab) { return wide_ws(L, H, tab).total; }
 
-// Enqueues the three kernels.  with_head_off: head_off is not on the stream yet and the compaction fills it
-// (select_wide_places_units() says when it can: every workgroup reads the budgets of the units in front of its own).
+// Enqueues the three kernels.  with_head_off: head_off is not on the stream yet and the second kernel fills it
+// (select_wide_places_units() says when it can: one workgroup reads all units' budgets).
 bool select_wide_places_units(int n_units) { return n_units <= 4096; }
 
 hipError_t launch_select_wide(const float *scores, const int32_t *k_per_head, int L, int H, const PromptTab &tab,
@@ -352,9 +366,10 @@ hipError_t launch_select_wide(const float *scores, const int32_t *k_per_head, in
     const unsigned threads = few ? 1024 : 256;
     (few ? slice_hist_kernel<1024> : slice_hist_kernel<256>)<<<(unsigned)slices, threads, 0, st>>>(scores, tab, stab, part);
     (few ? sel_collect_kernel<1024> : sel_collect_kernel<256>)<<<(unsigned)slices, threads, 0, st>>>(scores, k_per_head, L, H, tab,
-                                                                                                   stab, part, picks, seg, ss, near_count);
+                                                                                                   stab, part, picks, seg, ss, near_count,
+                                                                                                   with_head_off, head_off);
     (few ? sel_compact_kernel<1024> : sel_compact_kernel<256>)<<<(unsigned)slices, threads, 0, st>>>(
-        scores, k_per_head, L, H, tab, stab, picks, seg, ss, with_head_off, head_off, row_capacity, near_tol, kept_idx, near_count);
+        scores, k_per_head, L, H, tab, stab, picks, seg, ss, head_off, row_capacity, near_tol, kept_idx, near_count);
     return hipGetLastError();
 }
 
