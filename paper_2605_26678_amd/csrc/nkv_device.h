@@ -149,6 +149,16 @@ __device__ __forceinline__ uint32_t wave_suffix_sum(uint32_t x)
     return (uint32_t)__builtin_amdgcn_readlane((int)incl, 63) - incl + x;
 }
 
+// Adds the active lanes to their bins, those of the first lane's bin with one add: equal values would queue for one word,
+// a few cycles each.
+__device__ __forceinline__ void count_bin(uint32_t *hist, int bin)
+{
+    const unsigned long long same = __ballot(bin == __builtin_amdgcn_readfirstlane(bin));
+    const bool mine = (same >> (threadIdx.x & 63)) & 1ull;
+    const bool first = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) == 0u;
+    if (!mine || first) atomicAdd(&hist[bin], mine ? (uint32_t)__popcll(same) : 1u);
+}
+
 // The largest u in [0, n) with off[u] <= x, for ascending off[0 .. n) with off[0] <= x: a whole wavefront narrows the
 // range to a 64th with every step, so 4096 entries take two load latencies where a binary search takes twelve.
 template <typename T> __device__ __forceinline__ int wave_search(const T *__restrict__ off, int n, T x)

@@ -195,16 +195,6 @@ struct UnitCut {
     uint32_t lo, hi;                          // keys; better ones of the bin belong to the m, worse ones do not
 };
 
-// Adds the active lanes to their bins, those of the first lane's bin with one add: equal values would queue for one word,
-// a few cycles each.
-__device__ __forceinline__ void count_bin(uint32_t *hist, int bin)
-{
-    const unsigned long long same = __ballot(bin == __builtin_amdgcn_readfirstlane(bin));
-    const bool mine = (same >> (threadIdx.x & 63)) & 1ull;
-    const bool first = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) == 0u;
-    if (!mine || first) atomicAdd(&hist[bin], mine ? (uint32_t)__popcll(same) : 1u);
-}
-
 // monotone in x
 __device__ __forceinline__ int unit_bin(float x, float lo, float scale) { return min(max((int)((x - lo) * scale), 0), kBins - 1); }
 

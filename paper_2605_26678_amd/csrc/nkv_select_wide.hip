@@ -12,7 +12,7 @@
 //                                    kernel of its own in between); then ballots over 64 consecutive tokens + a scan
 //                                    over the slice's groups give every kept token its output row; optional count of
 //                                    near-threshold scores
-// If a segment overflows (thousands of equal scores in one bin), that wavefront walks the head's scores itself.
+// If a segment overflows (thousands of equal scores in one bin), the slice's workgroup walks the head's scores itself.
 #include "nkv_slices.h"
 
 namespace nkv {
@@ -183,6 +183,59 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// More scores in one bin than the lists hold (thousands of equal scores): the slice's whole workgroup walks the head's N scores
+// itself, four times for the threshold's digits and once to count -- slow, exact, and rare.  B: scores kept, 0 < B < N; begin:
+// the slice's first token.  found: as in sel_compact_kernel.  (By a single wavefront of every slice, as a unit's one
+// wavefront did before: 8 heads x 131 072 scores of 17 values 2006 us and 1800; this 190.)
+template <int TH>
+__device__ __forceinline__ void walk_head(const float *__restrict__ sc, int N, uint32_t B, int begin, uint32_t *hist, uint32_t *found)
+{
+    constexpr int U = 8;
+    const int tid = threadIdx.x;
+    auto for_keys = [&](int n, auto f) {                              // f(key, counts): the keys of [0, n), U loads in flight
+        for (int i0 = 0; i0 < n; i0 += U * TH) {
+            float x[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) x[j] = sc[min(i0 + j * TH + tid, n - 1)];
+#pragma unroll
+            for (int j = 0; j < U; ++j) f(ord_key(x[j]), i0 + j * TH + tid);
+        }
+    };
+    uint32_t want = B, T = 0u;
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        __syncthreads();                                             // (found and hist have been read)
+        for (int j = tid; j < 256; j += TH) hist[j] = 0u;
+        __syncthreads();
+        for_keys(N, [&](uint32_t key, int i) {
+            if (i < N && (shift == 24 || (key >> (shift + 8)) == (T >> (shift + 8)))) count_bin(hist, (int)((key >> shift) & 255u));
+        });
+        __syncthreads();
+        if (tid < 64) {
+            uint32_t dig, below;
+            wave_pick_digit(hist, want, dig, below);
+            if (tid == 0) { found[0] = dig; found[1] = below; }
+        }
+        __syncthreads();
+        T |= found[0] << shift;
+        want -= found[1];
+    }
+    __syncthreads();
+    if (tid == 0) { found[0] = T; found[1] = want; found[2] = found[3] = 0u; }     // (what is left of B is kept of the tied ones)
+    __syncthreads();
+    uint32_t g = 0u, e = 0u;
+    for_keys(begin, [&](uint32_t key, int i) {
+        g += i < begin && key > T ? 1u : 0u;
+        e += i < begin && key == T ? 1u : 0u;
+    });
+    g = wave_sum(g);
+    e = wave_sum(e);
+    if ((tid & 63) == 0) {
+        atomicAdd(&found[2], g);
+        atomicAdd(&found[3], e);
+    }
+    __syncthreads();
+}
+
 // grid: slices
 template <int TH>
 __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict__ scores, const int32_t *__restrict__ k_per_head,
@@ -197,7 +250,7 @@ __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict
     __shared__ unsigned long long near_acc[NW];
     __shared__ uint32_t keys[kList];
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t found[4];                                    // T, rem, kept-for-sure / tied scores of the unit before this slice
+    __shared__ uint32_t found[5];                                    // T, rem, kept-for-sure / tied scores of the unit before this slice; walk
     int p, lh, s, S;
     locate(st, tab, blockIdx.x, p, lh, s, S);
     const int u = p * L * H + lh;
@@ -216,6 +269,7 @@ __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict
         const SelSlice *unit_ss = ss + (blockIdx.x - s);
         const uint32_t *unit_seg = seg + (int64_t)(blockIdx.x - s) * kSeg;
         uint32_t T = 0u, rem = 0u, gt_before = 0u, eq_before = 0u;
+        bool walk = false;
         for (int q = lane; q < s; q += 64) gt_before += unit_ss[q].above;
         gt_before = wave_sum(gt_before);
         if (!all) {
@@ -234,24 +288,13 @@ __global__ __launch_bounds__(TH) void sel_compact_kernel(const float *__restrict
                 gt_before += wave_sum(g);
                 eq_before = wave_sum(e);
             } else {
-                // More scores in one bin than the lists hold (thousands of equal scores): this wavefront walks the
-                // head's scores itself -- slow, exact, and rare.
-                const uint32_t B = (uint32_t)min(max(k_per_head[u], 0), N);
-                T = wave_select_fn(N, B, hist, gt, eq, [sc](int i) { return ord_key(sc[i]); });
-                rem = B - gt;
-                uint32_t g = 0u, e = 0u;
-                for (int i = lane; i < s * kSlice; i += 64) {
-                    const uint32_t k = ord_key(sc[i]);
-                    g += k > T ? 1u : 0u;
-                    e += k == T ? 1u : 0u;
-                }
-                gt_before = wave_sum(g);
-                eq_before = wave_sum(e);
+                walk = true;
             }
         }
-        if (lane == 0) { found[0] = T; found[1] = rem; found[2] = gt_before; found[3] = eq_before; }
+        if (lane == 0) { found[0] = T; found[1] = rem; found[2] = gt_before; found[3] = eq_before; found[4] = walk; }
     }
     __syncthreads();
+    if (found[4]) walk_head<TH>(sc, N, (uint32_t)min(max(k_per_head[u], 0), N), s * kSlice, hist, found);
     const uint32_t T = found[0], rem = found[1], unit_gt = found[2], unit_eq = found[3];
     // population of every 64-token group (chunk j, wave w) = tokens s*kSlice + j*TH + w*64 ...
     uint32_t near = 0u;

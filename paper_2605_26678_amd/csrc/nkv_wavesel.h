@@ -5,6 +5,29 @@
 
 namespace nkv {
 
+// The digit that holds rank `want` (1-based) from the top of a 256-digit histogram, and how many entries lie above it.
+__device__ __forceinline__ void wave_pick_digit(const uint32_t *hist, uint32_t want, uint32_t &dig, uint32_t &below)
+{
+    // lane owns digits 4 lane .. 4 lane + 3; running count from the top
+    const int lane = threadIdx.x & 63;
+    const uint32_t c0 = hist[lane * 4], c1 = hist[lane * 4 + 1], c2 = hist[lane * 4 + 2], c3 = hist[lane * 4 + 3];
+    const uint32_t group = c0 + c1 + c2 + c3;
+    const uint32_t incl = wave_suffix_sum(group);
+    const uint32_t cum = incl - group;
+    dig = below = 0u;
+    const bool mine = cum < want && want <= incl;
+    if (mine) {
+        if (want <= cum + c3) { dig = lane * 4 + 3; below = cum; }
+        else if (want <= cum + c3 + c2) { dig = lane * 4 + 2; below = cum + c3; }
+        else if (want <= cum + c3 + c2 + c1) { dig = lane * 4 + 1; below = cum + c3 + c2; }
+        else { dig = lane * 4; below = cum + c3 + c2 + c1; }
+    }
+    const unsigned long long who = __ballot(mine);
+    const int src = __ffsll((long long)who) - 1;
+    dig = (uint32_t)__builtin_amdgcn_readlane((int)dig, src);
+    below = (uint32_t)__builtin_amdgcn_readlane((int)below, src);
+}
+
 // `want`-th largest (1-based) of the n keys key_at(0..n-1): byte-wise radix select by one wavefront; hist: 256
 // words of LDS owned by the wave.  Returns the key; gt = how many keys are larger, eq = how many are equal.
 template <typename F>
@@ -22,23 +45,8 @@ __device__ __forceinline__ uint32_t wave_select_fn(int n, uint32_t want, uint32_
             if (pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8))) atomicAdd(&hist[(k >> shift) & 255u], 1u);
         }
         __builtin_amdgcn_wave_barrier();
-        // lane owns digits 4 lane .. 4 lane + 3; running count from the top
-        const uint32_t c0 = hist[lane * 4], c1 = hist[lane * 4 + 1], c2 = hist[lane * 4 + 2], c3 = hist[lane * 4 + 3];
-        const uint32_t group = c0 + c1 + c2 + c3;
-        const uint32_t incl = wave_suffix_sum(group);
-        const uint32_t cum = incl - group;
-        uint32_t dig = 0u, below = 0u;
-        const bool mine = cum < want && want <= incl;
-        if (mine) {
-            if (want <= cum + c3) { dig = lane * 4 + 3; below = cum; }
-            else if (want <= cum + c3 + c2) { dig = lane * 4 + 2; below = cum + c3; }
-            else if (want <= cum + c3 + c2 + c1) { dig = lane * 4 + 1; below = cum + c3 + c2; }
-            else { dig = lane * 4; below = cum + c3 + c2 + c1; }
-        }
-        const unsigned long long who = __ballot(mine);
-        const int src = __ffsll((long long)who) - 1;
-        dig = (uint32_t)__builtin_amdgcn_readlane((int)dig, src);
-        below = (uint32_t)__builtin_amdgcn_readlane((int)below, src);
+        uint32_t dig, below;
+        wave_pick_digit(hist, want, dig, below);
         want -= below;
         prefix |= dig << shift;
         __builtin_amdgcn_wave_barrier();

@@ -11,8 +11,8 @@ import torch
 import nkv_inputs
 import oracle
 import paper_2605_26678_amd as nkv
-from parity_util import (SCORE_TOL, bits, check_against_oracle, compare_end_to_end, compare_stages, oracle_params,
-                         run_gpu, shape_of)
+from parity_util import (SCORE_TOL, bits, check_against_oracle, compare_end_to_end, compare_stages, near_threshold_count,
+                         oracle_params, run_gpu, shape_of)
 
 pytestmark = pytest.mark.gpu
 
@@ -546,6 +546,33 @@ def test_selection_routes_meet_the_stage_bar(flags):
     Kc = K.clone()
     Kc[:, 1] = Kc[:, 1, :1]
     compare_stages(w, Kc, V, 0.6, params=nkv.params_default(flags=flags), label=f"select const flags={flags}")
+
+
+@pytest.mark.parametrize("L,H,N,levels", [(1, 2, 70000, 17), (1, 1, 16385, 1), (9, 8, 60000, 5), (1, 3, 24576, 3000)])
+def test_selection_of_scores_with_thousands_of_ties(L, H, N, levels):
+    """Scores of a few values each, so that a unit's boundary bin holds more of them than the slice-wise selection's lists
+    and every slice's workgroup walks the head: few slices (1024 threads) and more than 512 (256 threads), thresholds in
+    the first and the last slice, one value only; and one with lists that hold.  Fed given budgets, against the oracle."""
+    rng = np.random.default_rng(N)
+    w = nkv_inputs.small_workload(f"ties_{N}", L, H, 8, [N], n_out=0)
+    sc = (np.floor(rng.random((L, H, N)) * levels) / levels).astype(np.float32)
+    sc[:, :, :4] = oracle.PIN
+    sc[:, 0] = np.sort(sc[:, 0], axis=-1)                       # ties of one value side by side
+    B = rng.integers(1, N, (1, L, H)).astype(np.int32)
+    B[0, 0, 0] = 5
+    K, V = _kv(w)
+    out, _ = run_gpu(w, K, V, 0.5, scores=torch.from_numpy(sc).to(DEV), k_per_head=torch.from_numpy(B).to(DEV))
+    off, idx = out.head_off.cpu().numpy(), out.kept_idx.cpu().numpy()
+    pk = bits(out.packed_k)
+    assert np.array_equal(np.diff(off), B.reshape(-1))
+    for l in range(L):
+        for h in range(H):
+            u = l * H + h
+            want = oracle.select_head(sc[l, h], int(B[0, l, h]))
+            assert np.array_equal(idx[off[u]:off[u + 1]], want), (l, h)
+            assert np.array_equal(pk[off[u]:off[u + 1]], bits(K[l, h])[want]), (l, h)
+    near = sum(near_threshold_count(sc[l], B[0, l], nkv.params_default().near_tol) for l in range(L))
+    assert int(out.near_count.item()) == near
 
 
 def test_budget_without_workspace_uses_the_generic_kernel():
