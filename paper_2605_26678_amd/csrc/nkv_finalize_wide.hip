@@ -17,8 +17,8 @@
 //   stats_finish_kernel  (unit, scale)   two wavefronts, one per boundary bin: exact thresholds inside the bins, the
 //                                        two means, min, 1/range, gap
 //   route_slice_kernel   (slice)         weights, surprise statistics of the head, routed scores, pinning
-// A list that overflows (hundreds of values of one slice in one bin) marks the (unit, scale) and the per-head
-// kernel, launched behind and idle otherwise, computes it.
+// A list that overflows (hundreds of values of one slice in one bin) marks the (unit, scale), and the first wavefront of its
+// finishing workgroup walks the head's values itself.
 #include "nkv_learner.h"
 #include "nkv_slices.h"
 
@@ -491,8 +491,7 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
     return hipGetLastError();
 }
 
-// Final scores from the statistics (complete, including what the per-head kernel redid) and the slices'
-// surprise sums left by launch_stats_wide in the same scratch.
+// Final scores from the statistics and the slices' surprise sums that launch_stats_wide left in the same scratch.
 hipError_t launch_route_wide(const float *a_raw, int L, int H, const PromptTab &tab, const LearnerConsts &lc,
                              const float *stats, void *ws, float *scores, hipStream_t st)
 {

@@ -434,8 +434,9 @@ hipError_t launch_select_compact(const void *keys, const void *values, const Row
 #define NKV_SELECT_FAST(EPT)                                                                              \
     select_fast_kernel<EPT><<<(unsigned)n, kSelThreads, 0, st>>>(scores, k_per_head, L, H, tab, u0, near_tol, \
                                                                  head_off, row_capacity, kept_idx, near_count, near_units)
-    // Slice-wise kernels where a head has more than two slices or there are thousands of units, and the caller
-    // gave scratch (for a few hundred units of up to two slices the six launches cost what they save).
+    // Slice-wise kernels (three launches) where a head has more than two slices or there are thousands of units, and the caller
+    // gave scratch.  Slice-wise / per unit, gather included: 16 400 tokens, one layer of 8 heads 21.0 / 41.8 us, 36 layers 83 /
+    // 110; 2048 units of 1000 tokens 82 / 76, of 4096 tokens 151 / 147.
     if (wide) {
         const hipError_t e = launch_select_wide(scores, k_per_head, L, H, tab, near_tol, head_off, row_capacity,
                                                 kept_idx, near_count, wide_places, wide_ws, st);

@@ -93,9 +93,9 @@ SWEEP = [
     ("heads_16_long", 1, 16, 128, [20000], "bf16", 0),
     ("slice_edges", 1, 2, 128, [8193, 16385, 100, 24576], "bf16", 0),   # one token past a slice, exact slices
     ("slices_d64", 1, 3, 64, [17000], "bf16", 0),
-    ("nine_slices", 1, 2, 128, [70000, 9000], "bf16", 0), # 274 blocks in the unit: two rounds of the dies' runs;
-                                                          # more than the matrix-core scan takes: vector scan
-    ("unit_256_blocks", 1, 2, 128, [65533, 300], "bf16", 0),   # the longest unit the matrix-core scan takes
+    ("nine_slices", 1, 2, 128, [70000, 9000], "bf16", 0), # 274 blocks in the unit: two rounds of the dies' runs; the
+                                                          # matrix-core scan's instance for long units
+    ("unit_256_blocks", 1, 2, 128, [65533, 300], "bf16", 0),   # the longest unit of its instance for units of up to 256 blocks
     ("units_4096", 16, 8, 64, [60] * 31 + [9000], "bf16", 0),  # slice-wise selection, which also places the units in the output
     ("units_4224", 33, 8, 64, [50 + i for i in range(16)], "bf16", 0),   # more units than it places: the scan kernel in front
 ]
@@ -537,8 +537,8 @@ def test_statistics_of_crowded_anomalies(kind, N):
 def test_selection_routes_meet_the_stage_bar(flags):
     """Slice-wise and per-unit selection kernels, fed the oracle's scores and budgets: bit-exact kept indices and
     packed rows either way, for ratios that keep nearly nothing, a quarter, nearly everything, and with one
-    head of constant keys (all of its scores tie: more than the slice-wise kernels' lists hold, so their
-    finishing wavefront walks the head itself)."""
+    head of constant keys (all of its scores tie: more than the slice-wise kernels' lists hold, so every slice's
+    workgroup walks the head itself)."""
     w = nkv_inputs.small_workload("select_routes", 2, 3, 128, [20000, 700, 16384])
     K, V = _kv(w)
     for r in (0.999, 0.75, 0.02):
