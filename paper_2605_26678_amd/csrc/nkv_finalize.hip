@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
         st.inv_range[k] = uniform(range < kFlat ? 0.f : 1.0f / range);
         const bool inner = inner_hi > inner_lo && N >= 2 * kSelThreads;
         bins_lo[k] = uniform(inner ? inner_lo : st.lo[k]);
-        to_bin[k] = uniform(range < kFlat ? 0.f : (float)kBins / (inner ? inner_hi - inner_lo : range));
+        to_bin[k] = uniform(range < kFlat ? 0.f : (float)kBins * __builtin_amdgcn_rcpf(inner ? inner_hi - inner_lo : range));
     }
     if (tid == 0) {
 #pragma unroll
@@ -354,15 +354,18 @@ __global__ __launch_bounds__(kSelThreads, EPT <= 4 ? 8 : 4) void finalize_unit_k
     __syncthreads();
     auto key_of = [](int i, float x) { return i & 1 ? ~ord_key(x) : ord_key(x); };   // inverted: the smallest value has the largest key
     auto crowded = [](const UnitCut &q) { return q.pop > (uint32_t)kUnitList && q.lo != q.hi; };
+    uint32_t most_pop = 0u;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) most_pop = max(most_pop, s_cut[i].pop);
     auto any_crowded = [&]() {                                        // the same for every thread
         bool any = false;
         for (int i = 0; i < 6; ++i) any |= crowded(s_cut[i]);
         return any;
     };
-    if (any_crowded()) {
-        // f(list, its cut, up to 16 of a thread's keys, which of them are in the list's boundary bin).  From 16 values a thread
+    if (most_pop > (uint32_t)kUnitList) {
+        // f(list, its cut, up to 8 of a thread's keys, which of them are in the list's boundary bin).  From 16 values a thread
         // on they are read again: the rare path then costs the common one no registers.
-        constexpr int kKeys = EPT < 16 ? EPT : 16, kLists = EPT < 16 ? 6 : 1;
+        constexpr int kKeys = EPT < 16 ? EPT : 8, kLists = EPT < 16 ? 6 : 1;
         auto for_crowded = [&](auto f) {
 #pragma unroll kLists
             for (int i = 0; i < 6; ++i) {
