@@ -5,30 +5,41 @@
 // their way from the load; other head dims are padded with zeros to 32 KS, which no dot product and no norm sees.)
 //
 // The pass is a stream over the keys and nothing else is read from memory, but written for the vector unit it
-// needs ~2300 instructions per 64 tokens and is bound by their issue.  Here the vector unit keeps only the work
-// that is a sum over tokens (the partial sums of normalised keys that the anchors are made of); everything that
-// is a contraction over the head dimension goes through v_mfma_f32_16x16x32_bf16, whose products of bf16 values
-// are exact and whose sums are fp32:
+// needs ~2300 instructions per 64 tokens and is bound by their issue.  Here everything that is a contraction over the head
+// dimension goes through v_mfma_f32_16x16x32_bf16, whose products of bf16 values are exact and whose sums are fp32, and what
+// is done per token is done for 64 tokens at a time, one per lane:
 //
-//   * a block is cut into groups of 16 tokens.  T_q = sum of k_hat over group q (vector unit).  The window sum in
+//   * a block is cut into groups of 16 tokens.  T_q = sum of k_hat over group q.  The window sum in
 //     front of group q's first token is exact in terms of groups: Seed_q = T_{q-4} + ... + T_{q-1}.
 //   * for token i of group G, with P the group 64 tokens earlier (token i' = i - 64 leaves as i enters),
 //         W_i = Seed_G + sum_{j in G, j <= i} k_hat_j - sum_{j' in P, j' <= i'} k_hat_j',
 //     so <k_i, W_i> = <k_i, Seed_G> + sum_{j <= i} w_j A[i][j] - sum_{j' <= i'} w_j' X[i][j'] with the Gram tiles
-//     A = K_G K_G^T and X = K_G K_P^T of the raw keys and w = 1 / ||k||.
+//     A = K_G K_G^T and X = K_G K_P^T of the raw keys and w = 1 / ||k||, ||k||^2 being A's diagonal.
 //   * ||W_i||^2 follows the window inside the group: it is ||Seed_G||^2 plus the running sum of
 //         ||W_i||^2 - ||W_{i-1}||^2 = 2 <W_i, d_i> - ||d_i||^2,   d_i = k_hat_i - k_hat_i',
 //     which needs <k_i', W_i> (same tiles, the other triangle) and X[i][i'].  At most 16 terms are added up.
 //   * <k, anchor> for the anchors that are vectors (Seed_G, the block total, the unit sum): the fp32 anchor is
-//     split into three bf16 terms (8 + 8 + 8 mantissa bits, exact) that form rows of the left operand.
+//     split into three bf16 terms (8 + 8 + 8 mantissa bits, exact) that form rows of the left operand.  One left operand
+//     holds the seeds of a wave's four groups and the block total.
+//   * T_q: a product with a selector matrix takes 16 dims out of a group as fp32 (exact), four tokens a lane, which the vector
+//     unit weights and adds up.
 //
 // Layouts.  A wave owns the groups q = w, w + 4, w + 8, w + 12 of the block (so the group 64 tokens earlier is
-// its own previous group) and the group of the halo in front of them.  A group is loaded row-wise (lane (g, c):
-// rows 4g .. 4g+3, dims 8c .. 8c+7; four contiguous 256-byte pieces per load instruction), which is the layout
-// the partial sums want, and passes through 4 KB of LDS private to the wave to become a matrix operand (lane
-// (q, n): token n, dims 32 kk + 8q .. + 7 in operand register kk).  Operands stay in registers until the unit's
+// its own previous group) and the group of the halo in front of them.  A group is loaded row by row (64 pieces of 16 bytes
+// an instruction, whatever the row's length) and passes through rows of LDS private to the wave to become a matrix operand
+// (lane (q, n): token n, dims 32 kk + 8q .. + 7 in operand register kk).  Operands stay in registers until the unit's
 // sum has arrived.  A 16 x 16 result leaves lane (q, n) with column n, rows 4q .. 4q+3: sums over rows are four
-// multiply-adds per lane followed by a sum over the four lanes n, n+16, n+32, n+48.
+// multiply-adds per lane, and the four groups' partial sums then change places across the lanes so that lane (q, n) ends up
+// with group q's token n: one square root, one store an anomaly and so on for 64 tokens.  In calls whose blocks have at most
+// 128 tokens no wave has more than two groups: an instance of its own (MG = 2, 94 registers: five workgroups a CU).
+//
+// What bounds it.  36 layers x 8 heads x 32768 tokens of head dim 128: 530 us (555 with the tokens' arithmetic group by
+// group, dot-product instructions for the norms and unpacking on the vector unit: 1480 vector instructions per 64 tokens,
+// 890 now), keys at 4.6 TB/s, where reading them alone takes 350 us.  No unit is saturated: of a workgroup's 28 000 cycles
+// 4 400 pass until its keys are there, 16 000 in dependent phases that share the vector unit with three other workgroups,
+// 6 000 in waiting for the slowest of the unit's 128 workgroups.  What was measured instead and is slower: workgroups that
+// stay and bring the next block's keys to LDS meanwhile, with a_s one block later, two of four waves (612 us) or of eight
+// (790 us) a CU: half the waves, or half the tokens a wave, hide less of the chains than the loads and waits cost.
 //
 // Protocol.  A block's workgroup adds its total to the unit's self-counting accumulators (nkv_scan_common.h) as
 // soon as it has it; the add returns the word's previous contents, and whoever finds that it was the last of the
@@ -47,6 +58,7 @@
 namespace nkv {
 namespace {
 
+using bf16x2 = __bf16 __attribute__((ext_vector_type(2)));
 using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
 using f16x8 = _Float16 __attribute__((ext_vector_type(8)));
 using f32x4 = float __attribute__((ext_vector_type(4)));
@@ -54,9 +66,6 @@ using f32x4 = float __attribute__((ext_vector_type(4)));
 constexpr int kNoByte = 0x40000000;              // an offset past any buffer of the pass, also with a token's offset added:
                                                  // loads read zeros there, stores are dropped
 constexpr int kGroup = 16;                       // tokens per group
-constexpr int kPitch = 272;                      // bytes between the rows of a staged group: 16 lanes that read the
-                                                 // same piece of 16 rows touch every LDS bank once
-constexpr int kStageBytes = kGroup * kPitch;
 constexpr int kTileWaves = 4;
 
 
@@ -78,8 +87,7 @@ template <int KF, int KS> __device__ __forceinline__ f32x4 tile(const u32x4 (&a)
     return c;
 }
 
-// The same, as two halves where FINE: sums of half the length.  (Four quarters are closer still, but do not fit the
-// registers; for the products of keys with keys, neither do two where KS = 4.)
+// The same, as two halves where FINE: shorter chains of additions.
 template <int KF, int KS, bool FINE> __device__ __forceinline__ f32x4 fine_tile(const u32x4 (&a)[KS], const u32x4 (&b)[KS])
 {
     if constexpr (!FINE) {
@@ -108,26 +116,7 @@ __device__ __forceinline__ float sum_over_rows16(float x)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// T[e], e < 8: partial sums of dims 8c + e held by lane (g, c).  Summed over g; lane (g, c) receives the totals
-// of dims 8c + 2g and 8c + 2g + 1.  Each step halves the number of live values.
-__device__ __forceinline__ float2 sum_over_rows16_transposing(const float (&T)[8])
-{
-    float U[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {                // lower half: dim e, upper half: dim e + 4
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(T[e]), __float_as_uint(T[e + 4]), false, false);
-        U[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    float V[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {                // rows 0..3 of 16 lanes: dims e, e + 2, e + 4, e + 6
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(U[e]), __float_as_uint(U[e + 2]), false, false);
-        V[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    return make_float2(V[0], V[1]);
-}
-
-// The same in 64 bits, and over the whole wavefront.
+// Inclusive running sum over the 16 lanes of a row (lanes n = 0 .. 15 of every group of 16), in 64 and in 32 bits.
 template <int CTRL> __device__ __forceinline__ double row_shr(double x)       // 0 in front of the row
 {
     const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
@@ -144,7 +133,6 @@ __device__ __forceinline__ double row_prefix_sum(double x)
     return x;
 }
 
-// inclusive running sum over the 16 lanes of a row (lanes n = 0 .. 15 of every group of 16)
 __device__ __forceinline__ float row_prefix_sum(float x)
 {
     x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x111, 0xf, 0xf, true));   // row_shr:1
@@ -154,131 +142,111 @@ __device__ __forceinline__ float row_prefix_sum(float x)
     return x;
 }
 
-// fp32 -> three 16-bit terms whose sum is the value.  bf16: each term takes the next 8 mantissa bits, exact.  fp16:
-// each term is the rounded remainder (11 bits each; the remainders are exact, the last term is off by at most 2^-33
-// of the value or by fp16's smallest step, 6e-8, whichever is larger); the value must be below fp16's largest, 65504.
-template <int KF> __device__ __forceinline__ void split3(float x, uint32_t &hi, uint32_t &mid, uint32_t &lo)
+// A pair of fp32 values -> three 16-bit terms each, whose sum is the value.  bf16: each term takes the next 8 mantissa bits,
+// exact.  fp16: each term is the rounded remainder (11 bits each; the remainders are exact, the last term is off by at most
+// 2^-33 of the value or by fp16's smallest step, 6e-8, whichever is larger); the value must be below fp16's largest, 65504.
+template <int KF> __device__ __forceinline__ void split3_pair(float x, float y, uint32_t (&t)[3])
 {
-    if constexpr (KF == kKeyF16) {
-        const _Float16 h = (_Float16)x;
-        const float r1 = x - (float)h;
-        const _Float16 m = (_Float16)r1;
-        const float r2 = r1 - (float)m;
-        const _Float16 l = (_Float16)r2;
-        hi = __builtin_bit_cast(unsigned short, h);
-        mid = __builtin_bit_cast(unsigned short, m);
-        lo = __builtin_bit_cast(unsigned short, l);
-        return;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        if constexpr (KF == kKeyF16) {
+            const _Float16 a = (_Float16)x, b = (_Float16)y;
+            t[i] = (uint32_t)__builtin_bit_cast(unsigned short, a) | (uint32_t)__builtin_bit_cast(unsigned short, b) << 16;
+            x -= (float)a;
+            y -= (float)b;
+        } else {
+            const uint32_t a = __float_as_uint(x), b = __float_as_uint(y);
+            t[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);          // the upper halves
+            x -= __uint_as_float(a & 0xffff0000u);
+            y -= __uint_as_float(b & 0xffff0000u);
+        }
     }
-    const uint32_t b0 = __float_as_uint(x) & 0xffff0000u;
-    const float r1 = x - __uint_as_float(b0);
-    const uint32_t b1 = __float_as_uint(r1) & 0xffff0000u;
-    const float r2 = r1 - __uint_as_float(b1);
-    hi = b0 >> 16;
-    mid = b1 >> 16;
-    lo = __float_as_uint(r2) >> 16;
 }
 
 // The factor that keeps a sum of N unit vectors inside fp16's range; the cosine does not see it.
 __device__ __forceinline__ float fp16_sum_scale(int N) { return N <= 131072 ? 0.25f : 0.03125f; }
 
-// A vector of which this lane holds dims 2 lane and 2 lane + 1, as the three terms of rows row0 .. row0 + 2
-// of a staged left operand.
-template <int KF> __device__ __forceinline__ void stage_anchor(uint8_t *stage, int row0, int lane, float v0, float v1)
+// Rows of 32 KS 16-bit values in LDS (staged keys, anchors): 16 lanes that read the same piece of 16 rows touch every bank once.
+template <int KS> constexpr int kPitch = 64 * KS + 16;
+
+// A vector of which this lane holds dims 2 lane and 2 lane + 1 as its three terms, the largest first, into rows r0, r1, r2.
+template <int KF, int KS> __device__ __forceinline__ void stage_anchor(uint8_t *rows, int r0, int r1, int r2, int lane, float v0, float v1)
 {
-    uint32_t h0, m0, l0, h1, m1, l1;
-    split3<KF>(v0, h0, m0, l0);
-    split3<KF>(v1, h1, m1, l1);
-    *reinterpret_cast<uint32_t *>(stage + (row0 + 0) * kPitch + 4 * lane) = h0 | (h1 << 16);
-    *reinterpret_cast<uint32_t *>(stage + (row0 + 1) * kPitch + 4 * lane) = m0 | (m1 << 16);
-    *reinterpret_cast<uint32_t *>(stage + (row0 + 2) * kPitch + 4 * lane) = l0 | (l1 << 16);
+    uint32_t t[3];
+    split3_pair<KF>(v0, v1, t);
+    if (KS < 4 && lane >= 16 * KS) return;
+    *reinterpret_cast<uint32_t *>(rows + r0 * kPitch<KS> + 4 * lane) = t[0];
+    *reinterpret_cast<uint32_t *>(rows + r1 * kPitch<KS> + 4 * lane) = t[1];
+    *reinterpret_cast<uint32_t *>(rows + r2 * kPitch<KS> + 4 * lane) = t[2];
 }
 
-// The staged 16 rows as a matrix operand: lane (q, n) takes dims 32 kk + 8 q .. + 7 of row n.
-template <int KS> __device__ __forceinline__ void read_operand(const uint8_t *stage, int lane, u32x4 (&x)[KS])
+// Staged rows as a matrix operand: lane (q, n) takes dims 32 kk + 8 q .. + 7 of row r.
+template <int KS> __device__ __forceinline__ void read_operand(const uint8_t *rows, int r, int q, u32x4 (&x)[KS])
 {
-    const uint8_t *mine = stage + (lane & 15) * kPitch + 16 * (lane >> 4);
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) x[kk] = *reinterpret_cast<const u32x4 *>(mine + 64 * kk);
+    for (int kk = 0; kk < KS; ++kk) x[kk] = *reinterpret_cast<const u32x4 *>(rows + r * kPitch<KS> + 16 * q + 64 * kk);
 }
 
-// The format the staged rows are in: 8-bit keys travel as bf16.
+// The format the operands are in: 8-bit keys travel as bf16.
 template <int KF> constexpr int kStaged = KF == kKeyF16 ? kKeyF16 : kKeyBF16;
 
-// A loaded row piece in the staged format.  E4M3 -> bf16 is exact (3 mantissa bits into 7, exponents -9 .. 8): the
-// upper halves of the fp32 values are the bf16 values.
-template <int KF> __device__ __forceinline__ u32x4 staged_piece(const Piece<KF> &r)
+// Eight values of a row in the operand format.  E4M3 -> bf16 is exact (3 mantissa bits into 7, exponents -9 .. 8).
+template <int KF> __device__ __forceinline__ u32x4 operand_piece(const Piece<KF> &r)
 {
     if constexpr (KF == kKeyF8) {
-        float k[8];
-        unpack8_f8(r, k);
-        u32x4 o;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = __builtin_amdgcn_perm(__float_as_uint(k[2 * i + 1]), __float_as_uint(k[2 * i]), 0x07060302u);
-        return o;
+        return u32x4{__builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.x, 1.0f, false)),
+                     __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.x, 1.0f, true)),
+                     __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.y, 1.0f, false)),
+                     __builtin_bit_cast(uint32_t, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(r.y, 1.0f, true))};
     } else {
         return r;
     }
 }
 
-// Sums of the squares of a lane's eight values of each of its four rows, ready to be read by any vector instruction (the
-// compiler does not see the writes inside the assembly): four independent chains of exact products.
-template <int KF> __device__ __forceinline__ void rows_sumsq(const u32x4 (&r)[4], float (&ss)[4])
+// The diagonal of a 16 x 16 result: lane (n / 4, n) receives element [n][n], the others 0.
+__device__ __forceinline__ float diagonal(const f32x4 &x, int qq, int n)
 {
-#define NKV_DOTS(OP)                                                                                                      \
-    asm(OP " %0, %4, %4\n\t" OP " %1, %8, %8\n\t" OP " %2, %12, %12\n\t" OP " %3, %16, %16\n\t"                            \
-        OP " %0, %5, %5\n\t" OP " %1, %9, %9\n\t" OP " %2, %13, %13\n\t" OP " %3, %17, %17\n\t"                            \
-        OP " %0, %6, %6\n\t" OP " %1, %10, %10\n\t" OP " %2, %14, %14\n\t" OP " %3, %18, %18\n\t"                          \
-        OP " %0, %7, %7\n\t" OP " %1, %11, %11\n\t" OP " %2, %15, %15\n\t" OP " %3, %19, %19\n\t"                          \
-        "s_nop 3"                                                                                                         \
-        : "+v"(ss[0]), "+v"(ss[1]), "+v"(ss[2]), "+v"(ss[3])                                                              \
-        : "v"(r[0].x), "v"(r[0].y), "v"(r[0].z), "v"(r[0].w), "v"(r[1].x), "v"(r[1].y), "v"(r[1].z), "v"(r[1].w),          \
-          "v"(r[2].x), "v"(r[2].y), "v"(r[2].z), "v"(r[2].w), "v"(r[3].x), "v"(r[3].y), "v"(r[3].z), "v"(r[3].w))
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ss[j] = 0.f;
-    if constexpr (KF == kKeyF16) NKV_DOTS("v_dot2c_f32_f16");
-    else NKV_DOTS("v_dot2c_f32_bf16");
-#undef NKV_DOTS
+    const float a = (n & 1) ? x[1] : x[0], b = (n & 1) ? x[3] : x[2];
+    return (n >> 2) == qq ? ((n & 2) ? b : a) : 0.f;
 }
-
-// One group of 16 tokens in row-wise layout (lane (g, c): rows 4g .. 4g+3, dims 8c .. 8c+7; tok0 = the group's
-// first token, which may lie in front of the prompt): ||k||^2 and the weight 1/||k|| of every row (0 for tokens
-// outside [0, tok_end)) go to ss_out / w_out.  The four rows of a lane are reduced together by a transposing butterfly,
-// after which lane (g, c) holds row 4g + c % 4: one square root per group instead of one per row.
-template <int KF> __device__ __forceinline__ void group_norms(const u32x4 (&raw)[4], int tok0, int tok_end, int g, int c, float *w_out,
-                                            float *ss_out)
+// v[m], m < 4: partial sums of group m's token n held by lane (q, n).  Lane (q, n) receives the total of group q's.
+__device__ __forceinline__ float sum_to_groups(const float (&v)[4])
 {
-    float ss[4];
-    rows_sumsq<KF>(raw, ss);
-    float s = merge_low4(ss);
-    s += dpp_mov<0x124>(s);                                           // row_ror:4
-    s += dpp_mov<0x128>(s);                                           // row_ror:8
-    const int tok = tok0 + 4 * g + (c & 3);
-    const float ww = tok >= 0 && tok < tok_end ? inv_norm(s) : 0.f;
-    if (c < 4) {                                                      // (the quads' sums may differ in the last bit: one of them counts)
-        w_out[4 * g + c] = ww;
-        ss_out[4 * g + c] = s;
+    float u[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[e]), __float_as_uint(v[e + 2]), false, false);
+        u[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(u[0]), __float_as_uint(u[1]), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-
-// The weighted sum of the group's rows to sum_out (32 KS floats), with the weights that group_norms left (same wave: in
-// order).
-template <int KF, int KS> __device__ __forceinline__ void group_sum(const u32x4 (&raw)[4], int g, int c, const float *w_in, float *sum_out)
+__device__ __forceinline__ double sum_to_groups(const double (&v)[4])
 {
-    const float4 w4 = *reinterpret_cast<const float4 *>(w_in + 4 * g);
-    const float ww[4] = {w4.x, w4.y, w4.z, w4.w};
-    float T[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) T[e] = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float k[8];
-        unpack8<KF>(raw[j], k);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) T[e] = fmaf(ww[j], k[e], T[e]);
-    }
-    const float2 t2 = sum_over_rows16_transposing(T);
-    if (KS == 4 || 8 * c < 32 * KS) *reinterpret_cast<float2 *>(sum_out + 8 * c + 2 * g) = t2;
+    auto merge = [](double x, double y, bool rows32) {
+        const unsigned long long a = __builtin_bit_cast(unsigned long long, x), b = __builtin_bit_cast(unsigned long long, y);
+        const auto lo = rows32 ? __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false) : __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+        const auto hi = rows32 ? __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false)
+                               : __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+        return __builtin_bit_cast(double, (unsigned long long)hi[0] << 32 | lo[0]) + __builtin_bit_cast(double, (unsigned long long)hi[1] << 32 | lo[1]);
+    };
+    return merge(merge(v[0], v[2], true), merge(v[1], v[3], true), false);
+}
+// the total over a row's 16 lanes
+__device__ __forceinline__ double row_total(double v)
+{
+    v += dpp_partner<0xB1>(v);
+    v += dpp_partner<0x4E>(v);
+    v += dpp_partner<0x141>(v);
+    return v + dpp_partner<0x140>(v);
+}
+__device__ __forceinline__ float row_total(float v) { return row_sum<16>(v); }
+// v[q] without an index that is not known at compile time
+__device__ __forceinline__ float of_group(const float (&v)[4], int q)
+{
+    const float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+    const float a = (q & 1) ? v1 : v0, b = (q & 1) ? v3 : v2;
+    return (q & 2) ? b : a;
 }
 
 // ||k_hat|| of a token, 1 unless its norm is below the clamp (rare: one uniform test instead of a square root per token)
@@ -327,7 +295,7 @@ template <int KS> __device__ __forceinline__ float2 sum_pair(const float *v, int
     return KS == 4 || lane < 16 * KS ? t : make_float2(0.f, 0.f);
 }
 
-__device__ __forceinline__ float sum3(const f32x4 &d) { return (d[0] + d[1]) + d[2]; }
+__device__ __forceinline__ float sum3(const f32x4 &d) { return d[0] + (d[1] + d[2]); }
 
 // sum over this lane's four rows of wm[rho] * d[rho]
 __device__ __forceinline__ float weighted(const f32x4 &d, const float (&wm)[4])
@@ -408,19 +376,21 @@ __global__ __launch_bounds__(256) void plan_kernel(TileItem *__restrict__ items,
     }
 }
 
+// MG: groups a wave has at most (2: no block of the call has more than 128 tokens).
 // grid: one workgroup of 256 threads per item, in the items' order.  (Resident workgroups that loop over the items
 // instead were tried: without the hardware handing out blocks as slots fall free, all workgroups of the chip move
 // through their loading and computing phases in step, and the pass takes 0.90 ms instead of 0.77.)
 // KS: head dims the pass works with, in steps of 32 (the rest of the last step reads as zeros); FULL: d = 32 KS.
-template <int KF, int KS, bool FULL, bool FINE> __global__ __launch_bounds__(64 * kTileWaves, 4)
+template <int KF, int KS, bool FULL, bool FINE, int MG> __global__ __launch_bounds__(64 * kTileWaves, 4)
 void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *__restrict__ items, float *__restrict__ a_raw,
                       unsigned long long *__restrict__ acc, unsigned long long *__restrict__ acc_group, float *__restrict__ ssum, uint32_t *__restrict__ sync, int64_t rows,
                       int poll_limit)
 {
     constexpr int D = 32 * KS, NW = kTileWaves, ES = key_bytes<KF>(), SF = kStaged<KF>;
+    constexpr int kPieces = D * ES / 16, kLoads = (kGroup * kPieces + 63) / 64;   // 16-byte pieces of a row; load instructions of a group
     const int row_bytes = FULL ? D * ES : d * ES;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[NW][kStageBytes];   // a wave's group on its way to operand layout, later its anchors
-    __shared__ __attribute__((aligned(16))) float lds_T[4 + 16][D];               // group sums: 4 halo groups, then the block's
+    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[NW][kGroup * kPitch<KS>];   // a wave's group on its way to operand layout, later its anchors
+    __shared__ __attribute__((aligned(16))) float lds_T[4 + 4 * MG][D];               // group sums: 4 halo groups, then the block's
     __shared__ __attribute__((aligned(16))) float lds_w[NW][5][kGroup];           // 1/||k|| per token of a wave's groups (0: no such token)
     __shared__ __attribute__((aligned(16))) float lds_ss[NW][5][kGroup];          // ||k||^2
     __shared__ __attribute__((aligned(16))) float lds_S[D];                       // the unit's sum, once complete
@@ -429,73 +399,186 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     const TileItem it = items[blockIdx.x];
     if (it.N < 0) return;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int g = lane >> 4, c = lane & 15;                           // row-wise layout: rows 4g .., dims 8c ..
-    const int qq = g, n = c;                                          // operand / result layout: token n, quarter qq
+    const int qq = lane >> 4, n = lane & 15;                          // operand / result layout: token n, quarter qq
     uint8_t *stage = lds_stage[w];
 
     const int N = it.N, blk_lo = it.blk_lo, blk_hi = it.blk_hi;
     const int ng = (blk_hi - blk_lo + kGroup - 1) / kGroup;           // groups of the block, <= 16
     const int64_t row0 = it.row0;                                     // row of the prompt's token 0
 
-    // ---- first touch: this wave's groups, then its group of the halo.  Rows outside the prompt read as zeros. ----
+    // ---- first touch: this wave's groups, then its group of the halo.  Rows outside the prompt read as zeros, and so do
+    // groups that the block does not have. ----
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t *>(keys) + it.key_off * ES, 0, N * row_bytes, 0x00020000);
-    const int piece_off = FULL && KS == 4 ? 8 * ES * c : (8 * c < (FULL ? D : d) ? 8 * ES * c : kNoByte);
-    Piece<KF> raw[5][4];
-    bool ex[5];                                                       // group m - 1 of the chain exists (m = 0: halo)
+    int load_off[kLoads];
 #pragma unroll
-    for (int mm = 0; mm < 5; ++mm) {
-        const int m = (mm + 1) % 5;                                   // the halo is needed last
+    for (int i = 0; i < kLoads; ++i) {
+        const int piece = 64 * i + lane, at = piece % kPieces * 16;
+        load_off[i] = (FULL || at < row_bytes) && piece < kGroup * kPieces ? piece / kPieces * row_bytes + at : kNoByte;
+    }
+    u32x4 raw[MG + 1][kLoads];
+#pragma unroll
+    for (int mm = 0; mm <= MG; ++mm) {
+        const int m = (mm + 1) % (MG + 1);                                   // the halo is needed last
         const int q = w + 4 * (m - 1);                                // block-local group index, < 0: halo
-        ex[m] = q < ng;
-        if (ex[m]) {
-            const int off = (blk_lo + kGroup * q + 4 * g) * row_bytes + piece_off;
+        const int base = q < ng ? (blk_lo + kGroup * q) * row_bytes : kNoByte;
 #pragma unroll
-            // a full block's last 64 tokens (m = 4) are read again, as the next block's halo, and the halo has just
-            // been read by the block in front: those stay in the L2; the other rows are marked non-temporal (aux 2)
-            for (int j = 0; j < 4; ++j)
-                raw[m][j] = (m >= 1 && m <= 3) ? row_load<KF, 2>(rsrc, off + j * row_bytes) : row_load<KF>(rsrc, off + j * row_bytes);
-        }
+        // a full block's last 64 tokens (m = 4) are read again, as the next block's halo, and the halo has just been read by
+        // the block in front: those stay in the L2; the other rows are marked non-temporal (aux 2)
+        for (int i = 0; i < kLoads; ++i)
+            raw[m][i] = (m >= 1 && m < MG) ? __builtin_amdgcn_raw_buffer_load_b128(rsrc, base + load_off[i], 0, 2)
+                                           : __builtin_amdgcn_raw_buffer_load_b128(rsrc, base + load_off[i], 0, 0);
     }
 
-    // ---- the block's own groups: norms and partial sums, nothing else in front of the block total ----
-    u32x4 row[5][4];                                                  // the rows in the staged format
+    // A group through the staging rows into operand layout; the diagonal of its Gram tile are the norms (partial sums: lane
+    // (n / 4, n) holds token n's).
+    u32x4 X[MG + 1][KS];
+    auto stage_group = [&](const u32x4 (&r)[kLoads], u32x4 (&x)[KS]) {
 #pragma unroll
-    for (int m = 1; m < 6; ++m) {                                     // a group's sum behind the next one's norms
-        if (m < 5 && ex[m]) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) row[m][j] = staged_piece<KF>(raw[m][j]);
-            group_norms<SF>(row[m], blk_lo + kGroup * (w + 4 * (m - 1)), blk_hi, g, c, lds_w[w][m], lds_ss[w][m]);
+        for (int i = 0; i < kLoads; ++i) {
+            const int piece = 64 * i + lane, row = piece / kPieces, at = piece % kPieces;
+            if (kGroup * kPieces % 64 == 0 || piece < kGroup * kPieces) {
+                if constexpr (KF == kKeyF8) {
+                    u32x4 *to = reinterpret_cast<u32x4 *>(stage + row * kPitch<KS> + 32 * at);
+                    to[0] = operand_piece<KF>(u32x2{r[i][0], r[i][1]});
+                    to[1] = operand_piece<KF>(u32x2{r[i][2], r[i][3]});
+                } else {
+                    *reinterpret_cast<u32x4 *>(stage + row * kPitch<KS> + 16 * at) = r[i];
+                }
+            }
         }
-        if (m > 1 && ex[m - 1]) group_sum<SF, KS>(row[m - 1], g, c, lds_w[w][m - 1], lds_T[4 + w + 4 * (m - 2)]);
+        __builtin_amdgcn_wave_barrier();
+        read_operand<KS>(stage, n, qq, x);
+        __builtin_amdgcn_wave_barrier();                              // the next group reuses the staging rows
+        float p = diagonal(fine_tile<SF, KS, true>(x, x), qq, n);
+        asm volatile("" : "+v"(p));                                   // (here: one register instead of four)
+        __builtin_amdgcn_sched_barrier(0);                            // one group at a time
+        return p;
+    };
+    // A group's sum: a product with a selector takes dims 32 kk + 16 u .. + 15 out of the group as fp32, lane (qq, n): dim n of
+    // those, rows 4 qq .. + 3.
+    auto selector = [&](int u) {
+        u32x4 pick;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            pick[i] = qq == 2 * u + (n >> 3) && (n & 7) >> 1 == i ? (SF == kKeyF16 ? 0x3c00u : 0x3f80u) << (16 * (n & 1)) : 0u;
+        return pick;
+    };
+    auto group_sum = [&](const u32x4 (&x)[KS], const u32x4 &pick, int u, const float *weights, float *to) {
+        const float4 f4 = *reinterpret_cast<const float4 *>(weights + 4 * qq);
+        const float w4[4] = {f4.x, f4.y, f4.z, f4.w};
+        float T[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            T[kk] = weighted(mma<SF>(x[kk], pick, z), w4);
+        }
+        const float t = sum_to_groups(T);                             // dim 32 qq + 16 u + n
+        if (KS == 4 || qq < KS) to[32 * qq + 16 * u + n] = t;
+        __builtin_amdgcn_sched_barrier(0);                            // one group at a time
+    };
+
+    // ---- the block's own groups: norms and sums, nothing else in front of the block total ----
+    auto token = [&] {                                                // lane (q, n): group q's token n (not kept: registers)
+        int at = 64 * qq + n;
+        asm volatile("" : "+v"(at));
+        return blk_lo + kGroup * w + at;
+    };
+    {
+        float own[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < MG; ++m) own[m] = stage_group(raw[m + 1], X[m + 1]);
+        const float ss = sum_to_groups(own);
+        lds_w[w][1 + qq][n] = token() < blk_hi ? inv_norm(ss) : 0.f;
+        lds_ss[w][1 + qq][n] = ss;
+        __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const u32x4 pick = selector(u);
+#pragma unroll
+        for (int m = 1; m <= MG; ++m) group_sum(X[m], pick, u, lds_w[w][m], lds_T[w + 4 * m]);
     }
     __syncthreads();
 
-    // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1 ----
-    unsigned long long *acc_mine = acc_group + (int64_t)it.group * D;
-    float bsq, b0 = 0.f, b1 = 0.f;
-    for (int q = 0; q < ng; ++q) {
-        const float2 t2 = dim_pair<KS>(lds_T[4 + q], lane);
-        b0 += t2.x;
-        b1 += t2.y;
+    // ---- window sums in front of the wave's groups = the four groups before each; block total = episodic anchor (up to
+    // length); lane: dims 2 lane, 2 lane + 1 ----
+    float2 seed[MG], total;
+    auto sum_of_four = [&](int r0, int r1, int r2, int r3) {
+        const float2 t0 = dim_pair<KS>(lds_T[r0], lane), t1 = dim_pair<KS>(lds_T[r1], lane), t2 = dim_pair<KS>(lds_T[r2], lane), t3 = dim_pair<KS>(lds_T[r3], lane);
+        return make_float2(((t0.x + t1.x) + t2.x) + t3.x, ((t0.y + t1.y) + t2.y) + t3.y);
+    };
+    // the block's groups that are in no seed but the first
+    total = sum_of_four(0 < w ? 4 : 4 * MG, 1 < w ? 5 : 4 * MG + 1, 2 < w ? 6 : 4 * MG + 2, 3 < w ? 7 : 4 * MG + 3);
+#pragma unroll
+    for (int m = 1; m < MG; ++m) {
+        seed[m] = sum_of_four(w + 4 * m, w + 4 * m + 1, w + 4 * m + 2, w + 4 * m + 3);
+        total.x += seed[m].x;
+        total.y += seed[m].y;
     }
+    unsigned long long *acc_mine = acc_group + (int64_t)it.group * D;
     const bool poster = w == (it.id & (NW - 1));                      // one wave adds the block total to the unit's sum
     unsigned long long after0 = 0ull, after1 = 0ull;                  // the accumulators right after this block's add
     if (poster && (KS == 4 || lane < D / 2)) {
-        const unsigned long long t0 = accum_term(b0), t1 = accum_term(b1);
+        const unsigned long long t0 = accum_term(total.x), t1 = accum_term(total.y);
         after0 = __hip_atomic_fetch_add(acc_mine + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
         after1 = __hip_atomic_fetch_add(acc_mine + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
     }
-    bsq = sum_over_rows16(row_sum<16>(fmaf(b0, b0, b1 * b1)));
-
-    // ---- the halo group's sum (the window sums in front of the block's first groups need it) ----
+    // ---- the halo group (the window sums in front of the block's first groups need its sum) ----
+    {
+        const float ss_h = sum_over_rows16(stage_group(raw[0], X[0]));
+        if (qq == 0) {
+            lds_w[w][0][n] = blk_lo + kGroup * (w - 4) + n >= 0 ? inv_norm(ss_h) : 0.f;
+            lds_ss[w][0][n] = ss_h;
+        }
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int j = 0; j < 4; ++j) row[0][j] = staged_piece<KF>(raw[0][j]);
-    group_norms<SF>(row[0], blk_lo + kGroup * (w - 4), blk_hi, g, c, lds_w[w][0], lds_ss[w][0]);
-    group_sum<SF, KS>(row[0], g, c, lds_w[w][0], lds_T[w]);
+        for (int u = 0; u < 2; ++u) group_sum(X[0], selector(u), u, lds_w[w][0], lds_T[w]);
+    }
+    const float bsq = sum_over_rows16(row_sum<16>(fmaf(total.x, total.x, total.y * total.y)));
+    __syncthreads();
+    seed[0] = sum_of_four(w, w + 1, w + 2, w + 3);
+    using Norm = std::conditional_t<FINE, double, float>;
+    Norm sq[4] = {};
+#pragma unroll
+    for (int m = 0; m < MG; ++m) {
+        const Norm x = seed[m].x, y = seed[m].y;
+        sq[m] = x * x + y * y;
+    }
+    Norm P0 = row_total(sum_to_groups(sq));                           // ||W||^2 in front of this lane's group
+    asm volatile("" : "+v"(P0));
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- one left operand: rows 4 m .. + 2 the terms of group m's seed, rows 7, 3, 11 those of the block total ----
+#pragma unroll
+    for (int m = 0; m < MG; ++m) stage_anchor<SF, KS>(stage, 4 * m, 4 * m + 1, 4 * m + 2, lane, seed[m].x, seed[m].y);
+    stage_anchor<SF, KS>(stage, 7, 3, 11, lane, total.x, total.y);      // (the small terms' products are added up first)
+    __builtin_amdgcn_wave_barrier();
+    // <k, anchor>: lanes of group q hold the seed's of their group's tokens, and of the tokens 64 in front
+    float c_seed, e_seed, bd;
+    {
+        u32x4 An[KS];
+        read_operand<KS>(stage, n, qq, An);                           // (row 15 holds a key's row: not used)
+        __builtin_amdgcn_wave_barrier();
+        float dot[5] = {}, b_part[4] = {};
+        dot[0] = sum3(fine_tile<SF, KS, FINE>(An, X[0]));
+#pragma unroll
+        for (int m = 0; m < MG; ++m) {
+            const f32x4 AG = fine_tile<SF, KS, FINE>(An, X[m + 1]);   // [anchor row][i in G]
+            dot[m + 1] = sum3(AG);
+            b_part[m] = qq < 3 ? AG[3] : 0.f;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const float e4[4] = {dot[0], dot[1], dot[2], dot[3]}, c4[4] = {dot[1], dot[2], dot[3], dot[4]};
+        c_seed = of_group(c4, qq);
+        e_seed = of_group(e4, qq);
+        bd = sum_to_groups(b_part);
+        asm volatile("" : "+v"(c_seed), "+v"(e_seed), "+v"(bd));
+    }
+    __builtin_amdgcn_sched_barrier(0);
 
     float *S_unit = ssum + (int64_t)it.unit * D;
-    // (The adds have had the halo group to come back.)  The last block to add to a word of the unit stores the word's final
+    // (The adds have had the anchors' products to come back.)  The last block to add to a word of the unit stores the word's final
     // value, the last block of a group adds its word's to the unit's word: a word's adds take turns, so exactly one does.
     const __amdgpu_buffer_rsrc_t prs = __builtin_amdgcn_make_buffer_rsrc(S_unit, 0, D * 4, 0x00020000);
     auto store_complete = [&](int adds) {
@@ -518,94 +601,53 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         }
     }
 
-    // ---- every group through the staging rows into operand layout ----
-    u32x4 X[5][KS];
-#pragma unroll
-    for (int m = 0; m < 5; ++m) {
-        if (ex[m]) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4 *>(stage + (4 * g + j) * kPitch + 16 * c) = row[m][j];
-            __builtin_amdgcn_wave_barrier();
-            read_operand<KS>(stage, lane, X[m]);
-            __builtin_amdgcn_wave_barrier();                          // the next group reuses the staging rows
-        }
-    }
-    if (poster && grouped) store_complete(it.unit_groups);            // (the second adds have had the staging to come back)
-    stage_anchor<SF>(stage, 4, lane, b0, b1);                             // rows 4 .. 6: the block total's three terms
-    __syncthreads();                                                  // the halo groups' sums
-    // ---- the chain of this wave's groups ----
-    // lane (qq, n) of a result holds rows 4 qq + rho, column n.  Masked weights of the rows: rows j <= n count.
-    const __amdgpu_buffer_rsrc_t out_c = __builtin_amdgcn_make_buffer_rsrc(a_raw + 2 * rows + row0, 0, blk_hi * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t out_e = __builtin_amdgcn_make_buffer_rsrc(a_raw + rows + row0, 0, blk_hi * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t out_s = __builtin_amdgcn_make_buffer_rsrc(a_raw + row0, 0, blk_hi * 4, 0x00020000);
-    const int off_q0 = qq == 0 ? 4 * n : kNoByte, off_q1 = qq == 1 ? 4 * n : kNoByte;
-    float wm_prev[4], alpha_prev;
+    // ---- inside the groups: lane (qq, n) of a result holds rows 4 qq + rho, column n; of those, rows up to n count ----
+    float c_in, e_in, xx;                                             // (the totals, lane (q, n): group q's token n)
     {
-        const float4 w4 = *reinterpret_cast<const float4 *>(&lds_w[w][0][4 * qq]);
-        const float ww[4] = {w4.x, w4.y, w4.z, w4.w};
+        float c_part[4] = {}, e_part[4] = {}, x_part[4] = {}, wm_prev[4], alpha_prev = 0.f;
 #pragma unroll
-        for (int rho = 0; rho < 4; ++rho) wm_prev[rho] = 4 * qq + rho <= n ? ww[rho] : 0.f;
-        alpha_prev = weighted(tile<SF, KS>(X[0], X[0]), wm_prev);          // halo group: its own triangle only
-    }
-#pragma unroll
-    for (int m = 1; m < 5; ++m) {
-        if (ex[m]) {
-            const int q = w + 4 * (m - 1);
-            // window sum in front of the group = the four groups before it
-            float s0, s1;
-            {
-                const float2 t0 = dim_pair<KS>(lds_T[q], lane);
-                const float2 t1 = dim_pair<KS>(lds_T[q + 1], lane);
-                const float2 t2 = dim_pair<KS>(lds_T[q + 2], lane);
-                const float2 t3 = dim_pair<KS>(lds_T[q + 3], lane);
-                s0 = ((t0.x + t1.x) + t2.x) + t3.x;
-                s1 = ((t0.y + t1.y) + t2.y) + t3.y;
-            }
-            std::conditional_t<FINE, double, float> P0;               // ||W||^2 in front of the group
-            if constexpr (FINE) P0 = wave_sum(fma((double)s0, (double)s0, (double)s1 * (double)s1));
-            else P0 = sum_over_rows16(row_sum<16>(fmaf(s0, s0, s1 * s1)));
-            stage_anchor<SF>(stage, 0, lane, s0, s1);                     // rows 0 .. 2: the seed's three terms
-            __builtin_amdgcn_wave_barrier();
-            u32x4 An[KS];
-            read_operand<KS>(stage, lane, An);
-            __builtin_amdgcn_wave_barrier();                          // the next group rewrites rows 0 .. 2
-            const f32x4 AT = fine_tile<SF, KS, FINE && KS < 4>(X[m], X[m]);                     // [j in G][i in G]
-            const f32x4 XT = fine_tile<SF, KS, FINE && KS < 4>(X[m - 1], X[m]);                 // [j' in P][i in G]
-            const f32x4 XX = fine_tile<SF, KS, FINE && KS < 4>(X[m], X[m - 1]);                 // [j in G][i' in P]
-            const f32x4 AG = fine_tile<SF, KS, FINE>(An, X[m]);                       // [anchor row][i in G]
-            const f32x4 AP = fine_tile<SF, KS, FINE && KS < 4>(An, X[m - 1]);                   // [anchor row][i' in P]
+        for (int m = 0; m <= MG; ++m) {
+            const float4 f4 = *reinterpret_cast<const float4 *>(&lds_w[w][m][4 * qq]);
+            const float w4[4] = {f4.x, f4.y, f4.z, f4.w};
             float wm[4];
-            {
-                const float4 w4 = *reinterpret_cast<const float4 *>(&lds_w[w][m][4 * qq]);
-                const float ww[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-                for (int rho = 0; rho < 4; ++rho) wm[rho] = 4 * qq + rho <= n ? ww[rho] : 0.f;
+            for (int rho = 0; rho < 4; ++rho) wm[rho] = 4 * qq + rho <= n ? w4[rho] : 0.f;
+            float alpha = weighted(fine_tile<SF, KS, FINE && KS < 4>(X[m], X[m]), wm);          // <k_i, rows of its own group up to i>
+            asm volatile("" : "+v"(alpha));
+            if (m > 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                const u32x4 (&G)[KS] = X[m], (&B)[KS] = X[m ? m - 1 : 0];
+                const f32x4 XT = fine_tile<SF, KS, FINE && KS < 4>(B, G);       // [j' in P][i in G]
+                c_part[m - 1] = alpha - weighted(XT, wm_prev);                  // <k_i, entered rows of G less left rows of P>
+                asm volatile("" : "+v"(c_part[m - 1]));
+                __builtin_amdgcn_sched_barrier(0);
+                const f32x4 XX = fine_tile<SF, KS, FINE && KS < 4>(G, B);       // [j in G][i' in P]
+                e_part[m - 1] = weighted(XX, wm) - alpha_prev;                  // the same of k_i'
+                x_part[m - 1] = diagonal(XX, qq, n);                            // <k_i, k_i'>
+                asm volatile("" : "+v"(e_part[m - 1]), "+v"(x_part[m - 1]));
             }
-            const float alpha = weighted(AT, wm);                     // <k_i, entered rows of G>, partial
-            const float beta = weighted(XT, wm_prev);                 // <k_i, left rows of P>, partial
-            const float gamma = weighted(XX, wm);                     // <k_i', entered rows of G>, partial
-            // X[i][i']: row i of this lane's column i' = n sits in lane group n / 4, register n % 4
-            float xd = (n & 2) ? ((n & 1) ? XX[3] : XX[2]) : ((n & 1) ? XX[1] : XX[0]);
-            xd = (n >> 2) == qq ? xd : 0.f;
-            // 1/||k|| (0: no such token) and ||k||^2 of token n of this group and of the one 64 tokens earlier
-            const float wn = lds_w[w][m][n], wp = lds_w[w][m - 1][n], ssn = lds_ss[w][m][n], ssp = lds_ss[w][m - 1][n];
-            const float c_part = (qq == 0 ? sum3(AG) : 0.f) + (alpha - beta);
-            const float e_part = (qq == 0 ? sum3(AP) : 0.f) + (gamma - alpha_prev);
-            const float gsum = qq == 0 ? wn * wn * ssn + wp * wp * ssp : 0.f;
-            const float d_part = 2.f * (wn * c_part - wp * e_part) + (2.f * wn * wp * xd - gsum);
-            const float cdot = sum_over_rows16(c_part);               // <k_i, W_i>
-            const decltype(P0) d_all = sum_over_rows16(d_part);
-            const float Pn = (float)(P0 + row_prefix_sum(d_all));
-            const float ac = token_cos<FINE>(cdot, wn, ssn, Pn);
-            const float ae = token_cos<FINE>(sum3(AG), wn, ssn, bsq); // meaningful in lane group 1 (rows 4 .. 6)
-            const int soff = (blk_lo + kGroup * q) * 4;                // (an offset that was past the buffer stays past it)
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ac), out_c, off_q0 + soff, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ae), out_e, off_q1 + soff, 0, 0);
 #pragma unroll
             for (int rho = 0; rho < 4; ++rho) wm_prev[rho] = wm[rho];
             alpha_prev = alpha;
             __builtin_amdgcn_sched_barrier(0);                        // one group at a time
         }
+        c_in = sum_to_groups(c_part);
+        e_in = sum_to_groups(e_part);
+        xx = sum_to_groups(x_part);
+    }
+    if (poster && grouped) store_complete(it.unit_groups);            // (the second adds have had the chain to come back)
+    {
+        // 1/||k|| and ||k||^2 of this lane's token and of the one 64 in front, which is the group before's
+        const float wt = lds_w[w][1 + qq][n], wp = lds_w[w][qq][n], ss = lds_ss[w][1 + qq][n], ssp = lds_ss[w][qq][n];
+        const float c = c_seed + c_in, e = e_seed + e_in;             // <k_i, W_i>, <k_i', W_i>
+        const Norm dd = 2.f * (wt * c - wp * e) + (2.f * wt * wp * xx - (wt * wt * ss + wp * wp * ssp));
+        const float Pn = (float)(P0 + row_prefix_sum(dd));
+        const float ac = token_cos<FINE>(c, wt, ss, Pn), ae = token_cos<FINE>(bd, wt, ss, bsq);
+        const __amdgpu_buffer_rsrc_t out_c = __builtin_amdgcn_make_buffer_rsrc(a_raw + 2 * rows + row0, 0, blk_hi * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t out_e = __builtin_amdgcn_make_buffer_rsrc(a_raw + rows + row0, 0, blk_hi * 4, 0x00020000);
+        const int at = 4 * token();
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ac), out_c, at, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ae), out_e, at, 0, 0);
     }
     // ---- stable dots against the unit's sum ----
     if (w == 0) {                                                     // D / 4 lanes look, the other waves sit at the barrier
@@ -632,20 +674,16 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         float2 s2 = sum_pair<KS>(lds_S, lane);
         if constexpr (KF == kKeyF16) { s2.x *= fp16_sum_scale(N); s2.y *= fp16_sum_scale(N); }
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
-        stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
+        stage_anchor<SF, KS>(stage, 0, 1, 2, lane, s2.x, s2.y);
         __builtin_amdgcn_wave_barrier();
         u32x4 An[KS];
-        read_operand<KS>(stage, lane, An);
+        read_operand<KS>(stage, min(n & 3, 2), qq, An);               // the three terms in every lane group's rows
+        float dot[4] = {};
 #pragma unroll
-        for (int m = 1; m < 5; ++m) {
-            if (ex[m]) {
-                const int q = w + 4 * (m - 1);
-                const f32x4 AS = fine_tile<SF, KS, FINE>(An, X[m]);
-                const float wn = lds_w[w][m][n], ssn = lds_ss[w][m][n];
-                const float as = token_cos<FINE>(sum3(AS), wn, ssn, ssq);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + (blk_lo + kGroup * q) * 4, 0, 0);
-            }
-        }
+        for (int m = 0; m < MG; ++m) dot[m] = sum3(fine_tile<SF, KS, FINE>(An, X[m + 1]));
+        const float as = token_cos<FINE>(of_group(dot, qq), lds_w[w][1 + qq][n], lds_ss[w][1 + qq][n], ssq);
+        const __amdgpu_buffer_rsrc_t out_s = __builtin_amdgcn_make_buffer_rsrc(a_raw + row0, 0, blk_hi * 4, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, 4 * token(), 0, 0);
     }
 }
 
@@ -661,14 +699,12 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
 {
     constexpr int D = 32 * KS, NW = kTileWaves, ES = key_bytes<KF>(), SF = kStaged<KF>;
     const int dims = FULL ? D : d, row_bytes = dims * ES;
-    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[NW][kStageBytes];
-    __shared__ __attribute__((aligned(16))) float lds_w[NW][kGroup], lds_ss[NW][kGroup];
+    __shared__ __attribute__((aligned(16))) uint8_t lds_stage[NW][3 * kPitch<KS>];
     const int nblk = tab.blk_off[tab.n];
     const uint32_t count = sync[kDeferCountWord];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int qq = lane >> 4, n = lane & 15, g = qq, c = n;
+    const int qq = lane >> 4, n = lane & 15;
     uint8_t *stage = lds_stage[w];
-    const int off_q0 = qq == 0 ? 4 * n : kNoByte;
     for (uint32_t i = blockIdx.x; i < count; i += gridDim.x) {
         const int id = (int)sync[kSyncWords + i], lh = id / nblk, blk = id - lh * nblk;
         const int p = prompt_of_block(tab, blk);
@@ -684,27 +720,19 @@ __global__ __launch_bounds__(64 * kTileWaves) void deferred_stable_tile_kernel(c
         if constexpr (KF == kKeyF16) { s2.x *= fp16_sum_scale(N); s2.y *= fp16_sum_scale(N); }   // as in scan_tile_kernel
         const float ssq = sum_over_rows16(row_sum<16>(fmaf(s2.x, s2.x, s2.y * s2.y)));
         __builtin_amdgcn_wave_barrier();                              // the previous block's reads of the staged rows
-        stage_anchor<SF>(stage, 0, lane, s2.x, s2.y);
+        stage_anchor<SF, KS>(stage, 0, 1, 2, lane, s2.x, s2.y);
         __builtin_amdgcn_wave_barrier();
         u32x4 An[KS];
-        read_operand<KS>(stage, lane, An);
+        read_operand<KS>(stage, min(n & 3, 2), qq, An);
         for (int q = w; q < ng; q += 4) {
-            const int tok0 = blk_lo + kGroup * q;
-            u32x4 raw[4], X[KS];                                      // the group row-wise (norms) and as an operand
-            const int roff = (tok0 + 4 * g) * row_bytes + (8 * c < dims ? 8 * ES * c : kNoByte);
-            const int off = (tok0 + n) * row_bytes + 8 * ES * qq;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) raw[j] = staged_piece<KF>(row_load<KF>(rsrc, roff + j * row_bytes));
+            const int tok = blk_lo + kGroup * q + n, off = tok * row_bytes + 8 * ES * qq;
+            u32x4 X[KS];
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk)
-                X[kk] = staged_piece<KF>(row_load<KF>(rsrc, 32 * kk + 8 * qq < dims ? off + 32 * ES * kk : kNoByte));
-            group_norms<SF>(raw, tok0, blk_hi, g, c, lds_w[w], lds_ss[w]);
-            __builtin_amdgcn_wave_barrier();
-            const float wn = lds_w[w][n], ss = lds_ss[w][n];
-            __builtin_amdgcn_wave_barrier();                          // the next group rewrites them
-            const f32x4 AS = fine_tile<SF, KS, FINE>(An, X);
-            const float as = token_cos<FINE>(sum3(AS), wn, ss, ssq);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, off_q0 + tok0 * 4, 0, 0);
+                X[kk] = operand_piece<KF>(row_load<KF>(rsrc, 32 * kk + 8 * qq < dims ? off + 32 * ES * kk : kNoByte));
+            const float ss = sum_over_rows16(diagonal(fine_tile<SF, KS, true>(X, X), qq, n)), wn = tok < blk_hi ? inv_norm(ss) : 0.f;
+            const float as = token_cos<FINE>(sum3(fine_tile<SF, KS, FINE>(An, X)), wn, ss, ssq);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(as), out_s, qq == 0 ? 4 * tok : kNoByte, 0, 0);
         }
     }
 }
@@ -715,7 +743,7 @@ int resident_tile_workgroups()
     if (cached < 0) {
         int per_cu = 0, dev = 0;
         hipDeviceProp_t prop;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_tile_kernel<kKeyBF16, 4, true, false>, 64 * kTileWaves, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, scan_tile_kernel<kKeyBF16, 4, true, false, 4>, 64 * kTileWaves, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
             return 0;
         cached = per_cu * prop.multiProcessorCount;
@@ -736,14 +764,15 @@ struct TileLaunch {
     uint32_t *sync;
     int64_t rows;
     int poll_limit;
-    bool fine;
+    bool fine, blocks_128;
     const Prof &prof;
     hipStream_t st;
 
     template <int KF, int KS, bool FULL, bool FINE> void run() const
     {
         prof.begin(NKV_KERNEL_SCAN, st);
-        scan_tile_kernel<KF, KS, FULL, FINE><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, accum_group, ssum, sync, rows, poll_limit);
+        if (blocks_128) scan_tile_kernel<KF, KS, FULL, FINE, 2><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, accum_group, ssum, sync, rows, poll_limit);
+        else scan_tile_kernel<KF, KS, FULL, FINE, 4><<<n_items, 64 * kTileWaves, 0, st>>>(keys, d, items, a_raw, accum, accum_group, ssum, sync, rows, poll_limit);
         prof.end(NKV_KERNEL_SCAN, st);
         deferred_stable_tile_kernel<KF, KS, FULL, FINE><<<n_deferred, 64 * kTileWaves, 0, st>>>(keys, d, km, tab, ssum, sync, a_raw);
     }
@@ -752,6 +781,8 @@ struct TileLaunch {
     // 128 and units of up to 256 blocks.  Root mean square errors of a_s, a_e, a_c in 1e-8, keys of the benchmark's kind: head dim 96, 8192
     // tokens 2.4, 3.3, 2.8 before, 2.6, 2.9, 3.1 without and 2.4, 2.7, 2.9 with FINE; head dim 128, 100 000 tokens 2.3, 2.2,
     // 2.6, then 2.5, 2.7, 2.9 and 2.2, 2.5, 2.7 (6 % of the scan's time); 8-bit keys 2.1, 2.2, 2.5 and 2.0, 2.2, 2.5 without.
+    // (Those figures are from norms by dot products and terms added up largest first.  With norms in two halves and the small
+    // terms first: head dim 96, 2.4, 2.6, 2.7; 128, 100 000 tokens 2.1, 2.4, 2.5; 8-bit 1.8, 2.1, 2.3; bf16, 128: 2.4, 2.6, 2.8.)
     template <int KF> void run_format() const
     {
         constexpr bool F = KF != kKeyF8;
@@ -772,9 +803,18 @@ static int longest_unit(const PromptTab &tab)                        // in block
     return most;
 }
 
+static int longest_block(const PromptTab &tab)                      // in tokens
+{
+    int most = 0;
+    for (int p = 0; p < tab.n; ++p) most = max(most, (int)tab.b[p]);
+    return most;
+}
+
 bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, int LH)
 {
-    // (head dim 64 stays with the vector formulation: half of the lanes of a row would hold nothing here)
+    // (head dim 64 stays with the vector formulation, whose window norms lose less where keys cancel inside the window: rms
+    // error of a_c 1.7e-7 against 7.4e-7 here for a common direction that changes sign every 64 tokens.  16 layers x 8 heads x
+    // 4096 tokens take 49.6 us there and 46.2 here.)
     if (dtype == NKV_DTYPE_F32 || d > 128 || d == 64 || window != 64) return false;
     for (int p = 0; p < tab.n; ++p) {
         const int N = tab.tok_off[p + 1] - tab.tok_off[p];
@@ -828,7 +868,7 @@ hipError_t launch_score_tile(const void *keys, const RowMap &km, int dtype, int 
         nu / 2);
     const TileLaunch go{(const uint8_t *)keys, d, km, tab, (const TileItem *)plan_area, n_items, defer_all ? 4096u : 256u, a_raw,
                         ssum, (unsigned long long *)accum, (unsigned long long *)accum + nu * 2, (uint32_t *)sync_area, (int64_t)LH * tab.T,
-                        defer_all ? -1 : kPollLimit, longest_unit(tab) > 256, prof, st};
+                        defer_all ? -1 : kPollLimit, longest_unit(tab) > 256, longest_block(tab) <= 128, prof, st};
     if (dtype == NKV_DTYPE_F16) go.run_format<kKeyF16>();
     else if (dtype == NKV_DTYPE_F8_E4M3) go.run_format<kKeyF8>();
     else go.run_format<kKeyBF16>();

@@ -194,6 +194,20 @@ def test_matrix_core_scan_of_every_head_dim(d, dtype):
     assert torch.equal(a.scores, b.scores)
 
 
+@pytest.mark.parametrize("lens", [[4127, 1, 16, 17, 63], [4128, 127, 128, 129], [113, 2049, 4096], [8191, 8192, 65, 130]])
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (96, "fp16"), (80, "fp8"), (80, "bf16"), (24, "fp16")])
+def test_matrix_core_scan_with_two_and_with_four_groups_a_wave(d, dtype, lens):
+    """Calls on both sides of the line between blocks of at most 128 tokens (two groups of 16 a wave) and longer ones: blocks
+    of 128, 129 and 255 tokens, tails of 1, 2, 15, 16, 17 and 113 tokens, prompts shorter than the window, row lengths that
+    do not fill a load instruction.  Against the oracle, and both routes of the stable anomaly bit for bit."""
+    w = nkv_inputs.small_workload(f"groups_d{d}_{dtype}_{lens[0]}", 1, 2, d, lens, dtype=dtype, dv=32, n_out=0)
+    K, V = _kv(w)
+    compare_end_to_end(w, K, V, 0.5, label=w.name)
+    a, _ = run_gpu(w, K, V, 0.5)
+    b, _ = run_gpu(w, K, V, 0.5, params=nkv.params_default(flags=nkv.FLAG_DEFER_STABLE))
+    assert torch.equal(a.scores, b.scores)
+
+
 @pytest.mark.parametrize("d,dtype,N", [(32, "fp16", 49153), (16, "bf16", 262145), (8, "fp16", 270001)])
 def test_matrix_core_scan_of_long_units(d, dtype, N):
     """Units whose block totals are added up in two steps (from 193 blocks on) and units of more blocks than the chip
