@@ -589,6 +589,35 @@ def test_selection_of_scores_with_thousands_of_ties(L, H, N, levels):
     assert int(out.near_count.item()) == near
 
 
+@pytest.mark.parametrize("L,H,N", [(3, 4, 16385), (2, 3, 24576), (22, 8, 24577)])
+@pytest.mark.parametrize("short", [0, 5000])
+def test_slicewise_selection_at_thresholds_of_every_sign(L, H, N, short):
+    """Thresholds that cut no tie and ones that do, above zero, at the two zeros (which tie), below zero, with one row kept and
+    all but one; few slices (1024 threads) and more than 512 (256); a capacity below the rows needed.  Against the oracle."""
+    rng = np.random.default_rng(N + L)
+    w = nkv_inputs.small_workload(f"signs_{N}", L, H, 8, [N], n_out=0)
+    sc = rng.random((L, H, N)).astype(np.float32)
+    sc[:, 1] -= np.float32(0.5)
+    sc[:, 2] = np.where(sc[:, 2] < 0.3, np.where(sc[:, 0] < 0.5, np.float32(0.0), np.float32(-0.0)), sc[:, 2])
+    B = rng.integers(N // 4, 3 * N // 4, (1, L, H)).astype(np.int32)
+    B[0, :, 1] = 3 * N // 4                                     # a threshold below zero
+    B[0, :, 2] = N - N // 5                                     # inside the zeros
+    B[0, 0, 0], B[0, 1, 0], B[0, 0, 2] = 1, N - 1, N // 2
+    K, V = _kv(w)
+    shape, p, total = shape_of(w), nkv.params_default(), int(B.sum())
+    cap = total - short
+    pk, pv = (torch.full((total, 8), 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    idx = torch.full((total,), -7, dtype=torch.int32, device=DEV)
+    off = torch.empty(L * H + 1, dtype=torch.int64, device=DEV)
+    near = torch.zeros(1, dtype=torch.int64, device=DEV)
+    nkv.select_compact(K, V, torch.from_numpy(sc).to(DEV), torch.from_numpy(B).to(DEV), shape, p, pk, pv, idx, off, cap, near,
+                       torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV))
+    want = np.concatenate([oracle.select_head(sc[l, h], int(B[0, l, h])) for l in range(L) for h in range(H)])
+    got = idx.cpu().numpy()
+    assert np.array_equal(got[:cap], want[:cap]) and (got[cap:] == -7).all()
+    assert int(near.item()) == sum(near_threshold_count(sc[l], B[0, l], p.near_tol) for l in range(L))
+
+
 def test_budget_without_workspace_uses_the_generic_kernel():
     w = nkv_inputs.small_workload("nows", 2, 4, 64, [3000, 200])
     K, V = _kv(w)
