@@ -132,7 +132,8 @@ __global__ __launch_bounds__(TH) void slice_hist_kernel(const float *__restrict_
 }
 
 // Copies the lists of a unit's S slices (segment s: `count(s)` keys from seg + s * kSeg on) one behind the other to
-// keys[0 .. cap), by one wavefront with the loads of four segments in flight; returns the number of keys, or -1 if a
+// keys[0 .. cap), by one wavefront with the loads of the next four segments in flight, the first four's while the counts are
+// on their way; returns the number of keys, or -1 if a
 // segment or the list overflows.  before: keys of the slices in front of slice `own`.
 template <typename F>
 __device__ __forceinline__ int gather_segments(const uint32_t *__restrict__ seg, int S, F count, uint32_t *keys, int cap, int own,
@@ -141,7 +142,13 @@ __device__ __forceinline__ int gather_segments(const uint32_t *__restrict__ seg,
     const int lane = threadIdx.x & 63;
     int n = 0;
     before = 0;
+    uint32_t next[4];
+    auto load = [&](int s0, int last) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) next[i] = seg[(int64_t)min(s0 + i, last) * kSeg + lane];
+    };
     for (int s0 = 0; s0 < S; s0 += 64) {
+        load(s0, S - 1);
         const uint32_t c = s0 + lane < S ? count(s0 + lane) : 0u;
         if (__any(c > (uint32_t)kSeg)) return -1;
         const uint32_t incl = wave_prefix_sum(c);
@@ -151,9 +158,8 @@ __device__ __forceinline__ int gather_segments(const uint32_t *__restrict__ seg,
         if (own >= s0 && own < s0 + 64) before = __builtin_amdgcn_readlane(off, own - s0);
         const int m = min(64, S - s0);
         for (int i0 = 0; i0 < m; i0 += 4) {
-            uint32_t first[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) first[i] = seg[(int64_t)(s0 + min(i0 + i, m - 1)) * kSeg + lane];
+            const uint32_t first[4] = {next[0], next[1], next[2], next[3]};
+            if (i0 + 4 < m) load(s0 + i0 + 4, S - 1);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (i0 + i >= m) break;

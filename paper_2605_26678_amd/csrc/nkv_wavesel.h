@@ -28,37 +28,45 @@ __device__ __forceinline__ void wave_pick_digit(const uint32_t *hist, uint32_t w
     below = (uint32_t)__builtin_amdgcn_readlane((int)below, src);
 }
 
-// `want`-th largest (1-based) of the n keys key_at(0..n-1): byte-wise radix select by one wavefront; hist: 256
-// words of LDS owned by the wave.  Returns the key; gt = how many keys are larger, eq = how many are equal.
+// `want`-th largest (1-based) of the n keys key_at(0..n-1): radix select by one wavefront, eight bits a pass, over the bits in
+// which the keys differ (those of one bin of values share half of theirs or more); hist: 256 words of LDS owned by the wave.
+// Returns the key; gt = how many keys are larger, eq = how many are equal.  (Always four passes, and one to count: a head of
+// 131 072 anomalies in slices, the finishing kernel of the statistics 10.8 us instead of 9.8.)
 template <typename F>
 __device__ __forceinline__ uint32_t wave_select_fn(int n, uint32_t want, uint32_t *hist, uint32_t &gt, uint32_t &eq,
                                                    F key_at)
 {
     const int lane = threadIdx.x & 63;
-    uint32_t prefix = 0u;
-    for (int pass = 0; pass < 4; ++pass) {
-        const int shift = 24 - 8 * pass;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    for (int i = lane; i < n; i += 64) {
+        const uint32_t k = key_at(i);
+        lo = min(lo, k);
+        hi = max(hi, k);
+    }
+    lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_reduce(lo, [](uint32_t a, uint32_t b) { return min(a, b); }));
+    hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_reduce(hi, [](uint32_t a, uint32_t b) { return max(a, b); }));
+    gt = 0u;
+    eq = (uint32_t)n;
+    int bits = 32 - __clz((int)(lo ^ hi));                           // low bits still open; the keys looked at share the others
+    uint32_t prefix = bits == 32 ? 0u : hi >> bits << bits;
+    while (bits > 0) {
+        const int shift = max(bits - 8, 0);
         for (int j = lane; j < 256; j += 64) hist[j] = 0u;
         __builtin_amdgcn_wave_barrier();
         for (int i = lane; i < n; i += 64) {
             const uint32_t k = key_at(i);
-            if (pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8))) atomicAdd(&hist[(k >> shift) & 255u], 1u);
+            if (bits == 32 || k >> bits == prefix >> bits) atomicAdd(&hist[(k >> shift) & 255u], 1u);
         }
         __builtin_amdgcn_wave_barrier();
         uint32_t dig, below;
         wave_pick_digit(hist, want, dig, below);
         want -= below;
+        gt += below;
         prefix |= dig << shift;
+        eq = hist[dig];
+        bits = shift;
         __builtin_amdgcn_wave_barrier();
     }
-    uint32_t g = 0u, e = 0u;
-    for (int i = lane; i < n; i += 64) {
-        const uint32_t k = key_at(i);
-        g += k > prefix ? 1u : 0u;
-        e += k == prefix ? 1u : 0u;
-    }
-    gt = wave_sum(g);
-    eq = wave_sum(e);
     return prefix;
 }
 
