@@ -394,6 +394,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     __shared__ __attribute__((aligned(16))) float lds_w[NW][5][kGroup];           // 1/||k|| per token of a wave's groups (0: no such token)
     __shared__ __attribute__((aligned(16))) float lds_ss[NW][5][kGroup];          // ||k||^2
     __shared__ __attribute__((aligned(16))) float lds_S[D];                       // the unit's sum, once complete
+    __shared__ __attribute__((aligned(16))) float lds_B[D];                       // the block's sum
     __shared__ int s_have;
 
     const TileItem it = items[blockIdx.x];
@@ -501,28 +502,33 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     }
     __syncthreads();
 
-    // ---- window sums in front of the wave's groups = the four groups before each; block total = episodic anchor (up to
-    // length); lane: dims 2 lane, 2 lane + 1 ----
-    float2 seed[MG], total;
-    auto sum_of_four = [&](int r0, int r1, int r2, int r3) {
-        const float2 t0 = dim_pair<KS>(lds_T[r0], lane), t1 = dim_pair<KS>(lds_T[r1], lane), t2 = dim_pair<KS>(lds_T[r2], lane), t3 = dim_pair<KS>(lds_T[r3], lane);
+    auto sum_of_four = [&](int r) {                                   // groups r .. r + 3 of lds_T
+        const float2 t0 = dim_pair<KS>(lds_T[r], lane), t1 = dim_pair<KS>(lds_T[r + 1], lane), t2 = dim_pair<KS>(lds_T[r + 2], lane), t3 = dim_pair<KS>(lds_T[r + 3], lane);
         return make_float2(((t0.x + t1.x) + t2.x) + t3.x, ((t0.y + t1.y) + t2.y) + t3.y);
     };
-    // the block's groups that are in no seed but the first
-    total = sum_of_four(0 < w ? 4 : 4 * MG, 1 < w ? 5 : 4 * MG + 1, 2 < w ? 6 : 4 * MG + 2, 3 < w ? 7 : 4 * MG + 3);
-#pragma unroll
-    for (int m = 1; m < MG; ++m) {
-        seed[m] = sum_of_four(w + 4 * m, w + 4 * m + 1, w + 4 * m + 2, w + 4 * m + 3);
-        total.x += seed[m].x;
-        total.y += seed[m].y;
-    }
+    // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1.  One wave adds it up, four groups at a time
+    // from the first on, posts it to the unit's sum and leaves it to the others in LDS.  The order is the same whichever wave that
+    // is and for both MG (groups that the block does not have are zeros), so a unit's scores depend neither on where it lies in
+    // the call nor on its neighbours' blocks.  (Every wave for itself, starting with its own seeds, gave each wave its own
+    // rounding and took as long.  Score calls this way and that way: 36 layers x 8 heads x 32768 tokens 620 and 625 us, 32 heads x
+    // ragged x head dim 96 112 and 114.) ----
     unsigned long long *acc_mine = acc_group + (int64_t)it.group * D;
-    const bool poster = w == (it.id & (NW - 1));                      // one wave adds the block total to the unit's sum
+    const bool poster = w == (it.id & (NW - 1));
     unsigned long long after0 = 0ull, after1 = 0ull;                  // the accumulators right after this block's add
-    if (poster && (KS == 4 || lane < D / 2)) {
-        const unsigned long long t0 = accum_term(total.x), t1 = accum_term(total.y);
-        after0 = __hip_atomic_fetch_add(acc_mine + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
-        after1 = __hip_atomic_fetch_add(acc_mine + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
+    if (poster) {
+        float2 total = sum_of_four(4);
+#pragma unroll
+        for (int m = 2; m <= MG; ++m) {
+            const float2 t = sum_of_four(4 * m);
+            total.x += t.x;
+            total.y += t.y;
+        }
+        if (KS == 4 || lane < D / 2) {
+            const unsigned long long t0 = accum_term(total.x), t1 = accum_term(total.y);
+            after0 = __hip_atomic_fetch_add(acc_mine + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
+            after1 = __hip_atomic_fetch_add(acc_mine + D / 2 + lane, t1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t1;
+            *reinterpret_cast<float2 *>(&lds_B[2 * lane]) = total;
+        }
     }
     // ---- the halo group (the window sums in front of the block's first groups need its sum) ----
     {
@@ -535,25 +541,28 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
 #pragma unroll
         for (int u = 0; u < 2; ++u) group_sum(X[0], selector(u), u, lds_w[w][0], lds_T[w]);
     }
-    const float bsq = sum_over_rows16(row_sum<16>(fmaf(total.x, total.x, total.y * total.y)));
     __syncthreads();
-    seed[0] = sum_of_four(w, w + 1, w + 2, w + 3);
+    // ---- one left operand: rows 4 m .. + 2 the terms of group m's seed, the window sum in front of it = the four groups before,
+    // rows 7, 3, 11 those of the block total ----
     using Norm = std::conditional_t<FINE, double, float>;
     Norm sq[4] = {};
 #pragma unroll
     for (int m = 0; m < MG; ++m) {
-        const Norm x = seed[m].x, y = seed[m].y;
+        const float2 seed = sum_of_four(w + 4 * m);
+        const Norm x = seed.x, y = seed.y;
         sq[m] = x * x + y * y;
+        stage_anchor<SF, KS>(stage, 4 * m, 4 * m + 1, 4 * m + 2, lane, seed.x, seed.y);
+    }
+    float bsq;
+    {
+        const float2 total = dim_pair<KS>(lds_B, lane);
+        bsq = sum_over_rows16(row_sum<16>(fmaf(total.x, total.x, total.y * total.y)));
+        stage_anchor<SF, KS>(stage, 7, 3, 11, lane, total.x, total.y);  // (the small terms' products are added up first)
     }
     Norm P0 = row_total(sum_to_groups(sq));                           // ||W||^2 in front of this lane's group
-    asm volatile("" : "+v"(P0));
-    __builtin_amdgcn_sched_barrier(0);
-
-    // ---- one left operand: rows 4 m .. + 2 the terms of group m's seed, rows 7, 3, 11 those of the block total ----
-#pragma unroll
-    for (int m = 0; m < MG; ++m) stage_anchor<SF, KS>(stage, 4 * m, 4 * m + 1, 4 * m + 2, lane, seed[m].x, seed[m].y);
-    stage_anchor<SF, KS>(stage, 7, 3, 11, lane, total.x, total.y);      // (the small terms' products are added up first)
+    asm volatile("" : "+v"(P0), "+v"(bsq));
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
     // <k, anchor>: lanes of group q hold the seed's of their group's tokens, and of the tokens 64 in front
     float c_seed, e_seed, bd;
     {

@@ -1003,6 +1003,72 @@ def test_layer_by_layer_calls_equal_the_batched_call():
                 assert np.array_equal(bits(out.packed_v[a:b]), bits(ref.packed_v[o:o + b - a]))
 
 
+def _raw_and_scores(K, lens):
+    """Raw anomalies [3, L, H, T] and scores [L, H, T] of one call."""
+    L, H, T, d = K.shape
+    code = {torch.bfloat16: nkv.DTYPE_BF16, torch.float16: nkv.DTYPE_F16, torch.float8_e4m3fn: nkv.DTYPE_F8_E4M3}[K.dtype]
+    shape, p = nkv.Shape(L, H, d, d, code, np.concatenate([[0], np.cumsum(lens)]).tolist()), nkv.params_default()
+    ws = torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV)
+    a, s = torch.empty(3, L, H, T, device=DEV), torch.empty(L, H, T, device=DEV)
+    nkv.score_raw(K, shape, p, a, ws)
+    nkv.score(K, shape, p, s, ws)
+    return a, s
+
+
+def _beside(*prompts):
+    """Keys [L, H, N, d] of several prompts, one behind the other."""
+    return torch.cat([k.contiguous().view(torch.uint8) for k in prompts], dim=2).view(prompts[0].dtype)
+
+
+PLACES = [(128, "bf16"), (96, "fp16"), (80, "fp8"), (24, "bf16")]
+
+
+@pytest.mark.parametrize("H", [1, 2, 3])
+@pytest.mark.parametrize("N", [2100, 8200])
+@pytest.mark.parametrize("d,dtype", PLACES)
+def test_scores_of_a_layer_do_not_depend_on_its_place_in_the_call(d, dtype, N, H):
+    """17 and 33 blocks a head: the blocks of layers 1 and 2 have other numbers, modulo the four waves of a workgroup, than in
+    a call of their own.  Bit for bit."""
+    K, _ = _kv(nkv_inputs.small_workload(f"place_{d}_{N}", 3, H, d, [N], dtype=dtype, dv=16))
+    a, s = _raw_and_scores(K, [N])
+    for l in range(3):
+        a1, s1 = _raw_and_scores(K[l:l + 1].contiguous(), [N])
+        assert torch.equal(a1[:, 0], a[:, l]) and torch.equal(s1[0], s[l]), f"layer {l}"
+
+
+@pytest.mark.parametrize("d,dtype", PLACES)
+def test_scores_of_a_prompt_do_not_depend_on_its_place_in_the_batch(d, dtype):
+    """One prompt at four places of a batch, its first block's number 0, 18, 37 and 55: all remainders modulo 4."""
+    N, between = 2100, [100, 200, 100]
+    K, _ = _kv(nkv_inputs.small_workload(f"batch_place_{d}", 1, 2, d, [N] + between, dtype=dtype, dv=16))
+    prompt, rest = K[:, :, :N], K[:, :, N:].split(between, dim=2)
+    batch = _beside(prompt, rest[0], prompt, rest[1], prompt, rest[2], prompt)
+    lens = [N, between[0], N, between[1], N, between[2], N]
+    a1, s1 = _raw_and_scores(prompt.contiguous(), [N])
+    a, s = _raw_and_scores(batch, lens)
+    at = 0
+    for i, n in enumerate(lens):
+        if n == N:
+            assert torch.equal(a[..., at:at + n], a1) and torch.equal(s[..., at:at + n], s1), f"prompt {i}"
+        at += n
+
+
+@pytest.mark.parametrize("N", [4127, 2100, 1000, 130, 17])
+@pytest.mark.parametrize("d,dtype", PLACES)
+def test_a_short_prompts_scores_do_not_depend_on_its_neighbours_blocks(d, dtype, N):
+    """Blocks of at most 128 tokens, alone (two groups of 16 tokens a wave) and behind prompts of longer blocks (four).  Raw
+    anomalies beside a prompt of 32768 tokens too, whose statistics go slice by slice for the whole call."""
+    for other in (4128, 8192, 32768):
+        K, _ = _kv(nkv_inputs.small_workload(f"beside_{d}_{N}", 1, 2, d, [N, other], dtype=dtype, dv=16))
+        a1, s1 = _raw_and_scores(K[:, :, :N].contiguous(), [N])
+        for lens, at in (([N, other], 0), ([other, N], other)):
+            batch = K if at == 0 else _beside(K[:, :, N:], K[:, :, :N])
+            a, s = _raw_and_scores(batch, lens)
+            assert torch.equal(a[..., at:at + N], a1), f"raw, lengths {lens}"
+            if other <= 16384:
+                assert torch.equal(s[..., at:at + N], s1), f"scores, lengths {lens}"
+
+
 def test_recompression_of_a_uniformly_compressed_cache():
     """Decode-time recompression, in the one form the calls express as they are: with a uniform budget
     (safeguard = 1) every head of a layer keeps k0 rows, so the packed cache is a dense [L][H][k0][d] tensor; new rows
