@@ -63,8 +63,11 @@ using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
 using f16x8 = _Float16 __attribute__((ext_vector_type(8)));
 using f32x4 = float __attribute__((ext_vector_type(4)));
 
-constexpr int kNoByte = 0x40000000;              // an offset past any buffer of the pass, also with a token's offset added:
-                                                 // loads read zeros there, stores are dropped
+// An offset past any buffer of the pass (which are shorter than kNoByte - 512 rows): loads read zeros there, stores are dropped.
+// It stays past them with the offset of a token, or of up to 64 tokens in front of the prompt, added, and with itself added (a
+// row's missing piece in a group that the block does not have); offsets are unsigned, so that these sums are defined.
+constexpr uint32_t kNoByte = 0x40000000u;
+static_assert(kNoByte + kNoByte > kNoByte, "the sum of two stays past every buffer (and is a constant: no signed overflow)");
 constexpr int kGroup = 16;                       // tokens per group
 constexpr int kTileWaves = 4;
 
@@ -411,7 +414,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     // groups that the block does not have. ----
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t *>(keys) + it.key_off * ES, 0, N * row_bytes, 0x00020000);
-    int load_off[kLoads];
+    uint32_t load_off[kLoads];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
         const int piece = 64 * i + lane, at = piece % kPieces * 16;
@@ -422,7 +425,7 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
     for (int mm = 0; mm <= MG; ++mm) {
         const int m = (mm + 1) % (MG + 1);                                   // the halo is needed last
         const int q = w + 4 * (m - 1);                                // block-local group index, < 0: halo
-        const int base = q < ng ? (blk_lo + kGroup * q) * row_bytes : kNoByte;
+        const uint32_t base = q < ng ? (uint32_t)((blk_lo + kGroup * q) * row_bytes) : kNoByte;
 #pragma unroll
         // a full block's last 64 tokens (m = 4) are read again, as the next block's halo, and the halo has just been read by
         // the block in front: those stay in the L2; the other rows are marked non-temporal (aux 2)
