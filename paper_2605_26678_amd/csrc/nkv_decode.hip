@@ -53,20 +53,6 @@ template <int LPR> __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
-// the value eight lanes further in the lane's row of 16
-__device__ __forceinline__ float dpp_ror8(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true));
-}
-// v of the lanes n, n + 16, n + 32, n + 48 put together; every lane receives the result
-template <typename F> __device__ __forceinline__ float over_rows16(float v, F op)
-{
-    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-
 // <a, b> over the eight bf16 pairs of two packed 16-byte pieces.  The compiler does not see the register
 // write inside the assembly, so the wait states a DPP read of the result needs are spent here.
 // F16: the sixteen-bit values are fp16 instead of bf16 (the only two places that know).
@@ -177,7 +163,7 @@ __device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, 
 
 // part: per chunk and query head D + 2 floats: running maximum (base-2 logits), sum of weights, weighted values.
 template <int D, int G, bool F16, bool SELF, int CH>
-__global__ __launch_bounds__(kDecThreads, G <= 4 ? 4 : 1) void decode_chunk_kernel(const uint16_t *__restrict__ q,
+__global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_t *__restrict__ q,
                                                                    const uint16_t *__restrict__ pk,
                                                                    const uint16_t *__restrict__ pv,
                                                                    const int64_t *__restrict__ head_off,
@@ -188,8 +174,8 @@ __global__ __launch_bounds__(kDecThreads, G <= 4 ? 4 : 1) void decode_chunk_kern
     constexpr int LPR = D / 8, RPW = 64 / LPR, NW = kDecThreads / 64;
     constexpr int WR = CH / NW, NLD = WR / RPW, U = NLD < 4 ? NLD : 4;   // rows of a wavefront, loads they take, in flight
     constexpr int kRowBytes = D * 2;
-    __shared__ float lds_m[NW][G], lds_l[NW][G];
-    __shared__ __attribute__((aligned(16))) float lds_o[NW][G][D];
+    __shared__ float lds_m[NW * RPW][G], lds_l[NW * RPW][G];
+    __shared__ float lds_o[NW * RPW][G][D];
     const int chunk = blockIdx.x;
     __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
     const int32_t *chunk_off = planned;
@@ -225,18 +211,17 @@ __global__ __launch_bounds__(kDecThreads, G <= 4 ? 4 : 1) void decode_chunk_kern
     const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(pv) + r0 * D, 0,
                                                                          n * kRowBytes, 0x00020000);
     if (w * WR < n) {
-        u32x4 kr[U], vr[U];
-        auto load = [&](const __amdgpu_buffer_rsrc_t &rs, int b0, u32x4 (&x)[U]) {
-            const int at = b0 < NLD ? (w * WR + b0 * RPW + gi) * kRowBytes + c * 16 : CH * kRowBytes;   // (past the end: no access)
-#pragma unroll
-            for (int i = 0; i < U; ++i) x[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, at + i * RPW * kRowBytes, 0, 2);   // aux 2: non-temporal
-        };
-        load(krs, 0, kr);
-        load(vrs, 0, vr);
 #pragma unroll 1
         for (int b0 = 0; b0 < NLD; b0 += U) {
             const int row0 = w * WR + b0 * RPW + gi;                 // this lane group's row in load b0
             if (w * WR + b0 * RPW >= n) break;                       // uniform in the wave
+            u32x4 kr[U], vr[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                kr[i] = __builtin_amdgcn_raw_buffer_load_b128(krs, (row0 + i * RPW) * kRowBytes + c * 16, 0, 2);   // aux 2: non-temporal
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                vr[i] = __builtin_amdgcn_raw_buffer_load_b128(vrs, (row0 + i * RPW) * kRowBytes + c * 16, 0, 2);
             float s[U][G];
 #pragma unroll
             for (int i = 0; i < U; ++i) {
@@ -246,12 +231,6 @@ __global__ __launch_bounds__(kDecThreads, G <= 4 ? 4 : 1) void decode_chunk_kern
                     const float d = group_sum<LPR>(dot8_for_dpp<F16>(kr[i], qv[g]));
                     s[i][g] = valid ? d * scale_log2 : kNone;
                 }
-            }
-            // the next batch's rows are asked for as soon as this one's are used up
-            if constexpr (NLD > U) {
-                __builtin_amdgcn_sched_barrier(0);
-                load(krs, b0 + U, kr);
-                __builtin_amdgcn_sched_barrier(0);
             }
             float p[U][G];
 #pragma unroll
@@ -279,55 +258,28 @@ __global__ __launch_bounds__(kDecThreads, G <= 4 ? 4 : 1) void decode_chunk_kern
 #pragma unroll
                     for (int e = 0; e < 8; ++e) o[g][e] = fmaf(p[i][g], v[e], o[g][e]);
             }
-            if constexpr (NLD > U) {
-                __builtin_amdgcn_sched_barrier(0);
-                load(vrs, b0 + U, vr);
-                __builtin_amdgcn_sched_barrier(0);
-            }
         }
     }
-    // ---- merge the lane groups in registers: rows of 16 lanes change places until row q holds dims 8 c + 2 q, + 1; then the waves ----
-    const int q16 = lane >> 4;
+    // ---- merge the lane groups and waves of the workgroup ----
+    const int slot = w * RPW + gi;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        float mm = m[g];
-        if (LPR == 8) mm = fmaxf(mm, dpp_ror8(mm));
-        mm = over_rows16(mm, [](float a, float b) { return fmaxf(a, b); });
-        const float f = __builtin_amdgcn_exp2f(m[g] - mm);
-        float x[8], ll = f * l[g];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = f * o[g][e];
-        if (LPR == 8) {
-            ll += dpp_ror8(ll);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] += dpp_ror8(x[e]);
+        if (c == 0) {
+            lds_m[slot][g] = m[g];
+            lds_l[slot][g] = l[g];
         }
-        ll = over_rows16(ll, [](float a, float b) { return a + b; });
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {                                 // the lower half of the wave keeps dims 0 .. 3
-            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 4]), false, false);
-            x[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {                                 // its even rows the first two of them
-            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[e]), __float_as_uint(x[e + 2]), false, false);
-            x[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        }
-        if (lane == 0) {
-            lds_m[w][g] = mm;
-            lds_l[w][g] = ll;
-        }
-        *reinterpret_cast<float2 *>(&lds_o[w][g][c * 8 + 2 * q16]) = make_float2(x[0], x[1]);   // (8 lanes a row: twice, the same)
+        *reinterpret_cast<float4 *>(&lds_o[slot][g][c * 8]) = make_float4(o[g][0], o[g][1], o[g][2], o[g][3]);
+        *reinterpret_cast<float4 *>(&lds_o[slot][g][c * 8 + 4]) = make_float4(o[g][4], o[g][5], o[g][6], o[g][7]);
     }
     __syncthreads();
     for (int idx = threadIdx.x; idx < G * D; idx += kDecThreads) {
         const int g = idx / D, e = idx - g * D;
         float mm = kNone;
 #pragma unroll
-        for (int sl = 0; sl < NW; ++sl) mm = fmaxf(mm, lds_m[sl][g]);
+        for (int sl = 0; sl < NW * RPW; ++sl) mm = fmaxf(mm, lds_m[sl][g]);
         float ll = 0.f, oo = 0.f;
 #pragma unroll
-        for (int sl = 0; sl < NW; ++sl) {
+        for (int sl = 0; sl < NW * RPW; ++sl) {
             const float f = __builtin_amdgcn_exp2f(lds_m[sl][g] - mm);
             ll = fmaf(f, lds_l[sl][g], ll);
             oo = fmaf(f, lds_o[sl][g][e], oo);
