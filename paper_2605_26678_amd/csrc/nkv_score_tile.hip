@@ -556,14 +556,12 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         sq[m] = x * x + y * y;
         stage_anchor<SF, KS>(stage, 4 * m, 4 * m + 1, 4 * m + 2, lane, seed.x, seed.y);
     }
-    float bsq;
     {
         const float2 total = dim_pair<KS>(lds_B, lane);
-        bsq = sum_over_rows16(row_sum<16>(fmaf(total.x, total.x, total.y * total.y)));
         stage_anchor<SF, KS>(stage, 7, 3, 11, lane, total.x, total.y);  // (the small terms' products are added up first)
     }
     Norm P0 = row_total(sum_to_groups(sq));                           // ||W||^2 in front of this lane's group
-    asm volatile("" : "+v"(P0), "+v"(bsq));
+    asm volatile("" : "+v"(P0));
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_sched_barrier(0);
     // <k, anchor>: lanes of group q hold the seed's of their group's tokens, and of the tokens 64 in front
@@ -654,6 +652,8 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         const float c = c_seed + c_in, e = e_seed + e_in;             // <k_i, W_i>, <k_i', W_i>
         const Norm dd = 2.f * (wt * c - wp * e) + (2.f * wt * wp * xx - (wt * wt * ss + wp * wp * ssp));
         const float Pn = (float)(P0 + row_prefix_sum(dd));
+        const float2 total = dim_pair<KS>(lds_B, lane);               // (again: its square would be one register too many until here)
+        const float bsq = sum_over_rows16(row_sum<16>(fmaf(total.x, total.x, total.y * total.y)));
         const float ac = token_cos<FINE>(c, wt, ss, Pn), ae = token_cos<FINE>(bd, wt, ss, bsq);
         const __amdgpu_buffer_rsrc_t out_c = __builtin_amdgcn_make_buffer_rsrc(a_raw + 2 * rows + row0, 0, blk_hi * 4, 0x00020000);
         const __amdgpu_buffer_rsrc_t out_e = __builtin_amdgcn_make_buffer_rsrc(a_raw + rows + row0, 0, blk_hi * 4, 0x00020000);
