@@ -509,23 +509,25 @@ void scan_tile_kernel(const uint8_t *__restrict__ keys, int d, const TileItem *_
         const float2 t0 = dim_pair<KS>(lds_T[r], lane), t1 = dim_pair<KS>(lds_T[r + 1], lane), t2 = dim_pair<KS>(lds_T[r + 2], lane), t3 = dim_pair<KS>(lds_T[r + 3], lane);
         return make_float2(((t0.x + t1.x) + t2.x) + t3.x, ((t0.y + t1.y) + t2.y) + t3.y);
     };
-    // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1.  One wave adds it up, four groups at a time
-    // from the first on, posts it to the unit's sum and leaves it to the others in LDS.  The order is the same whichever wave that
-    // is and for both MG (groups that the block does not have are zeros), so a unit's scores depend neither on where it lies in
-    // the call nor on its neighbours' blocks.  (Every wave for itself, starting with its own seeds, gave each wave its own
-    // rounding and took as long.  Score calls this way and that way: 36 layers x 8 heads x 32768 tokens 620 and 625 us, 32 heads x
-    // ragged x head dim 96 112 and 114.) ----
+    // ---- block total = episodic anchor (up to length); lane: dims 2 lane, 2 lane + 1.  One wave adds the groups up in order, posts
+    // the total to the unit's sum and leaves it to the others in LDS.  The order is the same whichever wave that is and for both
+    // MG (groups that the block does not have are zeros), so a unit's scores depend neither on where it lies in the call nor on
+    // its neighbours' blocks.  (Every wave for itself, starting with its own seeds, gave each wave its own rounding and took
+    // longer: 36 layers x 8 heads x 32768 tokens 627 us and 622 this way, 32 heads x ragged x head dim 96 113 and 110.)
+    // In 64 bits, because groups may cancel: rms error of a_e for keys whose common direction, 60 times the spread, changes
+    // sign every 64 tokens, 3.4e-7 added up in 32 bits and 2.5e-7 so (head dim 128; other keys 2.4e-8 both), for 0.5 % of the scan. ----
     unsigned long long *acc_mine = acc_group + (int64_t)it.group * D;
     const bool poster = w == (it.id & (NW - 1));
     unsigned long long after0 = 0ull, after1 = 0ull;                  // the accumulators right after this block's add
     if (poster) {
-        float2 total = sum_of_four(4);
+        double tx = 0., ty = 0.;
 #pragma unroll
-        for (int m = 2; m <= MG; ++m) {
-            const float2 t = sum_of_four(4 * m);
-            total.x += t.x;
-            total.y += t.y;
+        for (int q = 0; q < 4 * MG; ++q) {
+            const float2 c = dim_pair<KS>(lds_T[4 + q], lane);
+            tx += (double)c.x;
+            ty += (double)c.y;
         }
+        const float2 total = make_float2((float)tx, (float)ty);
         if (KS == 4 || lane < D / 2) {
             const unsigned long long t0 = accum_term(total.x), t1 = accum_term(total.y);
             after0 = __hip_atomic_fetch_add(acc_mine + lane, t0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + t0;
