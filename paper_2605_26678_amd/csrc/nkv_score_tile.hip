@@ -31,14 +31,16 @@
 // sum has arrived.  A 16 x 16 result leaves lane (q, n) with column n, rows 4q .. 4q+3: sums over rows are four
 // multiply-adds per lane, and the four groups' partial sums then change places across the lanes so that lane (q, n) ends up
 // with group q's token n: one square root, one store an anomaly and so on for 64 tokens.  In calls whose blocks have at most
-// 128 tokens no wave has more than two groups: an instance of its own (MG = 2, 94 registers: five workgroups a CU).
+// 128 tokens no wave has more than two groups: an instance of its own (MG = 2; 94 registers at head dim 128, five workgroups a
+// CU, or 98 and four where FINE).
 //
-// What bounds it.  36 layers x 8 heads x 32768 tokens of head dim 128: 530 us (555 with the tokens' arithmetic group by
-// group, dot-product instructions for the norms and unpacking on the vector unit: 1480 vector instructions per 64 tokens,
-// 890 now), keys at 4.6 TB/s, where reading them alone takes 350 us.  No unit is saturated: of a workgroup's 28 000 cycles
-// 4 400 pass until its keys are there, 16 000 in dependent phases that share the vector unit with three other workgroups,
-// 6 000 in waiting for the slowest of the unit's 128 workgroups.  What was measured instead and is slower: workgroups that
-// stay and bring the next block's keys to LDS meanwhile, with a_s one block later, two of four waves (612 us) or of eight
+// What bounds it.  36 layers x 8 heads x 32768 tokens of head dim 128: 531 us (552 with the tokens' arithmetic group by
+// group, dot-product instructions for the norms and unpacking on the vector unit: 1484 vector instructions per 64 tokens,
+// 942 now, 148 of them matrix products), keys at 4.6 TB/s, where reading them alone takes 350 us.  No unit is saturated: of a
+// workgroup's 27 500 cycles 5 500 pass until its first group is staged, 14 600 in dependent phases that share the vector unit with
+// three other workgroups (norms and group sums 5 600, block total and halo group 4 300, anchors and windows 4 800), 1 300 in the
+// stable products, and 6 100 in waiting for the slowest of the unit's 128 workgroups.  What was measured instead and is slower:
+// workgroups that stay and bring the next block's keys to LDS meanwhile, with a_s one block later, two of four waves (612 us) or of eight
 // (790 us) a CU: half the waves, or half the tokens a wave, hide less of the chains than the loads and waits cost.
 //
 // Protocol.  A block's workgroup adds its total to the unit's self-counting accumulators (nkv_scan_common.h) as
@@ -795,8 +797,11 @@ struct TileLaunch {
     // 128 and units of up to 256 blocks.  Root mean square errors of a_s, a_e, a_c in 1e-8, keys of the benchmark's kind: head dim 96, 8192
     // tokens 2.4, 3.3, 2.8 before, 2.6, 2.9, 3.1 without and 2.4, 2.7, 2.9 with FINE; head dim 128, 100 000 tokens 2.3, 2.2,
     // 2.6, then 2.5, 2.7, 2.9 and 2.2, 2.5, 2.7 (6 % of the scan's time); 8-bit keys 2.1, 2.2, 2.5 and 2.0, 2.2, 2.5 without.
-    // (Those figures are from norms by dot products and terms added up largest first.  With norms in two halves and the small
-    // terms first: head dim 96, 2.4, 2.6, 2.7; 128, 100 000 tokens 2.1, 2.4, 2.5; 8-bit 1.8, 2.1, 2.3; bf16, 128: 2.4, 2.6, 2.8.)
+    // (Those figures are from norms by dot products and terms added up largest first.  With norms in two halves, the small
+    // terms first and the block's groups in 64 bits: head dim 96, 2.4, 2.6, 2.6; 128, 100 000 tokens 1.7, 2.3, 2.5 (1.8, 2.5, 2.7 on the
+    // same keys before that); 8-bit 2.0, 2.1, 2.3; bf16, 128, 65 536 tokens 2.0, 2.6, 2.7.)
+    // Keys that cancel inside the window cost more: a common direction 60 times the spread that changes sign every 64 tokens leaves
+    // an rms error of a_c of 5.4e-7 at head dim 128, 2.7e-7 with FINE (96: 3.1e-7), where the vector scan has 0.9e-7.
     template <int KF> void run_format() const
     {
         constexpr bool F = KF != kKeyF8;

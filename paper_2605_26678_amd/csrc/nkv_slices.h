@@ -133,8 +133,8 @@ __global__ __launch_bounds__(TH) void slice_hist_kernel(const float *__restrict_
 
 // Copies the lists of a unit's S slices (segment s: `count(s)` keys from seg + s * kSeg on) one behind the other to
 // keys[0 .. cap), by one wavefront with the loads of the next four segments in flight, the first four's while the counts are
-// on their way; returns the number of keys, or -1 if a
-// segment or the list overflows.  before: keys of the slices in front of slice `own`.
+// on their way; returns the number of keys, or -1 if a segment or the list overflows.  before: keys of the slices in front of
+// slice `own`.
 template <typename F>
 __device__ __forceinline__ int gather_segments(const uint32_t *__restrict__ seg, int S, F count, uint32_t *keys, int cap, int own,
                                                int &before)
