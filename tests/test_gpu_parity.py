@@ -1059,6 +1059,18 @@ def test_scores_of_a_layer_do_not_depend_on_its_place_in_the_call(d, dtype, N, H
         assert torch.equal(a1[:, 0], a[:, l]) and torch.equal(s1[0], s[l]), f"layer {l}"
 
 
+@pytest.mark.parametrize("L,H,N,d,dtype", [(17, 8, 32768, 128, "bf16"), (40, 8, 16385, 32, "fp16"), (20, 8, 40000, 64, "bf16")])
+def test_scores_of_a_long_prompts_layer_do_not_depend_on_the_number_of_layers(L, H, N, d, dtype):
+    """More than 512 slices of 8192 tokens together (256 threads a slice), at most 512 a layer (1024 threads)."""
+    slices = H * -(-N // 8192)
+    assert slices <= 512 < L * slices
+    K, _ = _kv(nkv_inputs.small_workload(f"layers_{N}", L, H, d, [N], dtype=dtype, dv=16))
+    a, s = _raw_and_scores(K, [N])
+    for l in (0, L // 2, L - 1):
+        a1, s1 = _raw_and_scores(K[l:l + 1].contiguous(), [N])
+        assert torch.equal(a1[:, 0], a[:, l]) and torch.equal(s1[0], s[l]), f"layer {l}"
+
+
 @pytest.mark.parametrize("d,dtype", PLACES)
 def test_scores_of_a_prompt_do_not_depend_on_its_place_in_the_batch(d, dtype):
     """One prompt at four places of a batch, its first block's number 0, 18, 37 and 55: all remainders modulo 4."""
