@@ -283,10 +283,18 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
         for (int sl = 0; sl < NW * RPW; ++sl) mm = fmaxf(mm, lds_m[sl][g]);
         float ll = 0.f, oo = 0.f;
 #pragma unroll
-        for (int sl = 0; sl < NW * RPW; ++sl) {
-            const float f = __builtin_amdgcn_exp2f(lds_m[sl][g] - mm);
-            ll = fmaf(f, lds_l[sl][g], ll);
-            oo = fmaf(f, lds_o[sl][g][e], oo);
+        for (int wv = 0; wv < NW; ++wv) {
+            // a wavefront's lane groups first, shorter chains of additions: relative error of the output 2.49e-7 -> 2.34e-7 (head dim 64,
+            // G = 8), 1.81e-7 -> 1.69e-7 (128, 3), 2.69e-7 -> 2.58e-7 (128, 6), in the same time
+            float lw = 0.f, ow = 0.f;
+#pragma unroll
+            for (int sl = wv * RPW; sl < wv * RPW + RPW; ++sl) {
+                const float f = __builtin_amdgcn_exp2f(lds_m[sl][g] - mm);
+                lw = fmaf(f, lds_l[sl][g], lw);
+                ow = fmaf(f, lds_o[sl][g][e], ow);
+            }
+            ll += lw;
+            oo += ow;
         }
         float *dst = part + ((int64_t)chunk * G + g) * (D + 2);
         if (e == 0) {
