@@ -5,32 +5,37 @@
 // For unit u = (prompt, layer, KV head) and the G query heads that read it (grouped-query attention, query
 // head j reads KV head j / G):   out_j = sum_i softmax_i(scale <q_j, k_i>) v_i   over the unit's rows.
 //
-// The work is one read of every retained K and V row, so it is bound by HBM.  Units have different lengths
-// (head-wise budgets), so they are cut into chunks of 256 rows and one workgroup handles one chunk for all G
-// query heads at once (K and V are read once, not G times):
-//   decode_plan_kernel    : chunk_off[u] = chunks before unit u (exclusive scan of ceil(len_u / 256)); where the chunks are
-//                           of 64 rows (few chunks and units) every workgroup of the next kernel works its place out
-//                           itself and the first one leaves the offsets for the last kernel (SELF: one launch fewer,
-//                           17 -> 13 us for 64 units of 204 to 1638 rows; with thousands of chunks it costs more than it saves)
-//   decode_chunk_kernel   : per chunk, running-maximum softmax in base 2: (m, l, o[0..D)) per query head
-//   decode_combine_kernel : per (unit, query head) merges the chunks' partial results
-// Lane layout in decode_chunk_kernel as in the scoring kernel: a row is spread over D/8 lanes (16 bytes each),
+// The work is one read of every retained K and V row, so it is bound by HBM.  A workgroup handles rows of one unit for all G
+// query heads at once (K and V are read once, not G times).  Units have different lengths (head-wise budgets) that the host
+// does not know, and what a workgroup spends on finding its rows, merging its lanes' results and waiting for its stores costs as much
+// as 100 to 200 rows do, so large calls give every workgroup as many rows as there are for it:
+//   decode_run_kernel     : stretches of the cache of the same length, one for every workgroup the device holds, across the units' ends
+//   decode_piece_kernel   : pieces of 256 rows of a unit where units are short, of 64 rows where there are few
+//   decode_combine_kernel : per (unit, query head) merges the partial results: per query head running maximum, sum, weighted values
+//                           (m, l, o[0..D)) of a running-maximum softmax in base 2
+// All three work out from head_off which unit a piece belongs to: no kernel plans in front.  As chunks of 256 rows that a kernel of
+// its own numbered, 288 units of 8192 rows, head dim 128, G = 4, took 217 us (chunk kernel 5.9 TB/s, planning 4 us), now 202; 288 units of
+// 615 rows 29 and 26; 64 units of 768 rows, G = 8 20.8 and 18.4.  Reading the same rows without arithmetic or merging takes 179.
+// Lane layout in attend as in the scoring kernel: a row is spread over D/8 lanes (16 bytes each),
 // one wave load fetches 64/(D/8) rows; <q, k> uses the packed 16-bit dot instruction on the stored bits (exact
 // products, fp32 accumulation) and a DPP sum over the lanes of a row; every group of D/8 lanes keeps its own
 // running (m, l, o) for the rows it sees, rescaled once per batch of four rows, and the groups and waves are
-// merged through LDS at the end of the chunk.
+// merged through LDS at the end.
 // Anything outside bf16 / fp16 with d = dv in {64, 128} and G <= 8 goes to decode_generic_kernel (one workgroup per
 // unit and query head, no scratch).
 #include "nkv_device.h"
 
+#include <stdlib.h>
+
 #include <algorithm>
+#include <type_traits>
 
 namespace nkv {
 namespace {
 
 // Rows per workgroup: 256, or 64 where a call has too few rows to fill the chip with workgroups of 256 (a wavefront then
 // has one batch of rows instead of four in turn).
-constexpr int kChunk = 256, kSmallChunk = 64;
+constexpr int kChunk = 256, kSmallChunk = 64, kSmallUnits = 256;
 // Chunks per unit from which 512 threads combine them instead of one per dimension (64 units of G = 3, head dim 64: 7 chunks a
 // unit 8.0 -> 7.1 us; 256 units of G = 8, 300 rows in two chunks 21.4 us with 512, 19.4 with 64).
 constexpr int kManyChunks = 4;
@@ -78,128 +83,43 @@ template <bool F16> __device__ __forceinline__ float dot8_for_dpp(const u32x4 &a
     return acc;
 }
 
-template <bool F16> __device__ __forceinline__ void unpack8(const u32x4 &r, float k[8])
+template <bool F16> __device__ __forceinline__ void unpack2(uint32_t r, float (&v)[2])
 {
     if constexpr (F16) {
         using f16x2 = _Float16 __attribute__((ext_vector_type(2)));
-        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const f16x2 v = __builtin_bit_cast(f16x2, w[i]);
-            k[2 * i] = (float)v.x;
-            k[2 * i + 1] = (float)v.y;
-        }
+        const f16x2 x = __builtin_bit_cast(f16x2, r);
+        v[0] = (float)x.x;
+        v[1] = (float)x.y;
     } else {
-        k[0] = __uint_as_float(r.x << 16); k[1] = __uint_as_float(r.x & 0xffff0000u);
-        k[2] = __uint_as_float(r.y << 16); k[3] = __uint_as_float(r.y & 0xffff0000u);
-        k[4] = __uint_as_float(r.z << 16); k[5] = __uint_as_float(r.z & 0xffff0000u);
-        k[6] = __uint_as_float(r.w << 16); k[7] = __uint_as_float(r.w & 0xffff0000u);
+        v[0] = __uint_as_float(r << 16);
+        v[1] = __uint_as_float(r & 0xffff0000u);
     }
 }
 
 __device__ __forceinline__ int64_t clamp_row(int64_t r, int64_t rows) { return r < 0 ? 0 : (r > rows ? rows : r); }
 
-// One workgroup of 1024 threads.  chunk_off has n_units + 1 entries.
-__global__ __launch_bounds__(1024) void decode_plan_kernel(const int64_t *__restrict__ head_off, int n_units,
-                                                           int64_t rows, int32_t *__restrict__ chunk_off)
-{
-    __shared__ int32_t sums[16];                                      // per-wave totals
-    const int per = (n_units + 1023) / 1024;
-    const int u0 = min(threadIdx.x * per, n_units), u1 = min(u0 + per, n_units);
-    int32_t mine = 0;
-    for (int u = u0; u < u1; ++u) {
-        const int64_t len = clamp_row(head_off[u + 1], rows) - clamp_row(head_off[u], rows);
-        mine += (int32_t)((max(len, (int64_t)0) + kChunk - 1) / kChunk);
-    }
-    // exclusive scan of the 1024 per-thread counts: inside every wave by shuffles, then over the 16 wave totals
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int32_t incl = (int32_t)wave_prefix_sum((uint32_t)mine);
-    if (lane == 63) sums[wv] = incl;
-    __syncthreads();
-    int32_t before = 0, total = 0;
-    for (int i = 0; i < 16; ++i) {
-        const int32_t t = sums[i];
-        if (i < wv) before += t;
-        total += t;
-    }
-    if (threadIdx.x == 0) chunk_off[n_units] = total;
-    int32_t run = before + incl - mine;
-    for (int u = u0; u < u1; ++u) {
-        chunk_off[u] = run;
-        const int64_t len = clamp_row(head_off[u + 1], rows) - clamp_row(head_off[u], rows);
-        run += (int32_t)((max(len, (int64_t)0) + kChunk - 1) / kChunk);
-    }
-}
-
-// Few units: chunk_off of units 0 .. n_units (n_units <= kSelfUnits) to LDS, by a whole workgroup of TH threads.
-constexpr int kSelfUnits = 256;
-template <int TH, int CH>
-__device__ __forceinline__ void plan_here(const int64_t *__restrict__ head_off, int n_units, int64_t rows, int32_t *chunk_off)
-{
-    constexpr int PER = (kSelfUnits + TH - 1) / TH, NW = TH / 64;
-    __shared__ uint32_t wtot[NW];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    uint32_t c[PER], mine = 0u;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int u = tid * PER + i;
-        const int64_t a = clamp_row(head_off[min(u, n_units)], rows), b = clamp_row(head_off[min(u + 1, n_units)], rows);
-        c[i] = (uint32_t)((max(b - a, (int64_t)0) + CH - 1) / CH);
-        mine += c[i];
-    }
-    const uint32_t incl = wave_prefix_sum(mine);
-    if (lane == 63) wtot[w] = incl;
-    __syncthreads();
-    uint32_t run = incl - mine;
-    for (int i = 0; i < w; ++i) run += wtot[i];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        if (tid * PER + i <= min(n_units, kSelfUnits - 1)) chunk_off[tid * PER + i] = (int32_t)run;
-        run += c[i];
-    }
-    if (tid == TH - 1) chunk_off[kSelfUnits] = (int32_t)run;          // (only read if n_units == kSelfUnits)
-    __syncthreads();
-}
-
-// part: per chunk and query head D + 2 floats: running maximum (base-2 logits), sum of weights, weighted values.
+// One workgroup's pass over the n >= 1 rows of a unit from row r0 on, for the G heads whose queries start at q: D + 2 floats a head to
+// part: running maximum (base-2 logits), sum of weights, weighted values.  A wavefront takes U loads of rows at a time, the four
+// wavefronts in turn.  MOST: n is no larger (0: any n).
 // Measured instead: the next batch's rows asked for as soon as a batch's are used up, and the lane groups merged in registers
 // (permlane swaps) in front of the waves.  The registers that this holds cost waves: whole calls of 2 359 296 rows, us as it is and
 // that way, head dim 128 G = 3 213 / 210, 4 220 / 219, 6 253 / 277, 8 326 / 326; head dim 64 G = 3 105 / 103, 4 112 / 119,
 // 6 144 / 162, 8 192 / 212; small calls 11.0 / 11.2.
-template <int D, int G, bool F16, bool SELF, int CH>
-__global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_t *__restrict__ q,
-                                                                   const uint16_t *__restrict__ pk,
-                                                                   const uint16_t *__restrict__ pv,
-                                                                   const int64_t *__restrict__ head_off,
-                                                                   int32_t *planned, int n_units,
-                                                                   int64_t rows, float scale_log2,
-                                                                   float *__restrict__ part)
+template <int D, int G, bool F16, int MOST>
+__device__ __forceinline__ void attend(const uint16_t *__restrict__ q, const uint16_t *__restrict__ pk, const uint16_t *__restrict__ pv,
+                                       int64_t r0, int n, float scale_log2, float *__restrict__ part)
 {
     constexpr int LPR = D / 8, RPW = 64 / LPR, NW = kDecThreads / 64;
-    constexpr int WR = CH / NW, NLD = WR / RPW, U = NLD < 4 ? NLD : 4;   // rows of a wavefront, loads they take, in flight
+    constexpr int U = MOST > 0 && MOST < 4 * NW * RPW ? MOST / (NW * RPW) : 4;
+    constexpr int STRETCH = U * RPW, STEP = NW * STRETCH;            // rows of a wavefront at a time, of the workgroup
     constexpr int kRowBytes = D * 2;
     __shared__ float lds_m[NW * RPW][G], lds_l[NW * RPW][G];
     __shared__ float lds_o[NW * RPW][G][D];
-    const int chunk = blockIdx.x;
-    __shared__ int32_t lds_off[SELF ? kSelfUnits + 1 : 1];
-    const int32_t *chunk_off = planned;
-    if constexpr (SELF) {
-        plan_here<kDecThreads, CH>(head_off, n_units, rows, lds_off);
-        chunk_off = lds_off;
-        if (chunk == 0)                                               // for the combining kernel
-            for (int u = threadIdx.x; u <= n_units; u += kDecThreads) planned[u] = lds_off[u];
-    }
-    if (chunk >= chunk_off[n_units]) return;
-    const int u = wave_search(chunk_off, n_units, chunk), ci = chunk - chunk_off[u];
-    const int64_t first = clamp_row(head_off[u], rows), len = clamp_row(head_off[u + 1], rows) - first;
-    const int n = (int)min((int64_t)CH, len - (int64_t)ci * CH);     // rows of this chunk, >= 1
-    const int64_t r0 = first + (int64_t)ci * CH;
-
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, gi = lane / LPR, c = lane % LPR;
     u32x4 qv[G];
 #pragma unroll
     for (int g = 0; g < G; ++g)
-        qv[g] = *reinterpret_cast<const u32x4 *>(q + ((int64_t)u * G + g) * D + c * 8);
+        qv[g] = *reinterpret_cast<const u32x4 *>(q + (int64_t)g * D + c * 8);
 
     float m[G], l[G], o[G][8];
 #pragma unroll
@@ -209,16 +129,15 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
     }
-    // rows past the end of the chunk read as zeros and get weight 0
+    // rows past the end of the run read as zeros and get weight 0
     const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(pk) + r0 * D, 0,
                                                                          n * kRowBytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(pv) + r0 * D, 0,
                                                                          n * kRowBytes, 0x00020000);
-    if (w * WR < n) {
+    {
 #pragma unroll 1
-        for (int b0 = 0; b0 < NLD; b0 += U) {
-            const int row0 = w * WR + b0 * RPW + gi;                 // this lane group's row in load b0
-            if (w * WR + b0 * RPW >= n) break;                       // uniform in the wave
+        for (int at = w * STRETCH; at < n; at += STEP) {             // uniform in the wave
+            const int row0 = at + gi;                                // this lane group's row in the first load
             u32x4 kr[U], vr[U];
 #pragma unroll
             for (int i = 0; i < U; ++i)
@@ -236,31 +155,60 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
                     s[i][g] = valid ? d * scale_log2 : kNone;
                 }
             }
-            float p[U][G];
+            // Long sums (MOST = 0): a batch's terms are added up by themselves, then to what there was before: as many instructions as
+            // one by one and a quarter of the roundings (error of the output, 288 units of 8192 rows, G = 4, in 1e-7: 2.6, one by one 3.3,
+            // one by one in pieces of 256 rows 2.8).  Of pieces, calls of G = 5 to 8 would take 4 % longer that way.
+            constexpr bool BATCH = MOST == 0;
+            float p[U][G], corr[G];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 float mb = m[g];
 #pragma unroll
                 for (int i = 0; i < U; ++i) mb = fmaxf(mb, s[i][g]);
-                const float corr = __builtin_amdgcn_exp2f(m[g] - mb);    // 1 if nothing changed, 0 from kNone
+                corr[g] = __builtin_amdgcn_exp2f(m[g] - mb);         // 1 if nothing changed, 0 from kNone
                 m[g] = mb;
-                l[g] *= corr;
+                float lb = 0.f;
+                if (!BATCH) {
+                    l[g] *= corr[g];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[g][e] *= corr;
+                    for (int e = 0; e < 8; ++e) o[g][e] *= corr[g];
+                }
 #pragma unroll
                 for (int i = 0; i < U; ++i) {
                     p[i][g] = row0 + i * RPW < n ? __builtin_amdgcn_exp2f(s[i][g] - mb) : 0.f;
-                    l[g] += p[i][g];
+                    if (BATCH) lb = i == 0 ? p[i][g] : lb + p[i][g];
+                    else l[g] += p[i][g];
                 }
+                if (BATCH) l[g] = fmaf(l[g], corr[g], lb);
+            }
+            if constexpr (!BATCH) {
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    float v[8];
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) unpack2<F16>(vr[i][e / 2], *reinterpret_cast<float (*)[2]>(&v[e]));
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) o[g][e] = fmaf(p[i][g], v[e], o[g][e]);
+                }
+                if (MOST == STEP) break;                             // (and no loop)
+                continue;
             }
 #pragma unroll
-            for (int i = 0; i < U; ++i) {
-                float v[8];
-                unpack8<F16>(vr[i], v);
+            for (int e = 0; e < 8; e += 2) {
+                float v[U][2];
+#pragma unroll
+                for (int i = 0; i < U; ++i) unpack2<F16>(vr[i][e / 2], v[i]);
 #pragma unroll
                 for (int g = 0; g < G; ++g)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) o[g][e] = fmaf(p[i][g], v[e], o[g][e]);
+                    for (int h = 0; h < 2; ++h) {
+                        float t = p[0][g] * v[0][h];
+#pragma unroll
+                        for (int i = 1; i < U; ++i) t = fmaf(p[i][g], v[i][h], t);
+                        o[g][e + h] = fmaf(o[g][e + h], corr[g], t);
+                    }
             }
         }
     }
@@ -296,7 +244,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
             ll += lw;
             oo += ow;
         }
-        float *dst = part + ((int64_t)chunk * G + g) * (D + 2);
+        float *dst = part + g * (D + 2);
         if (e == 0) {
             dst[0] = mm;
             dst[1] = ll;
@@ -305,16 +253,60 @@ __global__ __launch_bounds__(kDecThreads) void decode_chunk_kernel(const uint16_
     }
 }
 
+// Pieces of CH rows of a unit, the first from its first row on.  Unit u's are numbered from off[u] / CH + u on, which leaves room for
+// all of them and ascends, so nothing needs to be planned: a search finds a piece's unit.  grid: as many numbers as there are.
+template <int D, int G, bool F16, int CH>
+__global__ __launch_bounds__(kDecThreads) void decode_piece_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ pk,
+                                                                   const uint16_t *__restrict__ pv, const int64_t *__restrict__ head_off,
+                                                                   int n_units, int64_t rows, float scale_log2, float *__restrict__ part)
+{
+    const int piece = blockIdx.x;
+    const int u = wave_search_fn(n_units, (int64_t)piece, [&](int i) { return i == 0 ? (int64_t)0 : clamp_row(head_off[i], rows) / CH + i; });
+    const int64_t first = clamp_row(head_off[u], rows), a = first + (piece - u - first / CH) * CH, b = min(clamp_row(head_off[u + 1], rows), a + CH);
+    if (first <= a && a < b) attend<D, G, F16, CH>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + (int64_t)piece * G * (D + 2));
+}
+
+// Long units: the cache is cut into stretches of `run` rows, whichever units they belong to, so that every workgroup of the call has
+// the same work.  What stretch i holds of unit u is piece i + u (no two share a number: both grow with the row).  grid: stretches.
+template <int D, int G, bool F16>
+__global__ __launch_bounds__(kDecThreads) void decode_run_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ pk,
+                                                                 const uint16_t *__restrict__ pv, const int64_t *__restrict__ head_off,
+                                                                 int n_units, int64_t rows, int run, float scale_log2,
+                                                                 float *__restrict__ part)
+{
+    const int64_t lo = max((int64_t)blockIdx.x * run, clamp_row(head_off[0], rows));
+    const int64_t hi = min((int64_t)blockIdx.x * run + run, clamp_row(head_off[n_units], rows));
+    if (lo >= hi) return;
+    for (int u = wave_search(head_off, n_units, lo); u < n_units; ++u) {
+        const int64_t a = max(clamp_row(head_off[u], rows), lo), b = min(clamp_row(head_off[u + 1], rows), hi);
+        if (a < b) attend<D, G, F16, 0>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + ((int64_t)blockIdx.x + u) * G * (D + 2));
+        if (b >= hi) break;
+        __syncthreads();                                              // (the merge's memory is used anew)
+    }
+}
+
+// Where the partial results of unit u lie: [x, y).  cut: < 0: pieces of -cut rows of a unit; > 0: stretches of cut rows (multiples of
+// 64; rows are fewer than 2^38).
+__device__ __forceinline__ int2 unit_pieces(const int64_t *head_off, int u, int64_t rows, int cut)
+{
+    const int64_t a = clamp_row(head_off[u], rows), b = clamp_row(head_off[u + 1], rows);
+    const uint32_t per = (uint32_t)abs(cut) / 64u;
+    const int x = (int)((uint32_t)(a / 64) / per) + u;
+    if (a >= b) return make_int2(x, x);
+    return make_int2(x, cut < 0 ? x + (int)((uint32_t)((b - a + 63) / 64 + per - 1) / per) : (int)((uint32_t)((b - 1) / 64) / per) + u + 1);
+}
+
 // grid: n_units * G workgroups of TH threads: TH / D slices of the unit's chunks, added up in the slices' order.
 template <int D, int TH>
-__global__ __launch_bounds__(TH) void decode_combine_kernel(const float *__restrict__ part, const int32_t *__restrict__ chunk_off, int G,
-                                                            float *__restrict__ out, float *__restrict__ lse)
+__global__ __launch_bounds__(TH) void decode_combine_kernel(const float *__restrict__ part, const int64_t *__restrict__ head_off,
+                                                            int64_t rows, int cut, int G, float *__restrict__ out, float *__restrict__ lse)
 {
     constexpr int NS = TH / D, NW = TH / 64, U = 4;
     __shared__ float red[NW];
     __shared__ float lds_l[NS], lds_o[NS][D];
     const int u = blockIdx.x / G, g = blockIdx.x - u * G, tid = threadIdx.x, e = tid % D, sl = tid / D;
-    const int c0 = chunk_off[u], c1 = chunk_off[u + 1];
+    const int2 pieces = unit_pieces(head_off, u, rows, cut);
+    const int c0 = pieces.x, c1 = pieces.y;
     // the largest running maximum: chunks spread over the threads, then one reduction
     float mm = kNone;
     for (int ch = c0 + tid; ch < c1; ch += TH) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
@@ -414,42 +406,87 @@ int64_t max_chunks(int64_t n_units, int64_t rows, int chunk) { return rows / chu
 // the chip holds at once (what a chunk merges, 16 or 32 partial results of G heads, takes 8 KB of LDS a head), if the caller's
 // scratch holds their partial results (it need not, see decode_ws_bytes).  128 units of G = 8, head dim 128, 700 rows: 34 us with
 // 1528 chunks of 64 rows, 27 with 478 of 256; 64 units: 19.7 with 704 of 64, 20.4 with 256 rows; 64 units of 300 rows 13 against 20.
+// (Those figures are from before the planning kernel went: 2 to 4 us less for 256 rows, up to 0.8 for 64.)
 int64_t small_chunks_limit(int G) { return 256 * std::min(8, 160 * 1024 / (8448 * G + 1032)); }
 bool decode_small(int64_t n_units, int64_t rows, int G)
 {
-    return n_units <= kSelfUnits && max_chunks(n_units, rows, kChunk) <= 512 && max_chunks(n_units, rows, kSmallChunk) <= small_chunks_limit(G);
+    return n_units <= kSmallUnits && max_chunks(n_units, rows, kChunk) <= 512 && max_chunks(n_units, rows, kSmallChunk) <= small_chunks_limit(G);
 }
 
+// (The units' words in front of the partial results are room that is not used: sizes that were asked for once stay what they are.)
 size_t part_offset(int64_t n_units) { return ((size_t)(n_units + 1) * 4 + 255) / 256 * 256; }
 size_t ws_for(int64_t chunks, int64_t n_units, int G, int d) { return part_offset(n_units) + (size_t)chunks * G * (d + 2) * 4; }
+
+// Workgroups of the kernel that the device holds at once.
+template <auto KERNEL> int resident_workgroups()
+{
+    static int cached = 0;                                           // (one per kernel; benign if raced)
+    if (cached == 0) {
+        int per_cu = 0, dev = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, kDecThreads, 0) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu * cus <= 0)
+            return 1024;
+        cached = per_cu * cus;
+    }
+    return cached;
+}
+
+// Stretches where every workgroup that the device holds gets 256 rows and more, and the units are long against a stretch or against
+// a piece.  Whole calls, chunks of 256 rows with a planning kernel in front (as it was) / pieces / stretches, us: 288 units
+// of 8192 rows, head dim 128, G = 1 201 / 205 / 190, 4 217 / 222 / 202, 8 323 / 325 / 276, head dim 64, G = 8 192 / 190 / 155; 288 units of
+// 750 rows, 128, G = 8 45.0 / 46.6 / 43.8; 512 of 768 rows, G = 6 53.6 / 51.5 / 57.4, head dim 64, G = 5 32.7 / 31.0 / 34.4; 896 of them, G = 4
+// 41.1 / 40.0 / 43.7.  (Held to the registers of a third workgroup, G = 6 takes 10 to 20 % longer: rows spilled in the loop.)
+bool by_stretches(int64_t n_units, int64_t rows, int resident)
+{
+    return rows >= (int64_t)kChunk * resident && (rows >= 1024 * n_units || 5 * n_units <= 3 * (int64_t)resident);
+}
+// Up to four stretches a workgroup, of 512 rows and more: what runs at a time lies closer together then, and the first pass over a cache
+// spends less on address translation (288 units of 8192 rows, G = 4, first pass / later ones, one stretch: 262 / 196 us, two 243 / 199,
+// four 233 / 203, eight 230 / 209; pieces of 256 rows 245 / 217); and sums are shorter.
+int rows_per_stretch(int64_t rows, int resident)
+{
+    const int64_t workgroups = std::min<int64_t>(4, std::max<int64_t>(1, rows / (512 * (int64_t)resident))) * resident, per = (rows + workgroups - 1) / workgroups;
+    return (int)std::min<int64_t>((per + kSmallChunk - 1) / kSmallChunk * kSmallChunk, 1 << 20);
+}
 
 template <int D, bool F16>
 hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, const int64_t *head_off, int n_units,
                     int G, int64_t rows, float scale_log2, float *out, float *lse, void *ws, size_t ws_bytes, const Prof &prof,
                     hipStream_t st)
 {
-    int32_t *chunk_off = (int32_t *)ws;
     float *part = (float *)((char *)ws + part_offset(n_units));
     const bool small = decode_small(n_units, rows, G) && ws_bytes >= ws_for(max_chunks(n_units, rows, kSmallChunk), n_units, G, D);
-    const unsigned groups = (unsigned)max_chunks(n_units, rows, small ? kSmallChunk : kChunk);
-    if (!small) decode_plan_kernel<<<1, 1024, 0, st>>>(head_off, n_units, rows, chunk_off);
+    int cut = 0;
+    int64_t pieces = 0;
     prof.begin(NKV_KERNEL_DECODE, st);
-#define NKV_DEC(GG)                                                                                                       \
-    case GG:                                                                                                             \
-        (small ? decode_chunk_kernel<D, GG, F16, true, kSmallChunk>                                                      \
-               : decode_chunk_kernel<D, GG, F16, false, kChunk>)<<<groups, kDecThreads, 0, st>>>(                         \
-            q, pk, pv, head_off, chunk_off, n_units, rows, scale_log2, part);                                            \
-        break
+    auto go = [&](auto heads) {
+        constexpr int GG = decltype(heads)::value;
+        const int resident = resident_workgroups<decode_run_kernel<D, GG, F16>>();
+        const bool stretches = !small && by_stretches(n_units, rows, resident);
+        cut = stretches ? rows_per_stretch(rows, resident) : small ? -kSmallChunk : -kChunk;
+        pieces = max_chunks(n_units, rows, std::abs(cut));
+        if (stretches)
+            decode_run_kernel<D, GG, F16><<<(unsigned)((rows + cut - 1) / cut), kDecThreads, 0, st>>>(q, pk, pv, head_off, n_units, rows, cut, scale_log2, part);
+        else
+            (small ? decode_piece_kernel<D, GG, F16, kSmallChunk> : decode_piece_kernel<D, GG, F16, kChunk>)<<<(unsigned)pieces, kDecThreads, 0, st>>>(
+                q, pk, pv, head_off, n_units, rows, scale_log2, part);
+    };
     switch (G) {
-        NKV_DEC(1); NKV_DEC(2); NKV_DEC(3); NKV_DEC(4); NKV_DEC(5); NKV_DEC(6); NKV_DEC(7); NKV_DEC(8);
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 6: go(std::integral_constant<int, 6>{}); break;
+    case 7: go(std::integral_constant<int, 7>{}); break;
+    case 8: go(std::integral_constant<int, 8>{}); break;
     default: return hipErrorInvalidValue;
     }
-#undef NKV_DEC
     prof.end(NKV_KERNEL_DECODE, st);
-    if (groups > (unsigned)(kManyChunks * n_units))
-        decode_combine_kernel<D, 512><<<(unsigned)(n_units * G), 512, 0, st>>>(part, chunk_off, G, out, lse);
+    if (pieces > (int64_t)kManyChunks * n_units)
+        decode_combine_kernel<D, 512><<<(unsigned)(n_units * G), 512, 0, st>>>(part, head_off, rows, cut, G, out, lse);
     else
-        decode_combine_kernel<D, D><<<(unsigned)(n_units * G), D, 0, st>>>(part, chunk_off, G, out, lse);
+        decode_combine_kernel<D, D><<<(unsigned)(n_units * G), D, 0, st>>>(part, head_off, rows, cut, G, out, lse);
     return hipGetLastError();
 }
 
@@ -484,7 +521,7 @@ size_t decode_ws_bytes(int dtype, int d, int dv, int G, int64_t n_units, int64_t
 {
     if (!decode_fast_supported(dtype, d, dv, G)) return 0;
     const size_t need = ws_for(max_chunks(n_units, rows, kChunk), n_units, G, d);
-    if (least || n_units > kSelfUnits) return need;
+    if (least || n_units > kSmallUnits) return need;
     // room for chunks of 64 rows up to the row count where they end, so that more rows never ask for less
     const int64_t most = std::max<int64_t>(0, std::min((512 - n_units) * kChunk + kChunk - 1, (small_chunks_limit(G) - n_units) * kSmallChunk + kSmallChunk - 1));
     const size_t small = ws_for(max_chunks(n_units, rows < most ? rows : most, kSmallChunk), n_units, G, d);

@@ -159,20 +159,24 @@ __device__ __forceinline__ void count_bin(uint32_t *hist, int bin)
     if (!mine || first) atomicAdd(&hist[bin], mine ? (uint32_t)__popcll(same) : 1u);
 }
 
-// The largest u in [0, n) with off[u] <= x, for ascending off[0 .. n) with off[0] <= x: a whole wavefront narrows the
+// The largest u in [0, n) with off(u) <= x, for ascending off(0 .. n - 1) with off(0) <= x: a whole wavefront narrows the
 // range to a 64th with every step, so 4096 entries take two load latencies where a binary search takes twelve.
-template <typename T> __device__ __forceinline__ int wave_search(const T *__restrict__ off, int n, T x)
+template <typename T, typename F> __device__ __forceinline__ int wave_search_fn(int n, T x, F off)
 {
     const int lane = threadIdx.x & (kWave - 1);
     int lo = 0;
     while (n > 1) {
         const int step = (n + kWave - 1) / kWave, at = lane * step;
-        const unsigned long long le = __ballot(at < n && off[lo + min(at, n - 1)] <= x);   // a prefix of the lanes, never empty
+        const unsigned long long le = __ballot(at < n && off(lo + min(at, n - 1)) <= x);   // a prefix of the lanes, never empty
         const int k = 63 - __builtin_clzll(le);
         lo += k * step;
         n = min(step, n - k * step);
     }
     return lo;
+}
+template <typename T> __device__ __forceinline__ int wave_search(const T *__restrict__ off, int n, T x)
+{
+    return wave_search_fn(n, x, [off](int i) { return off[i]; });
 }
 
 // Block-wide reductions for blockDim.x a multiple of 64 and <= 1024.  `scratch` holds >= 16 elements.

@@ -205,3 +205,29 @@ def test_both_chunk_lengths_and_both_ways_to_combine(units, G, rows):
     got, has = _f64(lse), np.isfinite(want_lse)
     assert np.array_equal(np.isfinite(got), has)
     assert (np.abs(got[has] - want_lse[has]) <= DECODE_TOL * np.maximum(1.0, np.abs(want_lse[has]))).all()
+
+
+@pytest.mark.parametrize("d,G,dtype,lens", [
+    (64, 8, "bf16", [70000, 0, 70001]),                              # units far longer than a stretch
+    (64, 8, "bf16", [319, 320, 321, 1, 0, 640, 639, 959] * 42 + [50000] * 2),   # ends around multiples of a stretch of 320 rows and of 64
+    (64, 7, "fp16", [450] * 305 + [0, 1]),                           # three units to five workgroups: the last call by stretches
+    (64, 7, "fp16", [450] * 308),                                    # and the first by pieces
+    (128, 6, "bf16", [1024] * 130 + [1] * 3),
+    (128, 3, "fp16", [0, 131072, 131071, 130, 1]),
+])
+def test_stretches_across_units(d, G, dtype, lens):
+    """Calls large enough that every workgroup takes a stretch of the cache whichever units it holds, against the oracle; the
+    cache is also handed over with more rows claimed than it has."""
+    w = nkv_inputs.small_workload(f"stretch_{d}_{G}_{len(lens)}", len(lens), 1, d, [1], dtype=dtype, n_out=0)
+    g = torch.Generator().manual_seed(len(lens) + d)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+    full = int(off[-1])
+    pk, pv = (torch.randn(full, d, generator=g).to(dt).to(DEV) for _ in range(2))
+    q = torch.randn(1, len(lens), G, d, generator=g).to(dt).to(DEV)
+    scale = 1.0 / float(np.sqrt(d))
+    for rows in (full, full - 37):
+        ho = off.numpy().clip(max=rows)
+        want, want_lse = oracle_decode(_f64(q), _f64(pk[:rows]), _f64(pv[:rows]), ho, 1, scale)
+        out, lse = _run(w, q, pk[:rows], pv[:rows], off.to(DEV), rows, G, scale)
+        _check(out, lse, want, want_lse, float(pv.abs().max()), f"stretches d={d} G={G} rows={rows}")
