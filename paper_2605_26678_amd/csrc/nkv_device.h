@@ -110,18 +110,63 @@ template <int ROWS, typename T, typename Op> __device__ __forceinline__ T swap_r
         return op(__builtin_bit_cast(T, (unsigned long long)xh << 32 | x), __builtin_bit_cast(T, (unsigned long long)yh << 32 | y));
     }
 }
-template <typename T, typename Op> __device__ __forceinline__ T wave_reduce(T v, Op op)
+// Two values whose lanes differ in that bit: lanes with the bit clear receive op over a's pair, the others op over b's.
+template <int ROWS, typename T, typename Op> __device__ __forceinline__ T swap_merge(T a, T b, Op op)
+{
+    auto swap = [](uint32_t u, uint32_t v, uint32_t &x, uint32_t &y) {
+        if constexpr (ROWS == 16) {
+            const auto r = __builtin_amdgcn_permlane16_swap(u, v, false, false);
+            x = r[0];
+            y = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(u, v, false, false);
+            x = r[0];
+            y = r[1];
+        }
+    };
+    uint32_t x, y;
+    if constexpr (sizeof(T) == 4) {
+        swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b), x, y);
+        return op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+    } else {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, a), v = __builtin_bit_cast(unsigned long long, b);
+        uint32_t xh, yh;
+        swap((uint32_t)u, (uint32_t)v, x, y);
+        swap((uint32_t)(u >> 32), (uint32_t)(v >> 32), xh, yh);
+        return op(__builtin_bit_cast(T, (unsigned long long)xh << 32 | x), __builtin_bit_cast(T, (unsigned long long)yh << 32 | y));
+    }
+}
+template <typename T, typename Op> __device__ __forceinline__ T row16_reduce(T v, Op op)     // over a row of 16 lanes
 {
     v = op(v, dpp_partner<0xB1>(v));             // quad_perm [1,0,3,2]
     v = op(v, dpp_partner<0x4E>(v));             // quad_perm [2,3,0,1]
     v = op(v, dpp_partner<0x141>(v));            // row_half_mirror: the other quad of the 8-lane half
-    v = op(v, dpp_partner<0x140>(v));            // row_mirror: the other half of the 16-lane row
+    return op(v, dpp_partner<0x140>(v));         // row_mirror: the other half of the 16-lane row
+}
+template <typename T, typename Op> __device__ __forceinline__ T wave_reduce(T v, Op op)
+{
+    v = row16_reduce(v, op);
     v = swap_reduce<16>(v, op);
     return swap_reduce<32>(v, op);
 }
 template <typename T> __device__ __forceinline__ T wave_sum(T v)
 {
     return wave_reduce(v, [](T a, T b) { return a + b; });
+}
+// Eight values reduced at once: lanes 8 i .. 8 i + 7 receive value i's result.  The halves of the wavefront share the values out, then
+// the rows of 16 lanes, then the halves of a row, so that there are 10 steps where eight reductions by themselves take 48.
+template <typename T, typename Op> __device__ __forceinline__ T wave_reduce8(const T (&v)[8], Op op)
+{
+    T x[4], y[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = swap_merge<32>(v[e], v[e + 4], op);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) y[e] = swap_merge<16>(x[e], x[e + 2], op);
+    const bool hi = (threadIdx.x & 8) != 0;
+    T r = op(hi ? y[1] : y[0], dpp_partner<0x128>(hi ? y[0] : y[1]));       // row_ror:8
+    r = op(r, dpp_partner<0xB1>(r));
+    r = op(r, dpp_partner<0x4E>(r));
+    return op(r, dpp_partner<0x141>(r));
 }
 __device__ __forceinline__ float wave_min(float v)
 {

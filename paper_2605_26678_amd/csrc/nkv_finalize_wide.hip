@@ -167,6 +167,8 @@ __global__ __launch_bounds__(256) void stats_pick_kernel(int L, int H, PromptTab
 
 // grid: slices.  All three scales of the slice in one pass: what stats_finish_kernel needs of each scale, and --
 // the ranges being known -- min, max and sum of the surprise statistic of the slice's tokens.
+// Bound by instruction issue: values are compared with the boundary bins' edges instead of binned (with that, the seven sums of a
+// wavefront at once and the weights in three lanes of the routing, score calls: 1 layer x 8 heads x 32768 tokens 53.3 -> 52.4 us, 36 layers 626.2 -> 622.4).
 template <int TH, bool ALL>
 __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                      int L, int H, PromptTab tab, SliceTab st,
@@ -188,13 +190,15 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
     const float *a = a_raw + (int64_t)lh * tab.T + tab.tok_off[p];
     const int tid = threadIdx.x;
     const int64_t job0 = ((int64_t)p * L * H + lh) * 3;
-    StatPick pk[3];
+    BinEdges top[3], bot[3];
     HeadStats hs;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        pk[k] = picks[job0 + k];
-        hs.lo[k] = pk[k].lo;
-        hs.inv_range[k] = pk[k].inv;
+        const StatPick pk = picks[job0 + k];
+        top[k] = bin_edges(pk.bTop);
+        bot[k] = bin_edges(pk.bBot);
+        hs.lo[k] = pk.lo;
+        hs.inv_range[k] = pk.inv;
     }
     if (tid < 3) { nTop[tid] = 0u; nBot[tid] = 0u; }
     __syncthreads();
@@ -225,15 +229,17 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
             if (s * kSlice + (half * HALF + j) * 256 + first < N) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    const float x = v[k][j];
-                    const int b = anomaly_bin(x);
-                    part[k] += b > pk[k].bTop ? x : 0.f;
-                    part[3 + k] += b < pk[k].bBot ? x : 0.f;
-                    if (b == pk[k].bTop) {
+                    const float x = v[k][j], y = anomaly_scaled(x);
+                    const bool over = y >= top[k].above, under = y < bot[k].below;
+                    part[k] += over ? x : 0.f;
+                    part[3 + k] += under ? x : 0.f;
+                    const bool in_top = !over && y >= top[k].from, in_bot = !under && y < bot[k].to;
+                    if (!in_top && !in_bot) continue;
+                    if (in_top) {
                         const uint32_t at = atomicAdd(&nTop[k], 1u);
                         if (at < (uint32_t)kSeg) segTop[((int64_t)k * n_slices + blockIdx.x) * kSeg + at] = ord_key(x);
                     }
-                    if (b == pk[k].bBot) {                           // inverted: the smallest value has the largest key
+                    if (in_bot) {                                    // inverted: the smallest value has the largest key
                         const uint32_t at = atomicAdd(&nBot[k], 1u);
                         if (at < (uint32_t)kSeg) segBot[((int64_t)k * n_slices + blockIdx.x) * kSeg + at] = ~ord_key(x);
                     }
@@ -262,15 +268,12 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
 #pragma unroll
     for (int i = 0; i < SUMS; ++i) sum[i] = HALF >= 8 ? parts[i][tid] : rounded(part[i]);
     const int w = tid >> 6;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double t = wave_sum(sum[k]), b = wave_sum(sum[3 + k]);
-        if ((tid & 63) == 0) { red[2 * k][w] = t; red[2 * k + 1][w] = b; }
-    }
-    const double ssum = wave_sum(sum[6]);
+    const double of_wave[8] = {sum[0], sum[3], sum[1], sum[4], sum[2], sum[5], sum[6], 0.0};
+    const double total = wave_reduce8(of_wave, [](double x, double y) { return x + y; });
+    if ((tid & 7) == 0) red[(tid & 63) >> 3][w] = total;
     smin = wave_min(smin);
     smax = wave_max(smax);
-    if ((tid & 63) == 0) { red[6][w] = ssum; fred[0][w] = smin; fred[1][w] = smax; }
+    if ((tid & 63) == 0) { fred[0][w] = smin; fred[1][w] = smax; }
     __syncthreads();
     if (tid < 3) {
         const int k = tid;
@@ -314,8 +317,11 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
     for (int k = 0; k < 3; ++k)
 #pragma unroll
         for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, j);
+    if (tid < 64) {
+        const float *sk = stats + ((int64_t)p * L * H + lh) * 12 + 4 * min(tid, 2);
+        head_weights(sk[0], sk[1], sk[2], lc, hs);
+    }
     if (tid == 0) {
-        head_weights(stats + ((int64_t)p * L * H + lh) * 12, lc, hs);
         float smin = INFINITY, smax = -INFINITY;
         double ssum = 0.0;
         const SliceSurprise *q = sur + (blockIdx.x - s);

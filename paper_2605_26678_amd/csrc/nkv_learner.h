@@ -58,23 +58,26 @@ __device__ __forceinline__ float routed_score(const float at[3], const HeadStats
     return (1.0f - alpha) * blend + alpha * win;
 }
 
-// Blend weights of a head from the three reliability gaps (Section 2.4): softmax of log prior + beta * gap,
-// in double precision.  stats3: {min, 1 / range, gap} of the three scales, 4 floats apart.
-__device__ __forceinline__ void head_weights(const float *stats3, const LearnerConsts &lc, HeadStats &hs)
+// Blend weights of a head from the three reliability gaps (Section 2.4): softmax of log prior + beta * gap, in double precision.
+// Called by a whole wavefront, lane k of which takes scale k: the divisions and exponentials are long chains, and three at a time take
+// as long as one.  lo, inv_range, gap: those of scale min(lane, 2); the wavefront fills in hs.lo, inv_range and w.
+__device__ __forceinline__ void head_weights(float lo, float inv_range, float gap, const LearnerConsts &lc, HeadStats &hs)
 {
-    double z[3], zmax = -INFINITY, zsum = 0.0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const float *st = stats3 + k * 4;
-        hs.lo[k] = st[0];
-        hs.inv_range[k] = st[1];
-        z[k] = lc.log_prior[k] + lc.beta * (double)st[2];
-        zmax = fmax(zmax, z[k]);
+    const int lane = threadIdx.x & 63;
+    auto of = [](double v, int k) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, k), b = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), k);
+        return __builtin_bit_cast(double, (unsigned long long)b << 32 | a);
+    };
+    const double prior = lane == 0 ? lc.log_prior[0] : lane == 1 ? lc.log_prior[1] : lc.log_prior[2];
+    double z = prior + lc.beta * (double)gap;
+    z = exp(z - fmax(fmax(of(z, 0), of(z, 1)), of(z, 2)));
+    const double w = z / ((of(z, 0) + of(z, 1)) + of(z, 2));
+    if (lane < 3) {
+        hs.lo[lane] = lo;
+        hs.inv_range[lane] = inv_range;
+        hs.w[lane] = (float)w;
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { z[k] = exp(z[k] - zmax); zsum += z[k]; }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) hs.w[k] = (float)(z[k] / zsum);
 }
 
 }  // namespace nkv

@@ -90,10 +90,24 @@ __device__ __forceinline__ int score_bin(float v)
 }
 
 // Anomalies (-cos, so in [-1, 1]): floor(1023.5 (a + 1)), clamped.  Monotone in a.
+__device__ __forceinline__ float anomaly_scaled(float a) { return (a + 1.0f) * 1023.5f; }
 __device__ __forceinline__ int anomaly_bin(float a)
 {
-    const float x = (a + 1.0f) * 1023.5f;
+    const float x = anomaly_scaled(a);
     return x >= 2047.0f ? 2047 : (x > 0.f ? (int)x : 0);
+}
+
+// Where y = a value on the scale of its bins lies to a boundary bin: bin > q <=> y >= above, bin < q <=> y < below, and what is neither is in
+// bin q.  (Of kBins bins, the end ones take what lies beyond; q = -1: every value is above.)  A comparison each instead of
+// forming the bin.
+struct BinEdges {
+    float above, below, from, to;        // from, to: the same edges from the other side (in bin q <=> y >= from and not y >= above)
+};
+__device__ __forceinline__ BinEdges bin_edges(int q)                  // q: the same in every lane
+{
+    auto uniform = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
+    const float low = uniform(q <= 0 ? -INFINITY : (float)q), high = uniform(q < 0 ? -INFINITY : q >= kBins - 1 ? INFINITY : (float)(q + 1));
+    return BinEdges{high, low, low, high};
 }
 
 // The 2048 counts of a workgroup's LDS histogram as 16-bit values: 8 bins per thread and 16-byte store, by 256 threads.
