@@ -9,7 +9,8 @@
 //                afresh in front of them (Section 2.2 current memory; Section 2.3); one wavefront per 16 tokens.  The window
 //                sum is held in 64 bits (the products of 32-bit factors are exact then), so that what has entered
 //                leaves again without a trace: in 32 bits, keys that cancel inside the window left twice the error of a
-//                window added up afresh for every token
+//                window added up afresh for every token.  One kernel for windows of 64 tokens of keys of up to 128 dims, one
+//                for any
 // Everywhere a lane owns dims lane, lane + 64, ... of a row.  The time of a small call is a chain of load latencies, so
 // loads go out eight or sixteen rows at a time.  (With the window added up for every token, a wave per token and a serial loop over
 // a block's tokens, 2 heads x 4096 fp32 tokens took 86 us.)
@@ -61,16 +62,27 @@ __global__ __launch_bounds__(kBlockThreads) void block_kernel(const T *__restric
     for (int t = lo + w; t < hi; t += U * NW) {
         float x[U][NQ], rn[U];
         load_rows<T, NQ, U>(unit, d, lane, t, NW, hi, x);
+        float ss[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            float ss = 0.f;
+            ss[j] = 0.f;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) ss = fmaf(x[j][q], x[j][q], ss);
-            rn[j] = 1.0f / fmaxf(sqrtf(wave_sum(ss)), kEps);
+            for (int q = 0; q < NQ; ++q) ss[j] = fmaf(x[j][q], x[j][q], ss[j]);
+        }
+        if constexpr (U == 8) {                                       // lanes 8 j .. 8 j + 7: token j's
+            const float r = 1.0f / fmaxf(sqrtf(wave_reduce8(ss, [](float a, float b) { return a + b; })), kEps);
+            if ((lane & 7) == 0 && t + (lane >> 3) * NW < hi) rnorm[row0 + t + (lane >> 3) * NW] = r;
+#pragma unroll
+            for (int j = 0; j < U; ++j) rn[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), 8 * j));
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                rn[j] = 1.0f / fmaxf(sqrtf(wave_sum(ss[j])), kEps);
+                if (lane == 0 && t + j * NW < hi) rnorm[row0 + t + j * NW] = rn[j];
+            }
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            if (lane == 0 && t + j * NW < hi) rnorm[row0 + t + j * NW] = rn[j];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) acc[q] = fmaf(rn[j], x[j][q], acc[q]);   // (rows past the block are zeros)
         }
@@ -216,6 +228,125 @@ __global__ __launch_bounds__(256) void anomaly_kernel(const T *__restrict__ keys
     }
 }
 
+// The same for windows of 64 tokens and head dims up to 128.  A workgroup takes 64 consecutive tokens of a prompt, a wavefront 16 of
+// them and the 16 rows that lie 64 tokens in front, which are the ones that leave the window: 32 rows, all on their way at once, and the
+// window in front of a wavefront's tokens is the sum of four of the workgroup's eight groups of rows.  (With every wavefront adding up
+// the 64 rows in front of its tokens, sixteen loads at a time, and every token's five sums over the lanes reduced by themselves, the
+// score call of 2 heads x 4096 fp32 tokens of head dim 128 took 43 us, 26 now; of 64 heads x 16384 640 and 290.)  grid (groups of 64 tokens, L*H).
+template <typename T, int NQ>
+__global__ __launch_bounds__(256) void anomaly_window64_kernel(const T *__restrict__ keys, RowMap km, const float *__restrict__ rnorm,
+                                                               const float *__restrict__ bsum, const float *__restrict__ ssum, int LH,
+                                                               int d, PromptTab tab, float *__restrict__ a_raw)
+{
+    constexpr int C = kChunk, NW = 4;
+    __shared__ double lds_sum[2][NW][NQ][kWave];                      // the groups' sums: in front of, and of, the workgroup's tokens
+    const int lane = threadIdx.x & (kWave - 1), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lh = blockIdx.y;
+    const int64_t rows = (int64_t)LH * tab.T;
+    int part = blockIdx.x, p = 0;
+    for (; p + 1 < tab.n; ++p) {                                      // (the grid ends with the last prompt)
+        const int np = (tab.tok_off[p + 1] - tab.tok_off[p] + NW * C - 1) / (NW * C);
+        if (part < np) break;
+        part -= np;
+    }
+    const int N = tab.tok_off[p + 1] - tab.tok_off[p], b = tab.b[p];
+    const int i0 = part * NW * C + C * w, i1 = min(i0 + C, N);        // this wavefront's tokens (none past the prompt's end)
+    const int64_t row0 = (int64_t)lh * tab.T + tab.tok_off[p];
+    const T *unit = keys + km.unit(lh, p, tab);
+    const float *rn_unit = rnorm + row0;
+    const float *S = ssum + ((int64_t)lh * tab.n + p) * d;
+    const float *B0 = bsum + ((int64_t)lh * tab.blk_off[tab.n] + tab.blk_off[p]) * d;
+
+    float x[C][NQ], y[C][NQ];                                         // rows that enter and that leave the window
+    load_rows<T, NQ, C>(unit, d, lane, i0 - NW * C, 1, N, y);
+    load_rows<T, NQ, C>(unit, d, lane, i0, 1, N, x);
+    // 1 / ||k||, 0 where there is no row: lanes 0 .. 15 of x's rows, 16 .. 31 of y's
+    const int mine = i0 + (lane & 15) - (lane < C ? 0 : NW * C);
+    float r = rn_unit[min(max(mine, 0), N - 1)];
+    r = mine >= 0 && mine < N ? r : 0.f;
+    auto of_row = [&](int j) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), j)); };
+    float s[NQ], e[NQ], ns = 0.f, ne = 0.f;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int c = lane + q * kWave;
+        s[q] = c < d ? S[c] : 0.f;
+        e[q] = 0.f;
+        ns = fmaf(s[q], s[q], ns);
+    }
+    ns = wave_sum(ns);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        double sx = 0.0, sy = 0.0;
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            sy = fma((double)of_row(C + j), (double)y[j][q], sy);
+            sx = fma((double)of_row(j), (double)x[j][q], sx);
+        }
+        lds_sum[0][w][q][lane] = sy;
+        lds_sum[1][w][q][lane] = sx;
+    }
+    __syncthreads();
+    double W[NQ];                                                     // the window in front of the next token
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        W[q] = 0.0;
+#pragma unroll
+        for (int g = 0; g < NW; ++g) W[q] += lds_sum[g >= w ? 0 : 1][g][q][lane];
+    }
+    if (i0 >= N) return;                                              // (no barrier follows)
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) asm volatile("" : "+v"(x[j][q]), "+v"(y[j][q]));   // (or all of them would be kept as doubles)
+    asm volatile("" : "+v"(r));
+    auto add = [](float u, float v) { return u + v; };
+    int blk_end = i0;                                                 // first token past the block whose sum e holds
+#pragma unroll
+    for (int h = 0; h < C; h += 8) {
+        float kk[8], ds[8], de[8], dc[8], nc[8], nb[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int tok = min(i0 + h + j, N - 1);                   // (what lies past the end is not stored)
+            if (tok >= blk_end) {                                     // the token's episodic block
+                const int blk = tok / b;
+                blk_end = (blk + 1) * b;
+                ne = 0.f;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const int c = lane + q * kWave;
+                    e[q] = c < d ? B0[(int64_t)blk * d + c] : 0.f;
+                    ne = fmaf(e[q], e[q], ne);
+                }
+            }
+            const float rx = of_row(h + j), ry = of_row(C + h + j);
+            kk[j] = ds[j] = de[j] = dc[j] = nc[j] = 0.f;
+            nb[j] = ne;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                W[q] = fma((double)rx, (double)x[h + j][q], fma(-(double)ry, (double)y[h + j][q], W[q]));
+                const float kh = rx * x[h + j][q], wq = (float)W[q];
+                kk[j] = fmaf(kh, kh, kk[j]);
+                ds[j] = fmaf(kh, s[q], ds[j]);
+                de[j] = fmaf(kh, e[q], de[j]);
+                dc[j] = fmaf(kh, wq, dc[j]);
+                nc[j] = fmaf(wq, wq, nc[j]);
+            }
+            __builtin_amdgcn_sched_barrier(0);                        // one token at a time: registers
+        }
+        // lanes 8 j .. 8 j + 7: token j's
+        const float nk = fmaxf(sqrtf(wave_reduce8(kk, add)), kEps);
+        const float as = -wave_reduce8(ds, add) / (nk * fmaxf(sqrtf(ns), kEps));
+        const float ae = -wave_reduce8(de, add) / (nk * fmaxf(sqrtf(wave_reduce8(nb, add)), kEps));
+        const float ac = -wave_reduce8(dc, add) / (nk * fmaxf(sqrtf(wave_reduce8(nc, add)), kEps));
+        const int tok = i0 + h + (lane >> 3);
+        if ((lane & 7) == 0 && tok < i1) {
+            float *out = a_raw + row0 + tok;
+            out[0] = as;
+            out[rows] = ae;
+            out[2 * rows] = ac;
+        }
+    }
+}
+
 template <typename T>
 hipError_t run(const T *keys, const RowMap &km, int LH, int d, int window, const PromptTab &tab, float *a_raw, float *rnorm,
                float *bsum, float *ssum, const Prof &prof, hipStream_t st)
@@ -223,6 +354,9 @@ hipError_t run(const T *keys, const RowMap &km, int LH, int d, int window, const
     int chunks = 0;
     for (int p = 0; p < tab.n; ++p) chunks += (tab.tok_off[p + 1] - tab.tok_off[p] + kChunk - 1) / kChunk;
     const dim3 blocks((unsigned)tab.blk_off[tab.n], (unsigned)LH), waves((unsigned)(chunks + 3) / 4, (unsigned)LH);
+    int parts = 0;
+    for (int p = 0; p < tab.n; ++p) parts += (tab.tok_off[p + 1] - tab.tok_off[p] + 4 * kChunk - 1) / (4 * kChunk);
+    const dim3 groups((unsigned)parts, (unsigned)LH);
     const int nq = (d + kWave - 1) / kWave;
 #define NKV_BY_DIMS(CALL) \
     do { if (nq <= 1) CALL(1); else if (nq <= 2) CALL(2); else if (nq <= 4) CALL(4); else if (nq <= 8) CALL(8); else CALL(16); } while (0)
@@ -231,7 +365,12 @@ hipError_t run(const T *keys, const RowMap &km, int LH, int d, int window, const
     NKV_BY_DIMS(NKV_BLOCK);
     ssum_kernel<<<dim3(tab.n, LH), kSsumThreads, 0, st>>>(bsum, d, tab, ssum);
     prof.begin(NKV_KERNEL_SCAN, st);
-    NKV_BY_DIMS(NKV_ANOM);
+    if (window == 4 * kChunk && nq <= 2) {
+        if (nq <= 1) anomaly_window64_kernel<T, 1><<<groups, 256, 0, st>>>(keys, km, rnorm, bsum, ssum, LH, d, tab, a_raw);
+        else anomaly_window64_kernel<T, 2><<<groups, 256, 0, st>>>(keys, km, rnorm, bsum, ssum, LH, d, tab, a_raw);
+    } else {
+        NKV_BY_DIMS(NKV_ANOM);
+    }
 #undef NKV_BLOCK
 #undef NKV_ANOM
 #undef NKV_BY_DIMS

@@ -1159,3 +1159,29 @@ def test_the_three_calls_can_be_captured_in_a_hip_graph_and_replayed():
                comp.packed_k[:comp.rows].view(torch.int16), comp.packed_v[:comp.rows].view(torch.int16))
         for a, b in zip(got, ref):
             assert torch.equal(a, b), f"replay {rep}"
+
+
+@pytest.mark.parametrize("lens", [[1, 15, 16, 17, 63, 64, 65], [129, 2, 300, 48], [700]])
+@pytest.mark.parametrize("d,dtype,block", [(8, "fp32", 0), (64, "fp32", 3), (72, "fp32", 0), (128, "fp32", 20), (128, "fp16", 5)])
+def test_shape_generic_window_of_64_tokens(d, dtype, block, lens):
+    """The shape-generic scoring kernel for windows of 64 tokens and head dims up to 128: prompts around the 16 tokens of a
+    wavefront and the 64 of a workgroup, both sides of the 64 dims a lane holds one of, blocks that end inside a wavefront's
+    tokens.  Against the oracle, and window by window against the kernel for any window (a window of 64 is one of 65 for the
+    first 64 tokens)."""
+    w = nkv_inputs.small_workload(f"window64_{d}_{dtype}_{block}", 1, 2, d, lens, dtype=dtype, dv=32, n_out=0)
+    K, V = _kv(w)
+    sizes = dict(block_min=block, block_max=block) if block else {}
+    p = nkv.params_default(flags=nkv.FLAG_GENERIC_KERNELS, **sizes)
+    compare_end_to_end(w, K, V, 0.5, params=p, label=w.name)
+    shape, raw = shape_of(w), []
+    for window in (64, 65):
+        p = nkv.params_default(flags=nkv.FLAG_GENERIC_KERNELS, window=window, **sizes)
+        a = torch.empty(3, w.L, w.H, sum(lens), dtype=torch.float32, device=DEV)
+        nkv.score_raw(K, shape, p, a, torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV))
+        raw.append(a)
+    torch.cuda.synchronize()
+    at = 0
+    for n in lens:
+        # fp32 cosines of 128 terms: both kernels are within a few 1e-7 of the exact value
+        assert (raw[0] - raw[1])[..., at:at + min(n, 64)].abs().max().item() < 2e-6
+        at += n
