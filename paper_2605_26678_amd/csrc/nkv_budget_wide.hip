@@ -28,7 +28,7 @@ namespace {
 
 constexpr int kListT = 512;              // keys a head's boundary-bin list holds
 constexpr int kListL = 4096;             // entries a layer's boundary-bin list holds
-constexpr int kMaxH = 8;
+constexpr int kMaxH = 8;                 // (as many as a wavefront reduces at once)
 constexpr int kMaxSeg = 1024;            // segments of a layer the finishing kernel takes (H * slices per head)
 
 struct LayerPick {
@@ -59,6 +59,8 @@ __device__ __forceinline__ uint32_t above_waves(const uint32_t *wsum)
     return wave_sum(lane < 16 && lane > (int)(threadIdx.x >> 6) ? wsum[lane & 15] : 0u);
 }
 
+// (Sums over the heads eight at a time through one butterfly, with the collecting kernel's comparisons: budgets + selection of 1 layer x
+// 8 heads x 32768 tokens 58.3 -> 56.7 us, 28 layers of the ragged batch 403.4 -> 399.4.)
 __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTab tab, SliceTab st,
                                                           const uint16_t *__restrict__ part,
                                                           LayerPick *__restrict__ picks, uint32_t *__restrict__ failed,
@@ -117,10 +119,20 @@ __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTa
     for (int h = 0; h < kMaxH; ++h) incl[h] = scan_from_top(a[h] + b[h], wsum[h]);
     __syncthreads();
     if (m_safe > 0) {
+        uint32_t above[kMaxH];                                       // the wavefronts above this one, all heads at once
+        {
+            uint32_t v[8];
+            const int lane = tid & 63;
+#pragma unroll
+            for (int h = 0; h < kMaxH; ++h) v[h] = lane < 16 && lane > (tid >> 6) ? wsum[h][lane & 15] : 0u;
+            const uint32_t t = wave_reduce8(v, [](uint32_t x, uint32_t y) { return x + y; });
+#pragma unroll
+            for (int h = 0; h < kMaxH; ++h) above[h] = (uint32_t)__builtin_amdgcn_readlane((int)t, 8 * h);
+        }
 #pragma unroll
         for (int h = 0; h < kMaxH; ++h) {
             if (h < H) {
-                const uint32_t up = incl[h] + above_waves(wsum[h]);
+                const uint32_t up = incl[h] + above[h];
                 const uint32_t cum = up - (a[h] + b[h]), want = (uint32_t)m_safe;
                 if (cum < want && want <= up) {
                     if (want <= cum + b[h]) { s_bT[h] = tid * 2 + 1; s_needT[h] = want - cum; }
@@ -155,13 +167,12 @@ __global__ __launch_bounds__(1024) void layer_pick_kernel(int L, int H, PromptTa
     __syncthreads();
     const int bL = (int)s_bL;
     // pool entries of every head in bins above bL
+    {
+        uint32_t v[8];
 #pragma unroll
-    for (int h = 0; h < kMaxH; ++h) {
-        if (h < H) {
-            uint32_t c = (tid * 2 > bL ? qa[h] : 0u) + (tid * 2 + 1 > bL ? qb[h] : 0u);
-            c = wave_sum(c);
-            if ((tid & 63) == 0 && c != 0u) atomicAdd(&s_gt[h], c);
-        }
+        for (int h = 0; h < kMaxH; ++h) v[h] = (tid * 2 > bL ? qa[h] : 0u) + (tid * 2 + 1 > bL ? qb[h] : 0u);   // (0 from head H on)
+        const uint32_t c = wave_reduce8(v, [](uint32_t x, uint32_t y) { return x + y; });
+        if ((tid & 7) == 0 && c != 0u) atomicAdd(&s_gt[(tid & 63) >> 3], c);
     }
     __syncthreads();
     if (tid < kMaxH) {
@@ -203,6 +214,7 @@ __global__ __launch_bounds__(TH) void slice_collect_kernel(const float *__restri
     const LayerPick *pk = picks + pl;
     const int bT = pk->bT[h], bL = pk->bL;
     const uint32_t done = pk->done;
+    const BinEdges eT = score_edges(bT), eL = score_edges(bL <= bT ? bL : kBins);   // bins above bT are protected as a whole
     if (tid == 0) { nT = 0u; nL = 0u; }
     __syncthreads();
     if (done) return;
@@ -210,12 +222,14 @@ __global__ __launch_bounds__(TH) void slice_collect_kernel(const float *__restri
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
         if (s * kSlice + j * TH + tid < N) {
-            const int b = score_bin(v[j]);
-            if (b == bT) {
+            const float y = score_scaled(v[j]);
+            const bool inT = y >= eT.from && !(y >= eT.above), inL = y >= eL.from && !(y >= eL.above);
+            if (!inT && !inL) continue;
+            if (inT) {
                 const uint32_t at = atomicAdd(&nT, 1u);
                 if (at < (uint32_t)kSeg) outT[at] = ord_key(v[j]);
             }
-            if (b == bL && b <= bT) {                                // bins above bT are protected as a whole
+            if (inL) {
                 const uint32_t at = atomicAdd(&nL, 1u);
                 if (at < (uint32_t)kSeg) outL[at] = ord_key(v[j]);
             }

@@ -110,6 +110,17 @@ __device__ __forceinline__ BinEdges bin_edges(int q)                  // q: the 
     return BinEdges{high, low, low, high};
 }
 
+// The same for scores, whose upper two bins are those of 1 and of everything above (y is infinite for the pinned ones): in bin q <=>
+// y >= from and not y >= above.  q = kBins: no value is.
+__device__ __forceinline__ float score_scaled(float v) { return v * 2046.0f; }
+__device__ __forceinline__ BinEdges score_edges(int q)               // q: the same in every lane
+{
+    auto uniform = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
+    auto from = [](int b) { return b <= 0 ? -INFINITY : b <= 2046 ? (float)b : b == 2047 ? 2046.0001220703125f : NAN; };   // the float after 2046
+    const float low = uniform(from(q)), high = uniform(from(q + 1));
+    return BinEdges{high, low, low, high};
+}
+
 // The 2048 counts of a workgroup's LDS histogram as 16-bit values: 8 bins per thread and 16-byte store, by 256 threads.
 __device__ __forceinline__ void store_hist16(const uint32_t *hist, uint16_t *row)
 {
