@@ -10,13 +10,13 @@
 // bin's entries, and only those entries are looked at exactly; likewise from below.
 //   stats_hist_kernel    (slice, scale)  2048-bin histogram as 16-bit counts; min and max of the slice
 //   stats_pick_kernel    (unit, scale)   the bins that hold the m-th largest and the m-th smallest value
-//   stats_collect_kernel (slice)         all three scales: sums of the values above the upper / below the lower
+//   stats_collect_kernel (slice, or a quarter of one where there are few) all three scales: sums of the values above the upper / below the lower
 //                                        boundary bin; the boundary bins' entries (as order-preserving keys)
 //                                        into two short lists per slice and scale; and, the ranges being known,
 //                                        min / max / sum of the slice's surprise statistic
 //   stats_finish_kernel  (unit, scale)   two wavefronts, one per boundary bin: exact thresholds inside the bins, the
 //                                        two means, min, 1/range, gap
-//   route_slice_kernel   (slice)         weights, surprise statistics of the head, routed scores, pinning
+//   route_slice_kernel   (the same)      weights, surprise statistics of the head, routed scores, pinning
 // A list that overflows (hundreds of values of one slice in one bin) marks the (unit, scale), and the first wavefront of its
 // finishing workgroup walks the head's values itself.
 #include "nkv_learner.h"
@@ -44,12 +44,21 @@ struct SlicePart {                       // what one slice contributes besides i
     double sTop, sBot;                   // sums above the upper / below the lower boundary bin
 };
 
+__device__ __forceinline__ double rounded_sum(float x)               // to a multiple of 2^-40
+{
+    constexpr double kRound = 6144.;                                 // 1.5 * 2^12: the last place of a sum with it is 2^-40
+    return ((double)x + kRound) - kRound;
+}
+
+constexpr int kQuarter = kSlice / 4;
+
 // grid (slices, 3)
 template <int TH>
 __global__ __launch_bounds__(TH) void stats_hist_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                   PromptTab tab, SliceTab st, int n_slices,
                                                                   uint16_t *__restrict__ part,
-                                                                  SlicePart *__restrict__ sp)
+                                                                  SlicePart *__restrict__ sp,
+                                                                  SliceSurprise *__restrict__ sur)
 {
     constexpr int PT = per_thread<TH>();
     __shared__ __attribute__((aligned(16))) uint32_t hist[kBins];
@@ -85,8 +94,8 @@ __global__ __launch_bounds__(TH) void stats_hist_kernel(const float *__restrict_
     const int64_t job_slice = (int64_t)k * n_slices + blockIdx.x;
     if (tid == 0) {
         for (int i = 1; i < TH / 64; ++i) { lo = fminf(lo, red[0][i]); hi = fmaxf(hi, red[1][i]); }
-        sp[job_slice].lo = lo;
-        sp[job_slice].hi = hi;
+        sp[job_slice] = SlicePart{lo, hi, 0u, 0u, 0.0, 0.0};          // (the quarters of a slice add to the rest)
+        if (k == 0) sur[blockIdx.x] = SliceSurprise{INFINITY, 0.f, 0.0};
     }
     store_hist16(hist, part + job_slice * kBins);
 }
@@ -169,8 +178,8 @@ __global__ __launch_bounds__(256) void stats_pick_kernel(int L, int H, PromptTab
 // the ranges being known -- min, max and sum of the surprise statistic of the slice's tokens.
 // Bound by instruction issue: values are compared with the boundary bins' edges instead of binned (with that, the seven sums of a
 // wavefront at once and the weights in three lanes of the routing, score calls: 1 layer x 8 heads x 32768 tokens 53.3 -> 52.4 us, 36 layers 626.2 -> 622.4).
-template <int TH, bool ALL>
-__global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows,
+template <bool ALL>
+__global__ __launch_bounds__(256, 5) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                      int L, int H, PromptTab tab, SliceTab st,
                                                                      int n_slices, int scale_mask,
                                                                      const StatPick *__restrict__ picks,
@@ -180,7 +189,7 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
                                                                      SliceSurprise *__restrict__ sur,
                                                                      uint32_t *__restrict__ failed)
 {
-    constexpr int HALF = per_thread<TH>() / 2;
+    constexpr int TH = 256, HALF = per_thread<TH>() / 2;
     __shared__ uint32_t nTop[3], nBot[3];
     __shared__ double red[8][TH / 64];
     __shared__ float fred[2][TH / 64];
@@ -203,30 +212,25 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
     if (tid < 3) { nTop[tid] = 0u; nBot[tid] = 0u; }
     __syncthreads();
     const __amdgpu_buffer_rsrc_t vals[3] = {slice_values(a, s, N), slice_values(a + rows, s, N), slice_values(a + 2 * rows, s, N)};
-    // Sums: eight tokens, 256 apart, in 32 bits, the same eight whatever TH; their sums, rounded to 2^-40, add up exactly in 64 bits
-    // (fewer than 2^13 in all), so that the statistics of a head do not depend on how many heads the call has.  A thread of 256 has
+    // Sums: eight tokens, 256 apart, in 32 bits, the same eight as for a workgroup of a quarter; their sums, rounded to 2^-40, add up exactly in 64 bits
+    // (fewer than 2^13 in all), so that the statistics of a head do not depend on how many heads the call has.  A thread has
     // four such sums of each kind; between its two halves they wait in LDS (in registers: five waves a SIMD instead of seven, and this
-    // kernel takes 93 us instead of 87 for 3584 slices; 86 with all of a thread's terms in 32 bits, 1024 threads: the same).
+    // kernel takes 93 us instead of 87 for 3584 slices; 86 with all of a thread's terms in 32 bits).
     constexpr int SUMS = 7;                                          // 0 .. 2 above, 3 .. 5 below the boundary bins, 6 the surprise
-    __shared__ double parts[SUMS][HALF >= 8 ? TH : 1];
+    __shared__ double parts[SUMS][TH];
     float part[SUMS] = {};
     double sum[SUMS];
-    auto rounded = [](float x) {
-        constexpr double kRound = 6144.;                             // 1.5 * 2^12: the last place of a sum with it is 2^-40
-        return ((double)x + kRound) - kRound;
-    };
     float smin = INFINITY, smax = -INFINITY;
-    const int first = (tid >> 8) * 8 * 256 + (tid & 255);            // this thread's elements: first + 256 j
 #pragma unroll 1
     for (int half = 0; half < 2; ++half) {
         float v[3][HALF];
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<256>(vals[k], first, half * HALF + j);
+            for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, half * HALF + j);
 #pragma unroll
         for (int j = 0; j < HALF; ++j) {
-            if (s * kSlice + (half * HALF + j) * 256 + first < N) {
+            if (s * kSlice + (half * HALF + j) * TH + tid < N) {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     const float x = v[k][j], y = anomaly_scaled(x);
@@ -252,21 +256,19 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
                 smax = fmaxf(smax, sv);
                 part[6] += sv;
             }
-            if (HALF >= 8 && j % 8 == 7) {
+            if (j % 8 == 7) {
 #pragma unroll
                 for (int i = 0; i < SUMS; ++i) {
-                    sum[i] = j == 7 ? rounded(part[i]) : sum[i] + rounded(part[i]);
+                    sum[i] = j == 7 ? rounded_sum(part[i]) : sum[i] + rounded_sum(part[i]);
                     part[i] = 0.f;
                 }
             }
         }
-        if (HALF >= 8) {
 #pragma unroll
-            for (int i = 0; i < SUMS; ++i) parts[i][tid] = half == 0 ? sum[i] : parts[i][tid] + sum[i];
-        }
+        for (int i = 0; i < SUMS; ++i) parts[i][tid] = half == 0 ? sum[i] : parts[i][tid] + sum[i];
     }
 #pragma unroll
-    for (int i = 0; i < SUMS; ++i) sum[i] = HALF >= 8 ? parts[i][tid] : rounded(part[i]);
+    for (int i = 0; i < SUMS; ++i) sum[i] = parts[i][tid];
     const int w = tid >> 6;
     const double of_wave[8] = {sum[0], sum[3], sum[1], sum[4], sum[2], sum[5], sum[6], 0.0};
     const double total = wave_reduce8(of_wave, [](double x, double y) { return x + y; });
@@ -294,9 +296,107 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void stats_collect_kernel(co
     }
 }
 
-// grid: slices.  Blend, gate, route and pinning of the slice's tokens (Section 2.4); every workgroup forms its
+// The same by four workgroups a slice, for calls of so few slices that a workgroup for each leaves most of the chip idle (one of 1024
+// threads a slice, with the routing: score call of 1 layer x 8 heads x 32768 tokens 52.4 us, 50.4 this way; 4 layers 96.9 and 95.0, 16
+// 296.4 and 295.7).  grid: 4 x slices.  What a quarter finds is added to its slice's: the sums by atomics that are exact (multiples of 2^-40 below 2^13),
+// and so do not depend on the order; the keys go to lists in LDS first and take their places in the slice's by one atomic a list.
+template <bool ALL>
+__global__ __launch_bounds__(256) void stats_collect_quarter_kernel(const float *__restrict__ a_raw, int64_t rows, int L, int H,
+                                                                    PromptTab tab, SliceTab st, int n_slices, int scale_mask,
+                                                                    const StatPick *__restrict__ picks, uint32_t *__restrict__ segTop,
+                                                                    uint32_t *__restrict__ segBot, SlicePart *__restrict__ sp,
+                                                                    SliceSurprise *__restrict__ sur, uint32_t *__restrict__ failed)
+{
+    constexpr int EACH = kQuarter / 256, NW = 4;
+    __shared__ uint32_t cnt[6], base[6], keys[6][kSeg];              // list 2 k: the upper boundary bin of scale k, 2 k + 1 the lower one
+    __shared__ double red[8][NW];
+    __shared__ float fred[2][NW];
+    const int slice = blockIdx.x / 4, quarter = blockIdx.x & 3;
+    int p, lh, s, S;
+    locate(st, tab, slice, p, lh, s, S);
+    const int N = tab.tok_off[p + 1] - tab.tok_off[p], first = quarter * kQuarter;
+    if (s * kSlice + first >= N) return;
+    const float *a = a_raw + (int64_t)lh * tab.T + tab.tok_off[p];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int64_t job0 = ((int64_t)p * L * H + lh) * 3;
+    float v[3][EACH];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const __amdgpu_buffer_rsrc_t vals = slice_values(a + k * rows, s, N);
+#pragma unroll
+        for (int j = 0; j < EACH; ++j) v[k][j] = slice_value<256>(vals, first + tid, j);
+    }
+    BinEdges top[3], bot[3];
+    HeadStats hs;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const StatPick pk = picks[job0 + k];
+        top[k] = bin_edges(pk.bTop);
+        bot[k] = bin_edges(pk.bBot);
+        hs.lo[k] = pk.lo;
+        hs.inv_range[k] = pk.inv;
+    }
+    if (tid < 6) cnt[tid] = 0u;
+    __syncthreads();
+    float part[7] = {}, smin = INFINITY, smax = 0.f;                  // (as in stats_collect_kernel)
+#pragma unroll
+    for (int j = 0; j < EACH; ++j) {
+        if (s * kSlice + first + j * 256 + tid >= N) continue;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float x = v[k][j], y = anomaly_scaled(x);
+            const bool over = y >= top[k].above, under = y < bot[k].below;
+            part[k] += over ? x : 0.f;
+            part[3 + k] += under ? x : 0.f;
+            const bool in[2] = {!over && y >= top[k].from, !under && y < bot[k].to};
+            if (!in[0] && !in[1]) continue;
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (in[e]) {
+                    const uint32_t at = atomicAdd(&cnt[2 * k + e], 1u);
+                    if (at < (uint32_t)kSeg) keys[2 * k + e][at] = e == 0 ? ord_key(x) : ~ord_key(x);
+                }
+        }
+        const float raw[3] = {v[0][j], v[1][j], v[2][j]};
+        float at[3];
+        normalised(raw, hs, at);
+        const float sv = surprise_std<ALL>(at, scale_mask);
+        smin = fminf(smin, sv);
+        smax = fmaxf(smax, sv);
+        part[6] += sv;
+    }
+    const double sums[8] = {rounded_sum(part[0]), rounded_sum(part[3]), rounded_sum(part[1]), rounded_sum(part[4]),
+                            rounded_sum(part[2]), rounded_sum(part[5]), rounded_sum(part[6]), 0.0};
+    const double total = wave_reduce8(sums, [](double x, double y) { return x + y; });
+    if ((lane & 7) == 0) red[lane >> 3][w] = total;
+    smin = wave_min(smin);
+    smax = wave_max(smax);
+    if (lane == 0) { fred[0][w] = smin; fred[1][w] = smax; }
+    __syncthreads();
+    if (tid < 6) {
+        SlicePart *q = sp + (int64_t)(tid >> 1) * n_slices + slice;
+        const uint32_t n = cnt[tid];
+        base[tid] = atomicAdd(tid & 1 ? &q->nBot : &q->nTop, n);
+        unsafeAtomicAdd(tid & 1 ? &q->sBot : &q->sTop, (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]));
+        if (base[tid] + n > (uint32_t)kSeg) failed[job0 + (tid >> 1)] = 1u;
+    } else if (tid == 64) {
+        unsafeAtomicAdd(&sur[slice].sum, (red[6][0] + red[6][1]) + (red[6][2] + red[6][3]));
+        // (no deviation is negative, so the floats compare as integers)
+        atomicMin((int *)&sur[slice].lo, __float_as_int(fminf(fminf(fred[0][0], fred[0][1]), fminf(fred[0][2], fred[0][3]))));
+        atomicMax((int *)&sur[slice].hi, __float_as_int(fmaxf(fmaxf(fred[1][0], fred[1][1]), fmaxf(fred[1][2], fred[1][3]))));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        uint32_t *seg = (i & 1 ? segBot : segTop) + ((int64_t)(i >> 1) * n_slices + slice) * kSeg;
+        if ((uint32_t)tid < min(cnt[i], (uint32_t)kSeg) && base[i] + tid < (uint32_t)kSeg) seg[base[i] + tid] = keys[i][tid];
+    }
+    static_assert(kSeg <= 256, "a key a thread");
+}
+
+// grid: slices, times PARTS: workgroups a slice.  Blend, gate, route and pinning of the slice's tokens (Section 2.4); every workgroup forms its
 // head's weights and surprise statistics itself from the few numbers they depend on.
-template <int TH, bool ALL>
+template <int TH, int PARTS, bool ALL>
 __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                    int L, int H, PromptTab tab, SliceTab st,
                                                                    LearnerConsts lc, const float *__restrict__ stats,
@@ -305,18 +405,20 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
 {
     __shared__ HeadStats hs;
     int p, lh, s, S;
-    locate(st, tab, blockIdx.x, p, lh, s, S);
+    const int slice = blockIdx.x / PARTS, first = (int)(blockIdx.x % PARTS) * (kSlice / PARTS);
+    locate(st, tab, slice, p, lh, s, S);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
+    if (PARTS > 1 && s * kSlice + first >= N) return;
     const int64_t base = (int64_t)lh * tab.T + tab.tok_off[p];
     const float *a = a_raw + base;
     const int tid = threadIdx.x;
-    constexpr int HALF = per_thread<TH>() / 2;
+    constexpr int HALF = per_thread<TH>() / PARTS / 2;
     float v[3][HALF];
     const __amdgpu_buffer_rsrc_t vals[3] = {slice_values(a, s, N), slice_values(a + rows, s, N), slice_values(a + 2 * rows, s, N)};
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
-        for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, j);
+        for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], first + tid, j);
     if (tid < 64) {
         const float *sk = stats + ((int64_t)p * L * H + lh) * 12 + 4 * min(tid, 2);
         head_weights(sk[0], sk[1], sk[2], lc, hs);
@@ -324,7 +426,7 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
     if (tid == 0) {
         float smin = INFINITY, smax = -INFINITY;
         double ssum = 0.0;
-        const SliceSurprise *q = sur + (blockIdx.x - s);
+        const SliceSurprise *q = sur + (slice - s);
         for (int i = 0; i < S; ++i) {                                // the head's slices in order
             smin = fminf(smin, q[i].lo);
             smax = fmaxf(smax, q[i].hi);
@@ -344,11 +446,11 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
-                for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, HALF + j);
+                for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], first + tid, HALF + j);
         }
 #pragma unroll
         for (int j = 0; j < HALF; ++j) {
-            const int i = s * kSlice + (half * HALF + j) * TH + tid;
+            const int i = s * kSlice + first + (half * HALF + j) * TH + tid;
             if (i < N) {
                 const float raw[3] = {v[0][j], v[1][j], v[2][j]};
                 float at[3];
@@ -503,17 +605,17 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
     StatPick *picks = (StatPick *)(base + lay.picks);
     uint32_t *segTop = (uint32_t *)(base + lay.segTop), *segBot = (uint32_t *)(base + lay.segBot);
     uint32_t *failed = (uint32_t *)(base + lay.failed);
+    SliceSurprise *sur = (SliceSurprise *)(base + lay.sur);
     const int64_t rows = (int64_t)L * H * tab.T;
     const unsigned units = (unsigned)(tab.n * L * H);
     const bool few = few_slices(slices);
     (few ? stats_hist_kernel<1024> : stats_hist_kernel<256>)<<<dim3((unsigned)slices, 3), few ? 1024 : 256, 0, st>>>(
-        a_raw, rows, tab, stab, slices, part, sp);
-    SliceSurprise *sur = (SliceSurprise *)(base + lay.sur);
+        a_raw, rows, tab, stab, slices, part, sp, sur);
     stats_pick_kernel<<<dim3(units, 3), 256, 0, st>>>(L, H, tab, stab, slices, part, sp, picks, failed);
     const bool all = scale_mask == 7;
-    const auto collect = few ? (all ? stats_collect_kernel<1024, true> : stats_collect_kernel<1024, false>)
-                             : (all ? stats_collect_kernel<256, true> : stats_collect_kernel<256, false>);
-    collect<<<(unsigned)slices, few ? 1024 : 256, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask, picks, segTop, segBot, sp,
+    const auto collect = few ? (all ? stats_collect_quarter_kernel<true> : stats_collect_quarter_kernel<false>)
+                             : (all ? stats_collect_kernel<true> : stats_collect_kernel<false>);
+    collect<<<(unsigned)(few ? 4 * slices : slices), 256, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask, picks, segTop, segBot, sp,
                                                            sur, failed);
     stats_finish_kernel<<<dim3(units, 3), 128, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, picks, segTop, segBot,
                                                        sp, failed, stats);
@@ -529,9 +631,9 @@ hipError_t launch_route_wide(const float *a_raw, int L, int H, const PromptTab &
     const WideWs lay = wide_ws(L, H, tab);
     const SliceSurprise *sur = (const SliceSurprise *)((char *)ws + lay.sur);
     const bool few = few_slices(slices), all = lc.scale_mask == 7;
-    const auto route = few ? (all ? route_slice_kernel<1024, true> : route_slice_kernel<1024, false>)
-                           : (all ? route_slice_kernel<256, true> : route_slice_kernel<256, false>);
-    route<<<(unsigned)slices, few ? 1024 : 256, 0, st>>>(a_raw, (int64_t)L * H * tab.T, L, H, tab, stab, lc, stats, sur, scores);
+    const auto route = few ? (all ? route_slice_kernel<256, 4, true> : route_slice_kernel<256, 4, false>)
+                           : (all ? route_slice_kernel<256, 1, true> : route_slice_kernel<256, 1, false>);
+    route<<<(unsigned)(few ? 4 * slices : slices), 256, 0, st>>>(a_raw, (int64_t)L * H * tab.T, L, H, tab, stab, lc, stats, sur, scores);
     return hipGetLastError();
 }
 

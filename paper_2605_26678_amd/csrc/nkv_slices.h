@@ -19,7 +19,7 @@ namespace {
 constexpr int kSlice = 8192;             // tokens per slice (the counts of a slice fit 16 bits)
 constexpr int kBins = 2048;
 // Up to two slices per compute unit: with 1024 threads each they are all resident, and quicker (one layer of 8 heads x
-// 32768 tokens, 32 slices: statistics' collecting kernel 17 -> 7 us); many slices keep the chip full either way, and the
+// 32768 tokens, 32 slices: the statistics' collecting kernel 17 -> 7 us; it and the routing now take four workgroups of 256); many slices keep the chip full either way, and the
 // smaller workgroup has fewer wavefronts at its barriers.  At 512 slices (16 layers of 8 x 32768 tokens), 256 threads / 1024:
 // score 255 / 248 us, budgets 30.4 / 28.3, selection 54.0 / 49.0; at 544 slices the two are within 1 % of each other.
 constexpr int kFewSlices = 512;

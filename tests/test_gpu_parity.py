@@ -1185,3 +1185,24 @@ def test_shape_generic_window_of_64_tokens(d, dtype, block, lens):
         # fp32 cosines of 128 terms: both kernels are within a few 1e-7 of the exact value
         assert (raw[0] - raw[1])[..., at:at + min(n, 64)].abs().max().item() < 2e-6
         at += n
+
+
+@pytest.mark.parametrize("lens", [[16385, 8191, 8193, 1], [18431, 2047, 2048, 2049], [18433, 6144, 6145, 10240]])
+@pytest.mark.parametrize("crowded", [False, True])
+def test_statistics_of_few_slices_at_the_ends_of_quarters(lens, crowded):
+    """Slice-wise statistics of so few slices that four workgroups share one (2048 tokens each): prompts that end just before, at
+    and behind a quarter's or a slice's end; crowded: one key repeated over half of each prompt, more values in a bin than the
+    lists hold.  Against the oracle, and whole calls bit for bit against the same prompts among so many that a workgroup takes a slice."""
+    w = nkv_inputs.small_workload(f"quarters_{lens[0]}", 1, 2, 64, lens, n_out=0)
+    K, V = _kv(w)
+    if crowded:
+        at = 0
+        for n in lens:
+            K[:, :, at + n // 4:at + n // 4 + n // 2] = K[:, :, at + n // 4:at + n // 4 + 1]
+            at += n
+    compare_end_to_end(w, K, V, 0.5, label=w.name)
+    few, _ = run_gpu(w, K, V, 0.5)
+    many = nkv_inputs.small_workload(f"quarters_many_{lens[0]}", 50, 2, 64, lens, n_out=0)
+    a, _ = run_gpu(many, K.expand(50, -1, -1, -1).contiguous(), V.expand(50, -1, -1, -1).contiguous(), 0.5)
+    assert sum((n + 8191) // 8192 for n in lens) * 100 > 512
+    assert torch.equal(a.scores[17], few.scores[0])
