@@ -76,16 +76,22 @@ __global__ __launch_bounds__(TH) void stats_hist_kernel(const float *__restrict_
     for (int j = 0; j < PT / 4; ++j) slice_values4<TH>(vals, tid, j, v[j]);
     __syncthreads();
     float lo = INFINITY, hi = -INFINITY;
+    auto count = [&](float x) {                                      // (medians of three: minimum and maximum in one instruction each)
+        lo = __builtin_amdgcn_fmed3f(x, lo, -INFINITY);
+        hi = __builtin_amdgcn_fmed3f(x, hi, INFINITY);
+        atomicAdd(&hist[anomaly_bin(x)], 1u);
+    };
+    if ((s + 1) * kSlice <= N) {
 #pragma unroll
-    for (int j = 0; j < PT / 4; ++j) {
+        for (int j = 0; j < PT / 4; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (s * kSlice + 4 * (j * TH + tid) + e < N) {
-                lo = fminf(lo, v[j][e]);
-                hi = fmaxf(hi, v[j][e]);
-                atomicAdd(&hist[anomaly_bin(v[j][e])], 1u);
-            }
-        }
+            for (int e = 0; e < 4; ++e) count(v[j][e]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < PT / 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (s * kSlice + 4 * (j * TH + tid) + e < N) count(v[j][e]);
     }
     lo = wave_min(lo);
     hi = wave_max(hi);
@@ -174,134 +180,16 @@ __global__ __launch_bounds__(256) void stats_pick_kernel(int L, int H, PromptTab
     }
 }
 
-// grid: slices.  All three scales of the slice in one pass: what stats_finish_kernel needs of each scale, and --
-// the ranges being known -- min, max and sum of the surprise statistic of the slice's tokens.
-// Bound by instruction issue: values are compared with the boundary bins' edges instead of binned (with that, the seven sums of a
-// wavefront at once and the weights in three lanes of the routing, score calls: 1 layer x 8 heads x 32768 tokens 53.3 -> 52.4 us, 36 layers 626.2 -> 622.4).
+// grid: quarters of slices.  All three scales of 2048 tokens in one pass: what stats_finish_kernel needs of each scale, and -- the ranges
+// being known -- min, max and sum of the surprise statistic.  Bound by instruction issue: values are compared with the boundary
+// bins' edges instead of binned.  What a quarter finds is added to its slice's; the keys go to lists in LDS first and take their places in the
+// slice's by one atomic a list.
+// Sums: a thread's eight tokens, 256 apart, in 32 bits; their sums, rounded to 2^-40, add up exactly in 64 bits (fewer than 2^13 in
+// all), across lanes and by atomics, so that they do not depend on the order.
+// (By one workgroup a slice, of 1024 threads up to 512 slices and of 256, four such sums a thread, from there on, score calls of 8 heads x
+// 32768 tokens: 1 layer 52.4 us, 50.4 this way; 4 layers 96.9 and 95.0; 17 312 and 304; 36 613 and 611; 8 layers of 131 072 8-bit keys 518 and 512.)
 template <bool ALL>
-__global__ __launch_bounds__(256, 5) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows,
-                                                                     int L, int H, PromptTab tab, SliceTab st,
-                                                                     int n_slices, int scale_mask,
-                                                                     const StatPick *__restrict__ picks,
-                                                                     uint32_t *__restrict__ segTop,
-                                                                     uint32_t *__restrict__ segBot,
-                                                                     SlicePart *__restrict__ sp,
-                                                                     SliceSurprise *__restrict__ sur,
-                                                                     uint32_t *__restrict__ failed)
-{
-    constexpr int TH = 256, HALF = per_thread<TH>() / 2;
-    __shared__ uint32_t nTop[3], nBot[3];
-    __shared__ double red[8][TH / 64];
-    __shared__ float fred[2][TH / 64];
-    int p, lh, s, S;
-    locate(st, tab, blockIdx.x, p, lh, s, S);
-    const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-    const float *a = a_raw + (int64_t)lh * tab.T + tab.tok_off[p];
-    const int tid = threadIdx.x;
-    const int64_t job0 = ((int64_t)p * L * H + lh) * 3;
-    BinEdges top[3], bot[3];
-    HeadStats hs;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const StatPick pk = picks[job0 + k];
-        top[k] = bin_edges(pk.bTop);
-        bot[k] = bin_edges(pk.bBot);
-        hs.lo[k] = pk.lo;
-        hs.inv_range[k] = pk.inv;
-    }
-    if (tid < 3) { nTop[tid] = 0u; nBot[tid] = 0u; }
-    __syncthreads();
-    const __amdgpu_buffer_rsrc_t vals[3] = {slice_values(a, s, N), slice_values(a + rows, s, N), slice_values(a + 2 * rows, s, N)};
-    // Sums: eight tokens, 256 apart, in 32 bits, the same eight as for a workgroup of a quarter; their sums, rounded to 2^-40, add up exactly in 64 bits
-    // (fewer than 2^13 in all), so that the statistics of a head do not depend on how many heads the call has.  A thread has
-    // four such sums of each kind; between its two halves they wait in LDS (in registers: five waves a SIMD instead of seven, and this
-    // kernel takes 93 us instead of 87 for 3584 slices; 86 with all of a thread's terms in 32 bits).
-    constexpr int SUMS = 7;                                          // 0 .. 2 above, 3 .. 5 below the boundary bins, 6 the surprise
-    __shared__ double parts[SUMS][TH];
-    float part[SUMS] = {};
-    double sum[SUMS];
-    float smin = INFINITY, smax = -INFINITY;
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        float v[3][HALF];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], tid, half * HALF + j);
-#pragma unroll
-        for (int j = 0; j < HALF; ++j) {
-            if (s * kSlice + (half * HALF + j) * TH + tid < N) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const float x = v[k][j], y = anomaly_scaled(x);
-                    const bool over = y >= top[k].above, under = y < bot[k].below;
-                    part[k] += over ? x : 0.f;
-                    part[3 + k] += under ? x : 0.f;
-                    const bool in_top = !over && y >= top[k].from, in_bot = !under && y < bot[k].to;
-                    if (!in_top && !in_bot) continue;
-                    if (in_top) {
-                        const uint32_t at = atomicAdd(&nTop[k], 1u);
-                        if (at < (uint32_t)kSeg) segTop[((int64_t)k * n_slices + blockIdx.x) * kSeg + at] = ord_key(x);
-                    }
-                    if (in_bot) {                                    // inverted: the smallest value has the largest key
-                        const uint32_t at = atomicAdd(&nBot[k], 1u);
-                        if (at < (uint32_t)kSeg) segBot[((int64_t)k * n_slices + blockIdx.x) * kSeg + at] = ~ord_key(x);
-                    }
-                }
-                const float raw[3] = {v[0][j], v[1][j], v[2][j]};
-                float at[3];
-                normalised(raw, hs, at);
-                const float sv = surprise_std<ALL>(at, scale_mask);
-                smin = fminf(smin, sv);
-                smax = fmaxf(smax, sv);
-                part[6] += sv;
-            }
-            if (j % 8 == 7) {
-#pragma unroll
-                for (int i = 0; i < SUMS; ++i) {
-                    sum[i] = j == 7 ? rounded_sum(part[i]) : sum[i] + rounded_sum(part[i]);
-                    part[i] = 0.f;
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < SUMS; ++i) parts[i][tid] = half == 0 ? sum[i] : parts[i][tid] + sum[i];
-    }
-#pragma unroll
-    for (int i = 0; i < SUMS; ++i) sum[i] = parts[i][tid];
-    const int w = tid >> 6;
-    const double of_wave[8] = {sum[0], sum[3], sum[1], sum[4], sum[2], sum[5], sum[6], 0.0};
-    const double total = wave_reduce8(of_wave, [](double x, double y) { return x + y; });
-    if ((tid & 7) == 0) red[(tid & 63) >> 3][w] = total;
-    smin = wave_min(smin);
-    smax = wave_max(smax);
-    if ((tid & 63) == 0) { fred[0][w] = smin; fred[1][w] = smax; }
-    __syncthreads();
-    if (tid < 3) {
-        const int k = tid;
-        double t = 0.0, b = 0.0;
-        for (int i = 0; i < TH / 64; ++i) { t += red[2 * k][i]; b += red[2 * k + 1][i]; }
-        SlicePart *q = sp + (int64_t)k * n_slices + blockIdx.x;
-        q->sTop = t;
-        q->sBot = b;
-        q->nTop = nTop[k];
-        q->nBot = nBot[k];
-        if (nTop[k] > (uint32_t)kSeg || nBot[k] > (uint32_t)kSeg) failed[job0 + k] = 1u;
-    }
-    if (tid == 64) {
-        double t = 0.0;
-        float lo = INFINITY, hi = -INFINITY;
-        for (int i = 0; i < TH / 64; ++i) { t += red[6][i]; lo = fminf(lo, fred[0][i]); hi = fmaxf(hi, fred[1][i]); }
-        sur[blockIdx.x] = SliceSurprise{lo, hi, t};
-    }
-}
-
-// The same by four workgroups a slice, for calls of so few slices that a workgroup for each leaves most of the chip idle (one of 1024
-// threads a slice, with the routing: score call of 1 layer x 8 heads x 32768 tokens 52.4 us, 50.4 this way; 4 layers 96.9 and 95.0, 16
-// 296.4 and 295.7).  grid: 4 x slices.  What a quarter finds is added to its slice's: the sums by atomics that are exact (multiples of 2^-40 below 2^13),
-// and so do not depend on the order; the keys go to lists in LDS first and take their places in the slice's by one atomic a list.
-template <bool ALL>
-__global__ __launch_bounds__(256) void stats_collect_quarter_kernel(const float *__restrict__ a_raw, int64_t rows, int L, int H,
+__global__ __launch_bounds__(256) void stats_collect_kernel(const float *__restrict__ a_raw, int64_t rows, int L, int H,
                                                                     PromptTab tab, SliceTab st, int n_slices, int scale_mask,
                                                                     const StatPick *__restrict__ picks, uint32_t *__restrict__ segTop,
                                                                     uint32_t *__restrict__ segBot, SlicePart *__restrict__ sp,
@@ -338,7 +226,7 @@ __global__ __launch_bounds__(256) void stats_collect_quarter_kernel(const float 
     }
     if (tid < 6) cnt[tid] = 0u;
     __syncthreads();
-    float part[7] = {}, smin = INFINITY, smax = 0.f;                  // (as in stats_collect_kernel)
+    float part[7] = {}, smin = INFINITY, smax = 0.f;
 #pragma unroll
     for (int j = 0; j < EACH; ++j) {
         if (s * kSlice + first + j * 256 + tid >= N) continue;
@@ -394,10 +282,10 @@ __global__ __launch_bounds__(256) void stats_collect_quarter_kernel(const float 
     static_assert(kSeg <= 256, "a key a thread");
 }
 
-// grid: slices, times PARTS: workgroups a slice.  Blend, gate, route and pinning of the slice's tokens (Section 2.4); every workgroup forms its
+// grid: quarters of slices.  Blend, gate, route and pinning of the slice's tokens (Section 2.4); every workgroup forms its
 // head's weights and surprise statistics itself from the few numbers they depend on.
-template <int TH, int PARTS, bool ALL>
-__global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(const float *__restrict__ a_raw, int64_t rows,
+template <bool ALL>
+__global__ __launch_bounds__(256) void route_slice_kernel(const float *__restrict__ a_raw, int64_t rows,
                                                                    int L, int H, PromptTab tab, SliceTab st,
                                                                    LearnerConsts lc, const float *__restrict__ stats,
                                                                    const SliceSurprise *__restrict__ sur,
@@ -405,25 +293,26 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
 {
     __shared__ HeadStats hs;
     int p, lh, s, S;
-    const int slice = blockIdx.x / PARTS, first = (int)(blockIdx.x % PARTS) * (kSlice / PARTS);
+    const int slice = blockIdx.x / 4, first = (int)(blockIdx.x & 3) * kQuarter;
     locate(st, tab, slice, p, lh, s, S);
     const int N = tab.tok_off[p + 1] - tab.tok_off[p];
-    if (PARTS > 1 && s * kSlice + first >= N) return;
+    if (s * kSlice + first >= N) return;
     const int64_t base = (int64_t)lh * tab.T + tab.tok_off[p];
     const float *a = a_raw + base;
     const int tid = threadIdx.x;
-    constexpr int HALF = per_thread<TH>() / PARTS / 2;
-    float v[3][HALF];
-    const __amdgpu_buffer_rsrc_t vals[3] = {slice_values(a, s, N), slice_values(a + rows, s, N), slice_values(a + 2 * rows, s, N)};
+    constexpr int EACH = kQuarter / 256;
+    float v[3][EACH];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 3; ++k) {
+        const __amdgpu_buffer_rsrc_t vals = slice_values(a + k * rows, s, N);
 #pragma unroll
-        for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], first + tid, j);
+        for (int j = 0; j < EACH; ++j) v[k][j] = slice_value<256>(vals, first + tid, j);
+    }
     if (tid < 64) {
         const float *sk = stats + ((int64_t)p * L * H + lh) * 12 + 4 * min(tid, 2);
         head_weights(sk[0], sk[1], sk[2], lc, hs);
     }
-    if (tid == 0) {
+    if (tid == 64) {
         float smin = INFINITY, smax = -INFINITY;
         double ssum = 0.0;
         const SliceSurprise *q = sur + (slice - s);
@@ -440,23 +329,14 @@ __global__ __launch_bounds__(TH, TH == 256 ? 5 : 4) void route_slice_kernel(cons
     __syncthreads();
     const HeadStats h = hs;
     float *out = scores + base;
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        if (half == 1) {
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int j = 0; j < HALF; ++j) v[k][j] = slice_value<TH>(vals[k], first + tid, HALF + j);
-        }
-#pragma unroll
-        for (int j = 0; j < HALF; ++j) {
-            const int i = s * kSlice + first + (half * HALF + j) * TH + tid;
-            if (i < N) {
-                const float raw[3] = {v[0][j], v[1][j], v[2][j]};
-                float at[3];
-                normalised(raw, h, at);
-                out[i] = i < lc.n_sink ? NKV_PIN : routed_score<ALL>(at, h, lc);
-            }
+    for (int j = 0; j < EACH; ++j) {
+        const int i = s * kSlice + first + j * 256 + tid;
+        if (i < N) {
+            const float raw[3] = {v[0][j], v[1][j], v[2][j]};
+            float at[3];
+            normalised(raw, h, at);
+            out[i] = i < lc.n_sink ? NKV_PIN : routed_score<ALL>(at, h, lc);
         }
     }
 }
@@ -613,10 +493,8 @@ hipError_t launch_stats_wide(const float *a_raw, int L, int H, const PromptTab &
         a_raw, rows, tab, stab, slices, part, sp, sur);
     stats_pick_kernel<<<dim3(units, 3), 256, 0, st>>>(L, H, tab, stab, slices, part, sp, picks, failed);
     const bool all = scale_mask == 7;
-    const auto collect = few ? (all ? stats_collect_quarter_kernel<true> : stats_collect_quarter_kernel<false>)
-                             : (all ? stats_collect_kernel<true> : stats_collect_kernel<false>);
-    collect<<<(unsigned)(few ? 4 * slices : slices), 256, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, scale_mask, picks, segTop, segBot, sp,
-                                                           sur, failed);
+    (all ? stats_collect_kernel<true> : stats_collect_kernel<false>)<<<4u * (unsigned)slices, 256, 0, st>>>(
+        a_raw, rows, L, H, tab, stab, slices, scale_mask, picks, segTop, segBot, sp, sur, failed);
     stats_finish_kernel<<<dim3(units, 3), 128, 0, st>>>(a_raw, rows, L, H, tab, stab, slices, picks, segTop, segBot,
                                                        sp, failed, stats);
     return hipGetLastError();
@@ -630,10 +508,8 @@ hipError_t launch_route_wide(const float *a_raw, int L, int H, const PromptTab &
     const int slices = fill_slices(L, H, tab, &stab);
     const WideWs lay = wide_ws(L, H, tab);
     const SliceSurprise *sur = (const SliceSurprise *)((char *)ws + lay.sur);
-    const bool few = few_slices(slices), all = lc.scale_mask == 7;
-    const auto route = few ? (all ? route_slice_kernel<256, 4, true> : route_slice_kernel<256, 4, false>)
-                           : (all ? route_slice_kernel<256, 1, true> : route_slice_kernel<256, 1, false>);
-    route<<<(unsigned)(few ? 4 * slices : slices), 256, 0, st>>>(a_raw, (int64_t)L * H * tab.T, L, H, tab, stab, lc, stats, sur, scores);
+    (lc.scale_mask == 7 ? route_slice_kernel<true> : route_slice_kernel<false>)<<<4u * (unsigned)slices, 256, 0, st>>>(
+        a_raw, (int64_t)L * H * tab.T, L, H, tab, stab, lc, stats, sur, scores);
     return hipGetLastError();
 }
 

@@ -82,19 +82,18 @@ template <int TH> __device__ __forceinline__ void slice_values4(__amdgpu_buffer_
     v[0] = __uint_as_float(q[0]); v[1] = __uint_as_float(q[1]); v[2] = __uint_as_float(q[2]); v[3] = __uint_as_float(q[3]);
 }
 
-// Scores: floor(2046 v) for 0 <= v <= 1, 0 below, 2047 above 1 (the pinned positions).  Monotone in v.
+// Scores: floor(2046 v) for 0 <= v <= 1, 0 below, 2047 above 1 (the pinned positions).  Monotone in v.  (The histogram kernels are
+// bound by the instructions they issue per value: a median of three clamps in one.)
 __device__ __forceinline__ int score_bin(float v)
 {
-    const float x = v * 2046.0f;
-    return x >= 2046.0f ? (v > 1.0f ? 2047 : 2046) : (x > 0.f ? (int)x : 0);
+    return (int)__builtin_amdgcn_fmed3f(v * 2046.0f, 0.f, 2046.0f) + (v > 1.0f ? 1 : 0);
 }
 
 // Anomalies (-cos, so in [-1, 1]): floor(1023.5 (a + 1)), clamped.  Monotone in a.
 __device__ __forceinline__ float anomaly_scaled(float a) { return (a + 1.0f) * 1023.5f; }
 __device__ __forceinline__ int anomaly_bin(float a)
 {
-    const float x = anomaly_scaled(a);
-    return x >= 2047.0f ? 2047 : (x > 0.f ? (int)x : 0);
+    return (int)__builtin_amdgcn_fmed3f(anomaly_scaled(a), 0.f, 2047.0f);
 }
 
 // Where y = a value on the scale of its bins lies to a boundary bin: bin > q <=> y >= above, bin < q <=> y < below, and what is neither is in
@@ -147,11 +146,18 @@ __global__ __launch_bounds__(TH) void slice_hist_kernel(const float *__restrict_
 #pragma unroll
     for (int j = 0; j < PT / 4; ++j) slice_values4<TH>(vals, tid, j, v[j]);
     __syncthreads();
+    if ((s + 1) * kSlice <= N) {
 #pragma unroll
-    for (int j = 0; j < PT / 4; ++j)
+        for (int j = 0; j < PT / 4; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (s * kSlice + 4 * (j * TH + tid) + e < N) atomicAdd(&hist[score_bin(v[j][e])], 1u);
+            for (int e = 0; e < 4; ++e) atomicAdd(&hist[score_bin(v[j][e])], 1u);
+    } else {
+#pragma unroll
+        for (int j = 0; j < PT / 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (s * kSlice + 4 * (j * TH + tid) + e < N) atomicAdd(&hist[score_bin(v[j][e])], 1u);
+    }
     __syncthreads();
     store_hist16(hist, part + (int64_t)blockIdx.x * kBins);
 }
