@@ -848,8 +848,10 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
 // A workgroup of this scan takes a block and loads 64 tokens in front of it whatever the block's length.  Blocks of fewer
 // than 8 tokens, more of a unit than fit the chip together (so that every one is deferred as well), are done sooner by
 // other kernels.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / vector scan / shape-generic: bf16, head
-// dim 128, one layer 466 / 1204 / 423 us, four layers 1722 / 1800 / 1128; head dim 40 457 / - / 291 and 1683 / - / 883; 8-bit,
-// head dim 128 470 / 1135 / 643 and 1727 / 1558 / 1988 (in blocks of one 6746 / 8167 / 6226).  In blocks of 8: bf16 258 / 639 / 288 and 891 / 946 / 785.
+// dim 128, one layer 455 / 1204 / 311 us, four layers 1697 / 1800 / 740; head dim 40 444 / - / 194 and 1659 / - / 552; 8-bit,
+// head dim 128 452 / 1135 / 474 and 1683 / 1548 / 1374 (in blocks of one 6586 / 8167 / 4866).  (In blocks of 8 to 32 the shape-generic kernels
+// have become quicker for 16-bit keys too, bf16 249 / 193 and 872 / 469 us in blocks of 8, 260 / 234 in deferred blocks of 32, but they need scratch
+// that callers of those shapes were not asked for.)
 TinyBlocks tile_tiny_blocks(int dtype, int d, const PromptTab &tab, int LH)
 {
     int shortest = 8;
