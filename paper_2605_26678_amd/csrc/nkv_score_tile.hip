@@ -845,19 +845,20 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
     return (int64_t)LH * (tab.blk_off[tab.n] + tab.n) < (1ll << 28);
 }
 
-// A workgroup of this scan takes a block and loads 64 tokens in front of it whatever the block's length.  Blocks of fewer
-// than 8 tokens, more of a unit than fit the chip together (so that every one is deferred as well), are done sooner by
-// other kernels.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / vector scan / shape-generic: bf16, head
+// A workgroup of this scan takes a block and loads 64 tokens in front of it whatever the block's length.  Where there are more blocks
+// of a unit than fit the chip together (so that every one is deferred as well), short ones are done sooner by other kernels: up to 24
+// tokens of 16-bit keys, up to 7 of 8-bit keys.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / vector scan / shape-generic: bf16, head
 // dim 128, one layer 455 / 1204 / 311 us, four layers 1697 / 1800 / 740; head dim 40 444 / - / 194 and 1659 / - / 552; 8-bit,
-// head dim 128 452 / 1135 / 474 and 1683 / 1548 / 1374 (in blocks of one 6586 / 8167 / 4866).  (In blocks of 8 to 32 the shape-generic kernels
-// have become quicker for 16-bit keys too, bf16 249 / 193 and 872 / 469 us in blocks of 8, 260 / 234 in deferred blocks of 32, but they need scratch
-// that callers of those shapes were not asked for.)
+// head dim 128 452 / 1135 / 474 and 1683 / 1548 / 1374 (in blocks of one 6586 / 8167 / 4866).  In blocks of 8: bf16 249 / 639 / 193 and 872 / 946 / 469,
+// 8-bit 247 / - / 309 and 864 / - / 907.  Bf16, this scan / shape-generic: 32768 tokens in blocks of 24, four layers 632 / 544, head dim 40
+// 599 / 373; 65536 in blocks of 32, one layer 263 / 287, four 942 / 892, head dim 40 248 / 192 and 874 / 604.
 TinyBlocks tile_tiny_blocks(int dtype, int d, const PromptTab &tab, int LH)
 {
-    int shortest = 8;
+    const int none = dtype == NKV_DTYPE_F8_E4M3 ? 8 : 25;
+    int shortest = none;
     for (int p = 0; p < tab.n; ++p)
         if (tab.blk_off[p + 1] - tab.blk_off[p] > resident_tile_workgroups()) shortest = min(shortest, (int)tab.b[p]);
-    if (shortest == 8) return kTinyNone;
+    if (shortest == none) return kTinyNone;
     if (dtype != NKV_DTYPE_F8_E4M3) return kTinyGeneric;
     return shortest > 1 && d == 128 && (int64_t)LH * tab.blk_off[tab.n] > 65536 ? kTinyVector : kTinyNone;
 }

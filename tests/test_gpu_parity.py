@@ -1206,3 +1206,14 @@ def test_statistics_of_few_slices_at_the_ends_of_quarters(lens, crowded):
     a, _ = run_gpu(many, K.expand(50, -1, -1, -1).contiguous(), V.expand(50, -1, -1, -1).contiguous(), 0.5)
     assert sum((n + 8191) // 8192 for n in lens) * 100 > 512
     assert torch.equal(a.scores[17], few.scores[0])
+
+
+@pytest.mark.parametrize("d,dtype", [(8, "fp16"), (128, "bf16")])
+@pytest.mark.parametrize("block,blocks", [(8, 1025), (24, 1024), (24, 1025), (25, 1025)])
+def test_short_blocks_of_16_bit_keys_on_both_sides_of_the_line(block, blocks, d, dtype):
+    """Blocks of up to 24 tokens, more of a unit than the chip holds (1024), leave the matrix-core scan, longer ones and units that
+    fit stay with it; a short last block and a short prompt beside it.  Against the oracle."""
+    N = block * (blocks - 1) + 1
+    w = nkv_inputs.small_workload(f"line_{d}_{block}_{blocks}", 1, 2, d, [N, 333], dtype=dtype, n_out=0)
+    K, V = _kv(w)
+    compare_end_to_end(w, K, V, 0.6, params=nkv.params_default(block_min=block, block_max=block), label=w.name)
