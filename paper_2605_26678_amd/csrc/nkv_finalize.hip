@@ -172,8 +172,8 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(const float *__restr
 // two kernels of radix selects, one workgroup per scale, 16 x 8 units of 4096 tokens took 33 us, this takes 12), and inside them the
 // instructions that sixteen wavefronts issue on four SIMDs.  Of 31 000 cycles of a unit of 4096 tokens with a bin formed for every value and
 // every wavefront's result reduced by itself, step 3 took 10 000, ranges and histograms 5 000 each.  Against that, values compared with
-// the boundary bins' edges, eight reductions at once, weights in three lanes: the score call of those units 49.4 -> 46.5 us, the batch below
-// 104.5 -> 92.5.
+// the boundary bins' edges, eight reductions at once, weights in three lanes, ranges and edges worked out a scale or list a lane: the score call
+// of those units 49.4 -> 45.8 us, the batch below 104.5 -> 90.5.
 //   1. min and max of each scale, then its histogram over that range (2048 bins);
 //   2. one scan per scale gives the bins that hold the m-th largest and the m-th smallest value; a bin that holds more
 //      than kUnitList values is narrowed down first (see below);
@@ -213,6 +213,7 @@ struct UnitScratch {
     float lo[3], to_bin[3];
     uint32_t range[6][2];                     // of a crowded bin: max of ~key and of key
     uint32_t cnt[6];
+    uint32_t crowded;                         // a boundary bin holds more values than a list
     double sums[7][kUnitWaves];               // beyond the boundary bins, per wavefront; the surprise
     float sext[2][kUnitWaves];
     double side[6];
@@ -268,6 +269,7 @@ __device__ __forceinline__ void finalize_unit(UnitScratch &sh, const float *__re
     };
     clear_buf();
     if (tid < 12) ext[tid] = 0u;
+    if (tid == 12) sh.crowded = 0u;
     if (tid < 6) {
         cnt[tid] = range[tid][0] = range[tid][1] = 0u;
         s_cut[tid] = UnitCut{-1, 0u, 0u, 0u, 0xffffffffu};            // (what a flat scale keeps: its gap does not count)
@@ -300,18 +302,22 @@ __device__ __forceinline__ void finalize_unit(UnitScratch &sh, const float *__re
         }
     }
     __syncthreads();
-    auto uniform = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
+    auto of_lane = [](float x, int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k)); };
     HeadStats st;
     float bins_lo[3], to_bin[3];                                      // to_bin: bins per unit of the scale; 0: the scale is flat
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        st.lo[k] = uniform(key_value(~ext[4 * k]));
-        const float hi = key_value(ext[4 * k + 1]), inner_lo = key_value(ext[4 * k + 2]), inner_hi = key_value(~ext[4 * k + 3]);
-        const float range = hi - st.lo[k];
-        st.inv_range[k] = uniform(range < kFlat ? 0.f : 1.0f / range);
+    {
+        const int k = min(lane, 2);                                   // (lane k: scale k)
+        const float lo = key_value(~ext[4 * k]), hi = key_value(ext[4 * k + 1]), inner_lo = key_value(ext[4 * k + 2]), inner_hi = key_value(~ext[4 * k + 3]);
+        const float range = hi - lo, inv = range < kFlat ? 0.f : 1.0f / range;
         const bool inner = inner_hi > inner_lo && N >= 2 * kSelThreads;
-        bins_lo[k] = uniform(inner ? inner_lo : st.lo[k]);
-        to_bin[k] = uniform(range < kFlat ? 0.f : (float)kBins * __builtin_amdgcn_rcpf(inner ? inner_hi - inner_lo : range));
+        const float from = inner ? inner_lo : lo, scale = range < kFlat ? 0.f : (float)kBins * __builtin_amdgcn_rcpf(inner ? inner_hi - inner_lo : range);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            st.lo[q] = of_lane(lo, q);
+            st.inv_range[q] = of_lane(inv, q);
+            bins_lo[q] = of_lane(from, q);
+            to_bin[q] = of_lane(scale, q);
+        }
     }
     if (tid == 0) {
 #pragma unroll
@@ -364,26 +370,25 @@ __device__ __forceinline__ void finalize_unit(UnitScratch &sh, const float *__re
             s_cut[2 * k + 1].bin = 2 * tid + (second ? 1 : 0);
             s_cut[2 * k + 1].need = m - below - (second ? c[k].x : 0u);
             s_cut[2 * k + 1].pop = second ? c[k].y : c[k].x;
+            if ((second ? c[k].y : c[k].x) > (uint32_t)kUnitList) sh.crowded = 1u;
         }
         if (above < m && m <= above + group) {                        // the m-th largest
             const bool first = above + c[k].y < m;
             s_cut[2 * k].bin = 2 * tid + (first ? 0 : 1);
             s_cut[2 * k].need = m - above - (first ? c[k].y : 0u);
             s_cut[2 * k].pop = first ? c[k].x : c[k].y;
+            if ((first ? c[k].x : c[k].y) > (uint32_t)kUnitList) sh.crowded = 1u;
         }
     }
     __syncthreads();
     auto key_of = [](int i, float x) { return i & 1 ? ~ord_key(x) : ord_key(x); };   // inverted: the smallest value has the largest key
     auto crowded = [](const UnitCut &q) { return q.pop > (uint32_t)kUnitList && q.lo != q.hi; };
-    uint32_t most_pop = 0u;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) most_pop = max(most_pop, s_cut[i].pop);
     auto any_crowded = [&]() {                                        // the same for every thread
         bool any = false;
         for (int i = 0; i < 6; ++i) any |= crowded(s_cut[i]);
         return any;
     };
-    if (most_pop > (uint32_t)kUnitList) {
+    if (__builtin_amdgcn_readfirstlane((int)sh.crowded) != 0) {
         // f(list, its cut, up to 8 of a thread's keys, which of them are in the list's boundary bin).  From 16 values a thread
         // on they are read again: the rare path then costs the common one no registers.
         constexpr int kKeys = EPT < 16 ? EPT : 8, kLists = EPT < 16 ? 6 : 1;
@@ -468,13 +473,18 @@ __device__ __forceinline__ void finalize_unit(UnitScratch &sh, const float *__re
 #pragma unroll
             for (int j = 0; j < EPT; ++j) asm volatile("" : "+v"(v[k][j]));
     }
-    UnitCut cut[6];                                                   // uniform
+    uint32_t cut_lo[6], cut_hi[6];                                    // uniform; lane i worked list i's out
     BinEdges edge[6];
+    {
+        const UnitCut q = s_cut[min(lane, 5)];
+        const float low = bin_low_edge(q.bin), high = bin_high_edge(q.bin);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        edge[i] = bin_edges(s_cut[i].bin);
-        cut[i].lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cut[i].lo);
-        cut[i].hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_cut[i].hi);
+        for (int i = 0; i < 6; ++i) {
+            const float l = of_lane(low, i), h = of_lane(high, i);
+            edge[i] = BinEdges{h, l, l, h};
+            cut_lo[i] = (uint32_t)__builtin_amdgcn_readlane((int)q.lo, i);
+            cut_hi[i] = (uint32_t)__builtin_amdgcn_readlane((int)q.hi, i);
+        }
     }
 
     // ---- 3: sums beyond the boundary bins, their entries, the surprise ----
@@ -499,9 +509,9 @@ __device__ __forceinline__ void finalize_unit(UnitScratch &sh, const float *__re
                     const int i = 2 * k + e;
                     if (in[e]) {
                         const uint32_t key = key_of(i, x);
-                        if (key > cut[i].hi) {
+                        if (key > cut_hi[i]) {
                             (e == 0 ? pt : pb)[k] += x;
-                        } else if (key >= cut[i].lo && cut[i].lo != cut[i].hi) {   // (a single key needs no list)
+                        } else if (key >= cut_lo[i] && cut_lo[i] != cut_hi[i]) {   // (a single key needs no list)
                             const uint32_t at = atomicAdd(&cnt[i], 1u);
                             if (at < (uint32_t)kUnitList) buf[i * kUnitList + at] = key;
                         }

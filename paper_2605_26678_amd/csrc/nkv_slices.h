@@ -102,10 +102,12 @@ __device__ __forceinline__ int anomaly_bin(float a)
 struct BinEdges {
     float above, below, from, to;        // from, to: the same edges from the other side (in bin q <=> y >= from and not y >= above)
 };
+__device__ __forceinline__ float bin_low_edge(int q) { return q <= 0 ? -INFINITY : (float)q; }
+__device__ __forceinline__ float bin_high_edge(int q) { return q < 0 ? -INFINITY : q >= kBins - 1 ? INFINITY : (float)(q + 1); }
 __device__ __forceinline__ BinEdges bin_edges(int q)                  // q: the same in every lane
 {
     auto uniform = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
-    const float low = uniform(q <= 0 ? -INFINITY : (float)q), high = uniform(q < 0 ? -INFINITY : q >= kBins - 1 ? INFINITY : (float)(q + 1));
+    const float low = uniform(bin_low_edge(q)), high = uniform(bin_high_edge(q));
     return BinEdges{high, low, low, high};
 }
 
