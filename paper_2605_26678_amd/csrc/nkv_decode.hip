@@ -418,19 +418,10 @@ bool decode_small(int64_t n_units, int64_t rows, int G)
 size_t part_offset(int64_t n_units) { return ((size_t)(n_units + 1) * 4 + 255) / 256 * 256; }
 size_t ws_for(int64_t chunks, int64_t n_units, int G, int d) { return part_offset(n_units) + (size_t)chunks * G * (d + 2) * 4; }
 
-// Workgroups of the kernel that the device holds at once.
-template <auto KERNEL> int resident_workgroups()
-{
-    static int cached = 0;                                           // (one per kernel; benign if raced)
-    if (cached == 0) {
-        int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, kDecThreads, 0) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu * cus <= 0)
-            return 1024;
-        cached = per_cu * cus;
-    }
-    return cached;
-}
+// Workgroups of decode_run_kernel that the device holds at once, by the registers it takes (the compiler's report), a wavefront of each
+// workgroup to a SIMD: 72, 105 to 113, 109 to 147, 149 to 161 and 211 to 256 for G = 1, 2, 3, 4 to 5 and 6 to 8.  A table, not a question
+// to the runtime: a call asks nothing and keeps nothing, also the first one of a process and one that is being captured.
+constexpr int resident_workgroups(int D, int G) { return 256 * (G == 1 ? (D == 128 ? 6 : 4) : G == 2 ? 4 : G <= 5 ? 3 : 2); }
 
 // Stretches where every workgroup that the device holds gets 256 rows and more, and the units are long against a stretch or against
 // a piece.  Whole calls, chunks of 256 rows with a planning kernel in front (as it was) / pieces / stretches, us: 288 units
@@ -462,7 +453,7 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     prof.begin(NKV_KERNEL_DECODE, st);
     auto go = [&](auto heads) {
         constexpr int GG = decltype(heads)::value;
-        const int resident = resident_workgroups<decode_run_kernel<D, GG, F16>>();
+        constexpr int resident = resident_workgroups(D, GG);
         const bool stretches = !small && by_stretches(n_units, rows, resident);
         cut = stretches ? rows_per_stretch(rows, resident) : small ? -kSmallChunk : -kChunk;
         pieces = max_chunks(n_units, rows, std::abs(cut));

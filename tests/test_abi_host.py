@@ -21,6 +21,15 @@ def test_every_declared_symbol_is_exported():
         assert hasattr(nkv.lib(), name), name
 
 
+def test_only_the_scans_ask_the_runtime_about_the_device():
+    """nkv.h tells callers that capture a graph which call to make once outside it: nkv_score, for its scan kernels' occupancy
+    (and nkv_budget_noalloc, for its scratch).  No other source asks the runtime anything."""
+    csrc = os.path.join(ROOT, "paper_2605_26678_amd", "csrc")
+    asks = {f for f in os.listdir(csrc)
+            if re.search(r"hipOccupancy|hipGetDevice|hipDeviceGet|hipGetSymbol\w+\(", open(os.path.join(csrc, f)).read())}
+    assert asks == {"nkv_score_fast.hip", "nkv_score_tile.hip", "nkv_api.hip"}
+
+
 def test_params_default_are_the_papers_constants():
     p = nkv.params_default()
     assert p.struct_size == C.sizeof(nkv.nkv_params)

@@ -231,3 +231,30 @@ def test_stretches_across_units(d, G, dtype, lens):
         want, want_lse = oracle_decode(_f64(q), _f64(pk[:rows]), _f64(pv[:rows]), ho, 1, scale)
         out, lse = _run(w, q, pk[:rows], pv[:rows], off.to(DEV), rows, G, scale)
         _check(out, lse, want, want_lse, float(pv.abs().max()), f"stretches d={d} G={G} rows={rows}")
+
+
+@pytest.mark.parametrize("lens,G", [([40000] * 8, 4), ([300] * 300, 5), ([200] * 8, 2)])
+def test_decode_captured_in_a_hip_graph(lens, G):
+    """Long units, many short ones and a small call, recorded without a call in front and replayed with eager work in between:
+    every replay gives the eager call's results bit for bit."""
+    w = nkv_inputs.small_workload(f"decode_graph_{len(lens)}", len(lens), 1, 64, [1], dtype="fp16", n_out=0)
+    g = torch.Generator().manual_seed(len(lens))
+    rows = sum(lens)
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64).to(DEV)
+    pk, pv = (torch.randn(rows, 64, generator=g).to(torch.float16).to(DEV) for _ in range(2))
+    q = torch.randn(1, len(lens), G, 64, generator=g).to(torch.float16).to(DEV)
+    shape, p = shape_of(w), nkv.params_default()
+    out = torch.zeros(1, len(lens), G, 64, dtype=torch.float32, device=DEV)
+    lse = torch.zeros(1, len(lens), G, dtype=torch.float32, device=DEV)
+    ws = torch.empty(max(nkv.decode_workspace_bytes(shape, G, rows), 256), dtype=torch.uint8, device=DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        nkv.decode_attention(q, pk, pv, off, rows, shape, p, G, 0.125, out, lse, ws)
+    want, want_lse = _run(w, q, pk, pv, off, rows, G, 0.125)
+    for rep in range(3):
+        out.zero_(), lse.zero_(), ws.fill_(255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(lse, want_lse), f"replay {rep}"
