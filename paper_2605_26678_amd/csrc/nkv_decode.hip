@@ -286,15 +286,18 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_run_kernel(const uint16
     }
 }
 
-// Where the partial results of unit u lie: [x, y).  cut: < 0: pieces of -cut rows of a unit; > 0: stretches of cut rows (multiples of
-// 64; rows are fewer than 2^38).
+__device__ __forceinline__ int64_t divide(int64_t a, int64_t b)     // for a >= 0, b > 0; in 32 bits where they do
+{
+    return (a | b) >> 32 == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
+}
+
+// Where the partial results of unit u lie: [x, y).  cut: < 0: pieces of -cut rows of a unit; > 0: stretches of cut rows.
 __device__ __forceinline__ int2 unit_pieces(const int64_t *head_off, int u, int64_t rows, int cut)
 {
-    const int64_t a = clamp_row(head_off[u], rows), b = clamp_row(head_off[u + 1], rows);
-    const uint32_t per = (uint32_t)abs(cut) / 64u;
-    const int x = (int)((uint32_t)(a / 64) / per) + u;
+    const int64_t a = clamp_row(head_off[u], rows), b = clamp_row(head_off[u + 1], rows), per = abs(cut);
+    const int x = (int)divide(a, per) + u;
     if (a >= b) return make_int2(x, x);
-    return make_int2(x, cut < 0 ? x + (int)((uint32_t)((b - a + 63) / 64 + per - 1) / per) : (int)((uint32_t)((b - 1) / 64) / per) + u + 1);
+    return make_int2(x, cut < 0 ? x + (int)divide(b - a + per - 1, per) : (int)divide(b - 1, per) + u + 1);
 }
 
 // grid: n_units * G workgroups of TH threads: TH / D slices of the unit's chunks, added up in the slices' order.
