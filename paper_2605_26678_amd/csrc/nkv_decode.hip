@@ -25,8 +25,6 @@
 // unit and query head, no scratch).
 #include "nkv_device.h"
 
-#include <stdlib.h>
-
 #include <algorithm>
 #include <type_traits>
 
@@ -36,6 +34,7 @@ namespace {
 // Rows per workgroup: 256, or 64 where a call has too few rows to fill the chip with workgroups of 256 (a wavefront then
 // has one batch of rows instead of four in turn).
 constexpr int kChunk = 256, kSmallChunk = 64, kSmallUnits = 256;
+constexpr int kLeastRun = 192;           // rows of a stretch at least
 // Chunks per unit from which 512 threads combine them instead of one per dimension (64 units of G = 3, head dim 64: 7 chunks a
 // unit 8.0 -> 7.1 us; 256 units of G = 8, 300 rows in two chunks 21.4 us with 512, 19.4 with 64).
 constexpr int kManyChunks = 4;
@@ -94,6 +93,27 @@ template <bool F16> __device__ __forceinline__ void unpack2(uint32_t r, float (&
         v[0] = __uint_as_float(r << 16);
         v[1] = __uint_as_float(r & 0xffff0000u);
     }
+}
+
+__host__ __device__ inline int64_t divide(int64_t a, int64_t b)      // for a >= 0, b > 0; in 32 bits where they do
+{
+    return (a | b) >> 32 == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
+}
+
+// How many stretches `rows` rows are cut into, and how long they are.  Up to four for every workgroup that the device holds, of 1024
+// rows and more: what runs at a time lies closer together then, and the first pass over a cache spends less on address translation (288
+// units of 8192 rows, G = 4, first pass / later ones, one stretch: 262 / 196 us, two 243 / 199, four 233 / 203, eight 230 / 209; pieces of 256
+// rows 245 / 217).  Of 512 rows and more instead: 384 units of 3518 rows, head dim 128, G = 4 122.8 us and 115.6, G = 8 181.7 and 168.9.
+__host__ __device__ inline int64_t stretch_count(int64_t rows, int resident)
+{
+    const int64_t each = divide(rows, (int64_t)1024 * resident);
+    return (each < 1 ? 1 : each > 4 ? 4 : each) * resident;
+}
+constexpr int64_t kMostRun = 1 << 20;
+__host__ __device__ inline int64_t stretch_rows(int64_t rows, int resident)
+{
+    const int64_t n = stretch_count(rows, resident), per = (divide(rows + n - 1, n) + 15) / 16 * 16;
+    return per < kLeastRun ? kLeastRun : per > kMostRun ? kMostRun : per;
 }
 
 __device__ __forceinline__ int64_t clamp_row(int64_t r, int64_t rows) { return r < 0 ? 0 : (r > rows ? rows : r); }
@@ -266,50 +286,84 @@ __global__ __launch_bounds__(kDecThreads) void decode_piece_kernel(const uint16_
     if (first <= a && a < b) attend<D, G, F16, CH>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + (int64_t)piece * G * (D + 2));
 }
 
-// Long units: the cache is cut into stretches of `run` rows, whichever units they belong to, so that every workgroup of the call has
-// the same work.  What stretch i holds of unit u is piece i + u (no two share a number: both grow with the row).  grid: stretches.
+// x, which is the same in every lane, in scalar registers (64-bit comparisons are made in vector registers).
+__device__ __forceinline__ int64_t uniform(int64_t x)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// The rows of all units, one unit after the other, in stretches of `run`.  Their length follows from the rows that there are, which the
+// host does not know: a buffer may hold room for many more.  (288 units in buffers of 2 359 296 rows, stretches as for full ones / as they
+// are / chunks of 256 rows as it was: head dim 128, G = 4, 147 456 rows 28.6 / 25.7 / 25.9 us, 18 432 rows 43.5 / 19.1 / 16.5; head dim 64,
+// G = 8, 38.3 / 30.6 / 28.0 and 100 / 27 / 18.)
+struct Stretches {
+    const int64_t *head_off;
+    int64_t rows, base, len, run;
+    __device__ Stretches(const int64_t *off, int n_units, int64_t rows_, int resident) : head_off(off), rows(rows_)
+    {
+        base = clamp_row(off[0], rows);
+        len = max(clamp_row(off[n_units], rows) - base, (int64_t)0);
+        run = stretch_rows(len, resident);
+    }
+    __device__ int64_t first(int u) const { return clamp_row(head_off[u], rows); }
+    __device__ int64_t pos(int u) const { return first(u) - base; }
+};
+
+// Long units: the cache is cut into stretches, whichever units they belong to, so that every workgroup of the call has
+// the same work.  What stretch i holds of unit u is piece i + u (no two share a number: both grow with the row).  grid: stretches, or more.
 // (Two workgroups a compute unit: left to itself the compiler takes registers for one with fp16 and G = 8, 288 units of 1438 rows 93 us instead of 66.)
 template <int D, int G, bool F16>
 __global__ __launch_bounds__(kDecThreads, 2) void decode_run_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ pk,
                                                                  const uint16_t *__restrict__ pv, const int64_t *__restrict__ head_off,
-                                                                 int n_units, int64_t rows, int run, float scale_log2,
+                                                                 int n_units, int64_t rows, int resident, float scale_log2,
                                                                  float *__restrict__ part)
 {
-    const int64_t lo = max((int64_t)blockIdx.x * run, clamp_row(head_off[0], rows));
-    const int64_t hi = min((int64_t)blockIdx.x * run + run, clamp_row(head_off[n_units], rows));
+    const Stretches st(head_off, n_units, rows, resident);
+    const int64_t lo = uniform(blockIdx.x * st.run), hi = uniform(min(lo + st.run, st.len));
     if (lo >= hi) return;
-    for (int u = wave_search(head_off, n_units, lo); u < n_units; ++u) {
-        const int64_t a = max(clamp_row(head_off[u], rows), lo), b = min(clamp_row(head_off[u + 1], rows), hi);
-        if (a < b) attend<D, G, F16, 0>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + ((int64_t)blockIdx.x + u) * G * (D + 2));
-        if (b >= hi) break;
+    const int64_t base = uniform(st.base);
+    int u = __builtin_amdgcn_readfirstlane(wave_search_fn(n_units, lo, [&](int i) { return st.pos(i); }));
+    int64_t first = uniform(st.first(u));
+    for (; u < n_units; ++u) {
+        const int64_t next = uniform(st.first(u + 1)), at = first - base;
+        const int64_t a = uniform(first + max(lo - at, (int64_t)0)), n = uniform(min(next, first + hi - at) - a);
+        if (n > 0) attend<D, G, F16, 0>(q + (int64_t)u * G * D, pk, pv, a, (int)n, scale_log2, part + ((int64_t)blockIdx.x + u) * G * (D + 2));
+        if (next - base >= hi) break;
+        first = next;
         __syncthreads();                                              // (the merge's memory is used anew)
     }
 }
 
-__device__ __forceinline__ int64_t divide(int64_t a, int64_t b)     // for a >= 0, b > 0; in 32 bits where they do
+// Where the partial results of unit u lie: [x, y).  resident > 0: of stretches; else of pieces of `piece` rows of a unit.  limit: there are
+// no more (offsets that do not ascend are not read beyond it).
+__device__ __forceinline__ int2 unit_pieces(const int64_t *head_off, int n_units, int u, int64_t rows, int resident, int piece, int limit)
 {
-    return (a | b) >> 32 == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
-}
-
-// Where the partial results of unit u lie: [x, y).  cut: < 0: pieces of -cut rows of a unit; > 0: stretches of cut rows.
-__device__ __forceinline__ int2 unit_pieces(const int64_t *head_off, int u, int64_t rows, int cut)
-{
-    const int64_t a = clamp_row(head_off[u], rows), b = clamp_row(head_off[u + 1], rows), per = abs(cut);
-    const int x = (int)divide(a, per) + u;
-    if (a >= b) return make_int2(x, x);
-    return make_int2(x, cut < 0 ? x + (int)divide(b - a + per - 1, per) : (int)divide(b - 1, per) + u + 1);
+    int64_t x, y;
+    if (resident > 0) {
+        const Stretches st(head_off, n_units, rows, resident);
+        const int64_t at = max(st.pos(u), (int64_t)0), n = st.first(u + 1) - st.first(u);
+        x = divide(at, st.run) + u;
+        y = n > 0 ? divide(at + n - 1, st.run) + u + 1 : x;
+    } else {
+        const int64_t a = clamp_row(head_off[u], rows), n = clamp_row(head_off[u + 1], rows) - a;
+        x = divide(a, piece) + u;
+        y = n > 0 ? x + divide(n + piece - 1, piece) : x;
+    }
+    return make_int2((int)min(x, (int64_t)limit), (int)min(y, (int64_t)limit));
 }
 
 // grid: n_units * G workgroups of TH threads: TH / D slices of the unit's chunks, added up in the slices' order.
 template <int D, int TH>
 __global__ __launch_bounds__(TH) void decode_combine_kernel(const float *__restrict__ part, const int64_t *__restrict__ head_off,
-                                                            int64_t rows, int cut, int G, float *__restrict__ out, float *__restrict__ lse)
+                                                            int n_units, int64_t rows, int resident, int piece, int limit, int G, float *__restrict__ out,
+                                                            float *__restrict__ lse)
 {
     constexpr int NS = TH / D, NW = TH / 64, U = 4;
     __shared__ float red[NW];
     __shared__ float lds_l[NS], lds_o[NS][D];
     const int u = blockIdx.x / G, g = blockIdx.x - u * G, tid = threadIdx.x, e = tid % D, sl = tid / D;
-    const int2 pieces = unit_pieces(head_off, u, rows, cut);
+    const int2 pieces = unit_pieces(head_off, n_units, u, rows, resident, piece, limit);
     const int c0 = pieces.x, c1 = pieces.y;
     // the largest running maximum: chunks spread over the threads, then one reduction
     float mm = kNone;
@@ -422,9 +476,9 @@ size_t part_offset(int64_t n_units) { return ((size_t)(n_units + 1) * 4 + 255) /
 size_t ws_for(int64_t chunks, int64_t n_units, int G, int d) { return part_offset(n_units) + (size_t)chunks * G * (d + 2) * 4; }
 
 // Workgroups of decode_run_kernel that the device holds at once, by the registers it takes (the compiler's report), a wavefront of each
-// workgroup to a SIMD: 72, 105 to 113, 109 to 147, 149 to 161 and 211 to 256 for G = 1, 2, 3, 4 to 5 and 6 to 8.  A table, not a question
-// to the runtime: a call asks nothing and keeps nothing, also the first one of a process and one that is being captured.
-constexpr int resident_workgroups(int D, int G) { return 256 * (G == 1 ? (D == 128 ? 6 : 4) : G == 2 ? 4 : G <= 5 ? 3 : 2); }
+// workgroup to a SIMD: 64 and 97 for G = 1 and head dim 128 and 64, 101 to 109 for G = 2, 126 to 157 for 3 to 5, 207 to 255 from 6 on.  A
+// table, not a question to the runtime: a call asks nothing and keeps nothing, also the first one of a process and one being captured.
+constexpr int resident_workgroups(int D, int G) { return 256 * (G == 1 ? (D == 128 ? 8 : 4) : G == 2 ? 4 : G <= 5 ? 3 : 2); }
 
 // Stretches where every workgroup that the device holds gets 256 rows and more, and the units are long against a stretch or against
 // a piece.  Whole calls, chunks of 256 rows with a planning kernel in front (as it was) / pieces / stretches, us: 288 units
@@ -435,14 +489,9 @@ bool by_stretches(int64_t n_units, int64_t rows, int resident)
 {
     return rows >= (int64_t)kChunk * resident && (rows >= 1024 * n_units || 5 * n_units <= 3 * (int64_t)resident);
 }
-// Up to four stretches a workgroup, of 512 rows and more: what runs at a time lies closer together then, and the first pass over a cache
-// spends less on address translation (288 units of 8192 rows, G = 4, first pass / later ones, one stretch: 262 / 196 us, two 243 / 199,
-// four 233 / 203, eight 230 / 209; pieces of 256 rows 245 / 217); and sums are shorter.
-int rows_per_stretch(int64_t rows, int resident)
-{
-    const int64_t workgroups = std::min<int64_t>(4, std::max<int64_t>(1, rows / (512 * (int64_t)resident))) * resident, per = (rows + workgroups - 1) / workgroups;
-    return (int)std::min<int64_t>((per + kSmallChunk - 1) / kSmallChunk * kSmallChunk, 1 << 20);
-}
+// The stretches of a call that fills its buffer; one with fewer rows has no more.  (No more than pieces of 256 rows, for whose partial
+// results every caller's scratch has room: resident <= rows / 256 where there are stretches.)
+unsigned most_stretches(int64_t rows, int resident) { return (unsigned)std::max(stretch_count(rows, resident), rows / kMostRun + 1); }
 
 template <int D, bool F16>
 hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, const int64_t *head_off, int n_units,
@@ -451,20 +500,21 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
 {
     float *part = (float *)((char *)ws + part_offset(n_units));
     const bool small = decode_small(n_units, rows, G) && ws_bytes >= ws_for(max_chunks(n_units, rows, kSmallChunk), n_units, G, D);
-    int cut = 0;
-    int64_t pieces = 0;
+    const int piece = small ? kSmallChunk : kChunk;
+    int64_t pieces = max_chunks(n_units, rows, piece);
+    int in_stretches = 0;
     prof.begin(NKV_KERNEL_DECODE, st);
     auto go = [&](auto heads) {
-        constexpr int GG = decltype(heads)::value;
-        constexpr int resident = resident_workgroups(D, GG);
-        const bool stretches = !small && by_stretches(n_units, rows, resident);
-        cut = stretches ? rows_per_stretch(rows, resident) : small ? -kSmallChunk : -kChunk;
-        pieces = max_chunks(n_units, rows, std::abs(cut));
-        if (stretches)
-            decode_run_kernel<D, GG, F16><<<(unsigned)((rows + cut - 1) / cut), kDecThreads, 0, st>>>(q, pk, pv, head_off, n_units, rows, cut, scale_log2, part);
-        else
+        constexpr int GG = decltype(heads)::value, resident = resident_workgroups(D, GG);
+        if (!small && by_stretches(n_units, rows, resident)) {
+            const unsigned stretches = most_stretches(rows, resident);
+            in_stretches = resident;
+            pieces = (int64_t)stretches + n_units;
+            decode_run_kernel<D, GG, F16><<<stretches, kDecThreads, 0, st>>>(q, pk, pv, head_off, n_units, rows, resident, scale_log2, part);
+        } else {
             (small ? decode_piece_kernel<D, GG, F16, kSmallChunk> : decode_piece_kernel<D, GG, F16, kChunk>)<<<(unsigned)pieces, kDecThreads, 0, st>>>(
                 q, pk, pv, head_off, n_units, rows, scale_log2, part);
+        }
     };
     switch (G) {
     case 1: go(std::integral_constant<int, 1>{}); break;
@@ -479,9 +529,9 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     }
     prof.end(NKV_KERNEL_DECODE, st);
     if (pieces > (int64_t)kManyChunks * n_units)
-        decode_combine_kernel<D, 512><<<(unsigned)(n_units * G), 512, 0, st>>>(part, head_off, rows, cut, G, out, lse);
+        decode_combine_kernel<D, 512><<<(unsigned)(n_units * G), 512, 0, st>>>(part, head_off, n_units, rows, in_stretches, piece, (int)pieces, G, out, lse);
     else
-        decode_combine_kernel<D, D><<<(unsigned)(n_units * G), D, 0, st>>>(part, head_off, rows, cut, G, out, lse);
+        decode_combine_kernel<D, D><<<(unsigned)(n_units * G), D, 0, st>>>(part, head_off, n_units, rows, in_stretches, piece, (int)pieces, G, out, lse);
     return hipGetLastError();
 }
 

@@ -39,6 +39,23 @@ def _run(w, q, pk, pv, head_off, rows, Hq, scale, want_lse=True):
     return out, lse
 
 
+def _records(w, q, pk, pv, head_off, rows, G, scale):
+    """Which partial results a call of the kernels with scratch leaves there, by number: nothing else is written behind the
+    units' words in front.  The call's output too."""
+    n = len(w.prompt_lens) * w.L * w.H
+    shape = shape_of(w)
+    front = (4 * (n + 1) + 255) // 256 * 256
+    record = G * (w.d + 2)
+    ws = torch.full((nkv.decode_workspace_bytes(shape, G * w.H, rows),), 255, dtype=torch.uint8, device=DEV)
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device=DEV)
+    lse = torch.full(q.shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+    nkv.decode_attention(q, pk, pv, head_off, rows, shape, nkv.params_default(), G * w.H, scale, out, lse, ws)
+    torch.cuda.synchronize()
+    words = ws[front:].view(torch.int32)
+    words = words[:words.numel() // record * record].reshape(-1, record)
+    return (words[:, 0] != -1).nonzero()[:, 0].cpu().numpy(), out, lse
+
+
 def _check(out, lse, o_out, o_lse, vmax, what):
     err = np.abs(out.cpu().numpy().astype(np.float64) - o_out).max()
     assert err <= DECODE_TOL * max(1.0, vmax), f"{what}: out off by {err:.3e}"
@@ -258,3 +275,26 @@ def test_decode_captured_in_a_hip_graph(lens, G):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(lse, want_lse), f"replay {rep}"
+
+
+@pytest.mark.parametrize("G,d,dtype", [(4, 128, "bf16"), (8, 64, "fp16"), (1, 128, "fp16"), (3, 64, "bf16")])
+def test_buffers_with_room_for_many_more_rows(G, d, dtype):
+    """288 units of about 512 rows in buffers that hold 16 times as many (the rows behind them are not numbers): the oracle's
+    results, and the work in as many pieces as for buffers that just hold the rows."""
+    lens = [448 + 128 * (u % 2) for u in range(288)]
+    w = nkv_inputs.small_workload(f"room_{G}_{d}", 36, 8, d, [1], dtype=dtype, n_out=0)
+    g = torch.Generator(device=DEV).manual_seed(G)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+    rows = int(off[-1])
+    pk, pv = (torch.full((16 * rows, d), float("nan"), dtype=dt, device=DEV) for _ in range(2))
+    for t in (pk, pv):
+        t[:rows] = torch.randn(rows, d, generator=g, device=DEV).to(dt)
+    q = torch.randn(1, 36, 8 * G, d, generator=g, device=DEV).to(dt)
+    scale = 1.0 / float(np.sqrt(d))
+    want, want_lse = oracle_decode(_f64(q), _f64(pk[:rows]), _f64(pv[:rows]), off.numpy(), 8, scale)
+    spare, out, lse = _records(w, q, pk, pv, off.to(DEV), 16 * rows, G, scale)
+    _check(out, lse, want, want_lse, float(pv[:rows].abs().max()), f"spare rows, G={G}")
+    filled, out, lse = _records(w, q, pk[:rows].contiguous(), pv[:rows].contiguous(), off.to(DEV), rows, G, scale)
+    _check(out, lse, want, want_lse, float(pv[:rows].abs().max()), f"no spare rows, G={G}")
+    assert len(spare) >= len(filled)
