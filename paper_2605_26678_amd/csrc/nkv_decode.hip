@@ -34,9 +34,12 @@ namespace {
 // Rows per workgroup: 256, or 64 where a call has too few rows to fill the chip with workgroups of 256 (a wavefront then
 // has one batch of rows instead of four in turn).
 constexpr int kChunk = 256, kSmallChunk = 64, kSmallUnits = 256;
+constexpr int kUnitCost = 128;           // a unit's own work in a stretch, in rows
 constexpr int kLeastRun = 192;           // rows of a stretch at least
 // Chunks per unit from which 512 threads combine them instead of one per dimension (64 units of G = 3, head dim 64: 7 chunks a
 // unit 8.0 -> 7.1 us; 256 units of G = 8, 300 rows in two chunks 21.4 us with 512, 19.4 with 64).
+// Stretches have 256 at least: one unit may hold nearly all rows (511 units of one row beside one of 600 000, head dim 64, G = 3 100 us with 64
+// threads, 52 with 256; 288 units of 750, G = 8 29.5 and 31.2).
 constexpr int kManyChunks = 4;
 constexpr int kDecThreads = 256;
 constexpr float kNone = -1.0e30f;        // running maximum before any row was seen
@@ -100,7 +103,7 @@ __host__ __device__ inline int64_t divide(int64_t a, int64_t b)      // for a >=
     return (a | b) >> 32 == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
 }
 
-// How many stretches `rows` rows are cut into, and how long they are.  Up to four for every workgroup that the device holds, of 1024
+// How many stretches `rows` rows (with kUnitCost rows for every unit) are cut into, and how long they are.  Up to four for every workgroup that the device holds, of 1024
 // rows and more: what runs at a time lies closer together then, and the first pass over a cache spends less on address translation (288
 // units of 8192 rows, G = 4, first pass / later ones, one stretch: 262 / 196 us, two 243 / 199, four 233 / 203, eight 230 / 209; pieces of 256
 // rows 245 / 217).  Of 512 rows and more instead: 384 units of 3518 rows, head dim 128, G = 4 122.8 us and 115.6, G = 8 181.7 and 168.9.
@@ -293,7 +296,10 @@ __device__ __forceinline__ int64_t uniform(int64_t x)
     return (int64_t)((uint64_t)hi << 32 | lo);
 }
 
-// The rows of all units, one unit after the other, in stretches of `run`.  Their length follows from the rows that there are, which the
+// The rows of all units, one unit after the other, each with kUnitCost rows in front for its queries, its merge and its stores, in
+// stretches of `run`.  (Cut by rows alone, a stretch of short units took many of them in turn: 288 units of 26 rows beside 288 of 6554,
+// head dim 64, G = 3 134 us, 84 this way, about the same with 64, 96 or 192 rows a unit; chunks of 256 rows 92; 511 units of one row beside one of
+// 600 000, head dim 128, G = 8 2640, 126 and 175.)  Their length follows from the rows that there are, which the
 // host does not know: a buffer may hold room for many more.  (288 units in buffers of 2 359 296 rows, stretches as for full ones / as they
 // are / chunks of 256 rows as it was: head dim 128, G = 4, 147 456 rows 28.6 / 25.7 / 25.9 us, 18 432 rows 43.5 / 19.1 / 16.5; head dim 64,
 // G = 8, 38.3 / 30.6 / 28.0 and 100 / 27 / 18.)
@@ -303,11 +309,11 @@ struct Stretches {
     __device__ Stretches(const int64_t *off, int n_units, int64_t rows_, int resident) : head_off(off), rows(rows_)
     {
         base = clamp_row(off[0], rows);
-        len = max(clamp_row(off[n_units], rows) - base, (int64_t)0);
+        len = max(clamp_row(off[n_units], rows) - base, (int64_t)0) + (int64_t)kUnitCost * n_units;
         run = stretch_rows(len, resident);
     }
     __device__ int64_t first(int u) const { return clamp_row(head_off[u], rows); }
-    __device__ int64_t pos(int u) const { return first(u) - base; }
+    __device__ int64_t pos(int u) const { return first(u) - base + (int64_t)kUnitCost * u; }
 };
 
 // Long units: the cache is cut into stretches, whichever units they belong to, so that every workgroup of the call has
@@ -326,10 +332,10 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_run_kernel(const uint16
     int u = __builtin_amdgcn_readfirstlane(wave_search_fn(n_units, lo, [&](int i) { return st.pos(i); }));
     int64_t first = uniform(st.first(u));
     for (; u < n_units; ++u) {
-        const int64_t next = uniform(st.first(u + 1)), at = first - base;
+        const int64_t next = uniform(st.first(u + 1)), at = first - base + (int64_t)kUnitCost * (u + 1);   // of its first row
         const int64_t a = uniform(first + max(lo - at, (int64_t)0)), n = uniform(min(next, first + hi - at) - a);
         if (n > 0) attend<D, G, F16, 0>(q + (int64_t)u * G * D, pk, pv, a, (int)n, scale_log2, part + ((int64_t)blockIdx.x + u) * G * (D + 2));
-        if (next - base >= hi) break;
+        if (next - base + (int64_t)kUnitCost * (u + 1) >= hi) break;
         first = next;
         __syncthreads();                                              // (the merge's memory is used anew)
     }
@@ -342,7 +348,7 @@ __device__ __forceinline__ int2 unit_pieces(const int64_t *head_off, int n_units
     int64_t x, y;
     if (resident > 0) {
         const Stretches st(head_off, n_units, rows, resident);
-        const int64_t at = max(st.pos(u), (int64_t)0), n = st.first(u + 1) - st.first(u);
+        const int64_t at = max(st.pos(u), (int64_t)0) + kUnitCost, n = st.first(u + 1) - st.first(u);
         x = divide(at, st.run) + u;
         y = n > 0 ? divide(at + n - 1, st.run) + u + 1 : x;
     } else {
@@ -363,41 +369,53 @@ __global__ __launch_bounds__(TH) void decode_combine_kernel(const float *__restr
     __shared__ float red[NW];
     __shared__ float lds_l[NS], lds_o[NS][D];
     const int u = blockIdx.x / G, g = blockIdx.x - u * G, tid = threadIdx.x, e = tid % D, sl = tid / D;
-    const int2 pieces = unit_pieces(head_off, n_units, u, rows, resident, piece, limit);
-    const int c0 = pieces.x, c1 = pieces.y;
-    // the largest running maximum: chunks spread over the threads, then one reduction
-    float mm = kNone;
-    for (int ch = c0 + tid; ch < c1; ch += TH) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
-    mm = wave_max(mm);
+    // a unit of four or so pieces of stretches takes one slice: the other threads only meet it at the barriers
+    bool few = false;
+    if (NS > 1 && resident > 0) {
+        const int64_t len = clamp_row(head_off[n_units], rows) - clamp_row(head_off[0], rows) + (int64_t)kUnitCost * n_units;
+        few = (clamp_row(head_off[u + 1], rows) - clamp_row(head_off[u], rows)) * resident <= 4 * len;
+    }
+    const int slices = few ? 1 : NS;
+    const bool works = sl < slices;
+    float mm = kNone, ll = 0.f, oo = 0.f;
+    int c0 = 0, c1 = 0;
+    if (works) {
+        const int2 pieces = unit_pieces(head_off, n_units, u, rows, resident, piece, limit);
+        c0 = pieces.x, c1 = pieces.y;
+        // the largest running maximum: chunks spread over the threads, then one reduction
+        for (int ch = c0 + tid; ch < c1; ch += slices * D) mm = fmaxf(mm, part[((int64_t)ch * G + g) * (D + 2)]);
+        mm = wave_max(mm);
+    }
     if ((tid & 63) == 0) red[tid >> 6] = mm;
     __syncthreads();
+    if (works) {
 #pragma unroll
-    for (int i = 0; i < NW; ++i) mm = fmaxf(mm, red[i]);
-    // weighted sums, four chunks' loads in flight at a time; the order of the additions is fixed
-    float ll = 0.f, oo = 0.f;
-    for (int ch = c0 + sl; ch < c1; ch += U * NS) {
-        float pm[U], pl[U], po[U];
+        for (int i = 0; i < NW; ++i) mm = fmaxf(mm, red[i]);
+        // weighted sums, four chunks' loads in flight at a time; the order of the additions is fixed
+        for (int ch = c0 + sl; ch < c1; ch += U * slices) {
+            float pm[U], pl[U], po[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            const float *src = part + ((int64_t)min(ch + i * NS, c1 - 1) * G + g) * (D + 2);
-            pm[i] = src[0];
-            pl[i] = src[1];
-            po[i] = src[2 + e];
-        }
+            for (int i = 0; i < U; ++i) {
+                const float *src = part + ((int64_t)min(ch + i * slices, c1 - 1) * G + g) * (D + 2);
+                pm[i] = src[0];
+                pl[i] = src[1];
+                po[i] = src[2 + e];
+            }
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            if (ch + i * NS < c1) {
-                const float f = __builtin_amdgcn_exp2f(pm[i] - mm);
-                ll = fmaf(f, pl[i], ll);
-                oo = fmaf(f, po[i], oo);
+            for (int i = 0; i < U; ++i) {
+                if (ch + i * slices < c1) {
+                    const float f = __builtin_amdgcn_exp2f(pm[i] - mm);
+                    ll = fmaf(f, pl[i], ll);
+                    oo = fmaf(f, po[i], oo);
+                }
             }
         }
+        lds_o[sl][e] = oo;
+        if (e == 0) lds_l[sl] = ll;
     }
-    lds_o[sl][e] = oo;
-    if (e == 0) lds_l[sl] = ll;
     __syncthreads();
     if (sl > 0) return;
-    for (int i = 1; i < NS; ++i) {
+    for (int i = 1; i < slices; ++i) {
         oo += lds_o[i][e];
         ll += lds_l[i];
     }
@@ -490,8 +508,12 @@ bool by_stretches(int64_t n_units, int64_t rows, int resident)
     return rows >= (int64_t)kChunk * resident && (rows >= 1024 * n_units || 5 * n_units <= 3 * (int64_t)resident);
 }
 // The stretches of a call that fills its buffer; one with fewer rows has no more.  (No more than pieces of 256 rows, for whose partial
-// results every caller's scratch has room: resident <= rows / 256 where there are stretches.)
-unsigned most_stretches(int64_t rows, int resident) { return (unsigned)std::max(stretch_count(rows, resident), rows / kMostRun + 1); }
+// results every caller's scratch has room: where there are stretches, resident <= rows / 256 and kUnitCost * n_units <= rows / 3.)
+unsigned most_stretches(int64_t n_units, int64_t rows, int resident)
+{
+    const int64_t len = rows + kUnitCost * n_units;
+    return (unsigned)std::max(stretch_count(len, resident), len / kMostRun + 1);
+}
 
 template <int D, bool F16>
 hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, const int64_t *head_off, int n_units,
@@ -507,7 +529,7 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     auto go = [&](auto heads) {
         constexpr int GG = decltype(heads)::value, resident = resident_workgroups(D, GG);
         if (!small && by_stretches(n_units, rows, resident)) {
-            const unsigned stretches = most_stretches(rows, resident);
+            const unsigned stretches = most_stretches(n_units, rows, resident);
             in_stretches = resident;
             pieces = (int64_t)stretches + n_units;
             decode_run_kernel<D, GG, F16><<<stretches, kDecThreads, 0, st>>>(q, pk, pv, head_off, n_units, rows, resident, scale_log2, part);
@@ -528,10 +550,9 @@ hipError_t run_fast(const uint16_t *q, const uint16_t *pk, const uint16_t *pv, c
     default: return hipErrorInvalidValue;
     }
     prof.end(NKV_KERNEL_DECODE, st);
-    if (pieces > (int64_t)kManyChunks * n_units)
-        decode_combine_kernel<D, 512><<<(unsigned)(n_units * G), 512, 0, st>>>(part, head_off, n_units, rows, in_stretches, piece, (int)pieces, G, out, lse);
-    else
-        decode_combine_kernel<D, D><<<(unsigned)(n_units * G), D, 0, st>>>(part, head_off, n_units, rows, in_stretches, piece, (int)pieces, G, out, lse);
+    const bool many = pieces > (int64_t)kManyChunks * n_units;
+    (many ? decode_combine_kernel<D, 512> : in_stretches > 0 ? decode_combine_kernel<D, 256> : decode_combine_kernel<D, D>)
+        <<<(unsigned)(n_units * G), many ? 512 : in_stretches > 0 ? 256 : D, 0, st>>>(part, head_off, n_units, rows, in_stretches, piece, (int)pieces, G, out, lse);
     return hipGetLastError();
 }
 

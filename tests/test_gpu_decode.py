@@ -298,3 +298,25 @@ def test_buffers_with_room_for_many_more_rows(G, d, dtype):
     filled, out, lse = _records(w, q, pk[:rows].contiguous(), pv[:rows].contiguous(), off.to(DEV), rows, G, scale)
     _check(out, lse, want, want_lse, float(pv[:rows].abs().max()), f"no spare rows, G={G}")
     assert len(spare) >= len(filled)
+
+
+@pytest.mark.parametrize("d,G,dtype", [(128, 8, "bf16"), (64, 3, "fp16"), (128, 1, "fp16")])
+def test_short_units_beside_a_long_one(d, G, dtype):
+    """511 units of one row and one of 600 000: the oracle's results, and no workgroup takes more than 16 of the short units.  What
+    stretch i holds of unit u is partial result i + u, and a unit of one row has one."""
+    lens = [1] * 511 + [600000]
+    w = nkv_inputs.small_workload(f"short_{G}_{d}", 64, 8, d, [1], dtype=dtype, n_out=0)
+    g = torch.Generator(device=DEV).manual_seed(G)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+    rows = int(off[-1])
+    pk, pv = (torch.randn(rows, d, generator=g, device=DEV).to(dt) for _ in range(2))
+    q = torch.randn(1, 64, 8 * G, d, generator=g, device=DEV).to(dt)
+    scale = 1.0 / float(np.sqrt(d))
+    want, want_lse = oracle_decode(_f64(q), _f64(pk), _f64(pv), off.numpy(), 8, scale)
+    records, out, lse = _records(w, q, pk, pv, off.to(DEV), rows, G, scale)
+    _check(out, lse, want, want_lse, float(pv.abs().max()), f"short units, G={G}")
+    assert len(records) > 512                                         # (pieces of 256 rows would number 511 + 2344)
+    stretch = records[:511] - np.arange(511)
+    assert stretch.min() == 0 and (np.diff(stretch) >= 0).all()
+    assert np.bincount(stretch).max() <= 16
