@@ -850,17 +850,16 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
 // tokens of 16-bit keys, up to 7 of 8-bit keys.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / vector scan / shape-generic: bf16, head
 // dim 128, one layer 455 / 1204 / 311 us, four layers 1697 / 1800 / 740; head dim 40 444 / - / 194 and 1659 / - / 552; 8-bit,
 // head dim 128 452 / 1135 / 474 and 1683 / 1548 / 1374 (in blocks of one 6586 / 8167 / 4866).  In blocks of 8: bf16 249 / 639 / 193 and 872 / 946 / 469,
-// 8-bit 247 / - / 309 and 864 / - / 907.  Bf16, this scan / shape-generic: 32768 tokens in blocks of 24, four layers 632 / 544, head dim 40
-// 599 / 373; 65536 in blocks of 32, one layer 263 / 287, four 942 / 892, head dim 40 248 / 192 and 874 / 604.
+// 8-bit 247 / - / 309 and 864 / - / 907.  Bf16, this scan / shape-generic, units of 1100 blocks of 24, one layer, four and sixteen 164 / 164,
+// 519 / 427 and 1962 / 1550, of 28 165 / 172, 526 / 473 and 2011 / 1644; head dim 40, of 24 155 / 115 and 491 / 314.
+// A call's prompts take one scan, so the mean block of all of them decides: this scan's time goes with the blocks, the shape-generic
+// kernels' with the tokens.
 TinyBlocks tile_tiny_blocks(int dtype, int d, const PromptTab &tab, int LH)
 {
-    const int none = dtype == NKV_DTYPE_F8_E4M3 ? 8 : 25;
-    int shortest = none;
-    for (int p = 0; p < tab.n; ++p)
-        if (tab.blk_off[p + 1] - tab.blk_off[p] > resident_tile_workgroups()) shortest = min(shortest, (int)tab.b[p]);
-    if (shortest == none) return kTinyNone;
-    if (dtype != NKV_DTYPE_F8_E4M3) return kTinyGeneric;
-    return shortest > 1 && d == 128 && (int64_t)LH * tab.blk_off[tab.n] > 65536 ? kTinyVector : kTinyNone;
+    if (longest_unit(tab) <= resident_tile_workgroups()) return kTinyNone;
+    const int64_t blocks = tab.blk_off[tab.n];
+    if (dtype != NKV_DTYPE_F8_E4M3) return tab.T <= 24 * blocks ? kTinyGeneric : kTinyNone;
+    return tab.T <= 7 * blocks && tab.T > blocks && d == 128 && LH * blocks > 65536 ? kTinyVector : kTinyNone;
 }
 
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab)

@@ -1217,3 +1217,36 @@ def test_short_blocks_of_16_bit_keys_on_both_sides_of_the_line(block, blocks, d,
     w = nkv_inputs.small_workload(f"line_{d}_{block}_{blocks}", 1, 2, d, [N, 333], dtype=dtype, n_out=0)
     K, V = _kv(w)
     compare_end_to_end(w, K, V, 0.6, params=nkv.params_default(block_min=block, block_max=block), label=w.name)
+
+
+def _kernels_of(K, shape, **sizes):
+    """The scoring kernels whose raw anomalies (asked for by flag) a call without flags reproduces bit for bit."""
+    def raw(flags):
+        p = nkv.params_default(flags=flags, **sizes)
+        a = torch.empty(3, *K.shape[:3], dtype=torch.float32, device=DEV)
+        nkv.score_raw(K, shape, p, a, torch.empty(nkv.workspace_bytes(shape, p), dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+        return a
+    got = raw(0)
+    by_flag = {"matrix-core": nkv.FLAG_DEFER_STABLE, "shape-generic": nkv.FLAG_GENERIC_KERNELS}
+    if K.shape[3] == 128:
+        by_flag["vector"] = nkv.FLAG_VECTOR_SCAN
+    return [name for name, flag in by_flag.items() if torch.equal(got, raw(flag))]
+
+
+@pytest.mark.parametrize("dtype,lens,div,scan", [
+    ("bf16", [30000, 65536], 1250, "matrix-core"),                   # 1250 blocks of 24 tokens and 1261 of 52
+    ("fp16", [26400, 1100], 1100, "shape-generic"),                  # 1100 blocks of 24 tokens and 69 of 16
+    ("bf16", [27500], 1100, "matrix-core"),                          # 1100 blocks of 25 tokens
+    ("fp8", [8200, 65536], 1250, "matrix-core"),                     # 1367 blocks of 6 tokens and 1261 of 52
+])
+def test_the_mean_block_of_all_prompts_chooses_the_scan(dtype, lens, div, scan):
+    """A prompt whose blocks are too short for the matrix-core scan does not take the longer prompts beside it along, nor the
+    other way round; results against the oracle."""
+    heads = 32 if dtype == "fp8" else 2
+    w = nkv_inputs.small_workload(f"mean_block_{dtype}_{lens[0]}", 1, heads, 128, lens, dtype=dtype, n_out=0)
+    K, V = _kv(w)
+    sizes = dict(block_min=4 if dtype == "fp8" else 16, block_max=256, block_div=div)
+    assert _kernels_of(K, shape_of(w), **sizes) == [scan]
+    if heads == 2:
+        compare_end_to_end(w, K, V, 0.6, params=nkv.params_default(**sizes), label=w.name)
