@@ -846,20 +846,29 @@ bool tile_score_supported(int dtype, int d, int window, const PromptTab &tab, in
 }
 
 // A workgroup of this scan takes a block and loads 64 tokens in front of it whatever the block's length.  Where there are more blocks
-// of a unit than fit the chip together (so that every one is deferred as well), short ones are done sooner by other kernels: up to 24
-// tokens of 16-bit keys, up to 7 of 8-bit keys.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / vector scan / shape-generic: bf16, head
-// dim 128, one layer 455 / 1204 / 311 us, four layers 1697 / 1800 / 740; head dim 40 444 / - / 194 and 1659 / - / 552; 8-bit,
-// head dim 128 452 / 1135 / 474 and 1683 / 1548 / 1374 (in blocks of one 6586 / 8167 / 4866).  In blocks of 8: bf16 249 / 639 / 193 and 872 / 946 / 469,
-// 8-bit 247 / - / 309 and 864 / - / 907.  Bf16, this scan / shape-generic, units of 1100 blocks of 24, one layer, four and sixteen 164 / 164,
-// 519 / 427 and 1962 / 1550, of 28 165 / 172, 526 / 473 and 2011 / 1644; head dim 40, of 24 155 / 115 and 491 / 314.
-// A call's prompts take one scan, so the mean block of all of them decides: this scan's time goes with the blocks, the shape-generic
-// kernels' with the tokens.
+// of a unit than fit the chip together (so that every one is deferred as well), short ones are done sooner by other kernels.  A call's
+// prompts take one scan, so the mean block of all of them decides: this scan's time goes with the blocks, the shape-generic kernels'
+// with the tokens.
+// 16-bit keys, up to 24 tokens.  Score call of 8 heads x 16384 tokens in blocks of 4, this scan / shape-generic: bf16, head
+// dim 128, one layer 455 / 311 us, four layers 1697 / 740; head dim 40 444 / 194 and 1659 / 552.  In blocks of 8: 249 / 193 and
+// 872 / 469.  Units of 1100 blocks of 24, one layer, four and sixteen 164 / 164, 519 / 427 and 1962 / 1550, of 28 165 / 172,
+// 526 / 473 and 2011 / 1644; head dim 40, of 24 155 / 115 and 491 / 314.
+// 8-bit keys, head dim 128 (at others the shape-generic kernels leave more error in a_s, which they add up in 32 bits: head dim 32,
+// blocks of 3, 6.1e-8 against 5.3e-8).  Units of 2048 blocks, this scan / shape-generic / vector scan: 8 heads, of 2 tokens 445 / 427 / 1128, of 4
+// 239 / 251 / 486; 16 heads, of 4 440 / 398 / 827, of 6 449 / 464 / 833; 64 heads 1675 / 1292 / 2880 and 1683 / 1542 / 2905.  The vector scan holds
+// 2048 blocks at a time and is quick where a unit has more, so that none waits, and there are many of them: units of 2100, 32
+// heads, of 4 877 / 720 / 815, of 6 880 / 849 / 824; 64 heads 1715 / 1336 / 1088 and 1723 / 1587 / 1115; 256 heads, of 2 6762 / 4775 / 2991.  (Not
+// for single tokens: 32 heads x 16384 6586 / 4866 / 8167.)
 TinyBlocks tile_tiny_blocks(int dtype, int d, const PromptTab &tab, int LH)
 {
-    if (longest_unit(tab) <= resident_tile_workgroups()) return kTinyNone;
+    const int longest = longest_unit(tab), resident = resident_tile_workgroups();
+    if (longest <= resident) return kTinyNone;
     const int64_t blocks = tab.blk_off[tab.n];
     if (dtype != NKV_DTYPE_F8_E4M3) return tab.T <= 24 * blocks ? kTinyGeneric : kTinyNone;
-    return tab.T <= 7 * blocks && tab.T > blocks && d == 128 && LH * blocks > 65536 ? kTinyVector : kTinyNone;
+    if (d != 128) return kTinyNone;
+    const bool vector = longest > 2 * resident && tab.T > blocks;
+    if (tab.T <= (LH >= 16 ? 5 : 3) * blocks && !(vector && LH >= 64)) return kTinyGeneric;
+    return vector && tab.T <= 7 * blocks && LH >= 32 ? kTinyVector : kTinyNone;
 }
 
 size_t tile_score_plan_bytes(int LH, const PromptTab &tab)

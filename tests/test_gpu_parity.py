@@ -1250,3 +1250,19 @@ def test_the_mean_block_of_all_prompts_chooses_the_scan(dtype, lens, div, scan):
     assert _kernels_of(K, shape_of(w), **sizes) == [scan]
     if heads == 2:
         compare_end_to_end(w, K, V, 0.6, params=nkv.params_default(**sizes), label=w.name)
+
+
+@pytest.mark.parametrize("L,H,block,blocks,scan", [
+    (1, 8, 3, 1100, "shape-generic"), (1, 8, 4, 1100, "matrix-core"), (1, 8, 3, 1024, "matrix-core"),
+    (1, 16, 5, 2100, "shape-generic"), (1, 16, 6, 2100, "matrix-core"),
+    (1, 31, 6, 2100, "matrix-core"), (1, 32, 6, 2100, "vector"), (1, 32, 7, 2048, "matrix-core"), (1, 32, 5, 2100, "shape-generic"),
+    (2, 32, 5, 2048, "shape-generic"), (2, 32, 2, 2049, "vector"), (2, 32, 1, 2100, "shape-generic"), (2, 32, 8, 2100, "matrix-core"),
+])
+def test_short_blocks_of_8_bit_keys_on_both_sides_of_the_lines(L, H, block, blocks, scan):
+    """8-bit keys of head dim 128 in blocks of 1 to 8 tokens, more of a unit than the chip holds (1024 workgroups of the matrix-core
+    scan, 2048 of the vector scan): which kernels take them, and the results against the oracle."""
+    w = nkv_inputs.small_workload(f"line8_{L * H}_{block}_{blocks}", L, H, 128, [block * blocks], dtype="fp8", n_out=0)
+    K, V = _kv(w)
+    sizes = dict(block_min=block, block_max=block)
+    assert _kernels_of(K, shape_of(w), **sizes) == [scan]
+    compare_end_to_end(w, K, V, 0.6, params=nkv.params_default(**sizes), label=w.name)
