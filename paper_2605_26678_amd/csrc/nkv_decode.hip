@@ -276,18 +276,69 @@ __device__ __forceinline__ void attend(const uint16_t *__restrict__ q, const uin
     }
 }
 
-// Pieces of CH rows of a unit, the first from its first row on.  Unit u's are numbered from off[u] / CH + u on, which leaves room for
-// all of them and ascends, so nothing needs to be planned: a search finds a piece's unit.  grid: as many numbers as there are.
+// The unit that holds piece `piece` of all units' pieces of CH rows, and which of the unit's it is (unit < 0: there are fewer), for up to
+// PER * kDecThreads units: every workgroup counts all of them.
+template <int CH, int PER>
+__device__ __forceinline__ int2 counted_piece(const int64_t *__restrict__ head_off, int n_units, int64_t rows, uint32_t piece)
+{
+    constexpr int NW = kDecThreads / 64;
+    __shared__ uint32_t wsum[NW];
+    __shared__ int2 found;
+    const int tid = threadIdx.x, w = tid >> 6, u0 = tid * PER;
+    uint32_t c[PER], mine = 0u;
+    int64_t from = clamp_row(head_off[min(u0, n_units)], rows);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int64_t to = clamp_row(head_off[min(u0 + i + 1, n_units)], rows);
+        c[i] = (uint32_t)((max(to - from, (int64_t)0) + CH - 1) / CH);
+        mine += c[i];
+        from = to;
+    }
+    const uint32_t incl = wave_prefix_sum(mine);
+    if ((tid & 63) == 63) wsum[w] = incl;
+    if (tid == 0) found = make_int2(-1, 0);
+    __syncthreads();
+    uint32_t at = piece - (incl - mine);                              // from this thread's first piece on
+#pragma unroll
+    for (int i = 0; i < NW - 1; ++i) at -= i < w ? wsum[i] : 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (at < c[i]) found = make_int2(u0 + i, (int)at);
+        at -= c[i];
+    }
+    __syncthreads();
+    return make_int2(__builtin_amdgcn_readfirstlane(found.x), __builtin_amdgcn_readfirstlane(found.y));
+}
+
+// Pieces of CH rows of a unit, the first from its first row on.  Their partial results are numbered from off[u] / CH + u on, which leaves
+// room for all of them and needs no plan.  Workgroups take the pieces that there are, one after the other; more units than a workgroup
+// can count in less time than its rows take (2048 of them, G = 4 61 us, 68 with 16 units a thread) leave it with the numbers' pieces, some
+// of which are empty.  Workgroups go to the eight XCDs in turn, so what recurs every two, four or eight pieces, empty ones or a unit's short
+// last one, would be the same XCDs' share: every eight are dealt out one place further on than the eight before, and every 64 another
+// one.  Head dim 128, G = 8, as the numbers' pieces in their order / this way: 1024 units of 256 rows, every other number empty, 79 / 48 us; 512 of
+// 768, every fourth, 78 / 62; 4096 of 256 288 / 175; 1024 of 300 68 / 69, counted but not dealt out 79.
+// grid: as many numbers as there are.
 template <int D, int G, bool F16, int CH>
 __global__ __launch_bounds__(kDecThreads) void decode_piece_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ pk,
                                                                    const uint16_t *__restrict__ pv, const int64_t *__restrict__ head_off,
                                                                    int n_units, int64_t rows, float scale_log2, float *__restrict__ part)
 {
-    const int piece = blockIdx.x;
-    const int u = wave_search_fn(n_units, (int64_t)piece, [&](int i) { return i == 0 ? (int64_t)0 : clamp_row(head_off[i], rows) / CH + i; });
-    const int64_t first = clamp_row(head_off[u], rows), a = first + (piece - u - first / CH) * CH, b = min(clamp_row(head_off[u + 1], rows), a + CH);
-    if (first <= a && a < b) attend<D, G, F16, CH>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + (int64_t)piece * G * (D + 2));
+    const uint32_t eight = blockIdx.x / 8u;
+    const uint32_t i = (blockIdx.x | 7u) < gridDim.x ? eight * 8u + ((blockIdx.x + eight + eight / 8u) & 7u) : blockIdx.x;
+    int2 p;
+    if (CH == kSmallChunk || n_units <= kDecThreads) p = counted_piece<CH, 1>(head_off, n_units, rows, i);   // (kSmallUnits)
+    else if (n_units <= 4 * kDecThreads) p = counted_piece<CH, 4>(head_off, n_units, rows, i);
+    else {
+        p.x = wave_search_fn(n_units, (int64_t)i, [&](int u) { return u == 0 ? (int64_t)0 : clamp_row(head_off[u], rows) / CH + u; });
+        p.y = (int)((int64_t)i - p.x - clamp_row(head_off[p.x], rows) / CH);
+    }
+    const int u = p.x;
+    if (u < 0) return;
+    const int64_t first = clamp_row(head_off[u], rows), a = first + (int64_t)p.y * CH, b = min(clamp_row(head_off[u + 1], rows), a + CH);
+    if (first <= a && a < b)
+        attend<D, G, F16, CH>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + (first / CH + u + p.y) * G * (D + 2));
 }
+static_assert(kSmallUnits <= kDecThreads, "a thread counts one unit's pieces of 64 rows");
 
 // x, which is the same in every lane, in scalar registers (64-bit comparisons are made in vector registers).
 __device__ __forceinline__ int64_t uniform(int64_t x)

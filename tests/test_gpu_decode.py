@@ -320,3 +320,51 @@ def test_short_units_beside_a_long_one(d, G, dtype):
     stretch = records[:511] - np.arange(511)
     assert stretch.min() == 0 and (np.diff(stretch) >= 0).all()
     assert np.bincount(stretch).max() <= 16
+
+
+@pytest.mark.parametrize("rows_first", [0, 77])
+@pytest.mark.parametrize("units,lens", [(255, [300, 0, 64, 1]), (256, [63, 65, 128, 0, 1]), (257, [256, 0, 255, 257, 1, 512]),
+                                        (1024, [256]), (1024, [300, 0, 1]), (1025, [256, 511, 0, 513]), (2600, [256, 20])])
+def test_every_piece_of_a_unit_is_some_workgroups(units, lens, rows_first):
+    """Pieces of 64 and 256 rows that workgroups find by counting all units' pieces (up to 1024 units) or by their numbers, behind
+    rows that are no unit's: as many partial results as there are pieces, and the oracle's results."""
+    lens = (lens * units)[:units]
+    w = nkv_inputs.small_workload(f"pieces_{units}_{len(lens)}", units, 1, 64, [1], dtype="fp16", n_out=0)
+    g = torch.Generator(device=DEV).manual_seed(units)
+    off = torch.tensor(rows_first + np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+    rows = int(off[-1])
+    pk, pv = (torch.randn(rows, 64, generator=g, device=DEV).to(torch.float16) for _ in range(2))
+    q = torch.randn(1, units, 2, 64, generator=g, device=DEV).to(torch.float16)
+    want, want_lse = oracle_decode(_f64(q), _f64(pk), _f64(pv), off.numpy(), 1, 0.125)
+    records, out, lse = _records(w, q, pk, pv, off.to(DEV), rows, 2, 0.125)
+    _check(out, lse, want, want_lse, float(pv.abs().max()), f"{units} units")
+    assert len(records) in [sum((n + piece - 1) // piece for n in lens) for piece in (64, 256)]
+
+
+@pytest.mark.parametrize("units", [1024, 2560])
+def test_units_of_whole_pieces_keep_every_xcd_busy(units):
+    """Units of 256 rows, one piece each and room for two, take about as long as units of 255 (1.6 times as long where four of the
+    eight XCDs had all the pieces).  The least of many replays of a graph of ten calls."""
+    w = nkv_inputs.small_workload(f"xcds_{units}", units // 8, 8, 128, [1], n_out=0)
+    g = torch.Generator(device=DEV).manual_seed(units)
+    pk, pv = (torch.randn(256 * units, 128, generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(1, units // 8, 64, 128, generator=g, device=DEV).to(torch.bfloat16)
+    shape, p, took = shape_of(w), nkv.params_default(), {}
+    out = torch.empty(q.shape, dtype=torch.float32, device=DEV)
+    for n in (255, 256):
+        rows, off = n * units, n * torch.arange(units + 1, dtype=torch.int64, device=DEV)
+        ws = torch.empty(nkv.decode_workspace_bytes(shape, 64, rows), dtype=torch.uint8, device=DEV)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                nkv.decode_attention(q, pk[:rows], pv[:rows], off, rows, shape, p, 64, 0.1, out, None, ws)
+        for _ in range(25):
+            start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            graph.replay()
+            stop.record()
+            torch.cuda.synchronize()
+            took[n] = min(took.get(n, 1e9), start.elapsed_time(stop))
+    print(f"{units} units of 255 rows {100 * took[255]:.1f} us, of 256 {100 * took[256]:.1f}")
+    assert took[256] < 1.25 * took[255]
