@@ -549,14 +549,15 @@ size_t ws_for(int64_t chunks, int64_t n_units, int G, int d) { return part_offse
 // table, not a question to the runtime: a call asks nothing and keeps nothing, also the first one of a process and one being captured.
 constexpr int resident_workgroups(int D, int G) { return 256 * (G == 1 ? (D == 128 ? 8 : 4) : G == 2 ? 4 : G <= 5 ? 3 : 2); }
 
-// Stretches where every workgroup that the device holds gets 256 rows and more, and the units are long against a stretch or against
-// a piece.  Whole calls, chunks of 256 rows with a planning kernel in front (as it was) / pieces / stretches, us: 288 units
+// Stretches where every workgroup that the device holds gets 256 rows and more, and the units have more than three pieces in the mean (four
+// where there are many).  Whole calls, chunks of 256 rows with a planning kernel in front (as it was) / pieces / stretches, us: 288 units
 // of 8192 rows, head dim 128, G = 1 201 / 205 / 190, 4 217 / 222 / 202, 8 323 / 325 / 276, head dim 64, G = 8 192 / 190 / 155; 288 units of
-// 750 rows, 128, G = 8 45.0 / 46.6 / 43.8; 512 of 768 rows, G = 6 53.6 / 51.5 / 57.4, head dim 64, G = 5 32.7 / 31.0 / 34.4; 896 of them, G = 4
-// 41.1 / 40.0 / 43.7.  (Held to the registers of a third workgroup, G = 6 takes 10 to 20 % longer: rows spilled in the loop.)
+// 512 rows, 128, G = 8 36.0 / 34.8 / 37.5, 64, G = 8 24.5 / 22.9 / 26.5, of 700 43.8 / 41.2 / 44.5 and 29.6 / 27.3 / 30.1, of 768 44.5 / 43.3 / 44.6 and
+// 29.7 / 27.7 / 28.7, of 800 55.6 / 50.3 / 46.0 and 37.3 / 34.5 / 31.3; 456 units, 128, G = 5, of 700 41.6 / 41.2 / 41.9, of 800 54.0 / 50.2 / 46.3.  (Held
+// to the registers of a third workgroup, G = 6 takes 10 to 20 % longer: rows spilled in the loop.)
 bool by_stretches(int64_t n_units, int64_t rows, int resident)
 {
-    return rows >= (int64_t)kChunk * resident && (rows >= 1024 * n_units || 5 * n_units <= 3 * (int64_t)resident);
+    return rows >= (int64_t)kChunk * resident && (rows >= 1024 * n_units || (rows > 3 * kChunk * n_units && 5 * n_units <= 3 * (int64_t)resident));
 }
 // The stretches of a call that fills its buffer; one with fewer rows has no more.  (No more than pieces of 256 rows, for whose partial
 // results every caller's scratch has room: where there are stretches, resident <= rows / 256 and kUnitCost * n_units <= rows / 3.)

@@ -224,17 +224,65 @@ def test_both_chunk_lengths_and_both_ways_to_combine(units, G, rows):
     assert (np.abs(got[has] - want_lse[has]) <= DECODE_TOL * np.maximum(1.0, np.abs(want_lse[has]))).all()
 
 
-@pytest.mark.parametrize("d,G,dtype,lens", [
-    (64, 8, "bf16", [70000, 0, 70001]),                              # units far longer than a stretch
-    (64, 8, "bf16", [319, 320, 321, 1, 0, 640, 639, 959] * 42 + [50000] * 2),   # ends around multiples of a stretch of 320 rows and of 64
-    (64, 7, "fp16", [450] * 305 + [0, 1]),                           # three units to five workgroups: the last call by stretches
-    (64, 7, "fp16", [450] * 308),                                    # and the first by pieces
-    (128, 6, "bf16", [1024] * 130 + [1] * 3),
-    (128, 3, "fp16", [0, 131072, 131071, 130, 1]),
+UNIT_COST = 128                                                       # rows' room that a unit takes in a stretch
+
+
+def _stretch_length(rows, units, d, G):
+    """Rows of a stretch, and how many stretches a call of that many rows and units is cut into."""
+    resident = 256 * ((8 if d == 128 else 4) if G == 1 else 4 if G == 2 else 3 if G <= 5 else 2)
+    room = rows + UNIT_COST * units
+    most = resident * min(max(room // (1024 * resident), 1), 4)
+    return min(max(-(-(-(-room // most)) // 16) * 16, 192), 1 << 20), most
+
+
+def _stretch_records(off, run):
+    """The partial results that stretches of `run` rows leave: what stretch i holds of unit u is i + u."""
+    found = set()
+    for u in range(len(off) - 1):
+        at, n = int(off[u] - off[0]) + UNIT_COST * (u + 1), int(off[u + 1] - off[u])
+        if n > 0:
+            found |= set(range(at // run + u, (at + n - 1) // run + u + 1))
+    return found
+
+
+def _piece_records(off, piece):
+    return {int(off[u]) // piece + u + k for u in range(len(off) - 1) for k in range(-(-int(off[u + 1] - off[u]) // piece))}
+
+
+def _ends_around_stretches(units, run, stretches):
+    """Lengths of units whose first and last rows lie just before, at and behind multiples of `run`, units of 1 and no rows among them;
+    the last unit takes the rest of `stretches` stretches."""
+    lens, at = [], 0
+    for u in range(units - 1):
+        if u % 4 == 3:
+            n = u // 4 % 2
+        else:
+            edge = ((at + UNIT_COST) // run + 1 + 3 * u % 5) * run + (u % 3 - 1)          # where the unit's last row ends ...
+            n = edge - at - UNIT_COST * (1 + (u % 4 == 1))                              # ... or the next unit's first row lies
+        lens.append(n)
+        at += UNIT_COST + n
+    return lens + [run * stretches - at - UNIT_COST]
+
+
+@pytest.mark.parametrize("d,G,dtype,lens,piece", [
+    (64, 8, "bf16", [70000, 0, 70001], 0),                           # units far longer than a stretch
+    (64, 8, "bf16", _ends_around_stretches(120, 320, 512), 0),       # the first and last rows around a stretch's
+    (128, 8, "fp16", _ends_around_stretches(150, 336, 512), 0),
+    (128, 5, "fp16", _ends_around_stretches(170, 304, 768), 0),
+    (64, 2, "fp16", _ends_around_stretches(200, 304, 1024), 0),
+    (128, 1, "bf16", _ends_around_stretches(300, 288, 2048), 0),
+    (64, 7, "fp16", [800] * 305 + [0, 1], 0),                        # three units to five workgroups: the last call by stretches
+    (64, 7, "fp16", [800] * 308, 256),                               # and the first by pieces
+    (64, 8, "fp16", [769] * 200, 0),                                 # more than three pieces a unit: the first call by stretches
+    (64, 8, "fp16", [768] * 200, 256),                               # and the last by pieces
+    (128, 6, "bf16", [1024] * 130 + [1] * 3, 0),
+    (128, 3, "fp16", [0, 131072, 131071, 130, 1], 0),
+    (64, 4, "bf16", [700] * 300, 256),
 ])
-def test_stretches_across_units(d, G, dtype, lens):
-    """Calls large enough that every workgroup takes a stretch of the cache whichever units it holds, against the oracle; the
-    cache is also handed over with more rows claimed than it has."""
+def test_stretches_across_units(d, G, dtype, lens, piece):
+    """Calls large enough that every workgroup takes a stretch of the cache whichever units it holds, and calls on the other side of the
+    lines that take pieces of 256 rows: which partial results there are (a stretch's are not those of pieces), and the oracle's results.  Once
+    more with offsets that claim more rows than the cache has."""
     w = nkv_inputs.small_workload(f"stretch_{d}_{G}_{len(lens)}", len(lens), 1, d, [1], dtype=dtype, n_out=0)
     g = torch.Generator().manual_seed(len(lens) + d)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float16
@@ -243,11 +291,24 @@ def test_stretches_across_units(d, G, dtype, lens):
     pk, pv = (torch.randn(full, d, generator=g).to(dt).to(DEV) for _ in range(2))
     q = torch.randn(1, len(lens), G, d, generator=g).to(dt).to(DEV)
     scale = 1.0 / float(np.sqrt(d))
-    for rows in (full, full - 37):
+    for rows in (full, full - 37 if lens[-1] > 300 and piece == 0 and lens[0] != 769 else full):
         ho = off.numpy().clip(max=rows)
         want, want_lse = oracle_decode(_f64(q), _f64(pk[:rows]), _f64(pv[:rows]), ho, 1, scale)
-        out, lse = _run(w, q, pk[:rows], pv[:rows], off.to(DEV), rows, G, scale)
+        records, out, lse = _records(w, q, pk[:rows], pv[:rows], off.to(DEV), rows, G, scale)
         _check(out, lse, want, want_lse, float(pv.abs().max()), f"stretches d={d} G={G} rows={rows}")
+        expected = _piece_records(ho, piece) if piece else _stretch_records(ho, _stretch_length(rows, len(lens), d, G)[0])
+        assert set(records.tolist()) == expected
+
+
+def test_the_lengths_above_end_around_stretches():
+    """The units that _ends_around_stretches makes do begin and end on both sides of a stretch's end, at the lengths that the call uses."""
+    for units, run, stretches, d, G in ((120, 320, 512, 64, 8), (150, 336, 512, 128, 8), (170, 304, 768, 128, 5), (200, 304, 1024, 64, 2),
+                                        (300, 288, 2048, 128, 1)):
+        lens = _ends_around_stretches(units, run, stretches)
+        assert min(lens) == 0 and 1 in lens and _stretch_length(sum(lens), units, d, G) == (run, stretches)
+        ends = np.cumsum(np.array(lens) + UNIT_COST)
+        firsts = ends - np.array(lens)
+        assert {-1 % run, 0, 1} <= set((ends % run).tolist()) and {-1 % run, 0, 1} <= set((firsts % run).tolist())
 
 
 @pytest.mark.parametrize("lens,G", [([40000] * 8, 4), ([300] * 300, 5), ([200] * 8, 2)])
@@ -280,7 +341,7 @@ def test_decode_captured_in_a_hip_graph(lens, G):
 @pytest.mark.parametrize("G,d,dtype", [(4, 128, "bf16"), (8, 64, "fp16"), (1, 128, "fp16"), (3, 64, "bf16")])
 def test_buffers_with_room_for_many_more_rows(G, d, dtype):
     """288 units of about 512 rows in buffers that hold 16 times as many (the rows behind them are not numbers): the oracle's
-    results, and the work in as many pieces as for buffers that just hold the rows."""
+    results, and the work in stretches of a length that follows from the rows that are there."""
     lens = [448 + 128 * (u % 2) for u in range(288)]
     w = nkv_inputs.small_workload(f"room_{G}_{d}", 36, 8, d, [1], dtype=dtype, n_out=0)
     g = torch.Generator(device=DEV).manual_seed(G)
@@ -295,9 +356,7 @@ def test_buffers_with_room_for_many_more_rows(G, d, dtype):
     want, want_lse = oracle_decode(_f64(q), _f64(pk[:rows]), _f64(pv[:rows]), off.numpy(), 8, scale)
     spare, out, lse = _records(w, q, pk, pv, off.to(DEV), 16 * rows, G, scale)
     _check(out, lse, want, want_lse, float(pv[:rows].abs().max()), f"spare rows, G={G}")
-    filled, out, lse = _records(w, q, pk[:rows].contiguous(), pv[:rows].contiguous(), off.to(DEV), rows, G, scale)
-    _check(out, lse, want, want_lse, float(pv[:rows].abs().max()), f"no spare rows, G={G}")
-    assert len(spare) >= len(filled)
+    assert set(spare.tolist()) == _stretch_records(off.numpy(), _stretch_length(rows, len(lens), d, G)[0])
 
 
 @pytest.mark.parametrize("d,G,dtype", [(128, 8, "bf16"), (64, 3, "fp16"), (128, 1, "fp16")])
