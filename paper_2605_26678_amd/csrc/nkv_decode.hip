@@ -14,8 +14,8 @@
 //   decode_combine_kernel : per (unit, query head) merges the partial results: per query head running maximum, sum, weighted values
 //                           (m, l, o[0..D)) of a running-maximum softmax in base 2
 // All three work out from head_off which unit a piece belongs to: no kernel plans in front.  As chunks of 256 rows that a kernel of
-// its own numbered, 288 units of 8192 rows, head dim 128, G = 4, took 217 us (chunk kernel 5.9 TB/s, planning 4 us), now 202; 288 units of
-// 615 rows 29 and 26; 64 units of 768 rows, G = 8 20.8 and 18.4.  Reading the same rows without arithmetic or merging takes 179.
+// its own numbered, 288 units of 8192 rows, head dim 128, G = 4, took 217 us (chunk kernel 5.9 TB/s, planning 4 us), now 205; 288 units of
+// 615 rows 27.6 and 25.4; 64 units of 768 rows, G = 8 18.9 and 16.9.  Reading the same rows without arithmetic or merging takes 179.
 // Lane layout in attend as in the scoring kernel: a row is spread over D/8 lanes (16 bytes each),
 // one wave load fetches 64/(D/8) rows; <q, k> uses the packed 16-bit dot instruction on the stored bits (exact
 // products, fp32 accumulation) and a DPP sum over the lanes of a row; every group of D/8 lanes keeps its own
@@ -103,8 +103,9 @@ __host__ __device__ inline int64_t divide(int64_t a, int64_t b)      // for a >=
     return (a | b) >> 32 == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
 }
 
-// How many stretches `rows` rows (with kUnitCost rows for every unit) are cut into, and how long they are.  Up to four for every workgroup that the device holds, of 1024
-// rows and more: what runs at a time lies closer together then, and the first pass over a cache spends less on address translation (288
+// How many stretches `rows` rows (with kUnitCost rows for every unit) are cut into, and how long they are.  Up to four for every workgroup
+// that the device holds, of 1024 rows and more: what runs at a time lies closer together then, and the first pass over a cache spends less on
+// address translation (288
 // units of 8192 rows, G = 4, first pass / later ones, one stretch: 262 / 196 us, two 243 / 199, four 233 / 203, eight 230 / 209; pieces of 256
 // rows 245 / 217).  Of 512 rows and more instead: 384 units of 3518 rows, head dim 128, G = 4 122.8 us and 115.6, G = 8 181.7 and 168.9.
 __host__ __device__ inline int64_t stretch_count(int64_t rows, int resident)
@@ -124,8 +125,8 @@ __device__ __forceinline__ int64_t clamp_row(int64_t r, int64_t rows) { return r
 // One workgroup's pass over the n >= 1 rows of a unit from row r0 on, for the G heads whose queries start at q: D + 2 floats a head to
 // part: running maximum (base-2 logits), sum of weights, weighted values.  A wavefront takes U loads of rows at a time, the four
 // wavefronts in turn.  MOST: n is no larger (0: any n).
-// Measured instead: the next batch's rows asked for as soon as a batch's are used up, and the lane groups merged in registers
-// (permlane swaps) in front of the waves.  The registers that this holds cost waves: whole calls of 2 359 296 rows, us as it is and
+// Measured instead, in pieces of 256 rows: the next batch's rows asked for as soon as a batch's are used up, and the lane groups merged in
+// registers (permlane swaps) in front of the waves.  The registers that this holds cost waves: whole calls of 2 359 296 rows, us without and
 // that way, head dim 128 G = 3 213 / 210, 4 220 / 219, 6 253 / 277, 8 326 / 326; head dim 64 G = 3 105 / 103, 4 112 / 119,
 // 6 144 / 162, 8 192 / 212; small calls 11.0 / 11.2.
 template <int D, int G, bool F16, int MOST>

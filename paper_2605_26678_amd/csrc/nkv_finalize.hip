@@ -590,7 +590,8 @@ __device__ __forceinline__ void finalize_unit(UnitScratch &sh, const float *__re
 // grid: units.  Units of up to 1024 LO tokens, and of up to 1024 HI, are done in the same launch; those of other length classes are
 // passed over, so that a ragged batch takes one launch for prompts of up to 8192 tokens and one for longer ones (4 layers x 32 heads x
 // prompts of 1531, 4099, 777 and 2050 tokens, score call: 116.8 us with a launch for each of its two classes, 104.5 this way).  Up to 8192
-// tokens two workgroups share a compute unit.
+// tokens two workgroups share a compute unit, at 64 registers a thread: the instances with units of more than 4096 tokens spill one or
+// two of them.
 template <int LO, int HI, bool ALL>
 __global__ __launch_bounds__(kSelThreads, HI <= 8 ? 8 : 4) void finalize_unit_kernel(const float *__restrict__ a_raw, int L, int H,
                                                                                      PromptTab tab, LearnerConsts lc,

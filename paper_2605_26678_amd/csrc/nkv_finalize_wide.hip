@@ -10,13 +10,13 @@
 // bin's entries, and only those entries are looked at exactly; likewise from below.
 //   stats_hist_kernel    (slice, scale)  2048-bin histogram as 16-bit counts; min and max of the slice
 //   stats_pick_kernel    (unit, scale)   the bins that hold the m-th largest and the m-th smallest value
-//   stats_collect_kernel (slice, or a quarter of one where there are few) all three scales: sums of the values above the upper / below the lower
+//   stats_collect_kernel (quarter of a slice) all three scales: sums of the values above the upper / below the lower
 //                                        boundary bin; the boundary bins' entries (as order-preserving keys)
 //                                        into two short lists per slice and scale; and, the ranges being known,
 //                                        min / max / sum of the slice's surprise statistic
 //   stats_finish_kernel  (unit, scale)   two wavefronts, one per boundary bin: exact thresholds inside the bins, the
 //                                        two means, min, 1/range, gap
-//   route_slice_kernel   (the same)      weights, surprise statistics of the head, routed scores, pinning
+//   route_slice_kernel   (quarter)       weights, surprise statistics of the head, routed scores, pinning
 // A list that overflows (hundreds of values of one slice in one bin) marks the (unit, scale), and the first wavefront of its
 // finishing workgroup walks the head's values itself.
 #include "nkv_learner.h"

@@ -18,10 +18,11 @@ namespace {
 
 constexpr int kSlice = 8192;             // tokens per slice (the counts of a slice fit 16 bits)
 constexpr int kBins = 2048;
-// Up to two slices per compute unit: with 1024 threads each they are all resident, and quicker (one layer of 8 heads x
-// 32768 tokens, 32 slices: the statistics' collecting kernel 17 -> 7 us; it and the routing now take four workgroups of 256); many slices keep the chip full either way, and the
-// smaller workgroup has fewer wavefronts at its barriers.  At 512 slices (16 layers of 8 x 32768 tokens), 256 threads / 1024:
-// score 255 / 248 us, budgets 30.4 / 28.3, selection 54.0 / 49.0; at 544 slices the two are within 1 % of each other.
+// Threads of the kernels that take a slice a workgroup: the histograms, the budgets' and the selection's.  Up to two slices per compute unit
+// workgroups of 1024 are all resident, and quicker; many slices keep the chip full either way, and the smaller workgroup has fewer
+// wavefronts at its barriers.  Heads of 32768 tokens of bf16 keys, 256 threads / 1024, us: 32 slices budgets 26.9 / 24.8, selection with its
+// gather 33.1 / 30.7; 256 slices 28.7 / 26.4 and 115.1 / 112.4; 512 29.5 / 28.7 and 207.7 / 205.7; 544 30.2 / 30.7 and 223.9 / 226.8; 1152 38.5 / 39.3
+// and 453 / 461.  The score call, whose histograms alone are left, does not tell the two apart.
 constexpr int kFewSlices = 512;
 inline bool few_slices(int slices) { return slices <= kFewSlices; }
 template <int TH> constexpr int per_thread() { return kSlice / TH; }
