@@ -277,46 +277,74 @@ __device__ __forceinline__ void attend(const uint16_t *__restrict__ q, const uin
     }
 }
 
-// The unit that holds piece `piece` of all units' pieces of CH rows, and which of the unit's it is (unit < 0: there are fewer), for up to
-// PER * kDecThreads units: every workgroup counts all of them.
+// x, which is the same in every lane, in scalar registers (64-bit comparisons are made in vector registers).
+__device__ __forceinline__ int64_t uniform(int64_t x)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ int64_t of_lane(int64_t x, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+struct Piece {
+    int unit, k;                         // the unit's k-th piece; unit < 0: there are fewer pieces
+    int64_t first, end;                  // the unit's rows
+};
+
+// Piece i of all units' pieces of CH rows.  Up to 64 units every wavefront counts them by itself, up to PER * kDecThreads the workgroup.
+template <int CH>
+__device__ __forceinline__ Piece counted_by_wave(const int64_t *__restrict__ head_off, int n_units, int64_t rows, uint32_t i)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t from = clamp_row(head_off[min(lane, n_units)], rows), to = clamp_row(head_off[min(lane + 1, n_units)], rows);
+    const uint32_t c = (uint32_t)((max(to - from, (int64_t)0) + CH - 1) / CH), at = i - (wave_prefix_sum(c) - c);
+    const unsigned long long here = __ballot(at < c);
+    if (here == 0ull) return Piece{-1, 0, 0, 0};
+    const int u = __builtin_ctzll(here);
+    return Piece{u, __builtin_amdgcn_readlane((int)at, u), of_lane(from, u), of_lane(to, u)};
+}
 template <int CH, int PER>
-__device__ __forceinline__ int2 counted_piece(const int64_t *__restrict__ head_off, int n_units, int64_t rows, uint32_t piece)
+__device__ __forceinline__ Piece counted_by_workgroup(const int64_t *__restrict__ head_off, int n_units, int64_t rows, uint32_t piece)
 {
     constexpr int NW = kDecThreads / 64;
     __shared__ uint32_t wsum[NW];
-    __shared__ int2 found;
+    __shared__ Piece found;
     const int tid = threadIdx.x, w = tid >> 6, u0 = tid * PER;
     uint32_t c[PER], mine = 0u;
-    int64_t from = clamp_row(head_off[min(u0, n_units)], rows);
+    int64_t off[PER + 1];
+#pragma unroll
+    for (int i = 0; i <= PER; ++i) off[i] = clamp_row(head_off[min(u0 + i, n_units)], rows);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int64_t to = clamp_row(head_off[min(u0 + i + 1, n_units)], rows);
-        c[i] = (uint32_t)((max(to - from, (int64_t)0) + CH - 1) / CH);
+        c[i] = (uint32_t)((max(off[i + 1] - off[i], (int64_t)0) + CH - 1) / CH);
         mine += c[i];
-        from = to;
     }
     const uint32_t incl = wave_prefix_sum(mine);
     if ((tid & 63) == 63) wsum[w] = incl;
-    if (tid == 0) found = make_int2(-1, 0);
+    if (tid == 0) found.unit = -1;
     __syncthreads();
     uint32_t at = piece - (incl - mine);                              // from this thread's first piece on
 #pragma unroll
     for (int i = 0; i < NW - 1; ++i) at -= i < w ? wsum[i] : 0u;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        if (at < c[i]) found = make_int2(u0 + i, (int)at);
+        if (at < c[i]) found = Piece{u0 + i, (int)at, off[i], off[i + 1]};
         at -= c[i];
     }
     __syncthreads();
-    return make_int2(__builtin_amdgcn_readfirstlane(found.x), __builtin_amdgcn_readfirstlane(found.y));
+    return Piece{__builtin_amdgcn_readfirstlane(found.unit), __builtin_amdgcn_readfirstlane(found.k), uniform(found.first), uniform(found.end)};
 }
 
 // Pieces of CH rows of a unit, the first from its first row on.  Their partial results are numbered from off[u] / CH + u on, which leaves
 // room for all of them and needs no plan.  Workgroups take the pieces that there are, one after the other; more units than a workgroup
 // can count in less time than its rows take (2048 of them, G = 4 61 us, 68 with 16 units a thread) leave it with the numbers' pieces, some
-// of which are empty.  Workgroups go to the eight XCDs in turn, so what recurs every two, four or eight pieces, empty ones or a unit's short
-// last one, would be the same XCDs' share: every eight are dealt out one place further on than the eight before, and every 64 another
-// one.  Head dim 128, G = 8, as the numbers' pieces in their order / this way: 1024 units of 256 rows, every other number empty, 79 / 48 us; 512 of
+// of which are empty.  Empty ones in between would take the place of others, which then share a compute unit: 8 units of 8192 rows, head dim
+// 128, G = 8 24.0 us by numbers, 18.4 counted.  And workgroups go to the eight XCDs in turn, so what recurs every two, four or eight pieces,
+// empty ones or a unit's short last one, would be the same XCDs' share: every eight are dealt out one place further on than the eight
+// before, and every 64 another one.  By numbers in their order / this way: 1024 units of 256 rows, every other number empty, 79 / 48 us; 512 of
 // 768, every fourth, 78 / 62; 4096 of 256 288 / 175; 1024 of 300 68 / 69, counted but not dealt out 79.
 // grid: as many numbers as there are.
 template <int D, int G, bool F16, int CH>
@@ -326,27 +354,22 @@ __global__ __launch_bounds__(kDecThreads) void decode_piece_kernel(const uint16_
 {
     const uint32_t eight = blockIdx.x / 8u;
     const uint32_t i = (blockIdx.x | 7u) < gridDim.x ? eight * 8u + ((blockIdx.x + eight + eight / 8u) & 7u) : blockIdx.x;
-    int2 p;
-    if (CH == kSmallChunk || n_units <= kDecThreads) p = counted_piece<CH, 1>(head_off, n_units, rows, i);   // (kSmallUnits)
-    else if (n_units <= 4 * kDecThreads) p = counted_piece<CH, 4>(head_off, n_units, rows, i);
+    Piece p;
+    if (n_units <= kWave) p = counted_by_wave<CH>(head_off, n_units, rows, i);
+    else if (CH == kSmallChunk || n_units <= kDecThreads) p = counted_by_workgroup<CH, 1>(head_off, n_units, rows, i);   // (kSmallUnits)
+    else if (n_units <= 4 * kDecThreads) p = counted_by_workgroup<CH, 4>(head_off, n_units, rows, i);
     else {
-        p.x = wave_search_fn(n_units, (int64_t)i, [&](int u) { return u == 0 ? (int64_t)0 : clamp_row(head_off[u], rows) / CH + u; });
-        p.y = (int)((int64_t)i - p.x - clamp_row(head_off[p.x], rows) / CH);
+        p.unit = __builtin_amdgcn_readfirstlane(wave_search_fn(n_units, (int64_t)i, [&](int u) { return u == 0 ? (int64_t)0 : clamp_row(head_off[u], rows) / CH + u; }));
+        p.first = clamp_row(head_off[p.unit], rows);
+        p.end = clamp_row(head_off[p.unit + 1], rows);
+        p.k = (int)((int64_t)i - p.unit - p.first / CH);
     }
-    const int u = p.x;
-    if (u < 0) return;
-    const int64_t first = clamp_row(head_off[u], rows), a = first + (int64_t)p.y * CH, b = min(clamp_row(head_off[u + 1], rows), a + CH);
-    if (first <= a && a < b)
-        attend<D, G, F16, CH>(q + (int64_t)u * G * D, pk, pv, a, (int)(b - a), scale_log2, part + (first / CH + u + p.y) * G * (D + 2));
+    if (p.unit < 0) return;
+    const int64_t a = p.first + (int64_t)p.k * CH, b = min(p.end, a + CH);
+    if (p.first <= a && a < b)
+        attend<D, G, F16, CH>(q + (int64_t)p.unit * G * D, pk, pv, a, (int)(b - a), scale_log2, part + (p.first / CH + p.unit + p.k) * G * (D + 2));
 }
 static_assert(kSmallUnits <= kDecThreads, "a thread counts one unit's pieces of 64 rows");
-
-// x, which is the same in every lane, in scalar registers (64-bit comparisons are made in vector registers).
-__device__ __forceinline__ int64_t uniform(int64_t x)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32));
-    return (int64_t)((uint64_t)hi << 32 | lo);
-}
 
 // The rows of all units, one unit after the other, each with kUnitCost rows in front for its queries, its merge and its stores, in
 // stretches of `run`.  (Cut by rows alone, a stretch of short units took many of them in turn: 288 units of 26 rows beside 288 of 6554,
@@ -405,8 +428,9 @@ __device__ __forceinline__ int2 unit_pieces(const int64_t *head_off, int n_units
         y = n > 0 ? divide(at + n - 1, st.run) + u + 1 : x;
     } else {
         const int64_t a = clamp_row(head_off[u], rows), n = clamp_row(head_off[u + 1], rows) - a;
-        x = divide(a, piece) + u;
-        y = n > 0 ? x + divide(n + piece - 1, piece) : x;
+        const int shift = __builtin_ctz(piece);                       // (a power of two)
+        x = (a >> shift) + u;
+        y = n > 0 ? x + ((n + piece - 1) >> shift) : x;
     }
     return make_int2((int)min(x, (int64_t)limit), (int)min(y, (int64_t)limit));
 }
@@ -553,8 +577,8 @@ constexpr int resident_workgroups(int D, int G) { return 256 * (G == 1 ? (D == 1
 // Stretches where every workgroup that the device holds gets 256 rows and more, and the units have more than three pieces in the mean (four
 // where there are many).  Whole calls, chunks of 256 rows with a planning kernel in front (as it was) / pieces / stretches, us: 288 units
 // of 8192 rows, head dim 128, G = 1 201 / 205 / 190, 4 217 / 222 / 202, 8 323 / 325 / 276, head dim 64, G = 8 192 / 190 / 155; 288 units of
-// 512 rows, 128, G = 8 36.0 / 34.8 / 37.5, 64, G = 8 24.5 / 22.9 / 26.5, of 700 43.8 / 41.2 / 44.5 and 29.6 / 27.3 / 30.1, of 768 44.5 / 43.3 / 44.6 and
-// 29.7 / 27.7 / 28.7, of 800 55.6 / 50.3 / 46.0 and 37.3 / 34.5 / 31.3; 456 units, 128, G = 5, of 700 41.6 / 41.2 / 41.9, of 800 54.0 / 50.2 / 46.3.  (Held
+// 512 rows, 128, G = 8 36.4 / 34.3 / 37.5, 64, G = 8 24.4 / 22.2 / 26.5, of 700 43.8 / 40.3 / 44.5 and 29.3 / 27.1 / 30.1, of 768 43.9 / 43.0 / 44.6 and
+// 29.6 / 27.5 / 28.7, of 800 55.4 / 50.3 / 46.1 and 37.1 / 34.5 / 31.2; 456 units, 128, G = 5, of 700 42.0 / 39.1 / 41.9, of 800 54.2 / 50.2 / 45.6.  (Held
 // to the registers of a third workgroup, G = 6 takes 10 to 20 % longer: rows spilled in the loop.)
 bool by_stretches(int64_t n_units, int64_t rows, int resident)
 {

@@ -382,11 +382,12 @@ def test_short_units_beside_a_long_one(d, G, dtype):
 
 
 @pytest.mark.parametrize("rows_first", [0, 77])
-@pytest.mark.parametrize("units,lens", [(255, [300, 0, 64, 1]), (256, [63, 65, 128, 0, 1]), (257, [256, 0, 255, 257, 1, 512]),
+@pytest.mark.parametrize("units,lens", [(1, [1000]), (8, [8192]), (63, [300, 0, 64, 1]), (64, [256, 0, 255]), (65, [257, 1, 0]),
+                                        (255, [300, 0, 64, 1]), (256, [63, 65, 128, 0, 1]), (257, [256, 0, 255, 257, 1, 512]),
                                         (1024, [256]), (1024, [300, 0, 1]), (1025, [256, 511, 0, 513]), (2600, [256, 20])])
 def test_every_piece_of_a_unit_is_some_workgroups(units, lens, rows_first):
-    """Pieces of 64 and 256 rows that workgroups find by counting all units' pieces (up to 1024 units) or by their numbers, behind
-    rows that are no unit's: as many partial results as there are pieces, and the oracle's results."""
+    """Pieces of 64 and 256 rows that wavefronts (up to 64 units) or workgroups (up to 1024) find by counting all units' pieces or, of
+    more units, by their numbers, behind rows that are no unit's: as many partial results as there are pieces, and the oracle's results."""
     lens = (lens * units)[:units]
     w = nkv_inputs.small_workload(f"pieces_{units}_{len(lens)}", units, 1, 64, [1], dtype="fp16", n_out=0)
     g = torch.Generator(device=DEV).manual_seed(units)
